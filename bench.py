@@ -48,9 +48,9 @@ BF16_MFMA_PEAK_TFLOPS = 2500.0  # MI355X dense bf16 MFMA, published
 # HBM bytes per launch of the dominant kernel from rocprofv3 --pmc FETCH_SIZE / WRITE_SIZE runs
 # (profiles/stream_kernel_config5_hbm_traffic.md), scaled by the same counters on a plain 1 GiB copy.
 # Vector-ALU issue rate of the chip (one instruction per lane and clock: 256 CUs x 4 SIMDs x 16 lanes x 2.4 GHz)
-# and the vector instructions one FMAC-8 step takes on the single-precision path (rounded count from the ISA).
+# and the vector instructions one FMAC-8 step takes in its fp64 form (from the ISA; operands of ordinary size).
 VALU_LANE_INSTR_PER_S = 256 * 64 * 2.4e9
-FMAC8_INSTR_PER_MAC = 12.0
+FMAC8_INSTR_PER_MAC = 5.0
 MEASURED_TRAFFIC_BYTES = 2157514900   # profiles/stream_kernel_config5_hbm_traffic.md
 
 
@@ -617,10 +617,9 @@ def main() -> int:
                                     "frac": round(2048.0 * 2048 * 1024 / (f8_ms * 1e-3)
                                                   / (VALU_LANE_INSTR_PER_S / FMAC8_INSTR_PER_MAC), 4),
                                     "note": "vector issue rate 256 CUs x 64 lanes x 2.4 GHz = 39.3 T "
-                                            "lane-instructions/s over the 12 instructions of the fused step "
-                                            "of the single-precision path (16 are executed per step with the "
-                                            "midpoint handling, operand rounding and master additions: "
-                                            "profiles/fmac8_kernel_counters.md)"}}
+                                            "lane-instructions/s over the 5 instructions of the fused step "
+                                            "in fp64 (5.8 are executed per step with the master additions and "
+                                            "the LDS reads)"}}
     # loss-scale controller on the nine statistics records of configuration 4's gradient tensors
     recs = torch.stack([L["h"][2] for L in layers])
     st = fmt.fmt_dls_init(1024.0)

@@ -9,18 +9,25 @@
 // ALU work (no matrix cores), bound by the rate at which the vector units issue instructions: one per
 // lane and clock.
 //
-// Formats with e <= 6 and m <= 11 run the fused step in single precision around the hardware's own
-// fused multiply-add, s = fma(w, x, a): the exact sum rounded ONCE to 24 bits.  Rounding s to the
-// format afterwards equals rounding the exact sum directly unless s lands exactly on a midpoint of
-// the format's grid while the exact sum does not; only a wave that holds such a lane (rare) computes
-// the exact error of the sum and puts that lane on the side of the midpoint where the exact sum lies.
-// 14 vector instructions per fused step instead of 22.
-//
-// The fused step is done in fp64: the product of two <= 24-bit significands is exact; the sum
-// a + w*x is rounded to odd (TwoSum gives the exact error; if it is non-zero and the fp64 sum is
-// the even neighbour, step to the odd one), which makes the following rounding to the format
-// (<= 24 significant bits) equal to a single rounding of the exact sum.  That rounding uses
-// (|s| + C) - C with C = 2^(max(E,Emin) - m + 52), the fp64 adder's own round-to-nearest-even.
+// Three forms of the fused step, all giving the one rounding of the exact sum:
+//   wide    (e <= 6, m <= 11, operands of ordinary size: the common case) fp64 around the hardware's fused
+//           multiply-add, s = fma(w, x, a), and the rounding (s + C) - C with C = 1.5 * 2^(max(E, Emin) + 52 - m):
+//           5 vector instructions (7 with the flush), and the vector units issue fp64 adds and fused multiply-adds
+//           at the rate of single fp32 ones.  See fmac_wide for why the rounding to 53 bits on the way does no harm
+//           as long as |s| stays below `wide_limit`; a workgroup takes this form for a stage of 32 k when
+//           the largest operand magnitudes of the stage say that no sum can get there.
+//   single  (the same formats, a stage with larger, infinite or NaN operands) fp32 around the hardware FMA:
+//           the exact sum rounded once to 24 bits, then to the format, which equals rounding the exact sum
+//           unless the 24-bit sum lands exactly on a midpoint of the format's grid while the exact sum
+//           does not; a wave that holds such a lane computes the exact error of the sum and puts that lane on the
+//           side of the midpoint where the exact sum lies.  About 16 instructions.
+//   odd     (other formats) fp64: the product of two <= 24-bit significands is exact; the sum a + w*x is rounded
+//           to odd (TwoSum gives the exact error; if it is non-zero and the fp64 sum is the even neighbour, step
+//           to the odd one), which makes the following rounding to the format (<= 24 significant bits) equal to a
+//           single rounding of the exact sum.  That rounding uses (|s| + C) - C with C = 2^(max(E,Emin) - m + 52),
+//           the fp64 adder's own round-to-nearest-even.  About 25 instructions.
+#include <algorithm>
+#include <cmath>
 #include <cstdlib>
 #include <type_traits>
 
@@ -114,127 +121,268 @@ __device__ __forceinline__ float fmac_fix(float tried, float a, float w, float x
     return copysignf(r, s);
 }
 
-constexpr int kFTile = 64;     // outputs per workgroup edge
-constexpr int kFK = 32;        // k per LDS stage (a multiple of 8: FMAC-8 groups never straddle stages)
+// Constants of the wide step.
+struct WideConsts {
+    uint32_t minn_hi;    // hi word of 1.5 * 2^Emin
+    uint32_t exp_mask;   // 0x7FF00000 and 0x80000 in registers: with literals the compiler spends two instructions
+    uint32_t half;       // (and, or) where one (v_and_or_b32, which takes no literal) does
+    double scale;        // 2^(52 - m)
+    double minn;         // 2^Emin
+    float limit;         // the form is used while max|w| * max|x| of a stage stays below this
+};
 
-template <int MODE, bool FTZ, bool F32>
+// The fused step in fp64, for |a + w*x| < wide_limit = 2^(Emin - m + 52).
+//   * s = fma(w, x, a) is the exact sum rounded to 53 bits; r rounds s to the format's grid at s (C is 1.5 times a
+//     power of two whose last place is the grid's step, so s + C rounds to the grid for either sign, ties to the
+//     even multiple, and taking C off again is exact).
+//   * r is the single rounding of the exact sum: with s exact there is nothing to show.  a is a multiple of
+//     2^(Emin - m), which is at least the last place of s, so only bits of p = w*x can be lost.  p has at most
+//     2m + 2 bits, so a p with bits below the last place of s is smaller than 2^(E(s) - 51 + 2m) <=
+//     2^(E(s) - m - 18) (m <= 11): the exact sum and s then lie within a tiny fraction of a grid step of a,
+//     which is itself a grid point, and both round to a.
+//   * the sign of a zero is not kept (-0 may come out as +0).  Nothing in the result depends on it: a zero of
+//     either sign adds the same to a non-zero sum, and the fp32 master starts from +0, which stays +0 when a
+//     zero of either sign is added.
+// Results do not overflow below the limit (the caller's bound is below the format's overflow threshold as well).
+template <bool FTZ, bool FIRST>
+__device__ __forceinline__ double fmac_wide(double a, double w, double x, const WideConsts &k)
+{
+    const double s = FIRST ? __dmul_rn(w, x) : __fma_rn(w, x, a);
+    // u = 1.5 * 2^max(E, Emin); C = u * 2^(52 - m) is formed inside the two fused multiply-adds (exactly)
+    const double u = __hiloint2double((int)max(((uint32_t)__double2hiint(s) & k.exp_mask) | k.half, k.minn_hi), 0);
+    const double r = __fma_rn(u, -k.scale, __fma_rn(u, k.scale, s));
+    if (!FTZ) return r;
+    // r has at most 12 significant bits: its lo word is zero, clearing the hi word makes a zero of it
+    return __hiloint2double(fabs(r) < k.minn ? 0 : __double2hiint(r), __double2loint(r));
+}
+
+constexpr int kFK = 32;        // k per LDS stage (a multiple of 8: FMAC-8 groups never straddle stages)
+enum { kStepSingle = 0, kStepOdd = 1 };     // the form besides the wide one that an instantiation holds
+
+// One workgroup computes a tile of 16*T x 16*T outputs, T x T per thread.  The chains of an output are sequential, so
+// what counts is that every SIMD has instructions to issue: 16 chains per thread where there are tiles enough to
+// fill the chip, 4 or 1 where there are not (see launch).  Operand stages are rounded on the way into LDS, as fp64 (a
+// value converted once instead of once per use); the next stage's loads are in flight while a stage is computed.
+// Measured in 1/6/9: 2048 x 2048 x 1024 takes 0.76 ms (5.7 T fused steps/s; 1.97 ms with the single form alone),
+// 256 x 256 x 256 takes 17 us (224 us with 64 x 64 tiles and the single form alone).
+template <int MODE, bool FTZ, int STEP, int T>
 __global__ __launch_bounds__(256) void fmac8_kernel(const uint32_t *__restrict__ A, int64_t lda, int transA,
                                                     const uint32_t *__restrict__ B, int64_t ldb, int transB,
                                                     float *__restrict__ C, int64_t ldc, int M, int N, int K,
-                                                    int tiles_n, QuantParams qp, Fmac8Params fp)
+                                                    int tiles_n, QuantParams qp, Fmac8Params fp, WideConsts wc)
 {
-    __shared__ float sa[kFK][kFTile + 4];          // rounded operand values, [k][row]
-    __shared__ float sb[kFK][kFTile + 4];
+    constexpr int kTile = 16 * T;                  // outputs per workgroup edge
+    constexpr int kLoads = kTile * kFK / 256;      // elements of one operand per thread and stage
+    __shared__ __attribute__((aligned(16))) double sa[kFK][kTile + 2];   // rounded operand values, [k][row]
+    __shared__ __attribute__((aligned(16))) double sb[kFK][kTile + 2];
+    __shared__ uint32_t s_max[2][4];               // largest operand magnitude of the stage, per wave
     const int tid = threadIdx.x, tx = tid & 15, ty = tid >> 4;
-    const int row0 = (blockIdx.x / tiles_n) * kFTile, col0 = (blockIdx.x % tiles_n) * kFTile;
+    const int row0 = (blockIdx.x / tiles_n) * kTile, col0 = (blockIdx.x % tiles_n) * kTile;
 
-    typedef typename std::conditional<F32, float, double>::type acc_t;
-    float acc32[4][4];                             // the fp32 master accumulators
+    float acc32[T][T];                             // the fp32 master accumulators
 #pragma unroll
-    for (int i = 0; i < 4; ++i)
+    for (int i = 0; i < T; ++i)
 #pragma unroll
-        for (int j = 0; j < 4; ++j) acc32[i][j] = 0.0f;
+        for (int j = 0; j < T; ++j) acc32[i][j] = 0.0f;
     const FmaConsts fk = {__uint_as_float(qp.minn_bits), __uint_as_float(qp.t_ovf),
                           __uint_as_float((qp.t_ovf & 0x7F800000u) + 0x00800000u)};   // t_ovf lies in the top binade
 
-    for (int k0 = 0; k0 < K; k0 += kFK) {
-        // stage: 64 x 32 values of each operand, rounded to the format on the way in
+    uint32_t va[kLoads], vb[kLoads];
+    // element `it` of this thread: (row or column in the tile, k in the stage); consecutive lanes walk whichever
+    // of the two is contiguous in memory
+    auto a_at = [&](int it, int &r, int &k) {
+        const int idx = it * 256 + tid;
+        r = transA ? idx % kTile : idx / kFK;
+        k = transA ? idx / kTile : idx % kFK;
+    };
+    auto b_at = [&](int it, int &c, int &k) {
+        const int idx = it * 256 + tid;
+        c = transB ? idx / kFK : idx % kTile;
+        k = transB ? idx % kFK : idx / kTile;
+    };
+    auto load = [&](int k0) {
 #pragma unroll
-        for (int it = 0; it < 8; ++it) {
-            const int idx = it * 256 + tid;
-            // A: consecutive lanes walk k when k is contiguous in memory, rows otherwise
-            const int ar = transA ? idx % kFTile : idx / kFK, ak = transA ? idx / kFTile : idx % kFK;
-            const int br = transB ? idx / kFK : idx % kFTile, bk = transB ? idx % kFK : idx / kFTile;
-            const int gr = row0 + ar, gk = k0 + ak;
-            uint32_t va = 0u, vb = 0u;
-            if (gr < M && gk < K) va = transA ? A[(size_t)gk * lda + gr] : A[(size_t)gr * lda + gk];
-            const int gc = col0 + br, gkb = k0 + bk;
-            if (gc < N && gkb < K) vb = transB ? B[(size_t)gc * ldb + gkb] : B[(size_t)gkb * ldb + gc];
-            sa[ak][ar] = __uint_as_float(quantize_bits<MODE, FTZ>(va, qp));
-            sb[bk][br] = __uint_as_float(quantize_bits<MODE, FTZ>(vb, qp));
+        for (int it = 0; it < kLoads; ++it) {
+            int r, k;
+            a_at(it, r, k);
+            const int gr = row0 + r, gk = k0 + k;
+            va[it] = 0u;
+            if (gr < M && gk < K) va[it] = transA ? A[(size_t)gk * lda + gr] : A[(size_t)gr * lda + gk];
+            int c;
+            b_at(it, c, k);
+            const int gc = col0 + c, gkb = k0 + k;
+            vb[it] = 0u;
+            if (gc < N && gkb < K) vb[it] = transB ? B[(size_t)gc * ldb + gkb] : B[(size_t)gkb * ldb + gc];
+        }
+    };
+
+    if (STEP == kStepSingle) asm("" : "+v"(wc.half));      // a vector register: an instruction takes one scalar operand only
+
+    load(0);
+    for (int k0 = 0; k0 < K; k0 += kFK) {
+        uint32_t ma = 0u, mb = 0u;
+#pragma unroll
+        for (int it = 0; it < kLoads; ++it) {
+            int r, k;
+            const uint32_t qa = quantize_bits<MODE, FTZ>(va[it], qp), qb = quantize_bits<MODE, FTZ>(vb[it], qp);
+            ma = max(ma, qa & 0x7FFFFFFFu);
+            mb = max(mb, qb & 0x7FFFFFFFu);
+            a_at(it, r, k);
+            sa[k][r] = (double)__uint_as_float(qa);
+            b_at(it, r, k);
+            sb[k][r] = (double)__uint_as_float(qb);
+        }
+        if (STEP == kStepSingle) {
+#pragma unroll
+            for (int off = 32; off > 0; off >>= 1) {
+                ma = max(ma, (uint32_t)__shfl_xor((int)ma, off, 64));
+                mb = max(mb, (uint32_t)__shfl_xor((int)mb, off, 64));
+            }
+            if ((tid & 63) == 0) {
+                s_max[0][tid >> 6] = ma;
+                s_max[1][tid >> 6] = mb;
+            }
         }
         __syncthreads();
+        if (k0 + kFK < K) load(k0 + kFK);          // in flight while this stage is computed
+        bool wide = false;
+        if (STEP == kStepSingle) {
+            const uint32_t wa = max(max(s_max[0][0], s_max[0][1]), max(s_max[0][2], s_max[0][3]));
+            const uint32_t wb = max(max(s_max[1][0], s_max[1][1]), max(s_max[1][2], s_max[1][3]));
+            // infinities and NaN (patterns from 0x7F800000) are left to the other form
+            wide = wa < 0x7F800000u && wb < 0x7F800000u && __fmul_rn(__uint_as_float(wa), __uint_as_float(wb)) < wc.limit;
+            wide = __builtin_amdgcn_readfirstlane(wide ? 1 : 0) != 0;      // the same in the whole workgroup
+        }
         // groups of 8 k (the stage is zero-padded beyond K): 8 fused steps from a = 0, then one fp32 addition
-        for (int g = 0; g < kFK / 8; ++g) {
-            acc_t a16[4][4];
+        if (wide) {
+#pragma unroll 1
+            for (int g = 0; g < kFK / 8; ++g) {
+                double a16[T][T];
 #pragma unroll
-            for (int i = 0; i < 4; ++i)
+                for (int kk = 0; kk < 8; ++kk) {
+                    double w[T], x[T];
 #pragma unroll
-                for (int j = 0; j < 4; ++j) a16[i][j] = (acc_t)0;
-#pragma unroll
-            for (int kk = g * 8; kk < g * 8 + 8; ++kk) {
-                acc_t w[4], x[4];
-#pragma unroll
-                for (int i = 0; i < 4; ++i) {
-                    w[i] = (acc_t)sa[kk][ty * 4 + i];
-                    x[i] = (acc_t)sb[kk][tx * 4 + i];
-                }
-                if constexpr (F32) {
-                    // the 16 chains take their step; which lanes met a midpoint is kept as wave masks
-                    float nx[4][4];
-                    unsigned long long met[4][4], any = 0ull;
-                    const bool first = kk == g * 8;        // known at compile time: the loop over kk is unrolled
-#pragma unroll
-                    for (int i = 0; i < 4; ++i)
-#pragma unroll
-                        for (int j = 0; j < 4; ++j) {
-                            bool tie;
-                            nx[i][j] = first ? fmac_try<FTZ, true>(a16[i][j], w[i], x[j], qp, fk, tie)
-                                             : fmac_try<FTZ, false>(a16[i][j], w[i], x[j], qp, fk, tie);
-                            met[i][j] = __ballot(tie);
-                            any |= met[i][j];
-                        }
-                    if (any != 0ull) {                     // wave-uniform
-#pragma unroll
-                        for (int i = 0; i < 4; ++i)
-#pragma unroll
-                            for (int j = 0; j < 4; ++j)
-                                if (met[i][j] != 0ull) nx[i][j] = fmac_fix<FTZ>(nx[i][j], a16[i][j], w[i], x[j], qp, fk);
+                    for (int i = 0; i < T; ++i) {
+                        w[i] = sa[g * 8 + kk][ty * T + i];
+                        x[i] = sb[g * 8 + kk][tx * T + i];
                     }
 #pragma unroll
-                    for (int i = 0; i < 4; ++i)
+                    for (int i = 0; i < T; ++i)
 #pragma unroll
-                        for (int j = 0; j < 4; ++j) a16[i][j] = nx[i][j];
-                } else {
-#pragma unroll
-                    for (int i = 0; i < 4; ++i)
-#pragma unroll
-                        for (int j = 0; j < 4; ++j) a16[i][j] = quantize_f64(add_round_to_odd(a16[i][j], w[i] * x[j]), fp);
+                        for (int j = 0; j < T; ++j)
+                            a16[i][j] = kk == 0 ? fmac_wide<FTZ, true>(0.0, w[i], x[j], wc)
+                                                : fmac_wide<FTZ, false>(a16[i][j], w[i], x[j], wc);
                 }
+#pragma unroll
+                for (int i = 0; i < T; ++i)
+#pragma unroll
+                    for (int j = 0; j < T; ++j) acc32[i][j] = __fadd_rn(acc32[i][j], (float)a16[i][j]);
             }
+        } else {
+            typedef typename std::conditional<STEP == kStepSingle, float, double>::type acc_t;
+#pragma unroll 1
+            for (int g = 0; g < kFK / 8; ++g) {
+                acc_t a16[T][T];
 #pragma unroll
-            for (int i = 0; i < 4; ++i)
+                for (int i = 0; i < T; ++i)
 #pragma unroll
-                for (int j = 0; j < 4; ++j) acc32[i][j] = acc32[i][j] + (float)a16[i][j];   // single-precision addition
+                    for (int j = 0; j < T; ++j) a16[i][j] = (acc_t)0;
+#pragma unroll
+                for (int kk = 0; kk < 8; ++kk) {
+                    acc_t w[T], x[T];
+#pragma unroll
+                    for (int i = 0; i < T; ++i) {
+                        w[i] = (acc_t)sa[g * 8 + kk][ty * T + i];
+                        x[i] = (acc_t)sb[g * 8 + kk][tx * T + i];
+                    }
+                    if constexpr (STEP == kStepSingle) {
+                        // the chains take their step; which lanes met a midpoint is kept as wave masks
+                        float nx[T][T];
+                        unsigned long long met[T][T], any = 0ull;
+#pragma unroll
+                        for (int i = 0; i < T; ++i)
+#pragma unroll
+                            for (int j = 0; j < T; ++j) {
+                                bool tie;
+                                nx[i][j] = kk == 0 ? fmac_try<FTZ, true>(a16[i][j], w[i], x[j], qp, fk, tie)
+                                                   : fmac_try<FTZ, false>(a16[i][j], w[i], x[j], qp, fk, tie);
+                                met[i][j] = __ballot(tie);
+                                any |= met[i][j];
+                            }
+                        if (any != 0ull) {                     // wave-uniform
+#pragma unroll
+                            for (int i = 0; i < T; ++i)
+#pragma unroll
+                                for (int j = 0; j < T; ++j)
+                                    if (met[i][j] != 0ull) nx[i][j] = fmac_fix<FTZ>(nx[i][j], a16[i][j], w[i], x[j], qp, fk);
+                        }
+#pragma unroll
+                        for (int i = 0; i < T; ++i)
+#pragma unroll
+                            for (int j = 0; j < T; ++j) a16[i][j] = nx[i][j];
+                    } else {
+#pragma unroll
+                        for (int i = 0; i < T; ++i)
+#pragma unroll
+                            for (int j = 0; j < T; ++j) a16[i][j] = quantize_f64(add_round_to_odd(a16[i][j], w[i] * x[j]), fp);
+                    }
+                }
+#pragma unroll
+                for (int i = 0; i < T; ++i)
+#pragma unroll
+                    for (int j = 0; j < T; ++j) acc32[i][j] = acc32[i][j] + (float)a16[i][j];   // single-precision addition
+            }
         }
         __syncthreads();
     }
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
-        const int r = row0 + ty * 4 + i;
+    for (int i = 0; i < T; ++i) {
+        const int r = row0 + ty * T + i;
 #pragma unroll
-        for (int j = 0; j < 4; ++j) {
-            const int c = col0 + tx * 4 + j;
+        for (int j = 0; j < T; ++j) {
+            const int c = col0 + tx * T + j;
             if (r < M && c < N)
                 C[(size_t)r * ldc + c] = __uint_as_float(quantize_bits<MODE, FTZ>(__float_as_uint(acc32[i][j]), qp));
         }
     }
 }
 
-template <int MODE, bool FTZ, bool F32>
-static int launch(int transA, int transB, int M, int N, int K, const float *A, int64_t lda, const float *B, int64_t ldb,
-                  float *C, int64_t ldc, const QuantParams &qp, const Fmac8Params &fp, hipStream_t stream)
+template <int MODE, bool FTZ, int STEP, int T>
+static int launch_tile(int transA, int transB, int M, int N, int K, const float *A, int64_t lda, const float *B, int64_t ldb,
+                       float *C, int64_t ldc, const QuantParams &qp, const Fmac8Params &fp, const WideConsts &wc, hipStream_t stream)
 {
-    const int tiles_m = (M + kFTile - 1) / kFTile, tiles_n = (N + kFTile - 1) / kFTile;
+    const int tiles_m = (M + 16 * T - 1) / (16 * T), tiles_n = (N + 16 * T - 1) / (16 * T);
     if ((int64_t)tiles_m * tiles_n >= ((int64_t)1 << 31)) return FMT_ERR_SHAPE;
-    hipLaunchKernelGGL((fmac8_kernel<MODE, FTZ, F32>), dim3(tiles_m * tiles_n), dim3(256), 0, stream,
+    hipLaunchKernelGGL((fmac8_kernel<MODE, FTZ, STEP, T>), dim3(tiles_m * tiles_n), dim3(256), 0, stream,
                        reinterpret_cast<const uint32_t *>(A), lda, transA, reinterpret_cast<const uint32_t *>(B), ldb,
-                       transB, C, ldc, M, N, K, tiles_n, qp, fp);
+                       transB, C, ldc, M, N, K, tiles_n, qp, fp, wc);
     FMT_HIP_CHECK(hipGetLastError());
     return FMT_OK;
 }
 
-// FMT_FMAC8_F64=1 keeps every format on the double-precision step (tests compare the two).
+template <int MODE, bool FTZ, int STEP>
+static int launch(int transA, int transB, int M, int N, int K, const float *A, int64_t lda, const float *B, int64_t ldb,
+                  float *C, int64_t ldc, const QuantParams &qp, const Fmac8Params &fp, const WideConsts &wc, hipStream_t stream)
+{
+    int cus = 0;
+    const int rc = device_cu_count(&cus);
+    if (rc != FMT_OK) return rc;
+    auto tiles = [&](int t) { return (((int64_t)M + 16 * t - 1) / (16 * t)) * (((int64_t)N + 16 * t - 1) / (16 * t)); };
+    // Which tile: fitted to N x N x 256 products in 1/6/9 on 256 compute units.  One tile alone on a compute unit takes 16.8,
+    // 28.7 or 62.7 us (T = 1, 2, 4: the chains' latency with 1, 4 or 16 of them to interleave); with work enough a compute
+    // unit finishes one per 5.8, 15 or 48 us.  Measured (us, T = 1 / 2 / 4): N = 64: 16.8 / 28.5 / 62.6; 384: 24 / 30 / 63;
+    // 512: 30 / 30 / 64; 768: 59 / 52 / 66; 1024: 93 / 66 / 67; 1500: 190 / 129 / 153.
+    auto estimate = [&](int t, double alone, double each) {
+        return std::max(alone, (double)((tiles(t) + cus - 1) / cus) * each);
+    };
+    const double t1 = estimate(1, 16.8, 5.8), t2 = estimate(2, 28.7, 15.0), t4 = estimate(4, 62.7, 48.0);
+#define FMT_TILE(T) launch_tile<MODE, FTZ, STEP, T>(transA, transB, M, N, K, A, lda, B, ldb, C, ldc, qp, fp, wc, stream)
+    if (t4 <= t2 && t4 <= t1) return FMT_TILE(4);
+    return t2 <= t1 ? FMT_TILE(2) : FMT_TILE(1);
+#undef FMT_TILE
+}
+
+// FMT_FMAC8_F64=1 keeps every format on the round-to-odd form (tests compare the two).
 static bool fmac8_force_f64()
 {
     const char *env = getenv("FMT_FMAC8_F64");
@@ -253,14 +401,26 @@ int launch_gemm_fmac8(int transA, int transB, int64_t M, int64_t N, int64_t K, c
     fp.m = f.m;
     fp.ftz = f.denorm == 0;
     const bool ftz = f.denorm == 0;
-#define FMT_RUN(MD, F32)                                                                                              \
-    (ftz ? launch<MD, true, F32>(transA, transB, (int)M, (int)N, (int)K, A, lda, B, ldb, C, ldc, qp, fp, stream)      \
-         : launch<MD, false, F32>(transA, transB, (int)M, (int)N, (int)K, A, lda, B, ldb, C, ldc, qp, fp, stream))
-    // single-precision fused step where it is exact (see fmac_f32): 1/5/10, 1/6/9 and their neighbours
-    if (f.e <= 6 && f.m <= 11 && !fmac8_force_f64()) return FMT_RUN(kModeMagic, true);
-    if (qp.mode == kModeMagic) return FMT_RUN(kModeMagic, false);
-    if (qp.mode == kModeInteger) return FMT_RUN(kModeInteger, false);
-    return FMT_RUN(kModeMixed, false);
+    WideConsts wc;
+    wc.minn_hi = ((uint32_t)(1 - bias + 1023) << 20) | 0x80000u;
+    wc.exp_mask = 0x7FF00000u;
+    wc.half = 0x80000u;
+    wc.scale = ldexp(1.0, 52 - f.m);
+    wc.minn = fp.minn;
+    // Below 2^(Emin - m + 52) the wide step is exact (see fmac_wide), below 2^Emax nothing overflows.  Through the 8
+    // steps of a group |a + w*x| grows to at most max|w*x| times the sum of (1 + 2^-(m+1))^i, i = 0..8 (each step's
+    // rounding adds at most half a last place): that factor, and a little for the product of the maxima, comes off.
+    double growth = 0.0;
+    for (int i = 0; i <= 8; ++i) growth += pow(1.0 + ldexp(1.0, -(f.m + 1)), i);
+    wc.limit = (float)(0.99 * ldexp(1.0, 1 - bias - f.m + 52 < bias ? 1 - bias - f.m + 52 : bias) / growth);
+#define FMT_RUN(MD, STEP)                                                                                             \
+    (ftz ? launch<MD, true, STEP>(transA, transB, (int)M, (int)N, (int)K, A, lda, B, ldb, C, ldc, qp, fp, wc, stream) \
+         : launch<MD, false, STEP>(transA, transB, (int)M, (int)N, (int)K, A, lda, B, ldb, C, ldc, qp, fp, wc, stream))
+    // wide and single-precision fused steps where they are exact: 1/5/10, 1/6/9 and their neighbours
+    if (f.e <= 6 && f.m <= 11 && !fmac8_force_f64()) return FMT_RUN(kModeMagic, kStepSingle);
+    if (qp.mode == kModeMagic) return FMT_RUN(kModeMagic, kStepOdd);
+    if (qp.mode == kModeInteger) return FMT_RUN(kModeInteger, kStepOdd);
+    return FMT_RUN(kModeMixed, kStepOdd);
 #undef FMT_RUN
 }
 

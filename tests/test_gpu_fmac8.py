@@ -190,3 +190,45 @@ def test_against_the_plain_definition(fmt, e, m, d):
             assert np.array_equal(np.isnan(got), nan)
             assert_bits(np.where(nan, 0, got).astype(np.float32), np.where(nan, 0, want).astype(np.float32),
                         "definition, 1/%d/%d/%s layout %s" % (e, m, d, (tA, tB)))
+
+
+@pytest.mark.parametrize("M,N", [(17, 33), (16, 16), (700, 800), (2000, 2010)])
+@pytest.mark.parametrize("e,m,d", [(6, 9, True), (6, 9, False), (5, 10, True), (6, 11, False), (2, 11, True), (3, 1, True)])
+def test_forms_of_the_step_by_stage(fmt, e, m, d, M, N):
+    """Every tile size of the kernel (1, 4 and 16 outputs per thread), with stages of 32 k on both sides of the bound
+    that decides which form of the fused step a stage takes: products far below it, the largest product just below
+    and just above 2^(Emin-m+52) (or 2^Emax) over the growth of a group, a stage with an overflow, one with an infinity, one of
+    values around the smallest denormal, and large products that meet a tiny accumulator.  Bit for bit on sampled rows and columns."""
+    rng = np.random.default_rng(10 * e + m + M)
+    c = oracle.format_constants(e, m)
+    limit = min(c["Emin"] - m + 52, c["Emax"])
+    K = 32 * 7 + 5
+    A = workloads.log2_normal((M, K), -2.0, 3.0, 0.02, rng)
+    B = workloads.log2_normal((K, N), -2.0, 3.0, 0.02, rng)
+    top = 2.0 ** (limit / 2)
+
+    def clip(X, hi):
+        return np.clip(X, -hi, hi).astype(np.float32)
+    A, B = clip(A, top / 16), clip(B, top / 16)
+    for stage, factor in ((1, 0.30), (2, 0.36), (3, 1.5)):        # max|w| max|x| = factor^2 * 2^limit: 0.09, 0.13, 2.25
+        s = slice(32 * stage, 32 * stage + 32)
+        A[:, s] = clip(workloads.log2_normal((M, 32), limit / 2 - 4, 4.0, 0.0, rng), factor * top)
+        B[s, :] = clip(workloads.log2_normal((32, N), limit / 2 - 4, 4.0, 0.0, rng), factor * top)
+    A[M // 2, 32 * 4 + 3] = np.inf
+    s = slice(32 * 5, 32 * 6)
+    A[:, s] = workloads.log2_normal((M, 32), (c["Emin"] - m) / 2.0, 1.0, 0.0, rng)
+    B[s, :] = workloads.log2_normal((32, N), (c["Emin"] - m) / 2.0, 1.0, 0.0, rng)
+    s = slice(32 * 6, 32 * 7)                                     # tiny accumulator, then a product with its last bit set
+    A[:, s] = clip(workloads.log2_normal((M, 32), limit / 2 - 3, 0.5, 0.0, rng), 0.25 * top)
+    B[s, :] = clip(workloads.log2_normal((32, N), limit / 2 - 3, 0.5, 0.0, rng), 0.25 * top)
+    A[:, 32 * 6:32 * 7:2] = np.float32(c["minD"] if e > 2 else 1.0)
+    B[32 * 6:32 * 7:2, :] = np.float32(1.0)
+    C = fmt.fmt_gemm_fmac8(dev(A), dev(B), (e, m, d))
+    torch.cuda.synchronize()
+    rows = np.unique(np.concatenate([rng.integers(0, M, 30), [0, M // 2, M - 1]]))
+    cols = np.unique(np.concatenate([rng.integers(0, N, 30), [0, N - 1]]))
+    ref = oracle.gemm_fmac8(np.ascontiguousarray(A[rows]), np.ascontiguousarray(B[:, cols]), e, m, d)
+    got = np.ascontiguousarray(C.cpu().numpy()[np.ix_(rows, cols)])
+    nan = np.isnan(ref)
+    assert np.array_equal(np.isnan(got), nan)
+    assert_bits(np.where(nan, 0, got).astype(np.float32), np.where(nan, 0, ref).astype(np.float32), "stages")
