@@ -1002,7 +1002,8 @@ __global__ __launch_bounds__(256) void prepare_scaled_group_kernel(PrepGroup grp
         prepare_pair_tile<MODE, FTZ, ROUND, DEEP>(o0, o1, p, ty, tx, ROUND ? rg.Y[at] : nullptr, ROUND ? rg.ldy[at] : 0, tbl, w);
     }
     if constexpr (ROUND)
-        hist_end<kPairCopies, 256>(tbl, s_bins, s_cls, w, p, rg.partials[at], blockIdx.x % kShards, threadIdx.x);
+        hist_end<kPairCopies, 256>(tbl, s_bins, s_cls, w, p, HistSink{rg.partials[at], nullptr, 0ull, (uint32_t)kShards},
+                                   blockIdx.x, gridDim.x, threadIdx.x);
 }
 
 // Epilogue of one wave.  The MFMAs are fed operand B's fragment first and A's second, so a 32 x 32 accumulator
@@ -2371,7 +2372,7 @@ int launch_prepare_pair_batch(int64_t count, const PrepPairItem *items, fmt_form
             if (!(api_scheme(f, items[i].cols).scaled && api_scheme(f, items[i].rows).scaled && p.mode == kModeMagic))
                 return FMT_ERR_FORMAT;
         Scratch sc;
-        const int rc = get_scratch(stream, (size_t)(kMaxPrepGroup / 2) * kHistScratchBytes, 0, &sc);
+        const int rc = get_scratch(stream, (size_t)(kMaxPrepGroup / 2) * kHistRecordBytes, 0, &sc);
         if (rc != FMT_OK) return rc;
         records = static_cast<unsigned long long *>(sc.hist_partials);
         // steps per workgroup: as many as leave every compute unit four workgroups (measured on 12 tensors of 4 M to 16 M

@@ -85,12 +85,50 @@ __device__ __forceinline__ void hist_begin(uint32_t *tbl, uint32_t *s_bins, uint
     __syncthreads();
 }
 
-// Folds the workgroup's counters and table into 64 bins and adds the 72 counts, one 64-bit atomic
-// per non-zero slot, into partial record `shard` (< kShards).  All BLOCK threads call it.
+// Where a launch's counts go.
+//   records only (hist == nullptr)   every workgroup adds into record (workgroup % shards); a kernel that follows
+//                                    sums and clears the records (launch_hist_finalize)
+//   one workgroup (records == nullptr)  it writes the caller's record itself
+//   in one launch (otherwise)        as records only, and whoever adds last to a slot passes its sum on (see hist_end)
+struct HistSink {
+    unsigned long long *records;         // all zero between launches; the sums of the records go to record `shards`
+    unsigned long long *hist;            // the caller's fmt_hist_t
+    unsigned long long n;                // elements of the tensor
+    uint32_t shards;                     // records in use
+};
+
+// Slot `slot` of the caller's record from the 72 summed counts and the number of elements.
+__device__ __forceinline__ unsigned long long hist_slot(const unsigned long long *tot, unsigned long long n, int slot)
+{
+    const unsigned long long z = tot[P_Z], zu = tot[P_ZU], zud = tot[P_ZUD], top = tot[P_TOP], infnan = tot[P_INFNAN],
+                             nan = tot[P_NAN];
+    switch (slot) {
+        case 0: return n;                    // total
+        case 1: return z;                    // zero
+        case 2: return zu - z;               // underflow
+        case 3: return zud - zu;             // denormal
+        case 4: return n - zud - top;        // normal
+        case 5: return top - infnan;         // overflow
+        case 6: return infnan - nan;         // inf
+        case 7: return nan;                  // nan
+        default: return tot[slot];           // bins
+    }
+}
+
+// Folds the workgroup's counters and table into 64 bins and hands the 72 counts to the sink: one 64-bit atomic per
+// slot into a record, or (one workgroup) the caller's record itself.  All BLOCK threads call it.
+//
+// In one launch: the separate summing kernel costs a launch (3 us of host time, 3 - 4 us and a gap on the GPU: a third
+// of a pass over 2^20 elements).  Here every slot is independent of the others: its word holds a count (bits 0 .. 47)
+// and how many workgroups have added to it (bits 48 ..), both in one addition, so the lane whose addition returns
+// the last number but one holds the slot's sum, clears the word for the next launch and passes the sum on -- to the
+// sum of the records, in the same way, and from there to the caller's record.  Two additions that return, one after
+// the other, are all a launch waits for (an arrival counter behind a wait for the additions, and exchanges that
+// fetch the sums, are four such hops and cost as much as the summing kernel); device-scope atomics take effect where
+// all XCDs meet, so no cache has to be written back.
 template <int COPIES, int BLOCK>
 __device__ __forceinline__ void hist_end(uint32_t *tbl, uint32_t *s_bins, uint32_t *s_cls, const Counts &w,
-                                         const QuantParams &p, unsigned long long *partials, uint32_t shard,
-                                         uint32_t tid)
+                                         const QuantParams &p, const HistSink &sink, uint32_t wg, uint32_t nwg, uint32_t tid)
 {
     uint32_t c[6] = {w.z, w.zu, w.zud, w.top, w.infnan, w.nan};
 #pragma unroll
@@ -121,11 +159,41 @@ __device__ __forceinline__ void hist_end(uint32_t *tbl, uint32_t *s_bins, uint32
         if (sum) atomicAdd(&s_bins[b], sum);
     }
     __syncthreads();
-    unsigned long long *rec = partials + (size_t)shard * kSlots;
-    if (tid < kSlots) {
+    if (tid >= kSlots) return;
+    if (sink.hist == nullptr) {
         const uint32_t v = tid < 8 ? s_cls[tid] : s_bins[tid - 8];
-        if (v) atomicAdd(&rec[tid], (unsigned long long)v);
+        if (v) atomicAdd(&sink.records[(size_t)(wg % sink.shards) * kSlots + tid], (unsigned long long)v);
+        return;
     }
+    // this slot's share of the workgroup: the classes are differences of the counters; `normal` counts what it is not
+    uint32_t v = 0u;
+    switch (tid) {
+        case 0: break;                                                    // total: known
+        case 1: v = s_cls[P_Z]; break;                                    // zero
+        case 2: v = s_cls[P_ZU] - s_cls[P_Z]; break;                      // underflow
+        case 3: v = s_cls[P_ZUD] - s_cls[P_ZU]; break;                    // denormal
+        case 4: v = s_cls[P_ZUD] + s_cls[P_TOP]; break;                   // everything but normal
+        case 5: v = s_cls[P_TOP] - s_cls[P_INFNAN]; break;                // overflow
+        case 6: v = s_cls[P_INFNAN] - s_cls[P_NAN]; break;                // inf
+        case 7: v = s_cls[P_NAN]; break;                                  // nan
+        default: v = s_bins[tid - 8]; break;
+    }
+    unsigned long long sum = v;
+    if (sink.records != nullptr) {
+        constexpr unsigned long long kOne = 1ull << 48;
+        auto pass = [&](uint32_t record, uint32_t adders) __attribute__((always_inline)) {
+            unsigned long long *word = &sink.records[(size_t)record * kSlots + tid];
+            const unsigned long long had = __hip_atomic_fetch_add(word, sum | kOne, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            sum += had & (kOne - 1ull);
+            if ((had >> 48) + 1ull != adders) return false;
+            __hip_atomic_store(word, 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            return true;
+        };
+        const uint32_t shard = wg % sink.shards, mine = nwg / sink.shards + (shard < nwg % sink.shards ? 1u : 0u);
+        if (!pass(shard, mine)) return;
+        if (sink.shards > 1u && !pass(sink.shards, nwg < sink.shards ? nwg : sink.shards)) return;
+    }
+    sink.hist[tid] = tid == 0 ? sink.n : tid == 4 ? sink.n - sum : sum;
 }
 
 // Sums the partial records into the caller's fmt_hist_t and clears them (fmt_stream.hip).
@@ -140,7 +208,22 @@ struct FinalizeGroup {
 };
 int launch_hist_finalize_group(const FinalizeGroup &g, int count, hipStream_t stream);
 
-// Scratch bytes the partial records need.
-constexpr size_t kHistScratchBytes = (size_t)kShards * kSlots * sizeof(unsigned long long);
+// Scratch bytes the partial records need (one more than the shards: the sums of the records of a single launch).
+constexpr size_t kHistRecordBytes = (size_t)kShards * kSlots * sizeof(unsigned long long);
+constexpr size_t kHistScratchBytes = kHistRecordBytes + kSlots * sizeof(unsigned long long);
+
+// The sink of a launch of nwg workgroups whose counts end in `hist` (n elements, below 2^48), with library scratch at
+// `scratch` (kHistScratchBytes): one workgroup writes the record itself (scratch may be null), up to `most` workgroups
+// (and fewer than 2^21: a record counts its additions in 16 bits) finish in the launch, more leave their records to launch_hist_finalize (then sink.hist is null).
+// Records in use: additions to one address take about 12 ns each, so up to 64 workgroups share one record and
+// one hop; beyond that the additions are spread and a second hop sums the records.
+inline HistSink hist_sink(void *scratch, unsigned long long n, fmt_hist_t *hist, uint64_t nwg, uint64_t most)
+{
+    unsigned long long *rec = static_cast<unsigned long long *>(scratch);
+    unsigned long long *out = reinterpret_cast<unsigned long long *>(hist);
+    if (nwg == 1) return HistSink{nullptr, out, n, 1u};
+    if (nwg <= most && nwg < ((uint64_t)1 << 21)) return HistSink{rec, out, n, nwg <= 64 ? 1u : nwg <= 1024 ? 16u : (uint32_t)kShards};
+    return HistSink{rec, nullptr, n, (uint32_t)kShards};
+}
 
 }  // namespace fmt

@@ -22,16 +22,16 @@ namespace {
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
 constexpr int kLBlock = 256;
-constexpr int kLCopies = 32;
+constexpr int kLCopies = 8;
 constexpr int kLRows = 4;                 // rows per trip (independent loads in flight)
+constexpr uint64_t kLastArrival = 4096;   // workgroups up to which the statistics are summed in the launch (see hist_end)
 
 // A: accumulators (leading dimension lda); Y: output, fp32 patterns (== A, in place) or, with PACK,
 // uint16_t codes.  VEC: 128-bit loads and full-width stores are possible for whole lanes.
 template <int MODE, bool FTZ, bool HIST, bool DEEP, bool VEC, bool PACK>
 __global__ __launch_bounds__(kLBlock) void linear_epilogue_kernel(const uint32_t *A, int64_t lda, void *Yv, int64_t ldy,
                                                                   int M, int N, const uint32_t *__restrict__ bias,
-                                                                  int rows_per_wg, QuantParams p,
-                                                                  unsigned long long *__restrict__ partials)
+                                                                  int rows_per_wg, QuantParams p, HistSink sink)
 {
     constexpr int EM = MODE == kModeInteger ? kModeInteger : kModeMagic;
     uint32_t *Y = static_cast<uint32_t *>(Yv);
@@ -108,8 +108,8 @@ __global__ __launch_bounds__(kLBlock) void linear_epilogue_kernel(const uint32_t
         }
     }
     if (HIST)
-        hist_end<kLCopies, kLBlock>(tbl, s_bins, s_cls, w, p, partials,
-                                    (blockIdx.y * gridDim.x + blockIdx.x) % kShards, tid);
+        hist_end<kLCopies, kLBlock>(tbl, s_bins, s_cls, w, p, sink, blockIdx.y * gridDim.x + blockIdx.x,
+                                    gridDim.x * gridDim.y, tid);
 }
 
 template <int MODE, bool FTZ, bool HIST, bool DEEP, bool PACK>
@@ -134,12 +134,12 @@ int launch_v(const float *A, int64_t lda, void *Y, int64_t ldy, int M, int N, co
         rows_per_wg = ((M + 65534) / 65535 + kLRows - 1) / kLRows * kLRows;
         row_groups = (M + rows_per_wg - 1) / rows_per_wg;
     }
-    unsigned long long *partials = nullptr;
+    HistSink sink{};
     if (HIST) {
         Scratch s;
         rc = get_scratch(stream, kHistScratchBytes, 0, &s);
         if (rc != FMT_OK) return rc;
-        partials = static_cast<unsigned long long *>(s.hist_partials);
+        sink = hist_sink(s.hist_partials, (unsigned long long)M * (unsigned long long)N, hist, (uint64_t)strips * row_groups, kLastArrival);
     }
     const bool vec = (reinterpret_cast<uintptr_t>(A) % 16 == 0) && (lda % 4 == 0) &&
                      (reinterpret_cast<uintptr_t>(Y) % (PACK ? 8 : 16) == 0) && (ldy % 4 == 0);
@@ -148,12 +148,12 @@ int launch_v(const float *A, int64_t lda, void *Y, int64_t ldy, int M, int N, co
     const uint32_t *b = reinterpret_cast<const uint32_t *>(bias);
     if (vec)
         hipLaunchKernelGGL((linear_epilogue_kernel<MODE, FTZ, HIST, DEEP, true, PACK>), grid, dim3(kLBlock), 0, stream, a,
-                           lda, Y, ldy, M, N, b, (int)rows_per_wg, p, partials);
+                           lda, Y, ldy, M, N, b, (int)rows_per_wg, p, sink);
     else
         hipLaunchKernelGGL((linear_epilogue_kernel<MODE, FTZ, HIST, DEEP, false, PACK>), grid, dim3(kLBlock), 0, stream, a,
-                           lda, Y, ldy, M, N, b, (int)rows_per_wg, p, partials);
+                           lda, Y, ldy, M, N, b, (int)rows_per_wg, p, sink);
     FMT_HIP_CHECK(hipGetLastError());
-    if (HIST) return launch_hist_finalize(partials, (size_t)M * (size_t)N, hist, stream);
+    if (HIST && sink.hist == nullptr) return launch_hist_finalize(sink.records, (size_t)M * (size_t)N, hist, stream);
     return FMT_OK;
 }
 

@@ -16,12 +16,11 @@
 //   * overflow, zero and flush decisions are comparisons of |x|'s pattern with thresholds
 //     computed on the host (the ties at minD/2, minN - minD/2 and maxN + ulp/2 all go to the
 //     even neighbour).
-// Statistics: each element adds one to an LDS table indexed by its 8-bit fp32 exponent field,
-// replicated 32 times so that lane l only ever touches bank l%32 (no bank or address
-// conflicts, however concentrated the distribution); the class counts are per-lane
-// compare-and-add counters.  Each workgroup folds its table into 64 bins and adds them, with one
-// 64-bit atomic per non-zero slot, into one of 64 partial records in library scratch; a second
-// tiny kernel sums the 64 records into the caller's fmt_hist_t and clears them again.
+// Statistics: each element adds one to an LDS table indexed by its 8-bit fp32 exponent field, replicated 8 times
+// (lane l uses replica l % 8); the class counts are per-lane compare-and-add counters.  Each workgroup folds its table
+// into 64 bins and adds its 72 counts, with one 64-bit atomic per slot, into one of a few partial records in library
+// scratch; the workgroup that adds last to a slot passes the sum on to the caller's fmt_hist_t (hist_end), so a pass is one
+// launch.  fmt_quantize_static, whose records are shared by all streams, sums them in a second kernel.
 #include <mutex>
 
 #include "fmt_hist.h"
@@ -44,16 +43,18 @@ typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
 
 constexpr int kBlock = FMT_STREAM_BLOCK;  // threads per workgroup
-// Replicas of the exponent table in LDS, lane l uses replica l % copies.  The fused kernel that writes fp32 keeps
-// one replica per bank (32: 35 KiB, 4 workgroups per compute unit); the statistics-only kernel and the one that writes
-// 16-bit codes run 8 to 12 % faster with 16 (17.5 KiB, 8 workgroups per compute unit), the fused fp32 one does not.
-constexpr int kCopiesFused = 32;
-constexpr int kCopiesLight = 16;
+// Replicas of the exponent table in LDS, lane l uses replica l % copies.  8: 9 KiB, so that registers and not LDS bound the
+// resident workgroups, and little to clear and fold in a pass of one tile per workgroup (2^20 elements 6.4 us fused against 7.2
+// with 32, one per bank; 2^24 24.8 against 25.9; a tensor of one value included).  The fused fp32 pass over the largest tensors,
+// whose workgroups hold four tiles and more, is the faster with 32: 2^28 elements 351 against 355 us (2^26: alike).
+constexpr int kCopiesMost = 8;
+constexpr int kCopiesLarge = 32;
+constexpr size_t kLarge = (size_t)1 << 27;   // elements from which it takes them
 constexpr int kUnroll = FMT_STREAM_UNROLL;  // independent 128-bit loads in flight per thread
-constexpr int kGridPerCU = FMT_STREAM_GRID_PER_CU;   // workgroups launched per compute unit (at most): statistics only
+constexpr int kGridPerCU = FMT_STREAM_GRID_PER_CU;   // workgroups launched per compute unit (at most): statistics, alone or with codes out
 constexpr int kGridFused = 64;           // ... fused quantize + statistics, fp32 out
-constexpr int kGridPack = 128;           // ... fused quantize + statistics, 16-bit codes out
 constexpr int kGridStore = 256;          // ... quantize only
+
 template <int MODE, bool STORE, bool FTZ, bool HIST, bool DEEP, int kCopies>
 __device__ __forceinline__ u32x4 do_vec(u32x4 v, bool valid, const QuantParams &p, uint32_t *tbl, uint32_t lane32,
                                         Counts &w)
@@ -74,13 +75,11 @@ __device__ __forceinline__ u32x4 do_vec(u32x4 v, bool valid, const QuantParams &
 // for x and y misaligned relative to each other: the whole range goes one dword per lane.
 // PACK: y holds the format's 16-bit codes instead of fp32 values (two bytes written per element; the
 // vector body then needs y + head 8-byte aligned).
-template <int MODE, bool STORE, bool FTZ, bool HIST, bool DEEP, bool VEC, bool PACK>
+template <int MODE, bool STORE, bool FTZ, bool HIST, bool DEEP, bool VEC, bool PACK, int kCopies>
 __global__ __launch_bounds__(kBlock) void stream_kernel(const uint32_t *__restrict__ x, uint32_t *__restrict__ y,
-                                                        size_t n, size_t head, size_t nvec, QuantParams p,
-                                                        unsigned long long *__restrict__ partials)
+                                                        size_t n, size_t head, size_t nvec, QuantParams p, HistSink sink)
 {
     constexpr int EM = MODE == kModeInteger ? kModeInteger : kModeMagic;   // encode_bits' variant
-    constexpr int kCopies = (STORE && !PACK) ? kCopiesFused : kCopiesLight;
     uint16_t *__restrict__ y16 = reinterpret_cast<uint16_t *>(y);
     auto put = [&](size_t vec_index, u32x4 o) {
         if (PACK) {
@@ -105,7 +104,12 @@ __global__ __launch_bounds__(kBlock) void stream_kernel(const uint32_t *__restri
     const uint32_t lane32 = tid & (kCopies - 1);
     Counts w;
 
-    if (HIST) hist_begin<kCopies, kBlock>(tbl, s_bins, s_cls, tid);
+    // leftovers around the vector body, [0, head) and [head + 4*nvec, n): one per lane of the first wave, loaded before
+    // anything else so that the load is not a chain of its own at the end
+    const bool edge = VEC && blockIdx.x == 0 && tid < 64 && tid < n - 4 * nvec;
+    const size_t edge_at = tid < head ? tid : 4 * nvec + tid;
+    uint32_t edge_u = 0u;
+    if (edge) edge_u = x[edge_at];
 
     if (VEC) {
         const u32x4 *xv = reinterpret_cast<const u32x4 *>(x + head);
@@ -113,11 +117,31 @@ __global__ __launch_bounds__(kBlock) void stream_kernel(const uint32_t *__restri
         // Every lane of the workgroup runs the same trips, and all tiles but the last are full.
         constexpr size_t kTileVec = (size_t)kBlock * kUnroll;
         const size_t full_tiles = nvec / kTileVec;
-        for (size_t t = blockIdx.x; t < full_tiles; t += gridDim.x) {
+        u32x4 v[kUnroll];
+        auto load = [&](size_t t) __attribute__((always_inline)) {
             const size_t i = t * kTileVec + tid;
-            u32x4 v[kUnroll];
+            if (t < full_tiles) {
 #pragma unroll
-            for (int k = 0; k < kUnroll; ++k) v[k] = __builtin_nontemporal_load(xv + i + k * kBlock);
+                for (int k = 0; k < kUnroll; ++k) v[k] = __builtin_nontemporal_load(xv + i + k * kBlock);
+            } else {
+#pragma unroll
+                for (int k = 0; k < kUnroll; ++k) {
+                    v[k] = u32x4{0u, 0u, 0u, 0u};
+                    if (i + k * kBlock < nvec) v[k] = __builtin_nontemporal_load(xv + i + k * kBlock);
+                }
+            }
+        };
+        // With statistics a tile's loads are issued ahead of the work on the tile before it, the first tile's ahead of the
+        // clearing of the table (2^25 elements: statistics alone 27.3 -> 22.4 us, fused 50 -> 47); without them a workgroup
+        // has one tile, and the short kernel is the better one (2^28: 344 against 347 us).
+        size_t t = blockIdx.x;
+        if (HIST) {
+            load(t);
+            hist_begin<kCopies, kBlock>(tbl, s_bins, s_cls, tid);
+        }
+        while (t < full_tiles) {
+            if (!HIST) load(t);
+            const size_t i = t * kTileVec + tid;
             uint32_t amax = 0u;
 #pragma unroll
             for (int k = 0; k < kUnroll; ++k) {
@@ -138,31 +162,26 @@ __global__ __launch_bounds__(kBlock) void stream_kernel(const uint32_t *__restri
                     for (int j = 0; j < 4; ++j) flat[4 * k + j] = v[k][j];
                 account_run_top(flat, amax, p, w);
             }
+            t += gridDim.x;
+            if (HIST && t * kTileVec < nvec) load(t);
         }
-        if (blockIdx.x == full_tiles % gridDim.x && full_tiles * kTileVec < nvec) {
+        if (t == full_tiles && full_tiles * kTileVec < nvec) {
             // the ragged last tile, lane by lane
+            if (!HIST) load(t);
 #pragma unroll
             for (int k = 0; k < kUnroll; ++k) {
                 const size_t i = full_tiles * kTileVec + k * kBlock + tid;
                 const bool valid = i < nvec;
-                u32x4 v = {0u, 0u, 0u, 0u};
-                if (valid) v = __builtin_nontemporal_load(xv + i);
-                u32x4 o = do_vec<MODE, STORE, FTZ, HIST, DEEP, kCopies>(v, valid, p, tbl, lane32, w);
+                u32x4 o = do_vec<MODE, STORE, FTZ, HIST, DEEP, kCopies>(v[k], valid, p, tbl, lane32, w);
                 if (STORE && valid) put(i, o);
             }
         }
         if (blockIdx.x == 0 && tid < 64) {
-            // leftovers: [0, head) and [head + 4*nvec, n)
-            const size_t body_end = head + 4 * nvec;
-            const size_t ntail = n - body_end;
-            size_t idx = tid < head ? tid : body_end + (tid - head);
-            const bool valid = tid < head + ntail;
-            if (!valid) idx = 0;
-            const uint32_t u = valid ? x[idx] : 0u;
-            if (HIST) account<DEEP, kCopies>(u & 0x7FFFFFFFu, valid, p, tbl, lane32, w);
-            if (STORE && valid) put_one(idx, quantize_bits<MODE, FTZ>(u, p));
+            if (HIST) account<DEEP, kCopies>(edge_u & 0x7FFFFFFFu, edge, p, tbl, lane32, w);
+            if (STORE && edge) put_one(edge_at, quantize_bits<MODE, FTZ>(edge_u, p));
         }
     } else {
+        if (HIST) hist_begin<kCopies, kBlock>(tbl, s_bins, s_cls, tid);
         const size_t stride = (size_t)gridDim.x * kBlock;
         // every lane runs the same number of trips
         const size_t trips = (n + stride - 1) / stride;
@@ -175,7 +194,7 @@ __global__ __launch_bounds__(kBlock) void stream_kernel(const uint32_t *__restri
         }
     }
 
-    if (HIST) hist_end<kCopies, kBlock>(tbl, s_bins, s_cls, w, p, partials, blockIdx.x % kShards, tid);
+    if (HIST) hist_end<kCopies, kBlock>(tbl, s_bins, s_cls, w, p, sink, blockIdx.x, gridDim.x, tid);
 }
 
 // Sums the shard records into the caller's fmt_hist_t and clears them for the next call (one
@@ -203,23 +222,7 @@ __device__ __forceinline__ void finalize_body(unsigned long long *__restrict__ p
         tot[tid] = s;
     }
     __syncthreads();
-    if (tid < kSlots) {
-        unsigned long long v;
-        const unsigned long long z = tot[P_Z], zu = tot[P_ZU], zud = tot[P_ZUD], top = tot[P_TOP],
-                                 infnan = tot[P_INFNAN], nan = tot[P_NAN];
-        switch (tid) {
-            case 0: v = n; break;                    // total
-            case 1: v = z; break;                    // zero
-            case 2: v = zu - z; break;               // underflow
-            case 3: v = zud - zu; break;             // denormal
-            case 4: v = n - zud - top; break;        // normal
-            case 5: v = top - infnan; break;         // overflow
-            case 6: v = infnan - nan; break;         // inf
-            case 7: v = nan; break;                  // nan
-            default: v = tot[tid]; break;            // bins
-        }
-        hist[tid] = v;
-    }
+    if (tid < kSlots) hist[tid] = hist_slot(tot, n, tid);
 }
 
 __global__ __launch_bounds__(1024) void finalize_kernel(unsigned long long *__restrict__ partials, int nrec,
@@ -250,11 +253,17 @@ int launch_hist_finalize(unsigned long long *partials, size_t n, fmt_hist_t *his
     return FMT_OK;
 }
 
+// Workgroups up to which the statistics end in the pass itself: any grid (2^20 elements: one launch of 6.4 us against
+// 8.7 us for two; 2^25: 46.7 against 50.0; 2^28: alike).
+constexpr uint64_t kOneLaunch = ~(uint64_t)0;
+
 template <int MODE, bool STORE, bool FTZ, bool HIST, bool DEEP, bool VEC, bool PACK>
 static int launch_variant(const float *x, void *y, size_t n, size_t head, size_t nvec, const QuantParams &p,
                           fmt_hist_t *hist, hipStream_t stream, unsigned long long *fixed_partials)
 {
-    auto kern = stream_kernel<MODE, STORE, FTZ, HIST, DEEP, VEC, PACK>;
+    auto kern = stream_kernel<MODE, STORE, FTZ, HIST, DEEP, VEC, PACK, kCopiesMost>;
+    if constexpr (HIST && STORE && !PACK && VEC)
+        if (n >= kLarge) kern = stream_kernel<MODE, STORE, FTZ, HIST, DEEP, VEC, PACK, kCopiesLarge>;
     int cus = 0;
     int rc = device_cu_count(&cus);
     if (rc != FMT_OK) return rc;
@@ -262,10 +271,9 @@ static int launch_variant(const float *x, void *y, size_t n, size_t head, size_t
     const size_t want = (n + per_block - 1) / per_block;
     // Workgroups per compute unit, measured on 2^28 elements: a pure stream likes one 16 KiB tile per
     // workgroup (6.4 TB/s against 5.9 with 16 per CU: the hardware balances the tail); every workgroup
-    // of a statistics pass pays for clearing and folding its LDS table, so the read-only pass keeps 16
-    // per CU (6.3 TB/s) and the fused pass settles in between (64 per CU: 6.07 against 5.77 TB/s; 128 per
-    // CU when it writes 16-bit codes, where 8 workgroups fit a compute unit).
-    const size_t cap = (size_t)cus * (HIST ? (STORE ? (PACK ? kGridPack : kGridFused) : kGridPerCU) : kGridStore);
+    // of a statistics pass pays for clearing and folding its LDS table, so the read-only pass and the one that writes
+    // codes keep 16 per CU (165 us against 178 with 128; 283 against 290) and the fused fp32 pass takes 64 (355 against 370).
+    const size_t cap = (size_t)cus * (HIST ? (STORE && !PACK ? kGridFused : kGridPerCU) : kGridStore);
     size_t g = want;
     if (HIST) {
         // mid-size tensors: at least four tiles per workgroup (one tile does not pay for the table),
@@ -276,17 +284,21 @@ static int launch_variant(const float *x, void *y, size_t n, size_t head, size_t
     }
     int grid = (int)(g < cap ? g : cap);
     if (grid < 1) grid = 1;
-    unsigned long long *partials = fixed_partials;
-    if (HIST && partials == nullptr) {
-        Scratch s;
-        rc = get_scratch(stream, kHistScratchBytes, 0, &s);
-        if (rc != FMT_OK) return rc;
-        partials = static_cast<unsigned long long *>(s.hist_partials);
+    HistSink sink{};
+    if (HIST) {
+        void *records = fixed_partials;
+        if (records == nullptr) {
+            Scratch s;
+            rc = get_scratch(stream, kHistScratchBytes, 0, &s);
+            if (rc != FMT_OK) return rc;
+            records = s.hist_partials;
+        }
+        sink = hist_sink(records, n, hist, (uint64_t)grid, fixed_partials ? 0 : kOneLaunch);
     }
     hipLaunchKernelGGL(kern, dim3(grid), dim3(kBlock), 0, stream, reinterpret_cast<const uint32_t *>(x),
-                       reinterpret_cast<uint32_t *>(y), n, head, nvec, p, partials);
+                       reinterpret_cast<uint32_t *>(y), n, head, nvec, p, sink);
     FMT_HIP_CHECK(hipGetLastError());
-    if (HIST) return launch_hist_finalize(partials, n, hist, stream);
+    if (HIST && sink.hist == nullptr) return launch_hist_finalize(sink.records, n, hist, stream);
     return FMT_OK;
 }
 
@@ -375,16 +387,14 @@ int launch_stream_static(const float *x, float *y, size_t n, const QuantParams &
                          hipStream_t stream)
 {
     unsigned long long *rec = nullptr;
-    if (hist != nullptr) {
+    if (hist != nullptr && n > 0) {
         int rc = static_partials(&rec);
         if (rc != FMT_OK) return rc;
         // The array keeps whatever the last call on this GPU left in it.  A completed call leaves zeros
         // (its last kernel clears what it has summed), a call that failed half-way may not have: start clean.
         // A kernel, not a memset, so that the call can be recorded into a graph.
-        if (n > 0) {
-            hipLaunchKernelGGL(clear_records_kernel, dim3(kShards * kSlots / 256), dim3(256), 0, stream, rec, kShards * kSlots);
-            FMT_HIP_CHECK(hipGetLastError());
-        }
+        hipLaunchKernelGGL(clear_records_kernel, dim3(kShards * kSlots / 256), dim3(256), 0, stream, rec, kShards * kSlots);
+        FMT_HIP_CHECK(hipGetLastError());
     }
     return launch_stream(x, y, n, p, ftz, hist, stream, false, rec);
 }

@@ -394,3 +394,29 @@ def test_config2_every_tensor_of_a_step(fmt):
             got, ho = fmt.hist_to_dict(hist), oracle.histogram(flat, e, m)
             assert all(got[k] == ho[k] for k in fmt.CLASS_NAMES), (name, e, m, d, got, ho)
             assert np.array_equal(got["bins"], ho["bins"]), (name, e, m, d)
+
+
+@pytest.mark.parametrize("tiles,rest", [(0, 9), (1, 0), (2, 3), (64, 0), (64, 1), (65, 4095), (1024, 1), (4 * 1024 + 1, 17)])
+@pytest.mark.parametrize("offset", [0, 1])
+def test_statistics_in_one_launch(fmt, tiles, rest, offset):
+    """The statistics are summed by the pass itself: one workgroup (up to a tile of 4096 elements), one record (64 workgroups),
+    records summed by a second addition (more), several tiles per workgroup -- aligned and not, twice in a row with the
+    sizes and kinds of pass mixed, so that whatever a launch leaves in the records shows in the next one."""
+    n = 4096 * tiles + rest
+    x = mixed(n + offset, 40 + tiles + offset)[offset:]
+    buf = torch.empty(n + offset, device="cuda")
+    buf[offset:] = dev(x)
+    xd = buf[offset:]
+    want = oracle.histogram(x, 6, 9)
+    small = mixed(70001, 5)
+    small_d, want_small = dev(small), oracle.histogram(small, 5, 10)
+    for _ in range(2):
+        hist = [fmt.new_hist().fill_(-1) for _ in range(4)]
+        y = fmt.fmt_quantize(xd, (6, 9, True), hist=hist[0])
+        fmt.fmt_histogram(xd, (6, 9, True), hist=hist[1])
+        fmt.fmt_quantize(small_d, (5, 10, False), hist=hist[2])
+        fmt.fmt_pack16(xd, (6, 9, True), hist=hist[3])
+        torch.cuda.synchronize()
+        assert_same_values(y.cpu().numpy(), oracle.quantize(x, 6, 9, True), "n = %d" % n)
+        for i, w in ((0, want), (1, want), (2, want_small), (3, want)):
+            assert_same_hist(fmt, hist[i], w, "n = %d, pass %d" % (n, i))
