@@ -15,7 +15,7 @@ from typing import NamedTuple, Optional
 # runtime, and the tensors whose pointers are handed to libfmt live in that runtime's context.
 # Loading torch first makes libfmt bind to the same runtime (same SONAME) instead of bringing a
 # second one into the process, which would not see torch's device.
-import torch  # noqa: F401
+import torch
 
 _HERE = os.path.dirname(os.path.abspath(__file__))
 # FMT_LIB_PATH selects another build of the same library (tuning builds); default: the in-tree one
@@ -151,9 +151,18 @@ def _load() -> ctypes.CDLL:
 _lib = _load()
 
 
+_cfmt_made = {}      # the C structs of the formats seen so far (at most a few; never written to)
+
+
 def _cfmt(f) -> _CFormat:
     e, m, d = f
-    return _CFormat(int(e), int(m), 1 if d else 0)
+    key = (int(e), int(m), 1 if d else 0)
+    c = _cfmt_made.get(key)
+    if c is None:
+        c = _CFormat(*key)
+        if len(_cfmt_made) < 1024:
+            _cfmt_made[key] = c
+    return c
 
 
 def status_string(status: int) -> str:
@@ -166,14 +175,25 @@ def _check(rc: int, where: str) -> None:
 
 
 def _stream_ptr(stream) -> int:
-    import torch
     if stream is None:
         stream = torch.cuda.current_stream()
     return int(stream.cuda_stream)
 
 
+# A small call is bound by the host: 3 us per launch and, with torch.cuda.current_stream(), which makes a Stream object
+# (2.8 us), 5 us in this module.  torch's own handle lookup for the current device's current stream takes 0.3 us.
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+_raw_device = getattr(torch._C, "_cuda_getDevice", None)
+
+
+def _call_stream(stream) -> int:
+    """_stream_ptr for calls that have been handed a GPU tensor (so torch's runtime is up)."""
+    if stream is None and _raw_stream is not None and _raw_device is not None:
+        return _raw_stream(_raw_device())
+    return _stream_ptr(stream)
+
+
 def _dev_f32(t, name: str):
-    import torch
     if not isinstance(t, torch.Tensor) or not t.is_cuda or t.dtype != torch.float32:
         raise TypeError("%s must be a float32 tensor on the GPU" % name)
     return t
@@ -181,7 +201,6 @@ def _dev_f32(t, name: str):
 
 def new_hist(device="cuda"):
     """Device buffer for one fmt_hist_t (72 x int64)."""
-    import torch
     return torch.empty(8 + FMT_NBINS, dtype=torch.int64, device=device)
 
 
@@ -200,7 +219,6 @@ def fmt_quantize(x, fmt, out=None, hist=None, exp_lo: int = EXP_LO_DEFAULT, stre
     produced in the same pass.  Asynchronous on ``stream`` (default: torch's current stream).
     ``static=True`` calls ``fmt_quantize_static``, the entry point that allocates nothing (pass ``out``,
     or this wrapper's own ``torch.empty_like`` allocates the result)."""
-    import torch
     _dev_f32(x, "x")
     if not x.is_contiguous():
         raise ValueError("x must be contiguous")
@@ -215,14 +233,13 @@ def fmt_quantize(x, fmt, out=None, hist=None, exp_lo: int = EXP_LO_DEFAULT, stre
             raise TypeError("hist must be a GPU int64 tensor of 72 elements")
         hp = hist.data_ptr()
     entry = _lib.fmt_quantize_static if static else _lib.fmt_quantize
-    rc = entry(x.data_ptr(), out.data_ptr(), x.numel(), _cfmt(fmt), hp, int(exp_lo), _stream_ptr(stream))
+    rc = entry(x.data_ptr(), out.data_ptr(), x.numel(), _cfmt(fmt), hp, int(exp_lo), _call_stream(stream))
     _check(rc, "fmt_quantize_static" if static else "fmt_quantize")
     return out
 
 
 def fmt_histogram(x, fmt, hist=None, exp_lo: int = EXP_LO_DEFAULT, stream=None):
     """Per-tensor class counts and 64 binade bins (Sec. V) into a device fmt_hist_t; returns it."""
-    import torch
     _dev_f32(x, "x")
     if not x.is_contiguous():
         raise ValueError("x must be contiguous")
@@ -230,7 +247,7 @@ def fmt_histogram(x, fmt, hist=None, exp_lo: int = EXP_LO_DEFAULT, stream=None):
         hist = new_hist(x.device)
     if hist.dtype != torch.int64 or hist.numel() != 8 + FMT_NBINS or not hist.is_cuda:
         raise TypeError("hist must be a GPU int64 tensor of 72 elements")
-    rc = _lib.fmt_histogram(x.data_ptr(), x.numel(), _cfmt(fmt), hist.data_ptr(), int(exp_lo), _stream_ptr(stream))
+    rc = _lib.fmt_histogram(x.data_ptr(), x.numel(), _cfmt(fmt), hist.data_ptr(), int(exp_lo), _call_stream(stream))
     _check(rc, "fmt_histogram")
     return hist
 
@@ -253,7 +270,7 @@ def _gemm_call(entry, where, A, B, fmt, transA, transB, out, stream):
     ldb = B.stride(0) if B.shape[0] > 1 else max(B.shape[1], 1)
     ldc = out.stride(0) if M > 1 else max(N, 1)
     rc = entry(int(transA), int(transB), M, N, K, A.data_ptr(), lda, B.data_ptr(), ldb,
-               out.data_ptr(), ldc, _cfmt(fmt), _stream_ptr(stream))
+               out.data_ptr(), ldc, _cfmt(fmt), _call_stream(stream))
     _check(rc, where)
     return out
 
@@ -292,7 +309,6 @@ def fmt_prepare(X, fmt, trans: bool = False, out=None, stream=None) -> PreparedO
     """Rounds the 2-D float32 GPU tensor X to the format once and stores it as a prepared operand of
     X.shape[0] rows (``trans=False``) or, transposed, of X.shape[1] rows (``trans=True``).  ``out`` may be
     a uint8 GPU tensor (256-byte aligned, at least :func:`fmt_operand_bytes` long) to prepare into."""
-    import torch
     _dev_f32(X, "X")
     if X.dim() != 2 or (X.shape[1] > 1 and X.stride(1) != 1):
         raise ValueError("X must be 2-D with unit column stride")
@@ -305,7 +321,7 @@ def fmt_prepare(X, fmt, trans: bool = False, out=None, stream=None) -> PreparedO
     desc = _COperand()
     ld = X.stride(0) if X.shape[0] > 1 else max(X.shape[1], 1)
     rc = _lib.fmt_prepare(X.data_ptr(), ld, int(bool(trans)), rows, k, _cfmt(fmt), out.data_ptr(), out.numel(),
-                          ctypes.byref(desc), _stream_ptr(stream))
+                          ctypes.byref(desc), _call_stream(stream))
     _check(rc, "fmt_prepare")
     return PreparedOperand(out, desc)
 
@@ -313,7 +329,6 @@ def fmt_prepare(X, fmt, trans: bool = False, out=None, stream=None) -> PreparedO
 def fmt_prepare_pair(X, fmt, out=None, out_t=None, stream=None):
     """Both orientations of the 2-D float32 GPU tensor X as prepared operands in one call: returns
     (X as stored, X transposed), the operands :func:`fmt_prepare` gives with ``trans=False`` and ``trans=True``."""
-    import torch
     _dev_f32(X, "X")
     if X.dim() != 2 or (X.shape[1] > 1 and X.stride(1) != 1):
         raise ValueError("X must be 2-D with unit column stride")
@@ -328,14 +343,13 @@ def fmt_prepare_pair(X, fmt, out=None, out_t=None, stream=None):
     d0, d1 = _COperand(), _COperand()
     ld = X.stride(0) if rows > 1 else max(cols, 1)
     rc = _lib.fmt_prepare_pair(X.data_ptr(), ld, rows, cols, _cfmt(fmt), bufs[0].data_ptr(), bufs[0].numel(), ctypes.byref(d0),
-                               bufs[1].data_ptr(), bufs[1].numel(), ctypes.byref(d1), _stream_ptr(stream))
+                               bufs[1].data_ptr(), bufs[1].numel(), ctypes.byref(d1), _call_stream(stream))
     _check(rc, "fmt_prepare_pair")
     return PreparedOperand(bufs[0], d0), PreparedOperand(bufs[1], d1)
 
 
 def _pair_batch_args(Xs, fmt, outs, outs_t):
     """Checks and marshals what the two batch prepare calls share: the matrices and the operand buffers."""
-    import torch
     n = len(Xs)
     outs = [None] * n if outs is None else list(outs)
     outs_t = [None] * n if outs_t is None else list(outs_t)
@@ -388,7 +402,7 @@ def fmt_prepare_pair_batch(Xs, fmt, outs=None, outs_t=None, stream=None):
     Xs = list(Xs)
     bufs, bufs_t, c = _pair_batch_args(Xs, fmt, outs, outs_t)
     rc = _lib.fmt_prepare_pair_batch(len(Xs), c["X"], c["ld"], c["rows"], c["cols"], _cfmt(fmt), c["data"], c["bytes"], c["op"],
-                                     c["data_t"], c["bytes_t"], c["op_t"], _stream_ptr(stream))
+                                     c["data_t"], c["bytes_t"], c["op_t"], _call_stream(stream))
     _check(rc, "fmt_prepare_pair_batch")
     return _pair_batch_result(len(Xs), bufs, bufs_t, c)
 
@@ -406,7 +420,6 @@ def fmt_quantize_prepare_pair_batch(Xs, fmt, Ys, hists, exp_lo: int = EXP_LO_DEF
         _dev_f32(Y, "Y")
         if Y.dim() != 2 or tuple(Y.shape) != tuple(X.shape) or (Y.shape[1] > 1 and Y.stride(1) != 1):
             raise ValueError("every Y must have the shape of its X and unit column stride")
-    import torch
     for h in hists:
         if not isinstance(h, torch.Tensor) or h.dtype != torch.int64 or h.numel() != 8 + FMT_NBINS or not h.is_cuda:
             raise TypeError("every hist must be a GPU int64 tensor of 72 elements")
@@ -417,14 +430,13 @@ def fmt_quantize_prepare_pair_batch(Xs, fmt, Ys, hists, exp_lo: int = EXP_LO_DEF
     hp = (ctypes.c_void_p * m)(*[h.data_ptr() for h in hists])
     rc = _lib.fmt_quantize_prepare_pair_batch(n, c["X"], c["ld"], c["rows"], c["cols"], _cfmt(fmt), yp, ldy, hp, int(exp_lo),
                                               c["data"], c["bytes"], c["op"], c["data_t"], c["bytes_t"], c["op_t"],
-                                              _stream_ptr(stream))
+                                              _call_stream(stream))
     _check(rc, "fmt_quantize_prepare_pair_batch")
     return _pair_batch_result(n, bufs, bufs_t, c)
 
 
 def fmt_gemm_prepared(A: PreparedOperand, B: PreparedOperand, out=None, stream=None):
     """C[i][j] = sum_k Q(a)[i][k] Q(b)[j][k] on two prepared operands (FMACS, Sec. III-B): one launch."""
-    import torch
     M, N = A.rows, B.rows
     if out is None:
         out = torch.empty((M, N), dtype=torch.float32, device=A.buf.device)
@@ -432,7 +444,7 @@ def fmt_gemm_prepared(A: PreparedOperand, B: PreparedOperand, out=None, stream=N
     if out.dim() != 2 or tuple(out.shape) != (M, N) or (N > 1 and out.stride(1) != 1):
         raise ValueError("out must be an M x N tensor with unit column stride")
     ldc = out.stride(0) if M > 1 else max(N, 1)
-    rc = _lib.fmt_gemm_prepared(ctypes.byref(A.desc), ctypes.byref(B.desc), out.data_ptr(), ldc, _stream_ptr(stream))
+    rc = _lib.fmt_gemm_prepared(ctypes.byref(A.desc), ctypes.byref(B.desc), out.data_ptr(), ldc, _call_stream(stream))
     _check(rc, "fmt_gemm_prepared")
     return out
 
@@ -441,7 +453,6 @@ def fmt_gemm_prepared_batch(A, B, out=None, stream=None):
     """The products C[i] = A[i] B[i]^T of two equally long sequences of prepared operands in one call; the small
     ones share kernel launches (Sec. IV-A: the three products of every layer are known once the step's tensors
     are rounded).  Returns the list of results."""
-    import torch
     A, B = list(A), list(B)
     n = len(A)
     if len(B) != n:
@@ -461,7 +472,7 @@ def fmt_gemm_prepared_batch(A, B, out=None, stream=None):
     PB = (ctypes.POINTER(_COperand) * max(n, 1))(*[ctypes.pointer(b.desc) for b in B])
     PC = (ctypes.c_void_p * max(n, 1))(*[c.data_ptr() for c in out])
     LD = (ctypes.c_int64 * max(n, 1))(*ldc)
-    rc = _lib.fmt_gemm_prepared_batch(n, PA, PB, PC, LD, _stream_ptr(stream))
+    rc = _lib.fmt_gemm_prepared_batch(n, PA, PB, PC, LD, _call_stream(stream))
     _check(rc, "fmt_gemm_prepared_batch")
     return out
 
@@ -471,7 +482,6 @@ def fmt_linear_prepared(X: PreparedOperand, W: PreparedOperand, bias, out=None, 
     """:func:`fmt_linear` on operands prepared with :func:`fmt_prepare` (X: the batch rows, W: the rows of the
     weight matrix): product, bias, output roundings and the statistics of the output, with no rounding or
     layout pass over X and W in the call (Sec. IV-A)."""
-    import torch
     M, N = X.rows, W.rows
     bp = None
     if bias is not None:
@@ -491,7 +501,7 @@ def fmt_linear_prepared(X: PreparedOperand, W: PreparedOperand, bias, out=None, 
         hp = hist.data_ptr()
     ldy = out.stride(0) if M > 1 else max(N, 1)
     rc = _lib.fmt_linear_prepared(ctypes.byref(X.desc), ctypes.byref(W.desc), bp, out.data_ptr(), ldy, hp, int(exp_lo),
-                                  _stream_ptr(stream))
+                                  _call_stream(stream))
     _check(rc, "fmt_linear_prepared")
     return out
 
@@ -506,7 +516,6 @@ def fmt_linear(X, W, bias, fmt, out=None, hist=None, exp_lo: int = EXP_LO_DEFAUL
     """Quantized fully connected layer of Sec. IV-A: Y = R(R(R(X) R(W)^T) + R(b)) with X [batch, in],
     W [out, in], bias [out] or None.  With a ``hist`` buffer the statistics of t = R(acc) + R(b),
     the values entering the last rounding, are produced in the same pass."""
-    import torch
     for t, name in ((X, "X"), (W, "W")):
         _dev_f32(t, name)
         if t.dim() != 2 or (t.shape[1] > 1 and t.stride(1) != 1):
@@ -535,20 +544,18 @@ def fmt_linear(X, W, bias, fmt, out=None, hist=None, exp_lo: int = EXP_LO_DEFAUL
     ldw = W.stride(0) if N > 1 else max(K, 1)
     ldy = out.stride(0) if M > 1 else max(N, 1)
     rc = _lib.fmt_linear(M, N, K, X.data_ptr(), ldx, W.data_ptr(), ldw, bp, out.data_ptr(), ldy, _cfmt(fmt),
-                         hp, int(exp_lo), _stream_ptr(stream))
+                         hp, int(exp_lo), _call_stream(stream))
     _check(rc, "fmt_linear")
     return out
 
 
 def _dev_codes(t, name: str):
-    import torch
     if not isinstance(t, torch.Tensor) or t.dtype not in (torch.int16, torch.uint16) or not t.is_cuda:
         raise TypeError("%s must be a GPU int16 (or uint16) tensor holding the 16-bit codes" % name)
     return t
 
 
 def _hist_ptr(hist):
-    import torch
     if hist is None:
         return None
     if hist.dtype != torch.int64 or hist.numel() != 8 + FMT_NBINS or not hist.is_cuda:
@@ -559,7 +566,6 @@ def _hist_ptr(hist):
 def fmt_pack16(x, fmt, out=None, hist=None, exp_lo: int = EXP_LO_DEFAULT, stream=None):
     """:func:`fmt_quantize` with the result stored as the format's own 16-bit codes (Sec. III;
     needs 1 + e + m <= 16): returns an int16 tensor of x's shape holding the code bit patterns."""
-    import torch
     _dev_f32(x, "x")
     if not x.is_contiguous():
         raise ValueError("x must be contiguous")
@@ -569,14 +575,13 @@ def fmt_pack16(x, fmt, out=None, hist=None, exp_lo: int = EXP_LO_DEFAULT, stream
     if not out.is_contiguous() or out.numel() != x.numel():
         raise ValueError("out must be contiguous and as large as x")
     rc = _lib.fmt_pack16(x.data_ptr(), out.data_ptr(), x.numel(), _cfmt(fmt), _hist_ptr(hist), int(exp_lo),
-                         _stream_ptr(stream))
+                         _call_stream(stream))
     _check(rc, "fmt_pack16")
     return out
 
 
 def fmt_unpack16(codes, fmt, out=None, stream=None):
     """fp32 values of 16-bit codes (the inverse of :func:`fmt_pack16` on its results)."""
-    import torch
     _dev_codes(codes, "codes")
     if not codes.is_contiguous():
         raise ValueError("codes must be contiguous")
@@ -585,14 +590,13 @@ def fmt_unpack16(codes, fmt, out=None, stream=None):
     _dev_f32(out, "out")
     if not out.is_contiguous() or out.numel() != codes.numel():
         raise ValueError("out must be contiguous and as large as codes")
-    rc = _lib.fmt_unpack16(codes.data_ptr(), out.data_ptr(), codes.numel(), _cfmt(fmt), _stream_ptr(stream))
+    rc = _lib.fmt_unpack16(codes.data_ptr(), out.data_ptr(), codes.numel(), _cfmt(fmt), _call_stream(stream))
     _check(rc, "fmt_unpack16")
     return out
 
 
 def fmt_linear_pack16(X, W, bias, fmt, out=None, hist=None, exp_lo: int = EXP_LO_DEFAULT, stream=None):
     """:func:`fmt_linear` with the output stored as 16-bit codes (int16 tensor [batch, out])."""
-    import torch
     for t, name in ((X, "X"), (W, "W")):
         _dev_f32(t, name)
         if t.dim() != 2 or (t.shape[1] > 1 and t.stride(1) != 1):
@@ -616,7 +620,7 @@ def fmt_linear_pack16(X, W, bias, fmt, out=None, hist=None, exp_lo: int = EXP_LO
     ldw = W.stride(0) if N > 1 else max(K, 1)
     ldy = out.stride(0) if M > 1 else max(N, 1)
     rc = _lib.fmt_linear_pack16(M, N, K, X.data_ptr(), ldx, W.data_ptr(), ldw, bp, out.data_ptr(), ldy, _cfmt(fmt),
-                                _hist_ptr(hist), int(exp_lo), _stream_ptr(stream))
+                                _hist_ptr(hist), int(exp_lo), _call_stream(stream))
     _check(rc, "fmt_linear_pack16")
     return out
 
@@ -649,42 +653,39 @@ def fmt_conv2d_fwd(X, W, fmt, pad=1, stride=1, out=None, stream=None):
     """Y = conv(Q(X), Q(W)) with exact products and fp32 accumulation (Sec. IV-A); X [n,c,h,w], W [k,c,r,s],
     Y [n,k,P,Q].  No fp32 patch matrix is formed: the library gathers the patches from the rounded tensor
     straight into its 16-bit operand layout."""
-    import torch
     _dense4(X, "X")
     _dense4(W, "W")
     g, yshape = _conv_geom(X.shape, W.shape, pad, stride)
     if out is None:
         out = torch.empty(yshape, dtype=torch.float32, device=X.device)
     _dense4(out, "out", yshape)
-    _check(_lib.fmt_conv2d_fwd(g, X.data_ptr(), W.data_ptr(), out.data_ptr(), _cfmt(fmt), _stream_ptr(stream)),
+    _check(_lib.fmt_conv2d_fwd(g, X.data_ptr(), W.data_ptr(), out.data_ptr(), _cfmt(fmt), _call_stream(stream)),
            "fmt_conv2d_fwd")
     return out
 
 
 def fmt_conv2d_dgrad(dY, W, xshape, fmt, pad=1, stride=1, out=None, stream=None):
     """dX of the same convolution from dY [n,k,P,Q] and W [k,c,r,s]; ``xshape`` = (n, c, h, w)."""
-    import torch
     _dense4(W, "W")
     g, yshape = _conv_geom(xshape, W.shape, pad, stride)
     _dense4(dY, "dY", yshape)
     if out is None:
         out = torch.empty(tuple(int(v) for v in xshape), dtype=torch.float32, device=dY.device)
     _dense4(out, "out", xshape)
-    _check(_lib.fmt_conv2d_dgrad(g, dY.data_ptr(), W.data_ptr(), out.data_ptr(), _cfmt(fmt), _stream_ptr(stream)),
+    _check(_lib.fmt_conv2d_dgrad(g, dY.data_ptr(), W.data_ptr(), out.data_ptr(), _cfmt(fmt), _call_stream(stream)),
            "fmt_conv2d_dgrad")
     return out
 
 
 def fmt_conv2d_wgrad(dY, X, wshape, fmt, pad=1, stride=1, out=None, stream=None):
     """dW of the same convolution from dY [n,k,P,Q] and X [n,c,h,w]; ``wshape`` = (k, c, r, s)."""
-    import torch
     _dense4(X, "X")
     g, yshape = _conv_geom(X.shape, wshape, pad, stride)
     _dense4(dY, "dY", yshape)
     if out is None:
         out = torch.empty(tuple(int(v) for v in wshape), dtype=torch.float32, device=dY.device)
     _dense4(out, "out", wshape)
-    _check(_lib.fmt_conv2d_wgrad(g, dY.data_ptr(), X.data_ptr(), out.data_ptr(), _cfmt(fmt), _stream_ptr(stream)),
+    _check(_lib.fmt_conv2d_wgrad(g, dY.data_ptr(), X.data_ptr(), out.data_ptr(), _cfmt(fmt), _call_stream(stream)),
            "fmt_conv2d_wgrad")
     return out
 
@@ -694,12 +695,11 @@ DLS_STATE_BYTES = ctypes.sizeof(_CDlsState)
 
 def fmt_dls_init(loss_scale: float, device=None, state=None, stream=None):
     """A fresh loss-scale controller state in device memory (a uint8 tensor of DLS_STATE_BYTES)."""
-    import torch
     if state is None:
         state = torch.empty(DLS_STATE_BYTES, dtype=torch.uint8, device=device if device is not None else "cuda")
     if state.dtype != torch.uint8 or state.numel() != DLS_STATE_BYTES or not state.is_cuda:
         raise TypeError("state must be a GPU uint8 tensor of %d bytes" % DLS_STATE_BYTES)
-    _check(_lib.fmt_dls_init(state.data_ptr(), float(loss_scale), _stream_ptr(stream)), "fmt_dls_init")
+    _check(_lib.fmt_dls_init(state.data_ptr(), float(loss_scale), _call_stream(stream)), "fmt_dls_init")
     return state
 
 
@@ -708,7 +708,6 @@ def fmt_dls_step(hists, state, growth: float = 2.0, backoff: float = 0.5, interv
     """One step of the loss-scale controller / denormal-fraction monitor (Sec. II, Sec. V) on the
     statistics of the step's gradient tensors: ``hists`` is a GPU int64 tensor [count, 72] (rows as
     :func:`new_hist`), or None for a step without tensors.  Updates ``state`` on the device."""
-    import torch
     count, hp = 0, None
     if hists is not None:
         if hists.dtype != torch.int64 or not hists.is_cuda or not hists.is_contiguous() or \
@@ -717,7 +716,7 @@ def fmt_dls_step(hists, state, growth: float = 2.0, backoff: float = 0.5, interv
         count = hists.numel() // (8 + FMT_NBINS)
         hp = hists.data_ptr() if count else None
     prm = _CDlsParams(growth, backoff, interval, min_scale, max_scale)
-    _check(_lib.fmt_dls_step(hp, count, prm, state.data_ptr(), _stream_ptr(stream)), "fmt_dls_step")
+    _check(_lib.fmt_dls_step(hp, count, prm, state.data_ptr(), _call_stream(stream)), "fmt_dls_step")
     return state
 
 
