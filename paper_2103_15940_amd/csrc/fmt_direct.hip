@@ -1,0 +1,270 @@
+// Small products of two fp32 matrices in one launch: the operands are rounded on the way into the matrix cores
+// (fmt_gemm.hip chooses between this and its own route of prepared operands).
+#include <type_traits>
+
+#include "fmt_internal.h"
+#include "fmt_quant.h"
+#include "fmt_split.h"
+
+namespace fmt {
+
+// An fp32 matrix operand of a direct product: element (row, k) at X[row*row_step + k*k_step], one of the two 1.  VEC:
+// k_step == 1 and 16-byte vectors of k are aligned (X 16-byte aligned, row_step a multiple of 4).
+struct DirectOperand {
+    const uint32_t *X;
+    uint32_t row_step, k_step;       // every offset of an element fits 32 bits (the host checks)
+    int rows;
+};
+
+// Constants in registers: with literals the compiler spends two instructions (and, or) where one (v_and_or_b32, which takes no
+// literal) does.
+struct DirectMasks {
+    uint32_t exponent, half, minn;               // 0x7F800000, 0x00400000 and the pattern of 1.5 * minN
+};
+
+// Eight consecutive k of one row (fp32 patterns) as MFMA operand vectors, one per piece: Q and the split of
+// round_and_split.  What a product of network tensors meets is finite and far from overflow, so the
+// common path leaves those cases out and looks once per eight elements whether the wave holds one:
+//   e < 8   the rounding is (x + C) - C with C = 1.5 * 2^(max(E, Emin) + 23 - m) for either sign (C is formed inside the
+//           two fused multiply-adds); the sign of a zero is lost, which no sum can show (it starts from +0)
+//   e == 8  round to nearest even on the integer pattern
+// 5 to 8 vector instructions per element where the general path takes about 20.
+template <int MODE, bool FTZ, int PS>
+__device__ __forceinline__ void direct_convert(const uint32_t (&v)[8], const QuantParams &p, const DirectMasks &k,
+                                               u32x4 (&out)[pieces_of(PS)])
+{
+    constexpr int P = pieces_of(PS);
+    constexpr bool kMagicFast = MODE == kModeMagic;
+    static_assert((MODE == kModeMagic && PS <= 2) || (MODE == kModeInteger && PS == 1), "formats with a short form");
+    {
+        bool rare;
+        if constexpr (kMagicFast) {
+            // largest |x| (the instruction takes magnitudes; a NaN is passed over, and stays one below)
+            float top = 0.0f;
+#pragma unroll
+            for (int j = 0; j < 8; j += 2) asm("v_max3_f32 %0, |%1|, |%2|, %0" : "+v"(top) : "v"(v[j]), "v"(v[j + 1]));
+            rare = top >= __uint_as_float(p.t_ovf);
+        } else {
+            uint32_t top = 0u;                   // as a pattern: NaN on top
+#pragma unroll
+            for (int j = 0; j < 8; ++j) top = max(top, v[j] & 0x7FFFFFFFu);
+            rare = top >= p.t_ovf;
+        }
+        if (__ballot(rare) == 0ull) {            // the same in the whole wave
+            uint32_t r[8];
+            if constexpr (kMagicFast) {
+                const float scale = __uint_as_float((127u + p.shift) << 23), minn = __uint_as_float(p.minn_bits);
+#pragma unroll
+                for (int j = 0; j < 8; ++j) {
+                    const float x = __uint_as_float(v[j]);
+                    const float u = __uint_as_float(max((v[j] & k.exponent) | k.half, k.minn));
+                    float q = __fmaf_rn(u, -scale, __fmaf_rn(u, scale, x));
+                    if (FTZ) q = fabsf(q) < minn ? 0.0f : q;
+                    r[j] = __float_as_uint(q);
+                }
+            } else {
+#pragma unroll
+                for (int j = 0; j < 8; ++j) {
+                    r[j] = (v[j] + p.rbias + __builtin_amdgcn_ubfe(v[j], p.shift, p.lsb_width)) & p.nmask;
+                    if (FTZ) r[j] = (v[j] & 0x7FFFFFFFu) < p.t_den ? 0u : r[j];
+                }
+            }
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                if constexpr (PS == 0) {         // values of the format are binary16 values: the conversion is exact
+                    out[0][i] = __builtin_bit_cast(uint32_t, __builtin_amdgcn_cvt_pkrtz(__uint_as_float(r[2 * i]), __uint_as_float(r[2 * i + 1])));
+                } else {
+                    out[0][i] = __builtin_amdgcn_perm(r[2 * i + 1], r[2 * i], 0x07060302u);
+                    if constexpr (P >= 2) {
+                        const float l0 = __uint_as_float(r[2 * i]) - __uint_as_float(r[2 * i] & 0xFFFF0000u);              // exact
+                        const float l1 = __uint_as_float(r[2 * i + 1]) - __uint_as_float(r[2 * i + 1] & 0xFFFF0000u);
+                        out[P >= 2 ? 1 : 0][i] = __builtin_amdgcn_perm(__float_as_uint(l1), __float_as_uint(l0), 0x07060302u);
+                    }
+                }
+            }
+            return;
+        }
+    }
+    uint32_t pc[8][P];
+#pragma unroll
+    for (int j = 0; j < 8; ++j) round_and_split<MODE, FTZ, PS>(v[j], p, pc[j]);
+#pragma unroll
+    for (int q = 0; q < P; ++q)
+#pragma unroll
+        for (int i = 0; i < 4; ++i) out[q][i] = pc[2 * i][q] | (pc[2 * i + 1][q] << 16);
+}
+
+// C = Q(A) Q(B)^T of two fp32 matrices in one launch, for products so small that the three launches of the general route
+// (prepare, product, sum of the k parts: 5 - 6 us each on the GPU and 3 us each on the host) are what they cost.
+// A wave owns a block of 32 x 32 results and one of `parts` ranges of k; it loads its operands straight into
+// the layout of the MFMA fragments (lane l: row l % 32, eight consecutive k), rounds and splits them in
+// registers and multiplies: no LDS, no barrier, the next 32 k in flight meanwhile.  The parts of a block
+// meet in LDS and are summed in order.  Every element is rounded once per block of its row or column instead of
+// once, which is what bounds it (vector instructions) and why larger products keep the general route
+// (direct_parts).  The sums are those of the general route bit for bit when `parts` is its plan's: same pieces, same
+// steps of 16 k, same order.
+template <int MODE, bool FTZ, int PS, bool AVEC, bool BVEC>
+__global__ __launch_bounds__(512) void direct_product_kernel(DirectOperand a, DirectOperand b, float *__restrict__ C, int64_t ldc,
+                                                              int M, int N, int K, int kblocks, int tiles_m, int ntiles, int parts,
+                                                              int kb_per, int tiles_per_wg, QuantParams p)
+{
+    constexpr int P = pieces_of(PS);
+    extern __shared__ float s_part[];            // parts > 1: [wave][16][64]
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int part = wave % parts, tile = blockIdx.x * tiles_per_wg + wave / parts;
+    const bool live = tile < ntiles;
+    const int row0 = (tile % tiles_m) * 32, col0 = (tile / tiles_m) * 32;
+    const int kb0 = part * kb_per, kb1 = live ? min(kblocks, kb0 + kb_per) : 0;
+
+    DirectMasks masks{0x7F800000u, 0x00400000u, p.minn_bits | 0x00400000u};
+    asm("" : "+s"(masks.exponent), "+v"(masks.half));
+
+    // Rows beyond the operand read its last row: their results are not stored.  A load's address is one that is the same in
+    // the whole wave plus a lane's offset.
+    const int half = lane >> 5;
+    const uint32_t off_a = (uint32_t)min(row0 + (lane & 31), a.rows - 1) * a.row_step + (uint32_t)half * 8u * a.k_step;
+    const uint32_t off_b = (uint32_t)min(col0 + (lane & 31), b.rows - 1) * b.row_step + (uint32_t)half * 8u * b.k_step;
+    // no branch in here: the compiler keeps the loads of several blocks in flight
+    auto load_one = [&](auto vec, const DirectOperand &o, uint32_t off, int kb, uint32_t (&raw)[2][8]) __attribute__((always_inline)) {
+#pragma unroll
+        for (int kk = 0; kk < 2; ++kk) {
+            const uint32_t *src = o.X + (size_t)(uint32_t)(kb * kUnitK + kk * 16) * o.k_step;
+            if constexpr (decltype(vec)::value) {
+                const u32x4 lo = *reinterpret_cast<const u32x4 *>(src + off), hi = *reinterpret_cast<const u32x4 *>(src + off + 4);
+#pragma unroll
+                for (int j = 0; j < 4; ++j) {
+                    raw[kk][j] = lo[j];
+                    raw[kk][4 + j] = hi[j];
+                }
+            } else {
+#pragma unroll
+                for (int j = 0; j < 8; ++j, src += o.k_step) raw[kk][j] = src[off];
+            }
+        }
+    };
+    auto load = [&](int kb, uint32_t (&raw)[2][2][8]) __attribute__((always_inline)) {
+        load_one(std::integral_constant<bool, AVEC>{}, a, off_a, kb, raw[0]);
+        load_one(std::integral_constant<bool, BVEC>{}, b, off_b, kb, raw[1]);
+    };
+    floatx16 acc;
+#pragma unroll
+    for (int v = 0; v < 16; ++v) acc[v] = 0.0f;
+    auto multiply = [&](const uint32_t (&raw)[2][2][8]) __attribute__((always_inline)) {
+        u32x4 f[2][2][P];                                            // [operand][16 k][piece]
+#pragma unroll
+        for (int o = 0; o < 2; ++o)
+#pragma unroll
+            for (int kk = 0; kk < 2; ++kk) direct_convert<MODE, FTZ, PS>(raw[o][kk], p, masks, f[o][kk]);
+#pragma unroll
+        for (int kk = 0; kk < 2; ++kk)
+#pragma unroll
+            for (int qa = 0; qa < P; ++qa)
+#pragma unroll
+                for (int qb = 0; qb < P; ++qb)                       // B's fragment first: the block comes out transposed (see store_tile)
+                    acc = PS == 0 ? __builtin_amdgcn_mfma_f32_32x32x16_f16(__builtin_bit_cast(f16x8, f[1][kk][qb]),
+                                                                          __builtin_bit_cast(f16x8, f[0][kk][qa]), acc, 0, 0, 0)
+                                  : __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, f[1][kk][qb]),
+                                                                            __builtin_bit_cast(bf16x8, f[0][kk][qa]), acc, 0, 0, 0);
+    };
+    // kDepth blocks of 32 k are in flight: a block takes 0.4 us of rounding and multiplying, a load up to three times that
+    constexpr int kDepth = 4;
+    const int whole = min(kb1, K / kUnitK);                          // blocks [kb0, whole) lie inside K; at most one more follows
+    uint32_t raw[kDepth][2][2][8];
+#pragma unroll
+    for (int u = 0; u < kDepth; ++u)
+        if (kb0 + u < whole) load(kb0 + u, raw[u]);
+    for (int kb = kb0; kb < whole; kb += kDepth) {
+#pragma unroll
+        for (int u = 0; u < kDepth; ++u) {
+            if (kb + u >= whole) break;                              // the same in the whole wave
+            multiply(raw[u]);
+            if (kb + u + kDepth < whole) load(kb + u + kDepth, raw[u]);
+        }
+    }
+    if (kb0 <= whole && whole < kb1) {                                // the block that K ends in, if it is this part's
+#pragma unroll
+        for (int kk = 0; kk < 2; ++kk)
+#pragma unroll
+            for (int j = 0; j < 8; ++j) {
+                const int kw = whole * kUnitK + kk * 16, k = kw + half * 8 + j;
+                raw[0][0][kk][j] = k < K ? a.X[(size_t)(uint32_t)(kw + j) * a.k_step + off_a] : 0u;
+                raw[0][1][kk][j] = k < K ? b.X[(size_t)(uint32_t)(kw + j) * b.k_step + off_b] : 0u;
+            }
+        multiply(raw[0]);
+    }
+
+    // register 4g + c of lane l: row l % 32, column 8g + 4 (l / 32) + c of the block
+    typedef float f32x4u __attribute__((ext_vector_type(4), aligned(4)));
+    const int row = row0 + (lane & 31);
+    auto put = [&](int g, float x0, float x1, float x2, float x3) __attribute__((always_inline)) {
+        const int col = col0 + g * 8 + half * 4;
+        if (row >= M || col >= N) return;
+        float *dst = C + (size_t)row * ldc + col;
+        if (col + 3 < N) {
+            *reinterpret_cast<f32x4u *>(dst) = f32x4u{x0, x1, x2, x3};
+        } else {
+            dst[0] = x0;
+            if (col + 1 < N) dst[1] = x1;
+            if (col + 2 < N) dst[2] = x2;
+        }
+    };
+    if (parts == 1) {
+        if (!live) return;
+#pragma unroll
+        for (int g = 0; g < 4; ++g) put(g, acc[4 * g], acc[4 * g + 1], acc[4 * g + 2], acc[4 * g + 3]);
+        return;
+    }
+#pragma unroll
+    for (int v = 0; v < 16; ++v) s_part[(wave * 16 + v) * 64 + lane] = acc[v];
+    __syncthreads();
+    if (!live) return;
+    const int w0 = wave - part;                                      // the block's first wave
+    for (int g = part; g < 4; g += parts) {
+        float sum[4];
+#pragma unroll
+        for (int c = 0; c < 4; ++c) {
+            sum[c] = 0.0f;
+            for (int q = 0; q < parts; ++q) sum[c] += s_part[((w0 + q) * 16 + 4 * g + c) * 64 + lane];
+        }
+        put(g, sum[0], sum[1], sum[2], sum[3]);
+    }
+}
+
+template <int MODE, bool FTZ, int PS>
+static int launch(int M, int N, int K, const MatrixOperand &A, const MatrixOperand &B, float *C, int64_t ldc, int parts,
+                  const QuantParams &p, hipStream_t stream)
+{
+    auto operand = [](const MatrixOperand &m, int rows) {
+        return DirectOperand{reinterpret_cast<const uint32_t *>(m.X), m.kcontig ? (uint32_t)m.ld : 1u, m.kcontig ? 1u : (uint32_t)m.ld, rows};
+    };
+    auto vec = [](const MatrixOperand &m) { return m.kcontig && (reinterpret_cast<uintptr_t>(m.X) & 15) == 0 && m.ld % 4 == 0; };
+    const int kblocks = (K + kUnitK - 1) / kUnitK;
+    const int tiles_m = (M + 31) / 32, tiles = tiles_m * ((N + 31) / 32);
+    const int per_wg = parts >= 4 ? 1 : 4 / parts;
+    const int waves = parts * per_wg;
+    const size_t lds = parts > 1 ? (size_t)waves * 16 * 64 * sizeof(float) : 0;
+    auto kern = vec(A) ? (vec(B) ? direct_product_kernel<MODE, FTZ, PS, true, true> : direct_product_kernel<MODE, FTZ, PS, true, false>)
+                       : (vec(B) ? direct_product_kernel<MODE, FTZ, PS, false, true> : direct_product_kernel<MODE, FTZ, PS, false, false>);
+    hipLaunchKernelGGL(kern, dim3((unsigned)((tiles + per_wg - 1) / per_wg)), dim3(64 * waves), lds, stream, operand(A, M), operand(B, N), C,
+                       ldc, M, N, K, kblocks, tiles_m, tiles, parts, (kblocks + parts - 1) / parts, per_wg, p);
+    FMT_HIP_CHECK(hipGetLastError());
+    return FMT_OK;
+}
+
+// C (M x N) = Q(A) Q(B)^T; K >= 1, 1 <= parts <= kDirectParts, fewer than 2^31 blocks of 32 x 32 (the caller's size limit).
+int launch_direct_product(int M, int N, int K, const MatrixOperand &A, const MatrixOperand &B, float *C, int64_t ldc, int parts, int ps,
+                          bool ftz, const QuantParams &p, hipStream_t stream)
+{
+    if (parts < 1 || parts > kDirectParts) return FMT_ERR_SHAPE;
+#define FMT_RUN(MD, PSV)                                                                      \
+    (ftz ? launch<MD, true, PSV>(M, N, K, A, B, C, ldc, parts, p, stream)                      \
+         : launch<MD, false, PSV>(M, N, K, A, B, C, ldc, parts, p, stream))
+    if (p.mode == kModeMagic && ps == 0) return FMT_RUN(kModeMagic, 0);
+    if (p.mode == kModeMagic && ps == 1) return FMT_RUN(kModeMagic, 1);
+    if (p.mode == kModeMagic && ps == 2) return FMT_RUN(kModeMagic, 2);
+    if (p.mode == kModeInteger && ps == 1) return FMT_RUN(kModeInteger, 1);
+    return FMT_ERR_FORMAT;                       // direct_parts leaves the others to the general route
+#undef FMT_RUN
+}
+
+}  // namespace fmt

@@ -46,6 +46,7 @@
 #include "fmt_hist.h"
 #include "fmt_internal.h"
 #include "fmt_quant.h"
+#include "fmt_split.h"
 
 #ifndef FMT_GEMM_KS
 #define FMT_GEMM_KS 2      // 16-k steps per LDS stage
@@ -58,52 +59,6 @@
 #endif
 
 namespace fmt {
-
-typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
-typedef _Float16 f16x8 __attribute__((ext_vector_type(8)));
-
-// Piece scheme PS: 1, 2, 3 = that many bf16 pieces; 0 = one fp16 piece (formats inside binary16).
-constexpr int pieces_of(int ps) { return ps == 0 ? 1 : ps; }
-typedef float floatx16 __attribute__((ext_vector_type(16)));
-typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
-
-constexpr int kUnitRows = 32;                 // rows per unit (one MFMA fragment)
-constexpr int kUnitK = 32;                    // k per unit (two MFMA steps of 16)
-constexpr int kUnitVec = kUnitRows * kUnitK * 2 / 16;   // 16-byte vectors per unit per piece = 128
-constexpr int kFastRows = 4;                  // groups of 64 rows per workgroup in the fast patch gather (kRowPad = 64 * kFastRows)
-constexpr int kRowPad = 256;                  // prepared operands are padded to a multiple of this many rows
-
-// Rounds one fp32 pattern to the format and splits the result into the 16-bit patterns of its
-// pieces: P bf16 pieces, or the single fp16 pattern when the format's values are all binary16
-// values (e <= 5, m <= 10).
-template <int MODE, bool FTZ, int PS>
-__device__ __forceinline__ void round_and_split(uint32_t u, const QuantParams &p, uint32_t (&piece)[pieces_of(PS)])
-{
-    constexpr int P = pieces_of(PS);
-    const uint32_t r = quantize_bits<MODE, FTZ>(u, p);
-    if (PS == 0) {
-        // exact fp32 -> fp16 of a value known to be representable: normal numbers by moving the
-        // fields, denormals as the integer count of 2^-24 steps (an exact fp32 product)
-        const uint32_t a = r & 0x7FFFFFFFu;
-        uint32_t h = a >= 0x38800000u ? (a - 0x38000000u) >> 13 : (uint32_t)(__uint_as_float(a) * 16777216.0f);
-        h = a >= 0x7F800000u ? (a > 0x7F800000u ? 0x7E00u : 0x7C00u) : h;
-        piece[0] = h | ((r >> 16) & 0x8000u);
-        return;
-    }
-    const uint32_t hi = r & 0xFFFF0000u;
-    piece[0] = hi >> 16;
-    if (P >= 2) {
-        // infinities and NaN stay in the first piece alone
-        const bool finite = (r & 0x7F800000u) != 0x7F800000u;
-        const float rem = finite ? __uint_as_float(r) - __uint_as_float(hi) : 0.0f;   // exact
-        const uint32_t rb = __float_as_uint(rem);
-        piece[P >= 2 ? 1 : 0] = rb >> 16;
-        if (P >= 3) {
-            const float rem2 = rem - __uint_as_float(rb & 0xFFFF0000u);                // exact
-            piece[P >= 3 ? 2 : 0] = __float_as_uint(rem2) >> 16;
-        }
-    }
-}
 
 // Workspace address (in 16-byte vectors) of chunk c (8 consecutive k) of row `row` in unit
 // (rb, kb), piece `piece`.
@@ -2205,6 +2160,39 @@ static int prepare_operands(const OperandSpec &sa, const OperandLayout &la, cons
     return FMT_OK;
 }
 
+// Parts of k of a direct product (fmt_direct.hip), or 0 where the general route is the better one (or forced, for tuning and
+// tests).
+//   direct   one launch: 4.4 us, and 0.9 us per block of 32 k that a wave takes one after the other, or per 1024 waves' blocks
+//            where there are more waves (fitted to products of 64 x 64 x 32 to 4096 x 128 x 512, the slowest layout)
+//   general  two launches, 8.2 us at least; three when the plan splits k, 14.4 us at least with two pieces, 12.4 with one
+// Measured (us, general -> direct; 1/6/9 unless said): 64 x 64 x 32 8.0 -> 4.4; 256 x 10 x 1024 14.4 -> 9.6; 512 x 512 x 512 14.8 -> 6.9;
+// 256 x 1024 x 1024 18.9 -> 10.8; 1000 x 1000 x 64 in 1/8/7 8.2 -> 5.3; not taken: 1024 x 1024 x 256 9.9 against 11.1,
+// 768^3 15.4 against 19.6, 512^3 in 1/8/7 (whose sums must be the plan's) 9.2 against 17.5.
+static int direct_parts(int M, int N, int K, const OperandSpec &sa, const OperandSpec &sb, const Plan &plan, fmt_format_t f, Scheme sch,
+                        int mode)
+{
+    if (getenv("FMT_GEMM_PLAN") != nullptr) return 0;
+    // formats whose rounding has the short form of direct_convert
+    if (!(mode == kModeMagic && sch.ps <= 2) && !(mode == kModeInteger && sch.ps == 1)) return 0;
+    // offsets inside an operand in 32 bits
+    auto fits = [](const OperandSpec &o, int rows) { return o.kcontig ? (int64_t)rows * o.ld < ((int64_t)1 << 32) : o.ld < ((int64_t)1 << 28); };
+    if (!fits(sa, M) || !fits(sb, N)) return 0;
+    const int kblocks = (K + kUnitK - 1) / kUnitK;
+    const int64_t tiles = (((int64_t)M + 31) / 32) * (((int64_t)N + 31) / 32);
+    int parts = plan.nsplit;
+    if (planes_possible(f)) {
+        // the prepared calls of these formats take the planes, so no other call promises these sums and the parts are
+        // free: enough for two waves per SIMD (2048), two blocks each at least
+        parts = 1;
+        while (parts < kDirectParts && tiles * parts < 2048 && kblocks / (parts * 2) >= 2) parts *= 2;
+    }
+    if (parts > kDirectParts) return 0;
+    const double blocks = (double)((kblocks + parts - 1) / parts);
+    const double direct = 4.4 + std::max(0.9, 0.95 * (double)(tiles * parts) / 1024.0) * blocks;
+    const double general = plan.nsplit == 1 ? 8.2 : pieces_of(sch.ps) == 1 ? 12.4 : 14.4;
+    return direct < general ? parts : 0;
+}
+
 // Room for the split-k partial sums of a plan.
 static size_t part_bytes_of(const Plan &plan, int M, int N)
 {
@@ -2259,6 +2247,14 @@ static int run(int M, int N, int K, const OperandSpec &sa, const OperandSpec &sb
     Scratch s;
     rc = get_scratch(stream, 0, la.bytes + lb.bytes + part + pre_a + pre_b, &s);
     if (rc != FMT_OK) return rc;
+    // (the scratch of the general route is kept even where it is not used: what a call needs, and whether it can be
+    // recorded into a graph, does not depend on the route)
+    if (!scaled && sa.g.kind == kSrcMatrix && sb.g.kind == kSrcMatrix && out.img == 0) {
+        const int parts = direct_parts(M, N, K, sa, sb, plan, f, sch, p.mode);
+        if (parts > 0)
+            return launch_direct_product(M, N, K, MatrixOperand{sa.X, sa.ld, sa.kcontig}, MatrixOperand{sb.X, sb.ld, sb.kcontig}, out.C,
+                                         out.ldc, parts, PS, FTZ, p, stream);
+    }
     char *ws = static_cast<char *>(s.gemm_ws);
     const OperandView va = view_of(ws, la), vb = view_of(ws + la.bytes, lb);
     float *partp = reinterpret_cast<float *>(ws + la.bytes + lb.bytes);

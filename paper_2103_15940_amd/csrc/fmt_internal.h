@@ -62,6 +62,16 @@ int launch_gemm(int transA, int transB, int64_t M, int64_t N, int64_t K,
                 const float *A, int64_t lda, const float *B, int64_t ldb,
                 float *C, int64_t ldc, fmt_format_t f, const QuantParams &p, hipStream_t stream);
 
+// Small products in one launch (fmt_direct.hip): an fp32 operand with element (row, k) at X[row*ld + k] (kcontig) or X[k*ld + row].
+struct MatrixOperand {
+    const float *X;
+    int64_t ld;
+    bool kcontig;
+};
+constexpr int kDirectParts = 8;      // most parts of k (waves of a workgroup)
+int launch_direct_product(int M, int N, int K, const MatrixOperand &A, const MatrixOperand &B, float *C, int64_t ldc, int parts, int ps,
+                          bool ftz, const QuantParams &p, hipStream_t stream);
+
 // Prepared operands in caller-owned memory (fmt_gemm.hip).  scheme: opaque tag of the representation.
 int prepared_operand_bytes(int64_t rows, int64_t K, fmt_format_t f, size_t *bytes, int *scheme);
 int launch_prepare_operand(const float *X, int64_t ld, int trans, int64_t rows, int64_t K, fmt_format_t f,

@@ -1,0 +1,56 @@
+// How a rounded value reaches the matrix cores, shared by the kernels that prepare operands and the one that rounds
+// them on the way in.
+#pragma once
+
+#include "fmt_internal.h"
+#include "fmt_quant.h"
+
+namespace fmt {
+
+typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
+typedef _Float16 f16x8 __attribute__((ext_vector_type(8)));
+
+// Piece scheme PS: 1, 2, 3 = that many bf16 pieces; 0 = one fp16 piece (formats inside binary16).
+constexpr int pieces_of(int ps) { return ps == 0 ? 1 : ps; }
+typedef float floatx16 __attribute__((ext_vector_type(16)));
+typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+
+constexpr int kUnitRows = 32;                 // rows per unit (one MFMA fragment)
+constexpr int kUnitK = 32;                    // k per unit (two MFMA steps of 16)
+constexpr int kUnitVec = kUnitRows * kUnitK * 2 / 16;   // 16-byte vectors per unit per piece = 128
+constexpr int kFastRows = 4;                  // groups of 64 rows per workgroup in the fast patch gather (kRowPad = 64 * kFastRows)
+constexpr int kRowPad = 256;                  // prepared operands are padded to a multiple of this many rows
+
+// Rounds one fp32 pattern to the format and splits the result into the 16-bit patterns of its
+// pieces: P bf16 pieces, or the single fp16 pattern when the format's values are all binary16
+// values (e <= 5, m <= 10).
+template <int MODE, bool FTZ, int PS>
+__device__ __forceinline__ void round_and_split(uint32_t u, const QuantParams &p, uint32_t (&piece)[pieces_of(PS)])
+{
+    constexpr int P = pieces_of(PS);
+    const uint32_t r = quantize_bits<MODE, FTZ>(u, p);
+    if (PS == 0) {
+        // exact fp32 -> fp16 of a value known to be representable: normal numbers by moving the
+        // fields, denormals as the integer count of 2^-24 steps (an exact fp32 product)
+        const uint32_t a = r & 0x7FFFFFFFu;
+        uint32_t h = a >= 0x38800000u ? (a - 0x38000000u) >> 13 : (uint32_t)(__uint_as_float(a) * 16777216.0f);
+        h = a >= 0x7F800000u ? (a > 0x7F800000u ? 0x7E00u : 0x7C00u) : h;
+        piece[0] = h | ((r >> 16) & 0x8000u);
+        return;
+    }
+    const uint32_t hi = r & 0xFFFF0000u;
+    piece[0] = hi >> 16;
+    if (P >= 2) {
+        // infinities and NaN stay in the first piece alone
+        const bool finite = (r & 0x7F800000u) != 0x7F800000u;
+        const float rem = finite ? __uint_as_float(r) - __uint_as_float(hi) : 0.0f;   // exact
+        const uint32_t rb = __float_as_uint(rem);
+        piece[P >= 2 ? 1 : 0] = rb >> 16;
+        if (P >= 3) {
+            const float rem2 = rem - __uint_as_float(rb & 0xFFFF0000u);                // exact
+            piece[P >= 3 ? 2 : 0] = __float_as_uint(rem2) >> 16;
+        }
+    }
+}
+
+}  // namespace fmt

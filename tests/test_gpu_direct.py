@@ -1,0 +1,112 @@
+"""Small products of fp32 matrices: fmt_gemm in one launch, operands rounded on the way into the matrix cores, against the CPU
+oracle, against the general route (forced through FMT_GEMM_PLAN) and against the prepared calls."""
+import numpy as np
+import pytest
+
+import oracle
+import workloads
+
+pytestmark = pytest.mark.gpu
+
+torch = pytest.importorskip("torch")
+
+# every pair of rounding and pieces that takes the route: one fp16 piece, one bf16 piece (e < 8 and e == 8), two bf16 pieces
+FORMATS = [(5, 10, True), (5, 10, False), (4, 3, True), (8, 7, True), (8, 7, False), (8, 3, True), (6, 9, True), (6, 9, False),
+           (7, 8, True), (2, 15, False)]
+LAYOUTS = [(False, False), (False, True), (True, False), (True, True)]
+SHAPES = [(1, 1, 1), (31, 33, 31), (32, 32, 32), (33, 65, 33), (64, 40, 64), (7, 100, 129), (256, 10, 1024), (130, 70, 257),
+          (512, 200, 100)]
+
+
+@pytest.fixture(scope="module")
+def fmt():
+    if not torch.cuda.is_available():
+        pytest.skip("needs a GPU")
+    import paper_2103_15940_amd as lib
+    return lib
+
+
+@pytest.fixture(autouse=True)
+def plain_environment(monkeypatch):
+    for name in ("FMT_GEMM_PLAN", "FMT_GEMM_WINDOW"):
+        monkeypatch.delenv(name, raising=False)
+
+
+def stored(X, transposed, pad, offset):
+    """X (or its transpose) on the GPU with `pad` extra columns, the first element `offset` floats past a 16-byte boundary."""
+    S = np.ascontiguousarray(X.T if transposed else X)
+    ld = S.shape[1] + pad
+    buf = torch.full((S.shape[0] * ld + offset,), float("nan"), device="cuda")
+    view = buf[offset:].view(S.shape[0], ld)[:, :S.shape[1]]
+    view.copy_(torch.from_numpy(S))
+    return view
+
+
+def product(fmt, A, B, f, tA, tB, pad=0, offset=0):
+    C = torch.full((A.shape[0], B.shape[1] + pad), 7.0, device="cuda")
+    out = C[:, :B.shape[1]]
+    fmt.fmt_gemm(stored(A, tA, pad, offset), stored(B, tB, pad, offset), f, transA=tA, transB=tB, out=out)
+    torch.cuda.synchronize()
+    assert bool((C[:, B.shape[1]:] == 7.0).all())                    # nothing beyond the result is written
+    return out.cpu().numpy()
+
+
+@pytest.mark.parametrize("e,m,d", FORMATS)
+@pytest.mark.parametrize("shape", SHAPES)
+def test_every_layout_and_alignment(fmt, e, m, d, shape):
+    """Integers small enough for every partial sum to be exact: the oracle's bits whatever the order of the sums.  All layouts,
+    leading dimensions and base alignments (16-byte vectors possible or not); the general route gives the same bits."""
+    M, N, K = shape
+    rng = np.random.default_rng(M + 10 * N + 100 * K + e)
+    top = 3 if m >= 3 else 1
+    A = rng.integers(-top, top + 1, (M, K)).astype(np.float32) * np.float32(0.25)
+    B = rng.integers(-top, top + 1, (K, N)).astype(np.float32) * np.float32(0.25)
+    want = oracle.gemm(A, B, e, m, d)
+    for i, (tA, tB) in enumerate(LAYOUTS):
+        for pad, offset in ((0, 0), (4, 0), (1, 0), (3, 1)):
+            got = product(fmt, A, B, (e, m, d), tA, tB, pad, offset)
+            assert np.array_equal(got, want), (tA, tB, pad, offset)
+
+
+@pytest.mark.parametrize("e,m,d", FORMATS)
+def test_values_over_the_whole_range(fmt, e, m, d, monkeypatch):
+    """Random operands (normal, denormal and flushed values, zeros): within the accumulation bound of the oracle; the bits
+    of the prepared calls where they share the representation; and next to the general route."""
+    rng = np.random.default_rng(50 + e + m)
+    c = oracle.format_constants(e, m)
+    M, N, K = 96, 70, 128
+    A = workloads.log2_normal((M, K), max(c["Emin"] / 2.0, -20.0), 3.0, 0.05, rng)
+    A[5, :] = workloads.log2_normal(K, c["Emin"] - m / 2.0, 2.0, 0.0, rng) if e < 8 else 0.0
+    B = (rng.standard_normal((K, N)) * 0.5).astype(np.float32)
+    top = np.float32(min(c["maxN"], 1e30) / 2)                       # overflow is another test's: stay below it in the narrow formats
+    A, B = np.clip(A, -top, top), np.clip(B, -top, top)
+    got = product(fmt, A, B, (e, m, d), False, False)
+    ref = oracle.gemm(A, B, e, m, d).astype(np.float64)
+    assert np.linalg.norm(got - ref) <= 1e-6 * np.linalg.norm(ref)   # K = 128: sqrt(K) 2^-24 = 7e-7 at most
+    if not (e == 6 and m in (8, 9)):
+        pa = fmt.fmt_prepare(torch.from_numpy(A).cuda(), (e, m, d))
+        pb = fmt.fmt_prepare(torch.from_numpy(B).cuda(), (e, m, d), trans=True)
+        assert np.array_equal(fmt.fmt_gemm_prepared(pa, pb).cpu().numpy().view(np.uint32), got.view(np.uint32))
+    monkeypatch.setenv("FMT_GEMM_PLAN", "1,1,1")
+    general = product(fmt, A, B, (e, m, d), False, False)
+    assert np.linalg.norm(got - general) <= 1e-6 * np.linalg.norm(ref)
+
+
+@pytest.mark.parametrize("e,m,d", [(5, 10, True), (6, 9, False), (8, 7, True), (4, 3, True)])
+def test_overflow_infinity_nan(fmt, e, m, d):
+    """Elements that overflow the format, infinities and NaN: non-finite results exactly where the oracle has them, NaN where it
+    has NaN, and the other outputs untouched by them."""
+    rng = np.random.default_rng(9)
+    M, N, K = 70, 66, 100
+    A = rng.integers(-2, 3, (M, K)).astype(np.float32)
+    B = rng.integers(-2, 3, (K, N)).astype(np.float32)
+    A[3, 97], A[40, 0], A[69, 50], B[99, 65], B[10, 2], B[31, 33] = np.inf, np.nan, -3e38, -np.inf, np.nan, 3e38
+    A[12, 20], A[12, 21] = np.array([0x7F800001], dtype=np.uint32).view(np.float32)[0], np.inf
+    for tA, tB in LAYOUTS:
+        got, want = product(fmt, A, B, (e, m, d), tA, tB), oracle.gemm(A, B, e, m, d)
+        assert np.array_equal(np.isfinite(got), np.isfinite(want))
+        assert np.isnan(got[np.isnan(want)]).all()
+        inf = np.isinf(want)
+        assert ((got[inf] == want[inf]) | np.isnan(got[inf])).all()
+        fin = np.isfinite(want)
+        assert np.array_equal(got[fin], want[fin])
