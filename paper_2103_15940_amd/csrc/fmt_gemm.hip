@@ -924,7 +924,8 @@ __device__ __forceinline__ int run_of(const unsigned (&first)[CAP], unsigned id)
 struct RoundGroup {
     uint32_t *Y[kMaxPrepGroup / 2];
     int64_t ldy[kMaxPrepGroup / 2];
-    unsigned long long *partials[kMaxPrepGroup / 2];
+    unsigned long long *hist[kMaxPrepGroup / 2];     // the callers' records
+    unsigned long long *records;                     // kShards + 1 partial records per matrix
     int steps;                                   // steps of kPairTiles tiles per workgroup
 };
 
@@ -957,8 +958,10 @@ __global__ __launch_bounds__(256) void prepare_scaled_group_kernel(PrepGroup grp
         prepare_pair_tile<MODE, FTZ, ROUND, DEEP>(o0, o1, p, ty, tx, ROUND ? rg.Y[at] : nullptr, ROUND ? rg.ldy[at] : 0, tbl, w);
     }
     if constexpr (ROUND)
-        hist_end<kPairCopies, 256>(tbl, s_bins, s_cls, w, p, HistSink{rg.partials[at], nullptr, 0ull, (uint32_t)kShards},
-                                   blockIdx.x, gridDim.x, threadIdx.x);
+        hist_end<kPairCopies, 256>(tbl, s_bins, s_cls, w, p,
+                                   HistSink{rg.records + (size_t)at * (kShards + 1) * kSlots, rg.hist[at],
+                                            (unsigned long long)o0.rows * (unsigned long long)o1.rows, (uint32_t)kShards},
+                                   g, nwg, threadIdx.x);
 }
 
 // Epilogue of one wave.  The MFMAs are fed operand B's fragment first and A's second, so a 32 x 32 accumulator
@@ -1685,19 +1688,52 @@ static int tail_cols_for(uint64_t blocks256, int cus)
     return blocks256 / 4 >= want ? 1024 : blocks256 / 2 >= want ? 512 : 256;
 }
 
-// C[r][c] = sum over the k parts of part[s][r][c]  (parts are dense M x N slabs)
+// C[r][c] = sum over the k parts of part[s][r][c]  (parts are dense M x N slabs), in part order.  Four neighbouring elements
+// per thread, the slabs' loads issued eight at a time: what bounds the kernel is the latency of its loads (256 x 2304 in eight
+// parts: 10.9 us with one element and one load at a time).
 __global__ __launch_bounds__(256) void reduce_kernel(const float *__restrict__ part, int nsplit, float *__restrict__ C,
                                                      int M, int N, int64_t ldc, int img)
 {
+    typedef float f32x4u __attribute__((ext_vector_type(4), aligned(4)));
     const size_t total = (size_t)M * N;
-    for (size_t i = (size_t)blockIdx.x * 256 + threadIdx.x; i < total; i += (size_t)gridDim.x * 256) {
-        float s = 0.0f;
-        for (int q = 0; q < nsplit; ++q) s += part[(size_t)q * total + i];
+    for (size_t i = ((size_t)blockIdx.x * 256 + threadIdx.x) * 4; i < total; i += (size_t)gridDim.x * 1024) {
+        const bool four = i + 4 <= total;
+        float s[4] = {0.0f, 0.0f, 0.0f, 0.0f};
+        for (int q0 = 0; q0 < nsplit; q0 += 8) {
+            float v[8][4];
+#pragma unroll
+            for (int u = 0; u < 8; ++u) {
+                const float *src = part + (size_t)min(q0 + u, nsplit - 1) * total + i;
+                if (four) {
+                    const f32x4u w = *reinterpret_cast<const f32x4u *>(src);
+#pragma unroll
+                    for (int j = 0; j < 4; ++j) v[u][j] = w[j];
+                } else {
+#pragma unroll
+                    for (int j = 0; j < 4; ++j) v[u][j] = i + j < total ? src[j] : 0.0f;
+                }
+            }
+#pragma unroll
+            for (int u = 0; u < 8; ++u)
+                if (q0 + u < nsplit) {
+#pragma unroll
+                    for (int j = 0; j < 4; ++j) s[j] += v[u][j];
+                }
+        }
         const size_t row = i / N, col = i % N;
-        if (img > 0)
-            C[((col / img) * M + row) * img + col % img] = s;
-        else
-            C[row * ldc + col] = s;
+        if (img == 0 && four && col + 4 <= (size_t)N) {
+            *reinterpret_cast<f32x4u *>(C + row * ldc + col) = f32x4u{s[0], s[1], s[2], s[3]};
+            continue;
+        }
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            if (i + j >= total) break;
+            const size_t r = (i + j) / N, c = (i + j) % N;
+            if (img > 0)
+                C[((c / img) * M + r) * img + c % img] = s[j];
+            else
+                C[r * ldc + c] = s[j];
+        }
     }
 }
 
@@ -2361,16 +2397,14 @@ int launch_prepare_pair_batch(int64_t count, const PrepPairItem *items, fmt_form
     StatGroup sg;
     PrepGroup pg;
     RoundGroup rg{};
-    FinalizeGroup fg{};
-    unsigned long long *records = nullptr;
     if (round != nullptr) {
         for (int64_t i = 0; i < count; ++i)
             if (!(api_scheme(f, items[i].cols).scaled && api_scheme(f, items[i].rows).scaled && p.mode == kModeMagic))
                 return FMT_ERR_FORMAT;
         Scratch sc;
-        const int rc = get_scratch(stream, (size_t)(kMaxPrepGroup / 2) * kHistRecordBytes, 0, &sc);
+        const int rc = get_scratch(stream, (size_t)(kMaxPrepGroup / 2) * kHistScratchBytes, 0, &sc);
         if (rc != FMT_OK) return rc;
-        records = static_cast<unsigned long long *>(sc.hist_partials);
+        rg.records = static_cast<unsigned long long *>(sc.hist_partials);
         // steps per workgroup: as many as leave every compute unit four workgroups (measured on 12 tensors of 4 M to 16 M
         // elements: one step 267 us, four 242 us, eight 258 us; one tensor of 4 M elements: four 36 us)
         int cus = 0;
@@ -2412,10 +2446,6 @@ int launch_prepare_pair_batch(int64_t count, const PrepPairItem *items, fmt_form
         }
 #undef FMT_PAIR_LAUNCH
         FMT_HIP_CHECK(hipGetLastError());
-        if (round != nullptr) {
-            const int rc = launch_hist_finalize_group(fg, n / 2, stream);     // sums and clears the records
-            if (rc != FMT_OK) return rc;
-        }
         n = 0;
         stat_ids = prep_ids = 0;
         return FMT_OK;
@@ -2475,10 +2505,7 @@ int launch_prepare_pair_batch(int64_t count, const PrepPairItem *items, fmt_form
             const int slot = n / 2;
             rg.Y[slot] = reinterpret_cast<uint32_t *>(round[i].Y);
             rg.ldy[slot] = round[i].ldy;
-            rg.partials[slot] = records + (size_t)slot * kShards * kSlots;
-            fg.partials[slot] = rg.partials[slot];
-            fg.n[slot] = (unsigned long long)it.rows * (unsigned long long)it.cols;
-            fg.hist[slot] = reinterpret_cast<unsigned long long *>(round[i].hist);
+            rg.hist[slot] = reinterpret_cast<unsigned long long *>(round[i].hist);
         }
         const unsigned steps = round != nullptr ? (unsigned)rg.steps : 1u;
         prep_ids += ((tiles + steps - 1u) / steps + 7u) / 8u * 8u;

@@ -231,20 +231,6 @@ __global__ __launch_bounds__(1024) void finalize_kernel(unsigned long long *__re
     finalize_body(partials, nrec, n, hist);
 }
 
-// The same for up to kFinalizeGroup tensors in one launch: workgroup i sums the records of tensor i.
-__global__ __launch_bounds__(1024) void finalize_group_kernel(FinalizeGroup g)
-{
-    finalize_body(g.partials[blockIdx.x], kShards, g.n[blockIdx.x], g.hist[blockIdx.x]);
-}
-
-int launch_hist_finalize_group(const FinalizeGroup &g, int count, hipStream_t stream)
-{
-    if (count < 1 || count > kFinalizeGroup) return FMT_ERR_SHAPE;
-    hipLaunchKernelGGL(finalize_group_kernel, dim3(count), dim3(1024), 0, stream, g);
-    FMT_HIP_CHECK(hipGetLastError());
-    return FMT_OK;
-}
-
 int launch_hist_finalize(unsigned long long *partials, size_t n, fmt_hist_t *hist, hipStream_t stream)
 {
     hipLaunchKernelGGL(finalize_kernel, dim3(1), dim3(1024), 0, stream, partials, partials ? kShards : 0,
