@@ -106,7 +106,7 @@ __device__ __forceinline__ void direct_convert(const uint32_t (&v)[8], const Qua
 template <int MODE, bool FTZ, int PS, bool AVEC, bool BVEC>
 __global__ __launch_bounds__(512) void direct_product_kernel(DirectOperand a, DirectOperand b, float *__restrict__ C, int64_t ldc,
                                                               int M, int N, int K, int kblocks, int tiles_m, int ntiles, int parts,
-                                                              int kb_per, int tiles_per_wg, QuantParams p)
+                                                              int kb_per, int tiles_per_wg, QuantParams p, LinearOut lin, int linear)
 {
     constexpr int P = pieces_of(PS);
     extern __shared__ float s_part[];            // parts > 1: [wave][16][64]
@@ -115,6 +115,12 @@ __global__ __launch_bounds__(512) void direct_product_kernel(DirectOperand a, Di
     const bool live = tile < ntiles;
     const int row0 = (tile % tiles_m) * 32, col0 = (tile / tiles_m) * 32;
     const int kb0 = part * kb_per, kb1 = live ? min(kblocks, kb0 + kb_per) : 0;
+
+    uint32_t bias[16];                           // a layer's bias, loaded ahead of the products (columns as below)
+    if (linear) {
+#pragma unroll
+        for (int v = 0; v < 16; ++v) bias[v] = linear_bias(lin, col0 + (v >> 2) * 8 + (lane >> 5) * 4 + (v & 3), N);
+    }
 
     DirectMasks masks{0x7F800000u, 0x00400000u, p.minn_bits | 0x00400000u};
     asm("" : "+s"(masks.exponent), "+v"(masks.half));
@@ -199,6 +205,11 @@ __global__ __launch_bounds__(512) void direct_product_kernel(DirectOperand a, Di
     auto put = [&](int g, float x0, float x1, float x2, float x3) __attribute__((always_inline)) {
         const int col = col0 + g * 8 + half * 4;
         if (row >= M || col >= N) return;
+        if (linear) {                                                // a layer's output roundings
+            float y[4] = {x0, x1, x2, x3};
+            linear_round<4>(lin, [&](int i) { return y[i]; }, [&](int i, float v) { y[i] = v; }, [&](int i) { return bias[4 * g + i]; });
+            x0 = y[0], x1 = y[1], x2 = y[2], x3 = y[3];
+        }
         float *dst = C + (size_t)row * ldc + col;
         if (col + 3 < N) {
             *reinterpret_cast<f32x4u *>(dst) = f32x4u{x0, x1, x2, x3};
@@ -219,7 +230,9 @@ __global__ __launch_bounds__(512) void direct_product_kernel(DirectOperand a, Di
     __syncthreads();
     if (!live) return;
     const int w0 = wave - part;                                      // the block's first wave
-    for (int g = part; g < 4; g += parts) {
+#pragma unroll
+    for (int g = 0; g < 4; ++g) {
+        if (g % parts != part) continue;                             // the same in the whole wave
         float sum[4];
 #pragma unroll
         for (int c = 0; c < 4; ++c) {
@@ -232,7 +245,7 @@ __global__ __launch_bounds__(512) void direct_product_kernel(DirectOperand a, Di
 
 template <int MODE, bool FTZ, int PS>
 static int launch(int M, int N, int K, const MatrixOperand &A, const MatrixOperand &B, float *C, int64_t ldc, int parts,
-                  const QuantParams &p, hipStream_t stream)
+                  const QuantParams &p, const LinearOut *lin, hipStream_t stream)
 {
     auto operand = [](const MatrixOperand &m, int rows) {
         return DirectOperand{reinterpret_cast<const uint32_t *>(m.X), m.kcontig ? (uint32_t)m.ld : 1u, m.kcontig ? 1u : (uint32_t)m.ld, rows};
@@ -246,19 +259,20 @@ static int launch(int M, int N, int K, const MatrixOperand &A, const MatrixOpera
     auto kern = vec(A) ? (vec(B) ? direct_product_kernel<MODE, FTZ, PS, true, true> : direct_product_kernel<MODE, FTZ, PS, true, false>)
                        : (vec(B) ? direct_product_kernel<MODE, FTZ, PS, false, true> : direct_product_kernel<MODE, FTZ, PS, false, false>);
     hipLaunchKernelGGL(kern, dim3((unsigned)((tiles + per_wg - 1) / per_wg)), dim3(64 * waves), lds, stream, operand(A, M), operand(B, N), C,
-                       ldc, M, N, K, kblocks, tiles_m, tiles, parts, (kblocks + parts - 1) / parts, per_wg, p);
+                       ldc, M, N, K, kblocks, tiles_m, tiles, parts, (kblocks + parts - 1) / parts, per_wg, p,
+                       lin != nullptr ? *lin : LinearOut{}, lin != nullptr ? 1 : 0);
     FMT_HIP_CHECK(hipGetLastError());
     return FMT_OK;
 }
 
 // C (M x N) = Q(A) Q(B)^T; K >= 1, 1 <= parts <= kDirectParts, fewer than 2^31 blocks of 32 x 32 (the caller's size limit).
 int launch_direct_product(int M, int N, int K, const MatrixOperand &A, const MatrixOperand &B, float *C, int64_t ldc, int parts, int ps,
-                          bool ftz, const QuantParams &p, hipStream_t stream)
+                          bool ftz, const QuantParams &p, const LinearOut *lin, hipStream_t stream)
 {
     if (parts < 1 || parts > kDirectParts) return FMT_ERR_SHAPE;
 #define FMT_RUN(MD, PSV)                                                                      \
-    (ftz ? launch<MD, true, PSV>(M, N, K, A, B, C, ldc, parts, p, stream)                      \
-         : launch<MD, false, PSV>(M, N, K, A, B, C, ldc, parts, p, stream))
+    (ftz ? launch<MD, true, PSV>(M, N, K, A, B, C, ldc, parts, p, lin, stream)                      \
+         : launch<MD, false, PSV>(M, N, K, A, B, C, ldc, parts, p, lin, stream))
     if (p.mode == kModeMagic && ps == 0) return FMT_RUN(kModeMagic, 0);
     if (p.mode == kModeMagic && ps == 1) return FMT_RUN(kModeMagic, 1);
     if (p.mode == kModeMagic && ps == 2) return FMT_RUN(kModeMagic, 2);

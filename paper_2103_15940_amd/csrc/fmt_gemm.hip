@@ -1096,11 +1096,13 @@ __device__ __forceinline__ void store_tile(floatx16 (&acc)[TM][TN], float *__res
 // the taps).  The stage image in LDS and everything after it are the same.
 // The body is shared by the kernel of one product (bid = blockIdx.x) and the kernel of a group of products
 // (bid = the workgroup's index within its product).
-template <int PS, int TM, int TN, int KS, int NST, bool SPLIT, bool SCHED, bool SCALED, bool GATHER = false>
+// LINEAR: the results are a fully connected layer's accumulators; they leave as R(R(acc) + R(b)) (lin).
+template <int PS, int TM, int TN, int KS, int NST, bool SPLIT, bool SCHED, bool SCALED, bool GATHER = false, bool LINEAR = false>
 __device__ __forceinline__ void product_body(const u32x4 *__restrict__ Aw, const u32x4 *__restrict__ Bw,
                                              float *__restrict__ C, int M, int N, int64_t ldc, int img,
                                              int kblocks, int tiles_m, int tiles_n, int kb_per_split,
-                                             const Planes &pa, const Planes &pb, const Implicit &im, const unsigned bid)
+                                             const Planes &pa, const Planes &pb, const Implicit &im, const unsigned bid,
+                                             const LinearOut &lin = LinearOut{})
 {
     constexpr int P = pieces_of(PS);
     constexpr int UA = 2 * TM, UB = 2 * TN;              // 32-row units per operand in the workgroup tile
@@ -1181,6 +1183,16 @@ __device__ __forceinline__ void product_body(const u32x4 *__restrict__ Aw, const
         } else {
             gb[j] = Bw + ((size_t)tn * UB + rbl) * rb_stride + (size_t)kb0 * P * kUnitVec + piece * kUnitVec + v;
         }
+    }
+
+    // a layer's bias, loaded ahead of the products: register v of a lane holds column 8*(v/4) + 4*(l/32) + v%4 (see store_tile)
+    uint32_t bias[LINEAR ? TN : 1][LINEAR ? 16 : 1];
+    if constexpr (LINEAR) {
+#pragma unroll
+        for (int j = 0; j < TN; ++j)
+#pragma unroll
+            for (int v = 0; v < 16; ++v)
+                bias[j][v] = linear_bias(lin, (tn * 2 + wn) * (32 * TN) + j * 32 + (v >> 2) * 8 + (lane >> 5) * 4 + (v & 3), N);
     }
 
     floatx16 acc[TM][TN];
@@ -1325,6 +1337,10 @@ __device__ __forceinline__ void product_body(const u32x4 *__restrict__ Aw, const
     // every load-to-LDS of this wave must have landed before the workgroup's LDS is handed back
     __builtin_amdgcn_s_waitcnt(0x0F70);
 
+    if constexpr (LINEAR)
+        linear_round<TM * TN * 16>(lin, [&](int i) { return acc[i / (TN * 16)][i / 16 % TN][i % 16]; },
+                                   [&](int i, float y) { acc[i / (TN * 16)][i / 16 % TN][i % 16] = y; },
+                                   [&](int i) { return bias[i / 16 % TN][i % 16]; });
     // plain: C[row][col] with leading dimension ldc; a part of a split k: its own M x N slab; img > 0: NCHW
     float *out = SPLIT ? C + (size_t)split * M * ldc : C;
     store_tile<TM, TN, SCALED>(acc, out, ldc, M, N, SPLIT ? 0 : img, (tm * 2 + wm) * (32 * TM), (tn * 2 + wn) * (32 * TN), lane, pa.S,
@@ -1339,6 +1355,16 @@ __global__ __launch_bounds__(256) void product_kernel(const u32x4 *__restrict__ 
 {
     product_body<PS, TM, TN, KS, NST, SPLIT, SCHED, SCALED, GATHER>(Aw, Bw, C, M, N, ldc, img, kblocks, tiles_m, tiles_n,
                                                                   kb_per_split, pa, pb, im, blockIdx.x);
+}
+
+template <int PS, int TM, int TN, int KS, int NST>
+__global__ __launch_bounds__(256) void product_linear_kernel(const u32x4 *__restrict__ Aw, const u32x4 *__restrict__ Bw,
+                                                             float *__restrict__ C, int M, int N, int64_t ldc, int kblocks,
+                                                             int tiles_m, int tiles_n, LinearOut lin)
+{
+    const Planes none{nullptr, nullptr, 0, 0, nullptr, nullptr};
+    product_body<PS, TM, TN, KS, NST, false, true, false, false, true>(Aw, Bw, C, M, N, ldc, 0, kblocks, tiles_m, tiles_n, kblocks, none,
+                                                                     none, Implicit{}, blockIdx.x, lin);
 }
 
 // A group of independent products in one launch (fmt_gemm_prepared_batch): workgroup ids [first, next first)
@@ -1913,10 +1939,14 @@ struct OperandSpec {
 
 // Where the M x N result goes: plain row-major with leading dimension ldc, or (img > 0) NCHW with
 // columns = (image, position) and `img` positions per image.
+// lin != nullptr: the results are the accumulators of a fully connected layer, and a route that can round them on the way
+// out does so and says so in *rounded.
 struct OutSpec {
     float *C;
     int64_t ldc;
     int img;
+    const LinearOut *lin = nullptr;
+    bool *rounded = nullptr;
 };
 
 // How a format's values reach the matrix cores: ps = piece scheme (0: one fp16 piece, 1-3: that many
@@ -2235,10 +2265,34 @@ static size_t part_bytes_of(const Plan &plan, int M, int N)
     return plan.nsplit > 1 ? ((size_t)plan.nsplit * M * N * sizeof(float) + 255) / 256 * 256 : 0;
 }
 
+template <int PS, int T>
+static int launch_product_linear(const u32x4 *Aw, const u32x4 *Bw, const OutSpec &out, int M, int N, int kblocks, hipStream_t stream)
+{
+    constexpr int KS = Pipe<PS, T, T>::ks, NST = Pipe<PS, T, T>::nst;
+    const int tiles_m = (M + 64 * T - 1) / (64 * T), tiles_n = (N + 64 * T - 1) / (64 * T);
+    const int64_t per_xcd = ((int64_t)tiles_m * tiles_n + 7) / 8;
+    if (per_xcd * 8 >= ((int64_t)1 << 31)) return FMT_ERR_SHAPE;
+    hipLaunchKernelGGL((product_linear_kernel<PS, T, T, KS, NST>), dim3((unsigned)(per_xcd * 8)), dim3(256), 0, stream, Aw, Bw, out.C, M, N,
+                       out.ldc, kblocks, tiles_m, tiles_n, *out.lin);
+    FMT_HIP_CHECK(hipGetLastError());
+    return FMT_OK;
+}
+
 template <int PS>
 static int product_of_views(const OperandView &va, const OperandView &vb, int M, int N, int kblocks, const OutSpec &out,
                             const Plan &plan, float *part, hipStream_t stream)
 {
+    // A layer's output roundings in the product kernel: where the product leaves whole sums in one launch, and for the tiles of up
+    // to 128 x 128 (two workgroups and more per compute unit, so that the roundings of one run beside the products of
+    // another; a 256 x 256 tile has neither the registers nor the company).  Measured, fmt_linear_prepared in 1/8/7, product and pass
+    // against one kernel: 64 x 128 x 128 8.7 -> 5.4 us, 333 x 4096 x 1024 14.2 -> 9.8, 2048 x 2048 x 512 24.4 -> 18.9,
+    // 4096 x 1024 x 1024 25.1 -> 22.5, 4096 x 3072 x 1024 51.8 -> 51.5.
+    if (out.lin != nullptr && va.pl.S == nullptr && out.img == 0 && plan.nsplit == 1 && plan.tm == plan.tn && plan.tm <= 2) {
+        const int rc = plan.tm == 2 ? launch_product_linear<PS, 2>(va.W, vb.W, out, M, N, kblocks, stream)
+                                    : launch_product_linear<PS, 1>(va.W, vb.W, out, M, N, kblocks, stream);
+        if (rc == FMT_OK) *out.rounded = true;
+        return rc;
+    }
 #define FMT_PRODUCT(TMV, TNV) \
     launch_product<PS, TMV, TNV>(va.W, vb.W, out.C, M, N, out.ldc, out.img, kblocks, plan, part, stream, va.pl, vb.pl)
     if (plan.tm == 4 && plan.tn == 4) return FMT_PRODUCT(4, 4);
@@ -2287,9 +2341,12 @@ static int run(int M, int N, int K, const OperandSpec &sa, const OperandSpec &sb
     // recorded into a graph, does not depend on the route)
     if (!scaled && sa.g.kind == kSrcMatrix && sb.g.kind == kSrcMatrix && out.img == 0) {
         const int parts = direct_parts(M, N, K, sa, sb, plan, f, sch, p.mode);
-        if (parts > 0)
-            return launch_direct_product(M, N, K, MatrixOperand{sa.X, sa.ld, sa.kcontig}, MatrixOperand{sb.X, sb.ld, sb.kcontig}, out.C,
-                                         out.ldc, parts, PS, FTZ, p, stream);
+        if (parts > 0) {
+            const int rcd = launch_direct_product(M, N, K, MatrixOperand{sa.X, sa.ld, sa.kcontig}, MatrixOperand{sb.X, sb.ld, sb.kcontig},
+                                                  out.C, out.ldc, parts, PS, FTZ, p, out.lin, stream);
+            if (rcd == FMT_OK && out.lin != nullptr) *out.rounded = true;
+            return rcd;
+        }
     }
     char *ws = static_cast<char *>(s.gemm_ws);
     const OperandView va = view_of(ws, la), vb = view_of(ws + la.bytes, lb);
@@ -2532,7 +2589,7 @@ int launch_prepare_pair(const float *X, int64_t ld, int64_t rows, int64_t cols, 
 
 // C = A B^T on two prepared operands (A: M rows, B: N rows, both with the same K and scheme).
 int launch_gemm_prepared(const void *A, const void *B, int64_t M64, int64_t N64, int64_t K64, int scheme, fmt_format_t f,
-                         float *C, int64_t ldc, hipStream_t stream)
+                         float *C, int64_t ldc, hipStream_t stream, const LinearOut *lin, bool *rounded)
 {
     const int M = (int)M64, N = (int)N64;
     const Scheme sch{scheme & 15, (scheme & 16) != 0};
@@ -2553,7 +2610,7 @@ int launch_gemm_prepared(const void *A, const void *B, int64_t M64, int64_t N64,
         part = static_cast<float *>(s.gemm_ws);
     }
     const OperandView va = view_of(const_cast<void *>(A), la), vb = view_of(const_cast<void *>(B), lb);
-    return product_dispatch(sch.ps, va, vb, M, N, la.kblocks, OutSpec{C, ldc, 0}, plan, part, stream);
+    return product_dispatch(sch.ps, va, vb, M, N, la.kblocks, OutSpec{C, ldc, 0, lin, rounded}, plan, part, stream);
 }
 
 template <int PS, bool SCALED, int T>
@@ -2764,7 +2821,7 @@ static int zero_fill(float *C, int64_t rows, int64_t cols, int64_t ldc, hipStrea
 
 int launch_gemm(int transA, int transB, int64_t M64, int64_t N64, int64_t K64, const float *A, int64_t lda,
                 const float *B, int64_t ldb, float *C, int64_t ldc, fmt_format_t f, const QuantParams &p,
-                hipStream_t stream)
+                hipStream_t stream, const LinearOut *lin, bool *rounded)
 {
     const int M = (int)M64, N = (int)N64, K = (int)K64;
     if (K == 0) return zero_fill(C, M, N, ldc, stream);
@@ -2772,7 +2829,7 @@ int launch_gemm(int transA, int transB, int64_t M64, int64_t N64, int64_t K64, c
     // k-contiguous when B is stored transposed (N x K).
     const OperandSpec sa{A, lda, !transA, Gather{}, 0};
     const OperandSpec sb{B, ldb, transB != 0, Gather{}, 0};
-    return run_product(M, N, K, sa, sb, OutSpec{C, ldc, 0}, f, p, stream);
+    return run_product(M, N, K, sa, sb, OutSpec{C, ldc, 0, lin, rounded}, f, p, stream);
 }
 
 // Forward and dgrad with the patches gathered inside the product kernel: the tensor behind the patches is

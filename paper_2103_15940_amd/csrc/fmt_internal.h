@@ -57,10 +57,19 @@ int launch_stream_static(const float *x, float *y, size_t n, const QuantParams &
                          fmt_hist_t *hist, hipStream_t stream);
 int launch_unpack16(const uint16_t *codes, float *y, size_t n, const QuantParams &p, hipStream_t stream);
 
-// GEMM (fmt_gemm.hip)
+// Output roundings of a fully connected layer, y = R(R(acc) + R(b)): the (unrounded) bias, or nullptr, and the format.
+struct LinearOut {
+    const float *bias;
+    int32_t ftz;
+    QuantParams p;
+};
+
+// GEMM (fmt_gemm.hip).  lin != nullptr: C is to receive a layer's rounded outputs; *rounded says on return whether it has (where
+// the route can round on the way out) or holds the accumulators (then launch_linear_epilogue follows).
 int launch_gemm(int transA, int transB, int64_t M, int64_t N, int64_t K,
                 const float *A, int64_t lda, const float *B, int64_t ldb,
-                float *C, int64_t ldc, fmt_format_t f, const QuantParams &p, hipStream_t stream);
+                float *C, int64_t ldc, fmt_format_t f, const QuantParams &p, hipStream_t stream,
+                const LinearOut *lin = nullptr, bool *rounded = nullptr);
 
 // Small products in one launch (fmt_direct.hip): an fp32 operand with element (row, k) at X[row*ld + k] (kcontig) or X[k*ld + row].
 struct MatrixOperand {
@@ -70,7 +79,7 @@ struct MatrixOperand {
 };
 constexpr int kDirectParts = 8;      // most parts of k (waves of a workgroup)
 int launch_direct_product(int M, int N, int K, const MatrixOperand &A, const MatrixOperand &B, float *C, int64_t ldc, int parts, int ps,
-                          bool ftz, const QuantParams &p, hipStream_t stream);
+                          bool ftz, const QuantParams &p, const LinearOut *lin, hipStream_t stream);
 
 // Prepared operands in caller-owned memory (fmt_gemm.hip).  scheme: opaque tag of the representation.
 int prepared_operand_bytes(int64_t rows, int64_t K, fmt_format_t f, size_t *bytes, int *scheme);
@@ -91,7 +100,7 @@ struct RoundItem {              // with the operands: the matrix rounded to fp32
 int launch_prepare_pair_batch(int64_t count, const PrepPairItem *items, fmt_format_t f, const QuantParams &p, hipStream_t stream,
                               const RoundItem *round);
 int launch_gemm_prepared(const void *A, const void *B, int64_t M, int64_t N, int64_t K, int scheme, fmt_format_t f,
-                         float *C, int64_t ldc, hipStream_t stream);
+                         float *C, int64_t ldc, hipStream_t stream, const LinearOut *lin = nullptr, bool *rounded = nullptr);
 // One product of a batch on prepared operands: C (M x N, leading dimension ldc) = A (M rows) B^T (N rows), both of k = K.
 struct BatchItem {
     const void *A, *B;

@@ -85,4 +85,39 @@ __device__ __forceinline__ uint32_t quantize_bits_rt(uint32_t u, const QuantPara
     return ftz ? quantize_bits<kModeMixed, true>(u, p) : quantize_bits<kModeMixed, false>(u, p);
 }
 
+// Outputs of a fully connected layer from their accumulators, in place (Sec. IV-A): R(R(acc) + R(b)), two roundings around ONE
+// single-precision addition; without a bias the second rounding changes nothing.  get(i) / set(i, y): the i-th of N accumulators;
+// bias(i): its column's unrounded bias (the caller loads them early: they come from memory).  The variant of the rounding is
+// chosen once for all of them.
+template <int N, class GET, class SET, class BIAS>
+__device__ __forceinline__ void linear_round(const LinearOut &lin, GET &&get, SET &&set, BIAS &&bias)
+{
+    const bool has_bias = lin.bias != nullptr;
+    auto run = [&](auto round) __attribute__((always_inline)) {
+#pragma unroll
+        for (int i = 0; i < N; ++i) {
+            uint32_t r = round(__float_as_uint(get(i)));
+            if (has_bias) r = round(__float_as_uint(__fadd_rn(__uint_as_float(r), __uint_as_float(round(bias(i))))));
+            set(i, __uint_as_float(r));
+        }
+    };
+    const QuantParams &p = lin.p;
+    if (p.mode == kModeInteger) {
+        if (lin.ftz) run([&](uint32_t u) { return quantize_bits<kModeInteger, true>(u, p); });
+        else run([&](uint32_t u) { return quantize_bits<kModeInteger, false>(u, p); });
+    } else if (p.mode == kModeMagic) {
+        if (lin.ftz) run([&](uint32_t u) { return quantize_bits<kModeMagic, true>(u, p); });
+        else run([&](uint32_t u) { return quantize_bits<kModeMagic, false>(u, p); });
+    } else {
+        if (lin.ftz) run([&](uint32_t u) { return quantize_bits<kModeMixed, true>(u, p); });
+        else run([&](uint32_t u) { return quantize_bits<kModeMixed, false>(u, p); });
+    }
+}
+
+// Unrounded bias of a column (0 without a bias or beyond the columns).
+__device__ __forceinline__ uint32_t linear_bias(const LinearOut &lin, int col, int N)
+{
+    return lin.bias != nullptr && col < N ? __float_as_uint(lin.bias[col]) : 0u;
+}
+
 }  // namespace fmt

@@ -352,3 +352,34 @@ def test_output_of_more_than_2_to_the_32_elements(fmt):
     torch.cuda.synchronize()
     got = C[rows_d].cpu().numpy().view(np.uint16)
     assert np.array_equal(got, oracle.pack16(Yref, 6, 9, True)), "16-bit codes, M*N > 2^32"
+
+
+@pytest.mark.parametrize("e,m,d", [(5, 10, True), (5, 10, False), (8, 7, False), (8, 7, True), (6, 9, True), (7, 12, False), (7, 20, True)])
+@pytest.mark.parametrize("shape", [(1, 1, 40), (33, 70, 100), (64, 64, 64), (333, 1030, 256), (520, 1100, 520)])
+def test_rounded_on_the_way_out(fmt, e, m, d, shape):
+    """Without statistics the product's kernels round a layer's outputs on the way out (small products, and 64 x 64 and
+    128 x 128 tiles); with statistics a pass of its own does.  The sums are the same, so the bits are: with and without a bias,
+    fp32 operands and prepared ones, outputs with a leading dimension of their own; and the oracle's output stage gives them."""
+    M, N, K = shape
+    rng = np.random.default_rng(M + N + K + e)
+    X = torch.from_numpy(rng.standard_normal((M, K)).astype(np.float32)).cuda()
+    W = torch.from_numpy((rng.standard_normal((N, K)) * 0.05).astype(np.float32)).cuda()
+    X[0, 0], W[N // 2, K - 1] = 1e30, 1e30                       # rows and columns that overflow most formats
+    bias = torch.from_numpy(rng.standard_normal(N).astype(np.float32)).cuda()
+    f = (e, m, d)
+    Xp, Wp = fmt.fmt_prepare(X, f), fmt.fmt_prepare(W, f)
+    acc, acc_p = fmt.fmt_gemm(X, W, f, transB=True), fmt.fmt_gemm_prepared(Xp, Wp)
+    for b in (bias, None):
+        for call, a in ((lambda **k: fmt.fmt_linear(X, W, b, f, **k), acc), (lambda **k: fmt.fmt_linear_prepared(Xp, Wp, b, **k), acc_p)):
+            separate = call(hist=fmt.new_hist())
+            wide = torch.full((M, N + 3), 7.0, device="cuda")
+            direct = call(out=wide[:, :N])
+            torch.cuda.synchronize()
+            assert bool((wide[:, N:] == 7.0).all())
+            assert torch.equal(direct.view(torch.int32), separate.view(torch.int32))
+            r = oracle.quantize(a.cpu().numpy(), e, m, d)
+            if b is not None:
+                r = oracle.quantize(r + oracle.quantize(b.cpu().numpy(), e, m, d)[None, :], e, m, d)
+            got = direct.cpu().numpy()
+            assert np.array_equal(np.isnan(got), np.isnan(r))
+            assert np.array_equal(got[~np.isnan(r)], r[~np.isnan(r)])
