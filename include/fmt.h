@@ -45,7 +45,11 @@
  *     histogram counts; pre-split GEMM operands).  They are created on first use with
  *     hipMalloc, grow when a larger problem arrives, and live until fmt_release_scratch()
  *     or process exit.  Calls on one stream are serialised by the stream; calls on
- *     different streams use different scratch and may overlap.  Once a call of the same
+ *     different streams use different scratch and may overlap.  What shares scratch must not overlap in
+ *     time: replays of graphs recorded on one stream (with one another, or with calls on that stream), and
+ *     calls of several threads on hipStreamPerThread, which is one handle, and so one scratch, for all of them.
+ *     Such calls spoil each other's results, and may spoil the statistics of the next two passes on the
+ *     stream, which put the scratch right again.  Once a call of the same
  *     kind and size has run on a stream, further calls on it neither allocate nor
  *     synchronise (scratch is cleared by kernels, not by memset), so they can be recorded
  *     into a HIP graph on that stream and replayed.  A recorded graph holds the addresses of
@@ -286,8 +290,8 @@ int fmt_prepare_pair_batch(int64_t count, const float *const *X, const int64_t *
  * (same address and leading dimension: in place); otherwise nothing written may overlap anything else of the call
  * (FMT_ERR_ALIAS).  Arrays are HOST arrays of `count` entries; Y[i], hist[i], data[i], data_t[i] DEVICE pointers
  * (hist[i] 8-byte aligned).  Other arguments and errors as for fmt_prepare_pair_batch; FMT_ERR_RANGE for exp_lo as
- * for fmt_quantize.  Uses the stream's library scratch for the partial statistics records (576 KiB against the
- * 36 KiB of fmt_quantize: the first call on a stream makes that scratch grow, which invalidates graphs recorded on
+ * for fmt_quantize.  Uses the stream's library scratch for the partial statistics records (695 KiB against the
+ * 110 KiB of fmt_quantize: the first call on a stream makes that scratch grow, which invalidates graphs recorded on
  * the stream before it, and cannot happen inside a capture -- run the call once eagerly first; see the notes on
  * scratch at the top).
  */

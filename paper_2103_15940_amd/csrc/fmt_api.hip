@@ -9,6 +9,7 @@
 #include <mutex>
 #include <utility>
 
+#include "fmt_hist.h"
 #include "fmt_internal.h"
 
 namespace fmt {
@@ -96,6 +97,30 @@ int get_scratch(hipStream_t stream, size_t hist_bytes, size_t gemm_bytes, Scratc
     rc = grow(stream, &s.gemm_ws, &s.gemm_bytes, gemm_bytes);
     if (rc != FMT_OK) return rc;
     *out = s;
+    return FMT_OK;
+}
+
+int get_hist_records(hipStream_t stream, uint64_t nwg, HistRecords *out)
+{
+    int dev = 0;
+    FMT_HIP_CHECK(hipGetDevice(&dev));
+    std::lock_guard<std::mutex> lk(g_mu);
+    Scratch &s = g_scratch[std::make_pair(dev, stream)];
+    const int rc = grow(stream, &s.hist_partials, &s.hist_bytes, kHistScratchBytes);
+    if (rc != FMT_OK) return rc;
+    unsigned long long *rec = static_cast<unsigned long long *>(s.hist_partials);
+    *out = HistRecords{rec, nullptr, 0u};
+    if (nwg == 1) return FMT_OK;
+    // A recorded pass takes the same records at every replay, so there is no other set whose turn it would be: it takes the records
+    // that a second kernel sums and clears.  (The default stream cannot be captured, and asking about it while another
+    // stream is being captured is an error.)
+    hipStreamCaptureStatus capturing = hipStreamCaptureStatusNone;
+    if (stream != nullptr && stream != hipStreamLegacy) FMT_HIP_CHECK(hipStreamIsCapturing(stream, &capturing));
+    if (capturing != hipStreamCaptureStatusNone) return FMT_OK;
+    const unsigned many = nwg > kFew ? 1u : 0u, words = many ? kSetWords : kSlots;
+    const unsigned turn = s.hist_turn[many] ^= 1u;
+    unsigned long long *sets = rec + kShards * kSlots + many * 2 * kSlots;
+    *out = HistRecords{sets + turn * words, sets + (turn ^ 1u) * words, words};
     return FMT_OK;
 }
 

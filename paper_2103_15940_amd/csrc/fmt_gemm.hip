@@ -925,7 +925,7 @@ struct RoundGroup {
     uint32_t *Y[kMaxPrepGroup / 2];
     int64_t ldy[kMaxPrepGroup / 2];
     unsigned long long *hist[kMaxPrepGroup / 2];     // the callers' records
-    unsigned long long *records;                     // kShards + 1 partial records per matrix
+    unsigned long long *records;                     // kSetWords words of partial records per matrix
     int steps;                                   // steps of kPairTiles tiles per workgroup
 };
 
@@ -959,8 +959,8 @@ __global__ __launch_bounds__(256) void prepare_scaled_group_kernel(PrepGroup grp
     }
     if constexpr (ROUND)
         hist_end<kPairCopies, 256>(tbl, s_bins, s_cls, w, p,
-                                   HistSink{rg.records + (size_t)at * (kShards + 1) * kSlots, rg.hist[at],
-                                            (unsigned long long)o0.rows * (unsigned long long)o1.rows, (uint32_t)kShards},
+                                   HistSink{rg.records + (size_t)at * kSetWords, rg.hist[at],
+                                            (unsigned long long)o0.rows * (unsigned long long)o1.rows, (uint32_t)kShards, 0u, nullptr},
                                    g, nwg, threadIdx.x);
 }
 
@@ -2140,8 +2140,12 @@ struct StatGroup {
     int K[kMaxPrepGroup], kstep[kMaxPrepGroup];
 };
 
-__global__ __launch_bounds__(256) void window_stats_group_kernel(StatGroup grp, int emin, int m)
+// clear (nclear words): the partial records of the group kernel that follows.  A completed group leaves them zero; clearing them
+// here, in the same call, makes sure of it whatever an earlier call left (see hist_clear).
+__global__ __launch_bounds__(256) void window_stats_group_kernel(StatGroup grp, int emin, int m, unsigned long long *clear, unsigned nclear)
 {
+    for (unsigned i = blockIdx.x * 256u + threadIdx.x; i < nclear; i += gridDim.x * 256u)
+        __hip_atomic_store(&clear[i], 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     const int at = run_of(grp.first, blockIdx.x);
     window_stats_block(grp.o[at], grp.K[at], grp.kstep[at], emin, m, (int)(blockIdx.x - grp.first[at]));
 }
@@ -2445,7 +2449,7 @@ int launch_prepare_operand(const float *X, int64_t ld, int trans, int64_t rows, 
 // the records within a list may differ, which the product's tail sorts away).
 // round != nullptr: the same launch also writes every matrix rounded to fp32 (round[i].Y) and counts its elements
 // into round[i].hist, as fmt_quantize does (window from p.exp_lo); planes formats only (FMT_ERR_FORMAT otherwise).
-static_assert(sizeof(PrepGroup) + sizeof(RoundGroup) + sizeof(QuantParams) <= 4096 && sizeof(StatGroup) + 8 <= 4096,
+static_assert(sizeof(PrepGroup) + sizeof(RoundGroup) + sizeof(QuantParams) <= 4096 && sizeof(StatGroup) + 24 <= 4096,
               "group tables travel in the kernel arguments");
 
 int launch_prepare_pair_batch(int64_t count, const PrepPairItem *items, fmt_format_t f, const QuantParams &p, hipStream_t stream,
@@ -2459,9 +2463,9 @@ int launch_prepare_pair_batch(int64_t count, const PrepPairItem *items, fmt_form
             if (!(api_scheme(f, items[i].cols).scaled && api_scheme(f, items[i].rows).scaled && p.mode == kModeMagic))
                 return FMT_ERR_FORMAT;
         Scratch sc;
-        const int rc = get_scratch(stream, (size_t)(kMaxPrepGroup / 2) * kHistScratchBytes, 0, &sc);
+        const int rc = get_scratch(stream, kHistScratchBytes + (size_t)(kMaxPrepGroup / 2) * kSetWords * sizeof(unsigned long long), 0, &sc);
         if (rc != FMT_OK) return rc;
-        rg.records = static_cast<unsigned long long *>(sc.hist_partials);
+        rg.records = static_cast<unsigned long long *>(sc.hist_partials) + kHistScratchBytes / sizeof(unsigned long long);
         // steps per workgroup: as many as leave every compute unit four workgroups (measured on 12 tensors of 4 M to 16 M
         // elements: one step 267 us, four 242 us, eight 258 us; one tensor of 4 M elements: four 36 us)
         int cus = 0;
@@ -2488,7 +2492,8 @@ int launch_prepare_pair_batch(int64_t count, const PrepPairItem *items, fmt_form
             pg.first[i] = 0xFFFFFFFFu;
             pg.tiles[i] = 0u;
         }
-        hipLaunchKernelGGL(window_stats_group_kernel, dim3(stat_ids), dim3(256), 0, stream, sg, 1 - bias, f.m);
+        hipLaunchKernelGGL(window_stats_group_kernel, dim3(stat_ids), dim3(256), 0, stream, sg, 1 - bias, f.m, rg.records,
+                           round != nullptr ? (unsigned)(n / 2 * kSetWords) : 0u);
         FMT_HIP_CHECK(hipGetLastError());
 #define FMT_PAIR_LAUNCH(FTZV, ROUNDV, DEEPV)                                                                           \
     hipLaunchKernelGGL((prepare_scaled_group_kernel<kModeMagic, FTZV, ROUNDV, DEEPV>), dim3(prep_ids), dim3(256), 0, stream, pg, \

@@ -13,6 +13,14 @@ constexpr int kShards = 64;              // partial records in global memory (wo
 // slots of a partial record
 enum { P_Z = 0, P_ZU, P_ZUD, P_TOP, P_INFNAN, P_NAN, P_BINS = 8 };
 
+// Library scratch of a stream's statistics, in words of 8 bytes: kShards records for passes that are summed by a second kernel;
+// for the passes of one launch, which take two sets in turn (see hist_clear), two sets of one record for launches of
+// at most kFew workgroups, and two of kShards records and one of their sums for the others; and, where the stream has
+// rounded groups of matrices, one set per matrix of a group (cleared by the group's first launch).
+constexpr int kFew = 64;
+constexpr int kSetWords = (kShards + 1) * kSlots;
+constexpr size_t kHistScratchBytes = (size_t)(kShards * kSlots + 2 * kSlots + 2 * kSetWords) * sizeof(unsigned long long);
+
 struct Counts {                          // per-lane counters, reduced once at the end
     uint32_t z = 0, zu = 0, zud = 0, top = 0, infnan = 0, nan = 0;
 };
@@ -95,7 +103,21 @@ struct HistSink {
     unsigned long long *hist;            // the caller's fmt_hist_t
     unsigned long long n;                // elements of the tensor
     uint32_t shards;                     // records in use
+    uint32_t nclear;
+    unsigned long long *clear;           // nclear words to set to zero meanwhile (hist_clear)
 };
+
+// Clears the set of records that the next pass on the stream takes.  A completed pass leaves its records zero by itself; passes
+// that overlap on the same records (which the header forbids: replays of two graphs recorded on one stream, say) leave
+// counts and arrivals behind that no later arrival would ever put right.  So passes take two sets in turn, each clearing the
+// other's: what is left behind spoils at most the first pass that meets it.  At most one store per thread, beside the loads
+// of the first tiles (37 KB cleared by three workgroups cost 0.4 us of 5.3: hence the small sets).  All BLOCK threads call it.
+template <int BLOCK>
+__device__ __forceinline__ void hist_clear(const HistSink &sink, uint32_t wg, uint32_t nwg, uint32_t tid)
+{
+    for (uint32_t i = wg * BLOCK + tid; i < sink.nclear; i += nwg * BLOCK)
+        __hip_atomic_store(&sink.clear[i], 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
 
 // Slot `slot` of the caller's record from the 72 summed counts and the number of elements.
 __device__ __forceinline__ unsigned long long hist_slot(const unsigned long long *tot, unsigned long long n, int slot)
@@ -199,22 +221,19 @@ __device__ __forceinline__ void hist_end(uint32_t *tbl, uint32_t *s_bins, uint32
 // Sums the partial records into the caller's fmt_hist_t and clears them (fmt_stream.hip).
 int launch_hist_finalize(unsigned long long *partials, size_t n, fmt_hist_t *hist, hipStream_t stream);
 
-// Scratch bytes the partial records need (one more than the shards: the sums of the records of a single launch).
-constexpr size_t kHistRecordBytes = (size_t)kShards * kSlots * sizeof(unsigned long long);
-constexpr size_t kHistScratchBytes = kHistRecordBytes + kSlots * sizeof(unsigned long long);
-
-// The sink of a launch of nwg workgroups whose counts end in `hist` (n elements, below 2^48), with library scratch at
-// `scratch` (kHistScratchBytes): one workgroup writes the record itself (scratch may be null), up to `most` workgroups
-// (and fewer than 2^21: a record counts its additions in 16 bits) finish in the launch, more leave their records to launch_hist_finalize (then sink.hist is null).
-// Records in use: additions to one address take about 12 ns each, so up to 64 workgroups share one record and
+// The sink of a launch of nwg workgroups whose counts end in `hist` (n elements, below 2^48): one workgroup writes the
+// record itself (no records needed); up to `most` workgroups (and fewer than 2^21: a record counts its additions in 16 bits)
+// finish in the launch, more leave their records to launch_hist_finalize (then sink.hist is null), as do passes
+// whose records nobody clears ahead (at.clear null: captured ones).
+// Records in use: additions to one address take about 12 ns each, so up to kFew workgroups share one record and
 // one hop; beyond that the additions are spread and a second hop sums the records.
-inline HistSink hist_sink(void *scratch, unsigned long long n, fmt_hist_t *hist, uint64_t nwg, uint64_t most)
+inline HistSink hist_sink(const HistRecords &at, unsigned long long n, fmt_hist_t *hist, uint64_t nwg, uint64_t most)
 {
-    unsigned long long *rec = static_cast<unsigned long long *>(scratch);
     unsigned long long *out = reinterpret_cast<unsigned long long *>(hist);
-    if (nwg == 1) return HistSink{nullptr, out, n, 1u};
-    if (nwg <= most && nwg < ((uint64_t)1 << 21)) return HistSink{rec, out, n, nwg <= 64 ? 1u : nwg <= 1024 ? 16u : (uint32_t)kShards};
-    return HistSink{rec, nullptr, n, (uint32_t)kShards};
+    if (nwg == 1) return HistSink{nullptr, out, n, 1u, 0u, nullptr};
+    if (at.clear != nullptr && nwg <= most && nwg < ((uint64_t)1 << 21))
+        return HistSink{at.records, out, n, nwg <= kFew ? 1u : nwg <= 1024 ? 16u : (uint32_t)kShards, at.nclear, at.clear};
+    return HistSink{at.records, nullptr, n, (uint32_t)kShards, at.nclear, at.clear};
 }
 
 }  // namespace fmt

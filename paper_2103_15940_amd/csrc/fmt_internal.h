@@ -34,8 +34,9 @@ int make_quant_params(fmt_format_t f, int32_t exp_lo, QuantParams *p);
 
 // Library-owned scratch of one (device, stream) pair.
 struct Scratch {
-    void *hist_partials = nullptr;  // per-workgroup partial counts of the stream kernels
+    void *hist_partials = nullptr;  // partial records of the statistics (layout: fmt_hist.h)
     size_t hist_bytes = 0;
+    unsigned hist_turn[2] = {0, 0}; // which of the two sets of the one-launch passes the last pass took (few, many workgroups)
     void *gemm_ws = nullptr;        // pre-split GEMM operands
     size_t gemm_bytes = 0;
     void *acc_ws = nullptr;         // fp32 accumulators of fmt_linear_pack16
@@ -44,6 +45,15 @@ struct Scratch {
 
 // Returns the scratch record for (current device, stream), growing the requested buffers.
 int get_scratch(hipStream_t stream, size_t hist_bytes, size_t gemm_bytes, Scratch *out);
+
+// Room for the partial records of one statistics pass of nwg workgroups on `stream` (fmt_hist.h): the records it adds into, and
+// what the pass clears meanwhile for the pass after it (nullptr: the pass is being captured, and its records are summed
+// and cleared by launch_hist_finalize; or it has one workgroup and needs none).
+struct HistRecords {
+    unsigned long long *records, *clear;
+    unsigned nclear;                // words
+};
+int get_hist_records(hipStream_t stream, uint64_t nwg, HistRecords *out);
 
 int device_cu_count(int *cus);
 

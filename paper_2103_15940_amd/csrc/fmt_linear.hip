@@ -42,7 +42,10 @@ __global__ __launch_bounds__(kLBlock) void linear_epilogue_kernel(const uint32_t
     const uint32_t tid = threadIdx.x;
     const uint32_t copy = tid & (kLCopies - 1);
     Counts w;
-    if (HIST) hist_begin<kLCopies, kLBlock>(tbl, s_bins, s_cls, tid);
+    if (HIST) {
+        hist_begin<kLCopies, kLBlock>(tbl, s_bins, s_cls, tid);
+        hist_clear<kLBlock>(sink, blockIdx.y * gridDim.x + blockIdx.x, gridDim.x * gridDim.y, tid);
+    }
 
     const int64_t c0 = ((int64_t)blockIdx.x * kLBlock + (int64_t)tid) * 4;
     const int ncol = N - c0 < 4 ? (N - c0 < 0 ? 0 : (int)(N - c0)) : 4;      // valid columns of this lane
@@ -136,10 +139,10 @@ int launch_v(const float *A, int64_t lda, void *Y, int64_t ldy, int M, int N, co
     }
     HistSink sink{};
     if (HIST) {
-        Scratch s;
-        rc = get_scratch(stream, kHistScratchBytes, 0, &s);
+        HistRecords at;
+        rc = get_hist_records(stream, (uint64_t)strips * row_groups, &at);
         if (rc != FMT_OK) return rc;
-        sink = hist_sink(s.hist_partials, (unsigned long long)M * (unsigned long long)N, hist, (uint64_t)strips * row_groups, kLastArrival);
+        sink = hist_sink(at, (unsigned long long)M * (unsigned long long)N, hist, (uint64_t)strips * row_groups, kLastArrival);
     }
     const bool vec = (reinterpret_cast<uintptr_t>(A) % 16 == 0) && (lda % 4 == 0) &&
                      (reinterpret_cast<uintptr_t>(Y) % (PACK ? 8 : 16) == 0) && (ldy % 4 == 0);

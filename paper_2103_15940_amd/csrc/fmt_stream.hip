@@ -138,6 +138,7 @@ __global__ __launch_bounds__(kBlock) void stream_kernel(const uint32_t *__restri
         if (HIST) {
             load(t);
             hist_begin<kCopies, kBlock>(tbl, s_bins, s_cls, tid);
+            hist_clear<kBlock>(sink, blockIdx.x, gridDim.x, tid);
         }
         while (t < full_tiles) {
             if (!HIST) load(t);
@@ -181,7 +182,10 @@ __global__ __launch_bounds__(kBlock) void stream_kernel(const uint32_t *__restri
             if (STORE && edge) put_one(edge_at, quantize_bits<MODE, FTZ>(edge_u, p));
         }
     } else {
-        if (HIST) hist_begin<kCopies, kBlock>(tbl, s_bins, s_cls, tid);
+        if (HIST) {
+            hist_begin<kCopies, kBlock>(tbl, s_bins, s_cls, tid);
+            hist_clear<kBlock>(sink, blockIdx.x, gridDim.x, tid);
+        }
         const size_t stride = (size_t)gridDim.x * kBlock;
         // every lane runs the same number of trips
         const size_t trips = (n + stride - 1) / stride;
@@ -272,14 +276,12 @@ static int launch_variant(const float *x, void *y, size_t n, size_t head, size_t
     if (grid < 1) grid = 1;
     HistSink sink{};
     if (HIST) {
-        void *records = fixed_partials;
-        if (records == nullptr) {
-            Scratch s;
-            rc = get_scratch(stream, kHistScratchBytes, 0, &s);
+        HistRecords at{fixed_partials, nullptr, 0u};
+        if (fixed_partials == nullptr) {
+            rc = get_hist_records(stream, (uint64_t)grid, &at);
             if (rc != FMT_OK) return rc;
-            records = s.hist_partials;
         }
-        sink = hist_sink(records, n, hist, (uint64_t)grid, fixed_partials ? 0 : kOneLaunch);
+        sink = hist_sink(at, n, hist, (uint64_t)grid, kOneLaunch);
     }
     hipLaunchKernelGGL(kern, dim3(grid), dim3(kBlock), 0, stream, reinterpret_cast<const uint32_t *>(x),
                        reinterpret_cast<uint32_t *>(y), n, head, nvec, p, sink);

@@ -420,3 +420,67 @@ def test_statistics_in_one_launch(fmt, tiles, rest, offset):
         assert_same_values(y.cpu().numpy(), oracle.quantize(x, 6, 9, True), "n = %d" % n)
         for i, w in ((0, want), (1, want), (2, want_small), (3, want)):
             assert_same_hist(fmt, hist[i], w, "n = %d, pass %d" % (n, i))
+
+
+def test_statistics_after_records_left_over(fmt):
+    """Passes that overlap on one stream's scratch leave counts and arrivals in its partial records.  Here the test leaves them
+    there itself (every word of the buffer: seven arrivals and a count), so that nothing races: the first pass of few
+    workgroups and the first of many may be wrong, the next ones are right, whatever their sizes, and so are replays of a recorded pass."""
+    import ctypes
+    lib = fmt.raw_library()
+    stream = torch.cuda.Stream()
+    xs = [mixed(n, 3 + n) for n in (70001, 9000, 6 * 4096 * 1024 + 5, 4097, 300)]
+    xd = [dev(x) for x in xs]
+    want = [oracle.histogram(x, 6, 9) for x in xs]
+    A, W = torch.randint(-3, 4, (300, 64), device="cuda").float(), torch.randint(-3, 4, (2100, 64), device="cuda").float()
+    mats = [torch.randn(64 + 32 * i, 100, device="cuda") for i in range(3)]
+    bufs = [[torch.empty(fmt.fmt_operand_bytes(*m.shape[::o], (6, 9, True)), dtype=torch.uint8, device="cuda") for m in mats]
+            for o in (1, -1)]
+
+    def passes():
+        h = [fmt.new_hist().fill_(-1) for _ in range(2 * len(xs) + 1 + len(mats))]
+        for i, x in enumerate(xd):
+            fmt.fmt_quantize(x, (6, 9, True), hist=h[2 * i])
+            fmt.fmt_histogram(x, (6, 9, True), hist=h[2 * i + 1])
+        fmt.fmt_linear(A, W, None, (6, 9, True), hist=h[2 * len(xs)])
+        fmt.fmt_quantize_prepare_pair_batch(mats, (6, 9, True), [torch.empty_like(m) for m in mats], h[2 * len(xs) + 1:],
+                                            outs=bufs[0], outs_t=bufs[1])
+        return h
+
+    def leave():
+        scratch = (ctypes.c_uint64 * 8)()            # the library's record of the stream's buffers: address, bytes, ...
+        get = getattr(lib, "_ZN3fmt11get_scratchEP12ihipStream_tmmPNS_7ScratchE")
+        assert get(ctypes.c_void_p(stream.cuda_stream), ctypes.c_size_t(0), ctypes.c_size_t(0), scratch) == 0
+        left = np.full(scratch[1] // 8, (7 << 48) | 5, dtype=np.uint64)
+        lib.hipDeviceSynchronize()
+        assert lib.hipMemcpy(ctypes.c_void_p(scratch[0]), ctypes.c_void_p(left.ctypes.data), ctypes.c_size_t(left.nbytes), 1) == 0
+
+    torch.cuda.synchronize()
+    with torch.cuda.stream(stream):
+        right = passes()
+        graph = torch.cuda.CUDAGraph()
+        rec = [fmt.new_hist() for _ in xs]
+        y = [torch.empty_like(x) for x in xd]
+        stream.synchronize()
+        with torch.cuda.graph(graph, stream=stream):
+            for x, q, h in zip(xd, y, rec):
+                fmt.fmt_quantize(x, (6, 9, True), out=q, hist=h)
+        leave()
+        for first in ((0, 2), (2, 1), (1, 2)):       # one pass of 18 or 3 workgroups, one of 1024
+            for i in first:
+                fmt.fmt_histogram(xd[i], (6, 9, True))
+            after = passes()
+            stream.synchronize()
+            for a, r in zip(after, right):
+                assert torch.equal(a, r)
+            leave()
+        for replay in range(3):
+            for h in rec:
+                h.fill_(-1)
+            graph.replay()
+            stream.synchronize()
+            for i, h in enumerate(rec):
+                if replay > 0:
+                    assert_same_hist(fmt, h, want[i], "replay %d of n = %d" % (replay, xs[i].size))
+    for i in range(len(xs)):
+        assert_same_hist(fmt, right[2 * i], want[i], "n = %d" % xs[i].size)
