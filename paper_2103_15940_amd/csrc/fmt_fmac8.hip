@@ -156,6 +156,14 @@ __device__ __forceinline__ double fmac_wide(double a, double w, double x, const 
     return __hiloint2double(fabs(r) < k.minn ? 0 : __double2hiint(r), __double2loint(r));
 }
 
+// A stage's operand: a double, or (LOW) a float in the low word.
+template <class A, bool LOW>
+__device__ __forceinline__ A operand(double v)
+{
+    if constexpr (LOW) return __int_as_float(__double2loint(v));
+    else return (A)v;
+}
+
 constexpr int kFK = 32;        // k per LDS stage (a multiple of 8: FMAC-8 groups never straddle stages)
 enum { kStepSingle = 0, kStepOdd = 1 };     // the form besides the wide one that an instantiation holds
 
@@ -218,20 +226,34 @@ __global__ __launch_bounds__(256) void fmac8_kernel(const uint32_t *__restrict__
 
     if (STEP == kStepSingle) asm("" : "+v"(wc.half));      // a vector register: an instruction takes one scalar operand only
 
+    // The largest tile, whose thread uses a value four times, stores a stage for the form that the stage before it took: as fp64,
+    // or (the single form) as fp32 in the low words.  Converting at each use instead made the single form 4 % slower there
+    // (2048 x 2048 x 256 in 1/6/9: 512 us; 496 now); the smaller tiles, which gain nothing, are 2 us faster without the
+    // code for it (1024 x 1024 x 256, wide form: 66 us against 68).
+    constexpr bool kLow = STEP == kStepSingle && T > 2;
+    bool wide = true;
     load(0);
     for (int k0 = 0; k0 < K; k0 += kFK) {
         uint32_t ma = 0u, mb = 0u;
 #pragma unroll
         for (int it = 0; it < kLoads; ++it) {
-            int r, k;
-            const uint32_t qa = quantize_bits<MODE, FTZ>(va[it], qp), qb = quantize_bits<MODE, FTZ>(vb[it], qp);
-            ma = max(ma, qa & 0x7FFFFFFFu);
-            mb = max(mb, qb & 0x7FFFFFFFu);
-            a_at(it, r, k);
-            sa[k][r] = (double)__uint_as_float(qa);
-            b_at(it, r, k);
-            sb[k][r] = (double)__uint_as_float(qb);
+            va[it] = quantize_bits<MODE, FTZ>(va[it], qp);
+            vb[it] = quantize_bits<MODE, FTZ>(vb[it], qp);
+            ma = max(ma, va[it] & 0x7FFFFFFFu);
+            mb = max(mb, vb[it] & 0x7FFFFFFFu);
         }
+        auto store = [&](auto place) __attribute__((always_inline)) {
+#pragma unroll
+            for (int it = 0; it < kLoads; ++it) {
+                int r, k;
+                a_at(it, r, k);
+                sa[k][r] = place(va[it]);
+                b_at(it, r, k);
+                sb[k][r] = place(vb[it]);
+            }
+        };
+        if (!kLow || wide) store([](uint32_t q) { return (double)__uint_as_float(q); });
+        else store([](uint32_t q) { return __hiloint2double(0, (int)q); });
         if (STEP == kStepSingle) {
 #pragma unroll
             for (int off = 32; off > 0; off >>= 1) {
@@ -245,16 +267,30 @@ __global__ __launch_bounds__(256) void fmac8_kernel(const uint32_t *__restrict__
         }
         __syncthreads();
         if (k0 + kFK < K) load(k0 + kFK);          // in flight while this stage is computed
-        bool wide = false;
         if (STEP == kStepSingle) {
             const uint32_t wa = max(max(s_max[0][0], s_max[0][1]), max(s_max[0][2], s_max[0][3]));
             const uint32_t wb = max(max(s_max[1][0], s_max[1][1]), max(s_max[1][2], s_max[1][3]));
             // infinities and NaN (patterns from 0x7F800000) are left to the other form
-            wide = wa < 0x7F800000u && wb < 0x7F800000u && __fmul_rn(__uint_as_float(wa), __uint_as_float(wb)) < wc.limit;
-            wide = __builtin_amdgcn_readfirstlane(wide ? 1 : 0) != 0;      // the same in the whole workgroup
+            const bool fits = wa < 0x7F800000u && wb < 0x7F800000u && __fmul_rn(__uint_as_float(wa), __uint_as_float(wb)) < wc.limit;
+            const bool next = __builtin_amdgcn_readfirstlane(fits ? 1 : 0) != 0;      // the same in the whole workgroup
+            if (kLow && next != wide) {            // stored for the other form: every thread converts what it stored
+                auto other = [&](double v) {
+                    return next ? (double)operand<float, true>(v) : __hiloint2double(0, __float_as_int((float)v));
+                };
+#pragma unroll
+                for (int it = 0; it < kLoads; ++it) {
+                    int r, k;
+                    a_at(it, r, k);
+                    sa[k][r] = other(sa[k][r]);
+                    b_at(it, r, k);
+                    sb[k][r] = other(sb[k][r]);
+                }
+                __syncthreads();
+            }
+            wide = next;
         }
         // groups of 8 k (the stage is zero-padded beyond K): 8 fused steps from a = 0, then one fp32 addition
-        if (wide) {
+        if (STEP == kStepSingle && wide) {
 #pragma unroll 1
             for (int g = 0; g < kFK / 8; ++g) {
                 double a16[T][T];
@@ -280,57 +316,63 @@ __global__ __launch_bounds__(256) void fmac8_kernel(const uint32_t *__restrict__
             }
         } else {
             typedef typename std::conditional<STEP == kStepSingle, float, double>::type acc_t;
+            // four chains at a time: with sixteen the intermediates of a step take the registers of a third wave per SIMD, from
+            // the wide form as well (T = 4: 222 registers; 164 now; 2048 x 2048 x 1024, wide form: 776 -> 741 us)
+            constexpr int R = T > 2 ? 1 : T;
 #pragma unroll 1
             for (int g = 0; g < kFK / 8; ++g) {
-                acc_t a16[T][T];
 #pragma unroll
-                for (int i = 0; i < T; ++i)
+                for (int i0 = 0; i0 < T; i0 += R) {
+                    acc_t a16[R][T];
 #pragma unroll
-                    for (int j = 0; j < T; ++j) a16[i][j] = (acc_t)0;
+                    for (int i = 0; i < R; ++i)
 #pragma unroll
-                for (int kk = 0; kk < 8; ++kk) {
-                    acc_t w[T], x[T];
+                        for (int j = 0; j < T; ++j) a16[i][j] = (acc_t)0;
 #pragma unroll
-                    for (int i = 0; i < T; ++i) {
-                        w[i] = (acc_t)sa[g * 8 + kk][ty * T + i];
-                        x[i] = (acc_t)sb[g * 8 + kk][tx * T + i];
-                    }
-                    if constexpr (STEP == kStepSingle) {
-                        // the chains take their step; which lanes met a midpoint is kept as wave masks
-                        float nx[T][T];
-                        unsigned long long met[T][T], any = 0ull;
+                    for (int kk = 0; kk < 8; ++kk) {
+                        acc_t w[R], x[T];
 #pragma unroll
-                        for (int i = 0; i < T; ++i)
+                        for (int i = 0; i < R; ++i) w[i] = operand<acc_t, kLow>(sa[g * 8 + kk][ty * T + i0 + i]);
 #pragma unroll
-                            for (int j = 0; j < T; ++j) {
-                                bool tie;
-                                nx[i][j] = kk == 0 ? fmac_try<FTZ, true>(a16[i][j], w[i], x[j], qp, fk, tie)
-                                                   : fmac_try<FTZ, false>(a16[i][j], w[i], x[j], qp, fk, tie);
-                                met[i][j] = __ballot(tie);
-                                any |= met[i][j];
+                        for (int j = 0; j < T; ++j) x[j] = operand<acc_t, kLow>(sb[g * 8 + kk][tx * T + j]);
+                        if constexpr (STEP == kStepSingle) {
+                            // the chains take their step; which lanes met a midpoint is kept as wave masks
+                            float nx[R][T];
+                            unsigned long long met[R][T], any = 0ull;
+#pragma unroll
+                            for (int i = 0; i < R; ++i)
+#pragma unroll
+                                for (int j = 0; j < T; ++j) {
+                                    bool tie;
+                                    nx[i][j] = kk == 0 ? fmac_try<FTZ, true>(a16[i][j], w[i], x[j], qp, fk, tie)
+                                                       : fmac_try<FTZ, false>(a16[i][j], w[i], x[j], qp, fk, tie);
+                                    met[i][j] = __ballot(tie);
+                                    any |= met[i][j];
+                                }
+                            if (any != 0ull) {                     // wave-uniform
+#pragma unroll
+                                for (int i = 0; i < R; ++i)
+#pragma unroll
+                                    for (int j = 0; j < T; ++j)
+                                        if (met[i][j] != 0ull) nx[i][j] = fmac_fix<FTZ>(nx[i][j], a16[i][j], w[i], x[j], qp, fk);
                             }
-                        if (any != 0ull) {                     // wave-uniform
 #pragma unroll
-                            for (int i = 0; i < T; ++i)
+                            for (int i = 0; i < R; ++i)
 #pragma unroll
-                                for (int j = 0; j < T; ++j)
-                                    if (met[i][j] != 0ull) nx[i][j] = fmac_fix<FTZ>(nx[i][j], a16[i][j], w[i], x[j], qp, fk);
+                                for (int j = 0; j < T; ++j) a16[i][j] = nx[i][j];
+                        } else {
+#pragma unroll
+                            for (int i = 0; i < R; ++i)
+#pragma unroll
+                                for (int j = 0; j < T; ++j) a16[i][j] = quantize_f64(add_round_to_odd(a16[i][j], w[i] * x[j]), fp);
                         }
-#pragma unroll
-                        for (int i = 0; i < T; ++i)
-#pragma unroll
-                            for (int j = 0; j < T; ++j) a16[i][j] = nx[i][j];
-                    } else {
-#pragma unroll
-                        for (int i = 0; i < T; ++i)
-#pragma unroll
-                            for (int j = 0; j < T; ++j) a16[i][j] = quantize_f64(add_round_to_odd(a16[i][j], w[i] * x[j]), fp);
                     }
+#pragma unroll
+                    for (int i = 0; i < R; ++i)
+#pragma unroll
+                        for (int j = 0; j < T; ++j) acc32[i0 + i][j] = acc32[i0 + i][j] + (float)a16[i][j];   // single-precision addition
+                    if (R < T) __builtin_amdgcn_sched_barrier(0);  // the next rows' step stays behind this one's
                 }
-#pragma unroll
-                for (int i = 0; i < T; ++i)
-#pragma unroll
-                    for (int j = 0; j < T; ++j) acc32[i][j] = acc32[i][j] + (float)a16[i][j];   // single-precision addition
             }
         }
         __syncthreads();
