@@ -1715,8 +1715,10 @@ static int tail_cols_for(uint64_t blocks256, int cus)
 }
 
 // C[r][c] = sum over the k parts of part[s][r][c]  (parts are dense M x N slabs), in part order.  Four neighbouring elements
-// per thread, the slabs' loads issued eight at a time: what bounds the kernel is the latency of its loads (256 x 2304 in eight
-// parts: 10.9 us with one element and one load at a time).
+// per thread, the slabs' loads issued U at a time: what bounds the kernel is the latency of its loads (256 x 2304 in eight
+// parts: 10.9 us with one element and one load at a time, 5.3 with these).  U is the number of parts up to four, then
+// eight; an element's place in C takes one division, in 32 bits where they suffice.
+template <int U>
 __global__ __launch_bounds__(256) void reduce_kernel(const float *__restrict__ part, int nsplit, float *__restrict__ C,
                                                      int M, int N, int64_t ldc, int img)
 {
@@ -1725,10 +1727,10 @@ __global__ __launch_bounds__(256) void reduce_kernel(const float *__restrict__ p
     for (size_t i = ((size_t)blockIdx.x * 256 + threadIdx.x) * 4; i < total; i += (size_t)gridDim.x * 1024) {
         const bool four = i + 4 <= total;
         float s[4] = {0.0f, 0.0f, 0.0f, 0.0f};
-        for (int q0 = 0; q0 < nsplit; q0 += 8) {
-            float v[8][4];
+        for (int q0 = 0; q0 < nsplit; q0 += U) {
+            float v[U][4];
 #pragma unroll
-            for (int u = 0; u < 8; ++u) {
+            for (int u = 0; u < U; ++u) {
                 const float *src = part + (size_t)min(q0 + u, nsplit - 1) * total + i;
                 if (four) {
                     const f32x4u w = *reinterpret_cast<const f32x4u *>(src);
@@ -1740,27 +1742,40 @@ __global__ __launch_bounds__(256) void reduce_kernel(const float *__restrict__ p
                 }
             }
 #pragma unroll
-            for (int u = 0; u < 8; ++u)
+            for (int u = 0; u < U; ++u)
                 if (q0 + u < nsplit) {
 #pragma unroll
                     for (int j = 0; j < 4; ++j) s[j] += v[u][j];
                 }
         }
-        const size_t row = i / N, col = i % N;
-        if (img == 0 && four && col + 4 <= (size_t)N) {
+        size_t row = total >> 32 == 0 ? (uint32_t)i / (uint32_t)N : i / N;
+        int col = (int)(i - row * N);
+        if (img == 0 && four && col + 4 <= N) {
             *reinterpret_cast<f32x4u *>(C + row * ldc + col) = f32x4u{s[0], s[1], s[2], s[3]};
             continue;
         }
 #pragma unroll
         for (int j = 0; j < 4; ++j) {
             if (i + j >= total) break;
-            const size_t r = (i + j) / N, c = (i + j) % N;
             if (img > 0)
-                C[((c / img) * M + r) * img + c % img] = s[j];
+                C[((size_t)(col / img) * M + row) * img + col % img] = s[j];
             else
-                C[r * ldc + c] = s[j];
+                C[row * ldc + col] = s[j];
+            if (++col == N) {
+                col = 0;
+                ++row;
+            }
         }
     }
+}
+
+static int launch_reduce(const float *part, int nsplit, float *C, int M, int N, int64_t ldc, int img, hipStream_t stream)
+{
+    const size_t groups = ((size_t)M * N + 1023) / 1024;
+    auto kern = nsplit <= 2 ? reduce_kernel<2> : nsplit == 3 ? reduce_kernel<3> : nsplit == 4 ? reduce_kernel<4> : reduce_kernel<8>;
+    hipLaunchKernelGGL(kern, dim3((unsigned)(groups < 4096 ? groups : 4096)), dim3(256), 0, stream, part, nsplit, C, M, N, ldc, img);
+    FMT_HIP_CHECK(hipGetLastError());
+    return FMT_OK;
 }
 
 __global__ void zero_fill_kernel(float *__restrict__ C, int M, int N, int64_t ldc, int col_blocks)
@@ -1889,11 +1904,7 @@ static int launch_product(const u32x4 *Aw, const u32x4 *Bw, float *C, int M, int
         int rcg = launch_product_v2<PS, TM, TN, true, true, false, true>(Aw, nullptr, part, M, N, (int64_t)N, 0, kblocks,
                                                                         plan.nsplit, stream, pa, pb, *im);
         if (rcg != FMT_OK) return rcg;
-        const size_t total_g = (size_t)M * N;
-        const unsigned rgrid_g = (unsigned)((total_g + 1023) / 1024 < 4096 ? (total_g + 1023) / 1024 : 4096);
-        hipLaunchKernelGGL(reduce_kernel, dim3(rgrid_g ? rgrid_g : 1), dim3(256), 0, stream, part, plan.nsplit, C, M, N, ldc, img);
-        FMT_HIP_CHECK(hipGetLastError());
-        return FMT_OK;
+        return launch_reduce(part, plan.nsplit, C, M, N, ldc, img, stream);
     }
     // the elements outside plane 0 of exponent-plane operands follow the product (plain row-major results only)
     auto tail = [&]() -> int {
@@ -1920,11 +1931,8 @@ static int launch_product(const u32x4 *Aw, const u32x4 *Bw, float *C, int M, int
                  ? launch_product_v<PS, TM, TN, true, true>(Aw, Bw, part, M, N, (int64_t)N, 0, kblocks, plan.nsplit, stream, pa, pb)
                  : launch_product_v<PS, TM, TN, true, false>(Aw, Bw, part, M, N, (int64_t)N, 0, kblocks, plan.nsplit, stream, pa, pb);
     if (rc != FMT_OK) return rc;
-    const size_t total = (size_t)M * N;
-    const unsigned rgrid = (unsigned)((total + 1023) / 1024 < 4096 ? (total + 1023) / 1024 : 4096);
-    hipLaunchKernelGGL(reduce_kernel, dim3(rgrid ? rgrid : 1), dim3(256), 0, stream, part, plan.nsplit, C, M, N, ldc, img);
-    FMT_HIP_CHECK(hipGetLastError());
-    return tail();
+    rc = launch_reduce(part, plan.nsplit, C, M, N, ldc, img, stream);
+    return rc != FMT_OK ? rc : tail();
 }
 
 // One operand of a product as the caller describes it: a plain matrix (kind kSrcMatrix, leading
@@ -2794,11 +2802,9 @@ int launch_gemm_prepared_batch(int count, const BatchItem *items, int scheme, fm
             const GroupEntry &ge = grouped[g0 + j];
             if (ge.nparts == 1) continue;
             const BatchItem &it = items[ge.item];
-            const size_t total = (size_t)it.M * it.N;
-            const unsigned rgrid = (unsigned)((total + 1023) / 1024 < 4096 ? (total + 1023) / 1024 : 4096);
-            hipLaunchKernelGGL(reduce_kernel, dim3(rgrid ? rgrid : 1), dim3(256), 0, stream,
-                               reinterpret_cast<const float *>(scratch + ge.part_off), ge.nparts, it.C, (int)it.M, (int)it.N, it.ldc, 0);
-            FMT_HIP_CHECK(hipGetLastError());
+            const int rcr = launch_reduce(reinterpret_cast<const float *>(scratch + ge.part_off), ge.nparts, it.C, (int)it.M, (int)it.N,
+                                          it.ldc, 0, stream);
+            if (rcr != FMT_OK) return rcr;
         }
         if (sch.scaled) {
             hipLaunchKernelGGL(planes_tail_group_kernel, dim3((unsigned)blocks), dim3(256), 0, stream, tg);

@@ -63,6 +63,21 @@ def oracle_all(X, W, dY, f, pad, stride):
             oracle.conv2d_wgrad(dY, X, W.shape, e, m, d, pad, stride))
 
 
+@pytest.mark.parametrize("parts", [2, 3, 9])
+def test_parts_of_k_into_images(fmt, parts, monkeypatch):
+    """Forward and dgrad with k in parts: the sums go to NCHW, whose images (35 positions) end inside groups of four elements."""
+    monkeypatch.setenv("FMT_GEMM_PLAN", "1,1,%d" % parts)
+    rng = np.random.default_rng(parts)
+    X = rng.integers(-4, 5, (2, 96, 7, 5)).astype(np.float32)
+    W = rng.integers(-4, 5, (32, 96, 3, 3)).astype(np.float32)
+    dY = rng.integers(-4, 5, (2, 32, 7, 5)).astype(np.float32)
+    f, pad, stride = (6, 9, True), (1, 1), (1, 1)
+    Y, dX = fmt.fmt_conv2d_fwd(dev(X), dev(W), f, pad=pad, stride=stride), fmt.fmt_conv2d_dgrad(dev(dY), dev(W), X.shape, f, pad=pad, stride=stride)
+    torch.cuda.synchronize()
+    assert np.array_equal(Y.cpu().numpy(), oracle.conv2d_fwd(X, W, 6, 9, True, pad, stride))
+    assert np.array_equal(dX.cpu().numpy(), oracle.conv2d_dgrad(dY, W, X.shape, 6, 9, True, pad, stride))
+
+
 @pytest.mark.parametrize("geom", GEOMS)
 @pytest.mark.parametrize("f", [(6, 9, True), (5, 10, False), (8, 7, True)])
 def test_bit_exact_integer_data(fmt, geom, f):

@@ -312,6 +312,26 @@ def test_every_tile_shape_and_split(fmt, plan, monkeypatch):
     assert np.array_equal(got, ref)
 
 
+@pytest.mark.parametrize("parts", [2, 3, 4, 5, 8, 9, 16, 17])
+@pytest.mark.parametrize("M,N", [(70, 131), (33, 2), (1, 1), (64, 64)])
+def test_sum_of_every_number_of_parts(fmt, parts, M, N, monkeypatch):
+    """k in 2 to 17 parts of three blocks of 32 (the last one ragged): parts that are summed in one go, in one go with a part
+    to spare and in several, results whose groups of four elements end inside a row, and a leading dimension of its own.
+    Integer operands: exact, so the oracle's bits."""
+    monkeypatch.setenv("FMT_GEMM_PLAN", "1,1,%d" % parts)
+    rng = np.random.default_rng(parts)
+    K = 96 * parts - 5
+    A = rng.integers(-7, 8, (M, K)).astype(np.float32)
+    B = rng.integers(-7, 8, (K, N)).astype(np.float32)
+    want = oracle.gemm(A, B, 8, 7, True)
+    for pad in (0, 3):
+        C = torch.full((M, N + pad), 7.0, device="cuda")
+        fmt.fmt_gemm(dev(A), dev(B), (8, 7, True), out=C[:, :N])
+        torch.cuda.synchronize()
+        assert np.array_equal(C[:, :N].cpu().numpy(), want)
+        assert bool((C[:, N:] == 7.0).all())
+
+
 @pytest.mark.parametrize("plan", ["1,1,1", "2,2,1", "4,4,1", "4,2,1", "2,2,2"])
 @pytest.mark.parametrize("f", [(5, 10, True), (6, 9, True), (7, 18, True)])
 def test_every_depth_of_the_stage_ring(fmt, plan, f, monkeypatch):
