@@ -104,18 +104,42 @@ __global__ __launch_bounds__(kBlock) void stream_kernel(const uint32_t *__restri
     const uint32_t lane32 = tid & (kCopies - 1);
     Counts w;
 
-    // leftovers around the vector body, [0, head) and [head + 4*nvec, n): one per lane of the first wave, loaded before
-    // anything else so that the load is not a chain of its own at the end
-    const bool edge = VEC && blockIdx.x == 0 && tid < 64 && tid < n - 4 * nvec;
-    const size_t edge_at = tid < head ? tid : 4 * nvec + tid;
-    uint32_t edge_u = 0u;
-    if (edge) edge_u = x[edge_at];
+    // one full tile, in v
+    constexpr size_t kTileVec = (size_t)kBlock * kUnroll;
+    auto tile = [&](const u32x4 (&v)[kUnroll], size_t i) __attribute__((always_inline)) {
+        uint32_t amax = 0u;
+#pragma unroll
+        for (int k = 0; k < kUnroll; ++k) {
+            u32x4 o = {0u, 0u, 0u, 0u};
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                const uint32_t u = v[k][j];
+                if (HIST) account_run<DEEP, kCopies>(u & 0x7FFFFFFFu, p, tbl, lane32, w, amax);
+                if (STORE) o[j] = quantize_bits<MODE, FTZ>(u, p);
+            }
+            if (STORE) put(i + k * kBlock, o);
+        }
+        if (HIST) {
+            uint32_t flat[4 * kUnroll];
+#pragma unroll
+            for (int k = 0; k < kUnroll; ++k)
+#pragma unroll
+                for (int j = 0; j < 4; ++j) flat[4 * k + j] = v[k][j];
+            account_run_top(flat, amax, p, w);
+        }
+    };
 
-    if (VEC) {
+    // VEC: a tile is kBlock*kUnroll consecutive vectors; workgroup b takes tiles b, b+grid, ...  Every lane of the workgroup
+    // runs the same trips, and all tiles but the last are full.
+    if constexpr (VEC && HIST) {
+        // leftovers around the vector body, [0, head) and [head + 4*nvec, n): one per lane of the first wave, loaded before
+        // anything else so that the load is not a chain of its own at the end
+        const bool edge = blockIdx.x == 0 && tid < 64 && tid < n - 4 * nvec;
+        const size_t edge_at = tid < head ? tid : 4 * nvec + tid;
+        uint32_t edge_u = 0u;
+        if (edge) edge_u = x[edge_at];
+
         const u32x4 *xv = reinterpret_cast<const u32x4 *>(x + head);
-        // A tile is kBlock*kUnroll consecutive vectors; workgroup b takes tiles b, b+grid, ...
-        // Every lane of the workgroup runs the same trips, and all tiles but the last are full.
-        constexpr size_t kTileVec = (size_t)kBlock * kUnroll;
         const size_t full_tiles = nvec / kTileVec;
         u32x4 v[kUnroll];
         auto load = [&](size_t t) __attribute__((always_inline)) {
@@ -131,44 +155,19 @@ __global__ __launch_bounds__(kBlock) void stream_kernel(const uint32_t *__restri
                 }
             }
         };
-        // With statistics a tile's loads are issued ahead of the work on the tile before it, the first tile's ahead of the
-        // clearing of the table (2^25 elements: statistics alone 27.3 -> 22.4 us, fused 50 -> 47); without them a workgroup
-        // has one tile, and the short kernel is the better one (2^28: 344 against 347 us).
+        // A tile's loads are issued ahead of the work on the tile before it, the first tile's ahead of the clearing of the
+        // table (2^25 elements: statistics alone 27.3 -> 22.4 us, fused 50 -> 47).
         size_t t = blockIdx.x;
-        if (HIST) {
-            load(t);
-            hist_begin<kCopies, kBlock>(tbl, s_bins, s_cls, tid);
-            hist_clear<kBlock>(sink, blockIdx.x, gridDim.x, tid);
-        }
+        load(t);
+        hist_begin<kCopies, kBlock>(tbl, s_bins, s_cls, tid);
+        hist_clear<kBlock>(sink, blockIdx.x, gridDim.x, tid);
         while (t < full_tiles) {
-            if (!HIST) load(t);
-            const size_t i = t * kTileVec + tid;
-            uint32_t amax = 0u;
-#pragma unroll
-            for (int k = 0; k < kUnroll; ++k) {
-                u32x4 o = {0u, 0u, 0u, 0u};
-#pragma unroll
-                for (int j = 0; j < 4; ++j) {
-                    const uint32_t u = v[k][j];
-                    if (HIST) account_run<DEEP, kCopies>(u & 0x7FFFFFFFu, p, tbl, lane32, w, amax);
-                    if (STORE) o[j] = quantize_bits<MODE, FTZ>(u, p);
-                }
-                if (STORE) put(i + k * kBlock, o);
-            }
-            if (HIST) {
-                uint32_t flat[4 * kUnroll];
-#pragma unroll
-                for (int k = 0; k < kUnroll; ++k)
-#pragma unroll
-                    for (int j = 0; j < 4; ++j) flat[4 * k + j] = v[k][j];
-                account_run_top(flat, amax, p, w);
-            }
+            tile(v, t * kTileVec + tid);
             t += gridDim.x;
-            if (HIST && t * kTileVec < nvec) load(t);
+            if (t * kTileVec < nvec) load(t);
         }
         if (t == full_tiles && full_tiles * kTileVec < nvec) {
             // the ragged last tile, lane by lane
-            if (!HIST) load(t);
 #pragma unroll
             for (int k = 0; k < kUnroll; ++k) {
                 const size_t i = full_tiles * kTileVec + k * kBlock + tid;
@@ -178,8 +177,36 @@ __global__ __launch_bounds__(kBlock) void stream_kernel(const uint32_t *__restri
             }
         }
         if (blockIdx.x == 0 && tid < 64) {
-            if (HIST) account<DEEP, kCopies>(edge_u & 0x7FFFFFFFu, edge, p, tbl, lane32, w);
+            account<DEEP, kCopies>(edge_u & 0x7FFFFFFFu, edge, p, tbl, lane32, w);
             if (STORE && edge) put_one(edge_at, quantize_bits<MODE, FTZ>(edge_u, p));
+        }
+    } else if constexpr (VEC) {
+        // Without statistics a workgroup has one tile, and what counts is a short kernel (2^23 elements: 10.7 us; 11.4 with the
+        // other branch's loop and leftovers).
+        const u32x4 *xv = reinterpret_cast<const u32x4 *>(x + head);
+        const size_t full_tiles = nvec / kTileVec;
+        for (size_t t = blockIdx.x; t < full_tiles; t += gridDim.x) {
+            const size_t i = t * kTileVec + tid;
+            u32x4 v[kUnroll];
+#pragma unroll
+            for (int k = 0; k < kUnroll; ++k) v[k] = __builtin_nontemporal_load(xv + i + k * kBlock);
+            tile(v, i);
+        }
+        if (blockIdx.x == full_tiles % gridDim.x && full_tiles * kTileVec < nvec) {
+#pragma unroll
+            for (int k = 0; k < kUnroll; ++k) {
+                const size_t i = full_tiles * kTileVec + k * kBlock + tid;
+                const bool valid = i < nvec;
+                u32x4 v = {0u, 0u, 0u, 0u};
+                if (valid) v = __builtin_nontemporal_load(xv + i);
+                u32x4 o = do_vec<MODE, STORE, FTZ, HIST, DEEP, kCopies>(v, valid, p, tbl, lane32, w);
+                if (STORE && valid) put(i, o);
+            }
+        }
+        if (blockIdx.x == 0 && tid < 64 && tid < n - 4 * nvec) {
+            const size_t at = tid < head ? tid : 4 * nvec + tid;
+            const uint32_t u = x[at];
+            if (STORE) put_one(at, quantize_bits<MODE, FTZ>(u, p));
         }
     } else {
         if (HIST) {
