@@ -410,17 +410,25 @@ static int launch(int transA, int transB, int M, int N, int K, const float *A, i
     const int rc = device_cu_count(&cus);
     if (rc != FMT_OK) return rc;
     auto tiles = [&](int t) { return (((int64_t)M + 16 * t - 1) / (16 * t)) * (((int64_t)N + 16 * t - 1) / (16 * t)); };
-    // Which tile: fitted to N x N x 256 products in 1/6/9 on 256 compute units.  One tile alone on a compute unit takes 16.8,
-    // 28.7 or 62.7 us (T = 1, 2, 4: the chains' latency with 1, 4 or 16 of them to interleave); with work enough a compute
-    // unit finishes one per 5.8, 15 or 48 us.  Measured (us, T = 1 / 2 / 4): N = 64: 16.8 / 28.5 / 62.6; 384: 24 / 30 / 63;
-    // 512: 30 / 30 / 64; 768: 59 / 52 / 66; 1024: 93 / 66 / 67; 1500: 190 / 129 / 153.
+    // Which tile: fitted to N x N x 256 products on 256 compute units.  `alone` is what one tile on a compute unit takes (the chains'
+    // latency with 1, 4 or 16 of them to interleave), `each` the time per tile of a compute unit with work enough.
     auto estimate = [&](int t, double alone, double each) {
         return std::max(alone, (double)((tiles(t) + cus - 1) / cus) * each);
     };
-    const double t1 = estimate(1, 16.8, 5.8), t2 = estimate(2, 28.7, 15.0), t4 = estimate(4, 62.7, 48.0);
 #define FMT_TILE(T) launch_tile<MODE, FTZ, STEP, T>(transA, transB, M, N, K, A, lda, B, ldb, C, ldc, qp, fp, wc, stream)
-    if (t4 <= t2 && t4 <= t1) return FMT_TILE(4);
-    return t2 <= t1 ? FMT_TILE(2) : FMT_TILE(1);
+    if constexpr (STEP == kStepOdd) {
+        // Measured in 1/8/7 (us, T = 1 / 2; 16 outputs per thread are behind both everywhere: 943 at N = 2048): N = 256: 38 / 105;
+        // 512: 75 / 109; 640: 116 / 145; 768: 145 / 197; 1024: 239 / 246; 1500: 489 / 502; 2048: 880 / 859; 1/6/15 is alike.
+        return estimate(2, 104.0, 57.0) < estimate(1, 36.0, 14.2) ? FMT_TILE(2) : FMT_TILE(1);
+    } else {
+        // Measured in 1/6/9, wide form (us, T = 1 / 2 / 4): N = 64: 16.8 / 28.5 / 62.6; 384: 24 / 30 / 63; 512: 30 / 30 / 64; 768:
+        // 59 / 52 / 66; 1024: 93 / 66 / 67; 1500: 190 / 129 / 153; 2048: 335 / 211 / 197.  The values decide which form a stage takes, so
+        // the rule is the ordinary one's.  Where all stages take the single form it is off by up to a third
+        // (640: 65 / 83 / 228; 1024: 123 / 118 / 228; 1500: 240 / 220 / 448; 2048: 426 / 367 / 497).
+        const double t1 = estimate(1, 16.8, 5.8), t2 = estimate(2, 28.7, 15.0), t4 = estimate(4, 62.7, 48.0);
+        if (t4 <= t2 && t4 <= t1) return FMT_TILE(4);
+        return t2 <= t1 ? FMT_TILE(2) : FMT_TILE(1);
+    }
 #undef FMT_TILE
 }
 
