@@ -51,8 +51,8 @@ constexpr int kCopiesMost = 8;
 constexpr int kCopiesLarge = 32;
 constexpr size_t kLarge = (size_t)1 << 27;   // elements from which it takes them
 constexpr int kUnroll = FMT_STREAM_UNROLL;  // independent 128-bit loads in flight per thread
-constexpr int kGridPerCU = FMT_STREAM_GRID_PER_CU;   // workgroups launched per compute unit (at most): statistics, alone or with codes out
-constexpr int kGridFused = 64;           // ... fused quantize + statistics, fp32 out
+constexpr int kGridPerCU = FMT_STREAM_GRID_PER_CU;   // workgroups launched per compute unit (at most): statistics alone
+constexpr int kGridFused = 64;           // ... fused with rounding, fp32 or codes out
 constexpr int kGridStore = 256;          // ... quantize only
 
 template <int MODE, bool STORE, bool FTZ, bool HIST, bool DEEP, int kCopies>
@@ -288,9 +288,9 @@ static int launch_variant(const float *x, void *y, size_t n, size_t head, size_t
     const size_t want = (n + per_block - 1) / per_block;
     // Workgroups per compute unit, measured on 2^28 elements: a pure stream likes one 16 KiB tile per
     // workgroup (6.4 TB/s against 5.9 with 16 per CU: the hardware balances the tail); every workgroup
-    // of a statistics pass pays for clearing and folding its LDS table, so the read-only pass and the one that writes
-    // codes keep 16 per CU (165 us against 178 with 128; 283 against 290) and the fused fp32 pass takes 64 (355 against 370).
-    const size_t cap = (size_t)cus * (HIST ? (STORE && !PACK ? kGridFused : kGridPerCU) : kGridStore);
+    // of a statistics pass pays for clearing and folding its LDS table, so the read-only pass keeps 16 per CU (161 us; 168 with 32,
+    // 171 with 64 and 128) and the passes that write take 64 (fp32 355 us, codes 264; with 16: 367 and 290; with 128: alike).
+    const size_t cap = (size_t)cus * (HIST ? (STORE ? kGridFused : kGridPerCU) : kGridStore);
     size_t g = want;
     if (HIST) {
         // mid-size tensors: at least four tiles per workgroup (one tile does not pay for the table),
