@@ -168,10 +168,10 @@ constexpr int kFK = 32;        // k per LDS stage (a multiple of 8: FMAC-8 group
 enum { kStepSingle = 0, kStepOdd = 1 };     // the form besides the wide one that an instantiation holds
 
 // One workgroup computes a tile of 16*T x 16*T outputs, T x T per thread.  The chains of an output are sequential, so
-// what counts is that every SIMD has instructions to issue: 16 chains per thread where there are tiles enough to
-// fill the chip, 4 or 1 where there are not (see launch).  Operand stages are rounded on the way into LDS, as fp64 (a
+// what counts is that every SIMD has instructions to issue: for the wide step 16 chains per thread where there are tiles enough
+// to fill the chip, 4 or 1 where there are not; the round-to-odd step, five times as long, fills it with one (see launch).  Operand stages are rounded on the way into LDS, as fp64 (a
 // value converted once instead of once per use); the next stage's loads are in flight while a stage is computed.
-// Measured in 1/6/9: 2048 x 2048 x 1024 takes 0.76 ms (5.7 T fused steps/s; 1.97 ms with the single form alone),
+// Measured in 1/6/9: 2048 x 2048 x 1024 takes 0.74 ms (5.8 T fused steps/s; 1.97 ms with the single form alone),
 // 256 x 256 x 256 takes 17 us (224 us with 64 x 64 tiles and the single form alone).
 template <int MODE, bool FTZ, int STEP, int T>
 __global__ __launch_bounds__(256) void fmac8_kernel(const uint32_t *__restrict__ A, int64_t lda, int transA,
@@ -406,25 +406,25 @@ template <int MODE, bool FTZ, int STEP>
 static int launch(int transA, int transB, int M, int N, int K, const float *A, int64_t lda, const float *B, int64_t ldb,
                   float *C, int64_t ldc, const QuantParams &qp, const Fmac8Params &fp, const WideConsts &wc, hipStream_t stream)
 {
-    int cus = 0;
-    const int rc = device_cu_count(&cus);
-    if (rc != FMT_OK) return rc;
-    auto tiles = [&](int t) { return (((int64_t)M + 16 * t - 1) / (16 * t)) * (((int64_t)N + 16 * t - 1) / (16 * t)); };
-    // Which tile: fitted to N x N x 256 products on 256 compute units.  `alone` is what one tile on a compute unit takes (the chains'
-    // latency with 1, 4 or 16 of them to interleave), `each` the time per tile of a compute unit with work enough.
-    auto estimate = [&](int t, double alone, double each) {
-        return std::max(alone, (double)((tiles(t) + cus - 1) / cus) * each);
-    };
 #define FMT_TILE(T) launch_tile<MODE, FTZ, STEP, T>(transA, transB, M, N, K, A, lda, B, ldb, C, ldc, qp, fp, wc, stream)
+    // Which tile, from products of N x N x 256 on 256 compute units.
     if constexpr (STEP == kStepOdd) {
-        // Measured in 1/8/7 (us, T = 1 / 2; 16 outputs per thread are behind both everywhere: 943 at N = 2048): N = 256: 38 / 105;
-        // 512: 75 / 109; 640: 116 / 145; 768: 145 / 197; 1024: 239 / 246; 1500: 489 / 502; 2048: 880 / 859; 1/6/15 is alike.
-        return estimate(2, 104.0, 57.0) < estimate(1, 36.0, 14.2) ? FMT_TILE(2) : FMT_TILE(1);
+        // One output per thread at any size.  Measured in 1/8/7 (us, T = 1 / 2 / 4): N = 256: 38 / 105 / 362; 512: 75 / 109 / 363; 640:
+        // 116 / 145 / 360; 768: 145 / 197 / 361; 1024: 239 / 246 / 360; 1500: 489 / 502 / 722; 2048: 880 / 859 / 943; 1/6/15 is alike.
+        return FMT_TILE(1);
     } else {
-        // Measured in 1/6/9, wide form (us, T = 1 / 2 / 4): N = 64: 16.8 / 28.5 / 62.6; 384: 24 / 30 / 63; 512: 30 / 30 / 64; 768:
-        // 59 / 52 / 66; 1024: 93 / 66 / 67; 1500: 190 / 129 / 153; 2048: 335 / 211 / 197.  The values decide which form a stage takes, so
-        // the rule is the ordinary one's.  Where all stages take the single form it is off by up to a third
-        // (640: 65 / 83 / 228; 1024: 123 / 118 / 228; 1500: 240 / 220 / 448; 2048: 426 / 367 / 497).
+        // `alone` is what one tile on a compute unit takes (the chains' latency with 1, 4 or 16 of them to interleave), `each` the
+        // time per tile of a compute unit with work enough.  Measured in 1/6/9, wide form (us, T = 1 / 2 / 4): N = 64: 16.8 / 28.5 /
+        // 62.6; 384: 24 / 30 / 63; 512: 30 / 30 / 64; 768: 59 / 52 / 66; 1024: 93 / 66 / 67; 1500: 190 / 129 / 153; 2048: 335 / 211 /
+        // 197.  The values decide which form a stage takes, so the rule is the ordinary one's.  Where all stages take the single
+        // form it is off by up to a third (640: 65 / 83 / 228; 1024: 123 / 118 / 228; 1500: 240 / 220 / 448; 2048: 426 / 367 / 497).
+        int cus = 0;
+        const int rc = device_cu_count(&cus);
+        if (rc != FMT_OK) return rc;
+        auto estimate = [&](int t, double alone, double each) {
+            const int64_t tiles = (((int64_t)M + 16 * t - 1) / (16 * t)) * (((int64_t)N + 16 * t - 1) / (16 * t));
+            return std::max(alone, (double)((tiles + cus - 1) / cus) * each);
+        };
         const double t1 = estimate(1, 16.8, 5.8), t2 = estimate(2, 28.7, 15.0), t4 = estimate(4, 62.7, 48.0);
         if (t4 <= t2 && t4 <= t1) return FMT_TILE(4);
         return t2 <= t1 ? FMT_TILE(2) : FMT_TILE(1);
