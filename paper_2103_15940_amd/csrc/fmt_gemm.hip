@@ -1726,19 +1726,21 @@ __global__ __launch_bounds__(256) void reduce_kernel(const float *__restrict__ p
     const size_t total = (size_t)M * N;
     for (size_t i = ((size_t)blockIdx.x * 256 + threadIdx.x) * 4; i < total; i += (size_t)gridDim.x * 1024) {
         const bool four = i + 4 <= total;
+        const size_t last = total >= 4 ? total - 4 : 0;
         float s[4] = {0.0f, 0.0f, 0.0f, 0.0f};
         for (int q0 = 0; q0 < nsplit; q0 += U) {
             float v[U][4];
 #pragma unroll
             for (int u = 0; u < U; ++u) {
-                const float *src = part + (size_t)min(q0 + u, nsplit - 1) * total + i;
-                if (four) {
+                // the last elements are loaded as the last four and moved down (fewer than four in all: one by one)
+                const float *src = part + (size_t)min(q0 + u, nsplit - 1) * total + (four ? i : last);
+                if (total >= 4) {
                     const f32x4u w = *reinterpret_cast<const f32x4u *>(src);
 #pragma unroll
                     for (int j = 0; j < 4; ++j) v[u][j] = w[j];
                 } else {
 #pragma unroll
-                    for (int j = 0; j < 4; ++j) v[u][j] = i + j < total ? src[j] : 0.0f;
+                    for (int j = 0; j < 4; ++j) v[u][j] = j < (int)total ? src[j] : 0.0f;
                 }
             }
 #pragma unroll
@@ -1747,6 +1749,11 @@ __global__ __launch_bounds__(256) void reduce_kernel(const float *__restrict__ p
 #pragma unroll
                     for (int j = 0; j < 4; ++j) s[j] += v[u][j];
                 }
+        }
+        if (!four) {
+            const int by = (int)(i - last);
+            if (by & 1) s[0] = s[1], s[1] = s[2], s[2] = s[3];
+            if (by & 2) s[0] = s[2], s[1] = s[3];
         }
         size_t row = total >> 32 == 0 ? (uint32_t)i / (uint32_t)N : i / N;
         int col = (int)(i - row * N);
