@@ -2245,8 +2245,10 @@ static int prepare_operands(const OperandSpec &sa, const OperandLayout &la, cons
     return FMT_OK;
 }
 
-// Parts of k of a direct product (fmt_direct.hip), or 0 where the general route is the better one (or forced, for tuning and
-// tests).
+static Scheme api_scheme(fmt_format_t f, int64_t K);
+
+// Parts of k of a direct product (fmt_direct.hip), or 0 where the general route is the better one (or forced by a plan).
+// FMT_GEMM_DIRECT=0|1 (tuning, tests): never, or wherever the kernel can.
 //   direct   one launch: 4.4 us, and 0.9 us per block of 32 k that a wave takes one after the other, or per 1024 waves' blocks
 //            where there are more waves (fitted to products of 64 x 64 x 32 to 4096 x 128 x 512, the slowest layout)
 //   general  two launches, 8.2 us at least; three when the plan splits k, 14.4 us at least with two pieces, 12.4 with one
@@ -2265,13 +2267,14 @@ static int direct_parts(int M, int N, int K, const OperandSpec &sa, const Operan
     const int kblocks = (K + kUnitK - 1) / kUnitK;
     const int64_t tiles = (((int64_t)M + 31) / 32) * (((int64_t)N + 31) / 32);
     int parts = plan.nsplit;
-    if (planes_possible(f)) {
+    if (api_scheme(f, K).scaled) {
         // the prepared calls of these formats take the planes, so no other call promises these sums and the parts are
         // free: enough for two waves per SIMD (2048), two blocks each at least
         parts = 1;
         while (parts < kDirectParts && tiles * parts < 2048 && kblocks / (parts * 2) >= 2) parts *= 2;
     }
     if (parts > kDirectParts) return 0;
+    if (const char *env = getenv("FMT_GEMM_DIRECT")) return env[0] == '1' ? parts : 0;
     const double blocks = (double)((kblocks + parts - 1) / parts);
     const double direct = 4.4 + std::max(0.9, 0.95 * (double)(tiles * parts) / 1024.0) * blocks;
     const double general = plan.nsplit == 1 ? 8.2 : pieces_of(sch.ps) == 1 ? 12.4 : 14.4;

@@ -1,5 +1,7 @@
 """Small products of fp32 matrices: fmt_gemm in one launch, operands rounded on the way into the matrix cores, against the CPU
-oracle, against the general route (forced through FMT_GEMM_PLAN) and against the prepared calls."""
+oracle, against the general route (forced through FMT_GEMM_DIRECT=0) and against the prepared calls."""
+import ctypes
+
 import numpy as np
 import pytest
 
@@ -14,8 +16,8 @@ torch = pytest.importorskip("torch")
 FORMATS = [(5, 10, True), (5, 10, False), (4, 3, True), (8, 7, True), (8, 7, False), (8, 3, True), (6, 9, True), (6, 9, False),
            (7, 8, True), (2, 15, False)]
 LAYOUTS = [(False, False), (False, True), (True, False), (True, True)]
-SHAPES = [(1, 1, 1), (31, 33, 31), (32, 32, 32), (33, 65, 33), (64, 40, 64), (7, 100, 129), (256, 10, 1024), (130, 70, 257),
-          (512, 200, 100)]
+SHAPES = [(1, 1, 1), (2, 3, 7), (5, 4, 8), (31, 33, 31), (32, 32, 32), (33, 65, 33), (64, 40, 64), (9, 20, 86), (7, 100, 129),
+          (256, 10, 1024), (130, 70, 257), (512, 200, 100)]
 
 
 @pytest.fixture(scope="module")
@@ -28,7 +30,7 @@ def fmt():
 
 @pytest.fixture(autouse=True)
 def plain_environment(monkeypatch):
-    for name in ("FMT_GEMM_PLAN", "FMT_GEMM_WINDOW"):
+    for name in ("FMT_GEMM_PLAN", "FMT_GEMM_WINDOW", "FMT_GEMM_DIRECT"):
         monkeypatch.delenv(name, raising=False)
 
 
@@ -51,11 +53,33 @@ def product(fmt, A, B, f, tA, tB, pad=0, offset=0):
     return out.cpu().numpy()
 
 
+def launches(fmt, call):
+    """Kernels that a call launches: the nodes of a graph recorded from it."""
+    lib = fmt.raw_library()
+    stream = torch.cuda.Stream()
+    stream.wait_stream(torch.cuda.current_stream())
+    with torch.cuda.stream(stream):
+        call()                                                       # grows the stream's scratch
+        stream.synchronize()
+        graph, count = ctypes.c_void_p(), ctypes.c_size_t()
+        assert lib.hipStreamBeginCapture(ctypes.c_void_p(stream.cuda_stream), 1) == 0
+        call()
+        assert lib.hipStreamEndCapture(ctypes.c_void_p(stream.cuda_stream), ctypes.byref(graph)) == 0
+    assert lib.hipGraphGetNodes(graph, None, ctypes.byref(count)) == 0
+    assert lib.hipGraphDestroy(graph) == 0
+    return count.value
+
+
+def bits(t):
+    return t.view(torch.int32)
+
+
 @pytest.mark.parametrize("e,m,d", FORMATS)
 @pytest.mark.parametrize("shape", SHAPES)
-def test_every_layout_and_alignment(fmt, e, m, d, shape):
+def test_every_layout_and_alignment(fmt, e, m, d, shape, monkeypatch):
     """Integers small enough for every partial sum to be exact: the oracle's bits whatever the order of the sums.  All layouts,
-    leading dimensions and base alignments (16-byte vectors possible or not); the general route gives the same bits."""
+    leading dimensions and base alignments (k-contiguous rows of any alignment, k that ends inside a block of 32 or of 8)."""
+    monkeypatch.setenv("FMT_GEMM_DIRECT", "1")
     M, N, K = shape
     rng = np.random.default_rng(M + 10 * N + 100 * K + e)
     top = 3 if m >= 3 else 1
@@ -68,10 +92,36 @@ def test_every_layout_and_alignment(fmt, e, m, d, shape):
             assert np.array_equal(got, want), (tA, tB, pad, offset)
 
 
+@pytest.mark.parametrize("M,N,K,parts", [(60, 50, 200, 1), (40, 70, 512, 2), (40, 70, 523, 2), (33, 31, 800, 3), (100, 64, 1030, 4),
+                                         (64, 64, 2048, 8), (70, 130, 2075, 8), (250, 300, 777, 3)])
+@pytest.mark.parametrize("e,m,d", [(5, 10, True), (8, 7, True), (8, 7, False), (7, 8, True), (6, 9, True), (6, 9, False)])
+def test_bits_of_the_general_route_with_k_in_parts(fmt, e, m, d, M, N, K, parts, monkeypatch):
+    """Sums that round at every step, k in 1 to 8 parts (as the plan of the general route has it), K ragged or not: one launch
+    gives the bits of the general route's two or three, and of the prepared calls.  The formats whose prepared operands are planes
+    choose their parts themselves, and take the plan's where FMT_GEMM_WINDOW=0 turns the planes off."""
+    if e == 6:
+        monkeypatch.setenv("FMT_GEMM_WINDOW", "0")
+    g = torch.Generator(device="cuda").manual_seed(K + M)
+    f = (e, m, d)
+    for tA, tB in LAYOUTS:
+        A = torch.randn((K, M) if tA else (M, K), device="cuda", generator=g)
+        B = torch.randn((N, K) if tB else (K, N), device="cuda", generator=g)
+        C = [torch.full((M, N), float("nan"), device="cuda") for _ in range(3)]
+        monkeypatch.setenv("FMT_GEMM_DIRECT", "1")
+        assert launches(fmt, lambda: fmt.fmt_gemm(A, B, f, transA=tA, transB=tB, out=C[0])) == 1
+        monkeypatch.setenv("FMT_GEMM_DIRECT", "0")
+        assert launches(fmt, lambda: fmt.fmt_gemm(A, B, f, transA=tA, transB=tB, out=C[1])) == (2 if parts == 1 else 3)
+        fmt.fmt_gemm_prepared(fmt.fmt_prepare(A, f, trans=tA), fmt.fmt_prepare(B, f, trans=not tB), out=C[2])
+        torch.cuda.synchronize()
+        assert torch.equal(bits(C[0]), bits(C[1])), (tA, tB)
+        assert torch.equal(bits(C[0]), bits(C[2])), (tA, tB)
+
+
 @pytest.mark.parametrize("e,m,d", FORMATS)
 def test_values_over_the_whole_range(fmt, e, m, d, monkeypatch):
     """Random operands (normal, denormal and flushed values, zeros): within the accumulation bound of the oracle; the bits
     of the prepared calls where they share the representation; and next to the general route."""
+    monkeypatch.setenv("FMT_GEMM_DIRECT", "1")
     rng = np.random.default_rng(50 + e + m)
     c = oracle.format_constants(e, m)
     M, N, K = 96, 70, 128
@@ -87,15 +137,16 @@ def test_values_over_the_whole_range(fmt, e, m, d, monkeypatch):
         pa = fmt.fmt_prepare(torch.from_numpy(A).cuda(), (e, m, d))
         pb = fmt.fmt_prepare(torch.from_numpy(B).cuda(), (e, m, d), trans=True)
         assert np.array_equal(fmt.fmt_gemm_prepared(pa, pb).cpu().numpy().view(np.uint32), got.view(np.uint32))
-    monkeypatch.setenv("FMT_GEMM_PLAN", "1,1,1")
+    monkeypatch.setenv("FMT_GEMM_DIRECT", "0")
     general = product(fmt, A, B, (e, m, d), False, False)
     assert np.linalg.norm(got - general) <= 1e-6 * np.linalg.norm(ref)
 
 
 @pytest.mark.parametrize("e,m,d", [(5, 10, True), (6, 9, False), (8, 7, True), (4, 3, True)])
-def test_overflow_infinity_nan(fmt, e, m, d):
+def test_overflow_infinity_nan(fmt, e, m, d, monkeypatch):
     """Elements that overflow the format, infinities and NaN: non-finite results exactly where the oracle has them, NaN where it
     has NaN, and the other outputs untouched by them."""
+    monkeypatch.setenv("FMT_GEMM_DIRECT", "1")
     rng = np.random.default_rng(9)
     M, N, K = 70, 66, 100
     A = rng.integers(-2, 3, (M, K)).astype(np.float32)
