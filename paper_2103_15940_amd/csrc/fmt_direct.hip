@@ -9,7 +9,8 @@
 namespace fmt {
 
 // An fp32 matrix operand of a direct product: element (row, k) at X[row*row_step + k*k_step], one of the two 1.  VEC:
-// k_step == 1 and 16-byte vectors of k are aligned (X 16-byte aligned, row_step a multiple of 4).
+// k_step == 1; k is then loaded in 16-byte vectors, which global memory accesses take at any 4-byte alignment.
+typedef uint32_t u32x4u __attribute__((ext_vector_type(4), aligned(4)));
 struct DirectOperand {
     const uint32_t *X;
     uint32_t row_step, k_step;       // every offset of an element fits 32 bits (the host checks)
@@ -136,7 +137,7 @@ __global__ __launch_bounds__(512) void direct_product_kernel(DirectOperand a, Di
         for (int kk = 0; kk < 2; ++kk) {
             const uint32_t *src = o.X + (size_t)(uint32_t)(kb * kUnitK + kk * 16) * o.k_step;
             if constexpr (decltype(vec)::value) {
-                const u32x4 lo = *reinterpret_cast<const u32x4 *>(src + off), hi = *reinterpret_cast<const u32x4 *>(src + off + 4);
+                const u32x4u lo = *reinterpret_cast<const u32x4u *>(src + off), hi = *reinterpret_cast<const u32x4u *>(src + off + 4);
 #pragma unroll
                 for (int j = 0; j < 4; ++j) {
                     raw[kk][j] = lo[j];
@@ -151,6 +152,42 @@ __global__ __launch_bounds__(512) void direct_product_kernel(DirectOperand a, Di
     auto load = [&](int kb, uint32_t (&raw)[2][2][8]) __attribute__((always_inline)) {
         load_one(std::integral_constant<bool, AVEC>{}, a, off_a, kb, raw[0]);
         load_one(std::integral_constant<bool, BVEC>{}, b, off_b, kb, raw[1]);
+    };
+    // The block that K ends in, zero beyond K.  A lane's eight k that K cuts are loaded as the last eight of the row and
+    // moved down; single elements (and rows shorter than eight) beyond K read the last k: no load waits behind a test of its own.
+    auto load_last = [&](auto vec, const DirectOperand &o, uint32_t off, int kb, uint32_t (&raw)[2][8]) __attribute__((always_inline)) {
+        const uint32_t *row = o.X + (off - (uint32_t)half * 8u * o.k_step);
+        if (decltype(vec)::value && K >= 8) {
+            int skip[2];
+#pragma unroll
+            for (int kk = 0; kk < 2; ++kk) {
+                const int k0 = kb * kUnitK + kk * 16 + half * 8, at = min(k0, K - 8);
+                const u32x4 lo = *reinterpret_cast<const u32x4u *>(row + at), hi = *reinterpret_cast<const u32x4u *>(row + at + 4);
+                skip[kk] = k0 - at;
+#pragma unroll
+                for (int j = 0; j < 4; ++j) {
+                    raw[kk][j] = lo[j];
+                    raw[kk][4 + j] = hi[j];
+                }
+            }
+#pragma unroll
+            for (int kk = 0; kk < 2; ++kk)
+#pragma unroll
+                for (int by = 1; by <= 8; by *= 2) {
+                    const bool move = by < 8 ? (skip[kk] & by) != 0 : skip[kk] >= 8;
+#pragma unroll
+                    for (int j = 0; j < 8; ++j) raw[kk][j] = !move ? raw[kk][j] : j + by < 8 ? raw[kk][j + by < 8 ? j + by : 7] : 0u;
+                }
+        } else {
+#pragma unroll
+            for (int kk = 0; kk < 2; ++kk)
+#pragma unroll
+                for (int j = 0; j < 8; ++j) {
+                    const int k = kb * kUnitK + kk * 16 + half * 8 + j;
+                    const uint32_t v = row[(size_t)(uint32_t)min(k, K - 1) * o.k_step];
+                    raw[kk][j] = k < K ? v : 0u;
+                }
+        }
     };
     floatx16 acc;
 #pragma unroll
@@ -188,14 +225,8 @@ __global__ __launch_bounds__(512) void direct_product_kernel(DirectOperand a, Di
         }
     }
     if (kb0 <= whole && whole < kb1) {                                // the block that K ends in, if it is this part's
-#pragma unroll
-        for (int kk = 0; kk < 2; ++kk)
-#pragma unroll
-            for (int j = 0; j < 8; ++j) {
-                const int kw = whole * kUnitK + kk * 16, k = kw + half * 8 + j;
-                raw[0][0][kk][j] = k < K ? a.X[(size_t)(uint32_t)(kw + j) * a.k_step + off_a] : 0u;
-                raw[0][1][kk][j] = k < K ? b.X[(size_t)(uint32_t)(kw + j) * b.k_step + off_b] : 0u;
-            }
+        load_last(std::integral_constant<bool, AVEC>{}, a, off_a, whole, raw[0][0]);
+        load_last(std::integral_constant<bool, BVEC>{}, b, off_b, whole, raw[0][1]);
         multiply(raw[0]);
     }
 
@@ -250,14 +281,13 @@ static int launch(int M, int N, int K, const MatrixOperand &A, const MatrixOpera
     auto operand = [](const MatrixOperand &m, int rows) {
         return DirectOperand{reinterpret_cast<const uint32_t *>(m.X), m.kcontig ? (uint32_t)m.ld : 1u, m.kcontig ? 1u : (uint32_t)m.ld, rows};
     };
-    auto vec = [](const MatrixOperand &m) { return m.kcontig && (reinterpret_cast<uintptr_t>(m.X) & 15) == 0 && m.ld % 4 == 0; };
     const int kblocks = (K + kUnitK - 1) / kUnitK;
     const int tiles_m = (M + 31) / 32, tiles = tiles_m * ((N + 31) / 32);
-    const int per_wg = parts >= 4 ? 1 : 4 / parts;
+    const int per_wg = direct_blocks_per_workgroup(parts);
     const int waves = parts * per_wg;
     const size_t lds = parts > 1 ? (size_t)waves * 16 * 64 * sizeof(float) : 0;
-    auto kern = vec(A) ? (vec(B) ? direct_product_kernel<MODE, FTZ, PS, true, true> : direct_product_kernel<MODE, FTZ, PS, true, false>)
-                       : (vec(B) ? direct_product_kernel<MODE, FTZ, PS, false, true> : direct_product_kernel<MODE, FTZ, PS, false, false>);
+    auto kern = A.kcontig ? (B.kcontig ? direct_product_kernel<MODE, FTZ, PS, true, true> : direct_product_kernel<MODE, FTZ, PS, true, false>)
+                          : (B.kcontig ? direct_product_kernel<MODE, FTZ, PS, false, true> : direct_product_kernel<MODE, FTZ, PS, false, false>);
     hipLaunchKernelGGL(kern, dim3((unsigned)((tiles + per_wg - 1) / per_wg)), dim3(64 * waves), lds, stream, operand(A, M), operand(B, N), C,
                        ldc, M, N, K, kblocks, tiles_m, tiles, parts, (kblocks + parts - 1) / parts, per_wg, p,
                        lin != nullptr ? *lin : LinearOut{}, lin != nullptr ? 1 : 0);

@@ -2248,15 +2248,22 @@ static int prepare_operands(const OperandSpec &sa, const OperandLayout &la, cons
 static Scheme api_scheme(fmt_format_t f, int64_t K);
 
 // Parts of k of a direct product (fmt_direct.hip), or 0 where the general route is the better one (or forced by a plan).
-// FMT_GEMM_DIRECT=0|1 (tuning, tests): never, or wherever the kernel can.
-//   direct   one launch: 4.4 us, and 0.9 us per block of 32 k that a wave takes one after the other, or per 1024 waves' blocks
-//            where there are more waves (fitted to products of 64 x 64 x 32 to 4096 x 128 x 512, the slowest layout)
-//   general  two launches, 8.2 us at least; three when the plan splits k, 14.4 us at least with two pieces, 12.4 with one
-// Measured (us, general -> direct; 1/6/9 unless said): 64 x 64 x 32 8.0 -> 4.4; 256 x 10 x 1024 14.4 -> 9.6; 512 x 512 x 512 14.8 -> 6.9;
-// 256 x 1024 x 1024 18.9 -> 10.8; 1000 x 1000 x 64 in 1/8/7 8.2 -> 5.3; not taken: 1024 x 1024 x 256 9.9 against 11.1,
-// 768^3 15.4 against 19.6, 512^3 in 1/8/7 (whose sums must be the plan's) 9.2 against 17.5.
+// FMT_GEMM_DIRECT=0|1 (tuning, tests): never, or wherever the kernel can.  Both routes' times on the GPU (us), fitted to 664 products
+// of 16 x 40 to 328 x 3256 with k of 32 to 2393 in all layouts, replayed from graphs:
+//   direct   3.2, and per block of 32 k that a wave takes one after the other 1.0 (one piece 0.85), or, with n waves on a SIMD of
+//            the busiest compute unit, 0.72 n while the chip is not full and 0.95 n when it is; more for every operand whose
+//            rows lie along k (a load touches a line per lane); 0.7 per 10^6 results; up to 11 blocks (long chains came out
+//            slower than this: 224 x 440 x 2944 30 us in 12 blocks against 22)
+//   general  two launches: 5.8, 0.23 (one piece 0.07) per block of k, 2.05 per 10^6 operand elements, 1.06 (0.69) per 10^6
+//            results; three where the plan splits k: 6.7, 0.37 (0.25) per block of a part, 3.3 (1.9) and 0.9 (1.9)
+//            per part and 10^6 results; a layer's output roundings are then a launch of their own, 4
+// A launch less also saves the host 2.5 - 3 us (from Python 7.2, 9.7 and 12.2 us with one, two and three), so a direct product may
+// take 1 us more than two launches, and 2 more than three: with that, the 664 take 6.7 ms one after the other from Python and
+// 5.9 ms from graphs; 7.7 and 6.1 without the direct kernel.  Measured (us in a graph, general / direct): 64 x 64 x 32 in 1/6/9 5.9 / 3.4;
+// 256 x 256 x 511 10.9 / 6.3 - 7.7; 256 x 1024 x 1024 14.4 / 10.7 - 13.0; 1000 x 1000 x 80 8.0 / 6.6 - 7.1; not taken: 1000 x 1000
+// x 256 9.8 / 13.4, 256 x 256 x 2048 14.1 / 15 - 20, 64 x 64 x 2048 11.0 / 15 - 20, 256 x 1024 x 256 in 1/8/7 6.7 / 11.8.
 static int direct_parts(int M, int N, int K, const OperandSpec &sa, const OperandSpec &sb, const Plan &plan, fmt_format_t f, Scheme sch,
-                        int mode)
+                        int mode, bool layer, int cus)
 {
     if (getenv("FMT_GEMM_PLAN") != nullptr) return 0;
     // formats whose rounding has the short form of direct_convert
@@ -2275,9 +2282,20 @@ static int direct_parts(int M, int N, int K, const OperandSpec &sa, const Operan
     }
     if (parts > kDirectParts) return 0;
     if (const char *env = getenv("FMT_GEMM_DIRECT")) return env[0] == '1' ? parts : 0;
+    const bool one = pieces_of(sch.ps) == 1;
+    const double along = (sa.kcontig ? 1.0 : 0.0) + (sb.kcontig ? 1.0 : 0.0);
+    const int64_t per_wg = direct_blocks_per_workgroup(parts), wgs = (tiles + per_wg - 1) / per_wg;
+    const double n = (double)((wgs + cus - 1) / cus) * (double)(parts * per_wg) / 4.0;
+    const double shared = tiles * parts >= 4 * (int64_t)cus ? 0.95 + 0.125 * along : 0.72 * (1.0 + 0.05 * along);
     const double blocks = (double)((kblocks + parts - 1) / parts);
-    const double direct = 4.4 + std::max(0.9, 0.95 * (double)(tiles * parts) / 1024.0) * blocks;
-    const double general = plan.nsplit == 1 ? 8.2 : pieces_of(sch.ps) == 1 ? 12.4 : 14.4;
+    if (blocks > 11.0) return 0;
+    const double operands = ((double)M + N) * K * 1e-6, results = (double)M * N * 1e-6;
+    const double direct = 3.2 + blocks * std::max((one ? 0.85 : 1.0) * (1.0 + 0.05 * along), shared * n) + 0.7 * results;
+    const double kb_per = (double)((kblocks + plan.nsplit - 1) / plan.nsplit);
+    const double general = plan.nsplit == 1
+                               ? 5.8 + (one ? 0.07 : 0.23) * kb_per + 2.05 * operands + (one ? 0.69 : 1.06) * results + 1.0
+                               : 6.7 + (one ? 0.25 : 0.365) * kb_per + (one ? 1.9 : 3.3) * operands +
+                                     (one ? 1.9 : 0.9) * plan.nsplit * results + 2.0 + (layer ? 4.0 : 0.0);
     return direct < general ? parts : 0;
 }
 
@@ -2362,7 +2380,7 @@ static int run(int M, int N, int K, const OperandSpec &sa, const OperandSpec &sb
     // (the scratch of the general route is kept even where it is not used: what a call needs, and whether it can be
     // recorded into a graph, does not depend on the route)
     if (!scaled && sa.g.kind == kSrcMatrix && sb.g.kind == kSrcMatrix && out.img == 0) {
-        const int parts = direct_parts(M, N, K, sa, sb, plan, f, sch, p.mode);
+        const int parts = direct_parts(M, N, K, sa, sb, plan, f, sch, p.mode, out.lin != nullptr, cus);
         if (parts > 0) {
             const int rcd = launch_direct_product(M, N, K, MatrixOperand{sa.X, sa.ld, sa.kcontig}, MatrixOperand{sb.X, sb.ld, sb.kcontig},
                                                   out.C, out.ldc, parts, PS, FTZ, p, out.lin, stream);

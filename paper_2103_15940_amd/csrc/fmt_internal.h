@@ -88,6 +88,7 @@ struct MatrixOperand {
     bool kcontig;
 };
 constexpr int kDirectParts = 8;      // most parts of k (waves of a workgroup)
+constexpr int direct_blocks_per_workgroup(int parts) { return parts >= 4 ? 1 : 4 / parts; }   // blocks of 32 x 32 results
 int launch_direct_product(int M, int N, int K, const MatrixOperand &A, const MatrixOperand &B, float *C, int64_t ldc, int parts, int ps,
                           bool ftz, const QuantParams &p, const LinearOut *lin, hipStream_t stream);
 

@@ -117,6 +117,16 @@ def test_bits_of_the_general_route_with_k_in_parts(fmt, e, m, d, M, N, K, parts,
         assert torch.equal(bits(C[0]), bits(C[2])), (tA, tB)
 
 
+def test_which_route_a_product_takes(fmt):
+    """One launch where the rule's estimate is on its side, two or three where it is not: far on either side of the line."""
+    for f, shape, want in [((6, 9, True), (64, 64, 32), 1), ((8, 7, True), (64, 64, 32), 1), ((6, 9, True), (256, 256, 512), 1),
+                           ((6, 9, True), (1000, 1000, 256), 2), ((8, 7, True), (256, 1024, 512), 2), ((6, 9, True), (64, 64, 2400), 3),
+                           ((7, 18, True), (64, 64, 32), 2), ((7, 23, True), (64, 64, 32), 2)]:
+        M, N, K = shape
+        A, B, C = torch.ones(M, K, device="cuda"), torch.ones(N, K, device="cuda"), torch.empty(M, N, device="cuda")
+        assert launches(fmt, lambda: fmt.fmt_gemm(A, B, f, transB=True, out=C)) == want, (f, shape)
+
+
 @pytest.mark.parametrize("e,m,d", FORMATS)
 def test_values_over_the_whole_range(fmt, e, m, d, monkeypatch):
     """Random operands (normal, denormal and flushed values, zeros): within the accumulation bound of the oracle; the bits
