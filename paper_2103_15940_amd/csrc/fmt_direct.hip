@@ -35,56 +35,53 @@ __device__ __forceinline__ void direct_convert(const uint32_t (&v)[8], const Qua
                                                u32x4 (&out)[pieces_of(PS)])
 {
     constexpr int P = pieces_of(PS);
-    constexpr bool kMagicFast = MODE == kModeMagic;
     static_assert((MODE == kModeMagic && PS <= 2) || (MODE == kModeInteger && PS == 1), "formats with a short form");
-    {
-        bool rare;
-        if constexpr (kMagicFast) {
-            // largest |x| (the instruction takes magnitudes; a NaN is passed over, and stays one below)
-            float top = 0.0f;
+    bool rare;
+    if constexpr (MODE == kModeMagic) {
+        // largest |x| (the instruction takes magnitudes; a NaN is passed over, and stays one below)
+        float top = 0.0f;
 #pragma unroll
-            for (int j = 0; j < 8; j += 2) asm("v_max3_f32 %0, |%1|, |%2|, %0" : "+v"(top) : "v"(v[j]), "v"(v[j + 1]));
-            rare = top >= __uint_as_float(p.t_ovf);
+        for (int j = 0; j < 8; j += 2) asm("v_max3_f32 %0, |%1|, |%2|, %0" : "+v"(top) : "v"(v[j]), "v"(v[j + 1]));
+        rare = top >= __uint_as_float(p.t_ovf);
+    } else {
+        uint32_t top = 0u;                   // as a pattern: NaN on top
+#pragma unroll
+        for (int j = 0; j < 8; ++j) top = max(top, v[j] & 0x7FFFFFFFu);
+        rare = top >= p.t_ovf;
+    }
+    if (__ballot(rare) == 0ull) {            // the same in the whole wave
+        uint32_t r[8];
+        if constexpr (MODE == kModeMagic) {
+            const float scale = __uint_as_float((127u + p.shift) << 23), minn = __uint_as_float(p.minn_bits);
+#pragma unroll
+            for (int j = 0; j < 8; ++j) {
+                const float x = __uint_as_float(v[j]);
+                const float u = __uint_as_float(max((v[j] & k.exponent) | k.half, k.minn));
+                float q = __fmaf_rn(u, -scale, __fmaf_rn(u, scale, x));
+                if (FTZ) q = fabsf(q) < minn ? 0.0f : q;
+                r[j] = __float_as_uint(q);
+            }
         } else {
-            uint32_t top = 0u;                   // as a pattern: NaN on top
 #pragma unroll
-            for (int j = 0; j < 8; ++j) top = max(top, v[j] & 0x7FFFFFFFu);
-            rare = top >= p.t_ovf;
+            for (int j = 0; j < 8; ++j) {
+                r[j] = (v[j] + p.rbias + __builtin_amdgcn_ubfe(v[j], p.shift, p.lsb_width)) & p.nmask;
+                if (FTZ) r[j] = (v[j] & 0x7FFFFFFFu) < p.t_den ? 0u : r[j];
+            }
         }
-        if (__ballot(rare) == 0ull) {            // the same in the whole wave
-            uint32_t r[8];
-            if constexpr (kMagicFast) {
-                const float scale = __uint_as_float((127u + p.shift) << 23), minn = __uint_as_float(p.minn_bits);
 #pragma unroll
-                for (int j = 0; j < 8; ++j) {
-                    const float x = __uint_as_float(v[j]);
-                    const float u = __uint_as_float(max((v[j] & k.exponent) | k.half, k.minn));
-                    float q = __fmaf_rn(u, -scale, __fmaf_rn(u, scale, x));
-                    if (FTZ) q = fabsf(q) < minn ? 0.0f : q;
-                    r[j] = __float_as_uint(q);
-                }
+        for (int i = 0; i < 4; ++i) {
+            if constexpr (PS == 0) {         // values of the format are binary16 values: the conversion is exact
+                out[0][i] = __builtin_bit_cast(uint32_t, __builtin_amdgcn_cvt_pkrtz(__uint_as_float(r[2 * i]), __uint_as_float(r[2 * i + 1])));
             } else {
-#pragma unroll
-                for (int j = 0; j < 8; ++j) {
-                    r[j] = (v[j] + p.rbias + __builtin_amdgcn_ubfe(v[j], p.shift, p.lsb_width)) & p.nmask;
-                    if (FTZ) r[j] = (v[j] & 0x7FFFFFFFu) < p.t_den ? 0u : r[j];
+                out[0][i] = __builtin_amdgcn_perm(r[2 * i + 1], r[2 * i], 0x07060302u);
+                if constexpr (P >= 2) {
+                    const float l0 = __uint_as_float(r[2 * i]) - __uint_as_float(r[2 * i] & 0xFFFF0000u);              // exact
+                    const float l1 = __uint_as_float(r[2 * i + 1]) - __uint_as_float(r[2 * i + 1] & 0xFFFF0000u);
+                    out[P >= 2 ? 1 : 0][i] = __builtin_amdgcn_perm(__float_as_uint(l1), __float_as_uint(l0), 0x07060302u);
                 }
             }
-#pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                if constexpr (PS == 0) {         // values of the format are binary16 values: the conversion is exact
-                    out[0][i] = __builtin_bit_cast(uint32_t, __builtin_amdgcn_cvt_pkrtz(__uint_as_float(r[2 * i]), __uint_as_float(r[2 * i + 1])));
-                } else {
-                    out[0][i] = __builtin_amdgcn_perm(r[2 * i + 1], r[2 * i], 0x07060302u);
-                    if constexpr (P >= 2) {
-                        const float l0 = __uint_as_float(r[2 * i]) - __uint_as_float(r[2 * i] & 0xFFFF0000u);              // exact
-                        const float l1 = __uint_as_float(r[2 * i + 1]) - __uint_as_float(r[2 * i + 1] & 0xFFFF0000u);
-                        out[P >= 2 ? 1 : 0][i] = __builtin_amdgcn_perm(__float_as_uint(l1), __float_as_uint(l0), 0x07060302u);
-                    }
-                }
-            }
-            return;
         }
+        return;
     }
     uint32_t pc[8][P];
 #pragma unroll
