@@ -222,16 +222,17 @@ __device__ __forceinline__ void hist_end(uint32_t *tbl, uint32_t *s_bins, uint32
 int launch_hist_finalize(unsigned long long *partials, size_t n, fmt_hist_t *hist, hipStream_t stream);
 
 // The sink of a launch of nwg workgroups whose counts end in `hist` (n elements, below 2^48): one workgroup writes the
-// record itself (no records needed); up to `most` workgroups (and fewer than 2^21: a record counts its additions in 16 bits)
-// finish in the launch, more leave their records to launch_hist_finalize (then sink.hist is null), as do passes
-// whose records nobody clears ahead (at.clear null: captured ones).
+// record itself (no records needed); fewer than 2^21 (a record counts its additions in 16 bits) finish in the launch, at any
+// size (stream passes, one launch against two: 2^20 elements 6.4 us against 8.7, 2^25 46.7 against 50.0, 2^28 alike; a layer's
+// output pass of 4098 workgroups: 2 us less); more leave their records to launch_hist_finalize (then sink.hist is null),
+// as do passes whose records nobody clears ahead (at.clear null: captured ones, and fmt_quantize_static).
 // Records in use: additions to one address take about 12 ns each, so up to kFew workgroups share one record and
 // one hop; beyond that the additions are spread and a second hop sums the records.
-inline HistSink hist_sink(const HistRecords &at, unsigned long long n, fmt_hist_t *hist, uint64_t nwg, uint64_t most)
+inline HistSink hist_sink(const HistRecords &at, unsigned long long n, fmt_hist_t *hist, uint64_t nwg)
 {
     unsigned long long *out = reinterpret_cast<unsigned long long *>(hist);
     if (nwg == 1) return HistSink{nullptr, out, n, 1u, 0u, nullptr};
-    if (at.clear != nullptr && nwg <= most && nwg < ((uint64_t)1 << 21))
+    if (at.clear != nullptr && nwg < ((uint64_t)1 << 21))
         return HistSink{at.records, out, n, nwg <= kFew ? 1u : nwg <= 1024 ? 16u : (uint32_t)kShards, at.nclear, at.clear};
     return HistSink{at.records, nullptr, n, (uint32_t)kShards, at.nclear, at.clear};
 }

@@ -24,7 +24,6 @@ typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
 constexpr int kLBlock = 256;
 constexpr int kLCopies = 8;
 constexpr int kLRows = 4;                 // rows per trip (independent loads in flight)
-constexpr uint64_t kLastArrival = 4096;   // workgroups up to which the statistics are summed in the launch (see hist_end)
 
 // A: accumulators (leading dimension lda); Y: output, fp32 patterns (== A, in place) or, with PACK,
 // uint16_t codes.  VEC: 128-bit loads and full-width stores are possible for whole lanes.
@@ -142,7 +141,7 @@ int launch_v(const float *A, int64_t lda, void *Y, int64_t ldy, int M, int N, co
         HistRecords at;
         rc = get_hist_records(stream, (uint64_t)strips * row_groups, &at);
         if (rc != FMT_OK) return rc;
-        sink = hist_sink(at, (unsigned long long)M * (unsigned long long)N, hist, (uint64_t)strips * row_groups, kLastArrival);
+        sink = hist_sink(at, (unsigned long long)M * (unsigned long long)N, hist, (uint64_t)strips * row_groups);
     }
     const bool vec = (reinterpret_cast<uintptr_t>(A) % 16 == 0) && (lda % 4 == 0) &&
                      (reinterpret_cast<uintptr_t>(Y) % (PACK ? 8 : 16) == 0) && (ldy % 4 == 0);

@@ -270,10 +270,6 @@ int launch_hist_finalize(unsigned long long *partials, size_t n, fmt_hist_t *his
     return FMT_OK;
 }
 
-// Workgroups up to which the statistics end in the pass itself: any grid (2^20 elements: one launch of 6.4 us against
-// 8.7 us for two; 2^25: 46.7 against 50.0; 2^28: alike).
-constexpr uint64_t kOneLaunch = ~(uint64_t)0;
-
 template <int MODE, bool STORE, bool FTZ, bool HIST, bool DEEP, bool VEC, bool PACK>
 static int launch_variant(const float *x, void *y, size_t n, size_t head, size_t nvec, const QuantParams &p,
                           fmt_hist_t *hist, hipStream_t stream, unsigned long long *fixed_partials)
@@ -308,7 +304,7 @@ static int launch_variant(const float *x, void *y, size_t n, size_t head, size_t
             rc = get_hist_records(stream, (uint64_t)grid, &at);
             if (rc != FMT_OK) return rc;
         }
-        sink = hist_sink(at, n, hist, (uint64_t)grid, kOneLaunch);
+        sink = hist_sink(at, n, hist, (uint64_t)grid);
     }
     hipLaunchKernelGGL(kern, dim3(grid), dim3(kBlock), 0, stream, reinterpret_cast<const uint32_t *>(x),
                        reinterpret_cast<uint32_t *>(y), n, head, nvec, p, sink);
