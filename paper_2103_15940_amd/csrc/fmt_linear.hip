@@ -22,12 +22,16 @@ namespace {
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
 constexpr int kLBlock = 256;
-constexpr int kLCopies = 8;
+// Replicas of the exponent table (as in the stream kernels): 8; 32 where the fp32 output has 2^27 elements or more (65536 x 4096 in
+// 1/8/7, k = 64: 640 us against 665 with 8; 16384 x 4096 alike; codes out, 8: 583, 32: 616).
+constexpr int kCopiesMost = 8;
+constexpr int kCopiesLarge = 32;
+constexpr int64_t kLarge = (int64_t)1 << 27;
 constexpr int kLRows = 4;                 // rows per trip (independent loads in flight)
 
 // A: accumulators (leading dimension lda); Y: output, fp32 patterns (== A, in place) or, with PACK,
 // uint16_t codes.  VEC: 128-bit loads and full-width stores are possible for whole lanes.
-template <int MODE, bool FTZ, bool HIST, bool DEEP, bool VEC, bool PACK>
+template <int MODE, bool FTZ, bool HIST, bool DEEP, bool VEC, bool PACK, int kLCopies>
 __global__ __launch_bounds__(kLBlock) void linear_epilogue_kernel(const uint32_t *A, int64_t lda, void *Yv, int64_t ldy,
                                                                   int M, int N, const uint32_t *__restrict__ bias,
                                                                   int rows_per_wg, QuantParams p, HistSink sink)
@@ -148,12 +152,11 @@ int launch_v(const float *A, int64_t lda, void *Y, int64_t ldy, int M, int N, co
     const dim3 grid((unsigned)strips, (unsigned)row_groups);
     const uint32_t *a = reinterpret_cast<const uint32_t *>(A);
     const uint32_t *b = reinterpret_cast<const uint32_t *>(bias);
-    if (vec)
-        hipLaunchKernelGGL((linear_epilogue_kernel<MODE, FTZ, HIST, DEEP, true, PACK>), grid, dim3(kLBlock), 0, stream, a,
-                           lda, Y, ldy, M, N, b, (int)rows_per_wg, p, sink);
-    else
-        hipLaunchKernelGGL((linear_epilogue_kernel<MODE, FTZ, HIST, DEEP, false, PACK>), grid, dim3(kLBlock), 0, stream, a,
-                           lda, Y, ldy, M, N, b, (int)rows_per_wg, p, sink);
+    auto kern = vec ? linear_epilogue_kernel<MODE, FTZ, HIST, DEEP, true, PACK, kCopiesMost>
+                    : linear_epilogue_kernel<MODE, FTZ, HIST, DEEP, false, PACK, kCopiesMost>;
+    if constexpr (HIST && !PACK)
+        if (vec && (int64_t)M * N >= kLarge) kern = linear_epilogue_kernel<MODE, FTZ, HIST, DEEP, true, PACK, kCopiesLarge>;
+    hipLaunchKernelGGL(kern, grid, dim3(kLBlock), 0, stream, a, lda, Y, ldy, M, N, b, (int)rows_per_wg, p, sink);
     FMT_HIP_CHECK(hipGetLastError());
     if (HIST && sink.hist == nullptr) return launch_hist_finalize(sink.records, (size_t)M * (size_t)N, hist, stream);
     return FMT_OK;
