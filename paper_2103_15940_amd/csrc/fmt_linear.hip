@@ -45,10 +45,7 @@ __global__ __launch_bounds__(kLBlock) void linear_epilogue_kernel(const uint32_t
     const uint32_t tid = threadIdx.x;
     const uint32_t copy = tid & (kLCopies - 1);
     Counts w;
-    if (HIST) {
-        hist_begin<kLCopies, kLBlock>(tbl, s_bins, s_cls, tid);
-        hist_clear<kLBlock>(sink, blockIdx.y * gridDim.x + blockIdx.x, gridDim.x * gridDim.y, tid);
-    }
+    if (HIST) hist_begin<kLCopies, kLBlock>(tbl, s_bins, s_cls, tid);
 
     const int64_t c0 = ((int64_t)blockIdx.x * kLBlock + (int64_t)tid) * 4;
     const int ncol = N - c0 < 4 ? (N - c0 < 0 ? 0 : (int)(N - c0)) : 4;      // valid columns of this lane
@@ -113,9 +110,11 @@ __global__ __launch_bounds__(kLBlock) void linear_epilogue_kernel(const uint32_t
             }
         }
     }
-    if (HIST)
-        hist_end<kLCopies, kLBlock>(tbl, s_bins, s_cls, w, p, sink, blockIdx.y * gridDim.x + blockIdx.x,
-                                    gridDim.x * gridDim.y, tid);
+    if (HIST) {
+        const uint32_t wg = blockIdx.y * gridDim.x + blockIdx.x, nwg = gridDim.x * gridDim.y;
+        hist_clear<kLBlock>(sink, wg, nwg, tid);
+        hist_end<kLCopies, kLBlock>(tbl, s_bins, s_cls, w, p, sink, wg, nwg, tid);
+    }
 }
 
 template <int MODE, bool FTZ, bool HIST, bool DEEP, bool PACK>

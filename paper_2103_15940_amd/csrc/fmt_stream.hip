@@ -16,9 +16,9 @@
 //   * overflow, zero and flush decisions are comparisons of |x|'s pattern with thresholds
 //     computed on the host (the ties at minD/2, minN - minD/2 and maxN + ulp/2 all go to the
 //     even neighbour).
-// Statistics: each element adds one to an LDS table indexed by its 8-bit fp32 exponent field, replicated 8 times
-// (lane l uses replica l % 8); the class counts are per-lane compare-and-add counters.  Each workgroup folds its table
-// into 64 bins and adds its 72 counts, with one 64-bit atomic per slot, into one of a few partial records in library
+// Statistics: each element adds one to an LDS table indexed by its 8-bit fp32 exponent field, replicated 8, 16 or 32 times
+// (lane l uses replica l modulo that number); the class counts are per-lane compare-and-add counters.  Each workgroup folds its
+// table into 64 bins and adds its 72 counts, with one 64-bit atomic per slot, into one of a few partial records in library
 // scratch; the workgroup that adds last to a slot passes the sum on to the caller's fmt_hist_t (hist_end), so a pass is one
 // launch.  fmt_quantize_static, whose records are shared by all streams, sums them in a second kernel.
 #include <mutex>
@@ -45,11 +45,16 @@ typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
 constexpr int kBlock = FMT_STREAM_BLOCK;  // threads per workgroup
 // Replicas of the exponent table in LDS, lane l uses replica l % copies.  8: 9 KiB, so that registers and not LDS bound the
 // resident workgroups, and little to clear and fold in a pass of one tile per workgroup (2^20 elements 6.4 us fused against 7.2
-// with 32, one per bank; 2^24 24.8 against 25.9; a tensor of one value included).  The fused fp32 pass over the largest tensors,
-// whose workgroups hold four tiles and more, is the faster with 32: 2^28 elements 351 against 355 us (2^26: alike).
+// with 32, one per bank; 2^24 24.8 against 25.9; codes 2^26 70.5 against 76.5, 16 alike).  The fused fp32 pass over the largest
+// tensors, whose workgroups hold four tiles and more, is the faster with 32: 2^28 elements 351 against 355 us (2^26: alike).
+// Statistics alone, with nothing to write beside them, show the lanes that meet on one address where all values are alike: 16
+// from 2^26 elements up (all ones / normal: 2^26 44.4 / 42.9 us, with 8 45.4 / 43.8; 2^27 83.2 / 81.7, with 8 88.9 / 84.7; 2^28 160 /
+// 158, with 8 167 / 162); below that ordinary values are up to 4 % faster with 8 (2^22 7.7 against 8.1; 2^25 22.3 against 22.8).
 constexpr int kCopiesMost = 8;
+constexpr int kCopiesAlone = 16;
 constexpr int kCopiesLarge = 32;
-constexpr size_t kLarge = (size_t)1 << 27;   // elements from which it takes them
+constexpr size_t kAlone = (size_t)1 << 26;   // elements from which statistics alone take theirs,
+constexpr size_t kLarge = (size_t)1 << 27;   // ... and the fused fp32 pass its
 constexpr int kUnroll = FMT_STREAM_UNROLL;  // independent 128-bit loads in flight per thread
 constexpr int kGridPerCU = FMT_STREAM_GRID_PER_CU;   // workgroups launched per compute unit (at most): statistics alone
 constexpr int kGridFused = 64;           // ... fused with rounding, fp32 or codes out
@@ -104,34 +109,10 @@ __global__ __launch_bounds__(kBlock) void stream_kernel(const uint32_t *__restri
     const uint32_t lane32 = tid & (kCopies - 1);
     Counts w;
 
-    // one full tile, in v
     constexpr size_t kTileVec = (size_t)kBlock * kUnroll;
-    auto tile = [&](const u32x4 (&v)[kUnroll], size_t i) __attribute__((always_inline)) {
-        uint32_t amax = 0u;
-#pragma unroll
-        for (int k = 0; k < kUnroll; ++k) {
-            u32x4 o = {0u, 0u, 0u, 0u};
-#pragma unroll
-            for (int j = 0; j < 4; ++j) {
-                const uint32_t u = v[k][j];
-                if (HIST) account_run<DEEP, kCopies>(u & 0x7FFFFFFFu, p, tbl, lane32, w, amax);
-                if (STORE) o[j] = quantize_bits<MODE, FTZ>(u, p);
-            }
-            if (STORE) put(i + k * kBlock, o);
-        }
-        if (HIST) {
-            uint32_t flat[4 * kUnroll];
-#pragma unroll
-            for (int k = 0; k < kUnroll; ++k)
-#pragma unroll
-                for (int j = 0; j < 4; ++j) flat[4 * k + j] = v[k][j];
-            account_run_top(flat, amax, p, w);
-        }
-    };
-
     // VEC: a tile is kBlock*kUnroll consecutive vectors; workgroup b takes tiles b, b+grid, ...  Every lane of the workgroup
     // runs the same trips, and all tiles but the last are full.
-    if constexpr (VEC && HIST) {
+    if constexpr (VEC && (HIST || PACK)) {
         // leftovers around the vector body, [0, head) and [head + 4*nvec, n): one per lane of the first wave, loaded before
         // anything else so that the load is not a chain of its own at the end
         const bool edge = blockIdx.x == 0 && tid < 64 && tid < n - 4 * nvec;
@@ -155,19 +136,42 @@ __global__ __launch_bounds__(kBlock) void stream_kernel(const uint32_t *__restri
                 }
             }
         };
-        // A tile's loads are issued ahead of the work on the tile before it, the first tile's ahead of the clearing of the
-        // table (2^25 elements: statistics alone 27.3 -> 22.4 us, fused 50 -> 47).
+        // With statistics a tile's loads are issued ahead of the work on the tile before it, the first tile's ahead of the clearing
+        // of the table (2^25 elements: statistics alone 27.3 -> 22.4 us, fused 50 -> 47).
         size_t t = blockIdx.x;
-        load(t);
-        hist_begin<kCopies, kBlock>(tbl, s_bins, s_cls, tid);
-        hist_clear<kBlock>(sink, blockIdx.x, gridDim.x, tid);
+        if (HIST) {
+            load(t);
+            hist_begin<kCopies, kBlock>(tbl, s_bins, s_cls, tid);
+        }
         while (t < full_tiles) {
-            tile(v, t * kTileVec + tid);
+            if (!HIST) load(t);
+            const size_t i = t * kTileVec + tid;
+            uint32_t amax = 0u;
+#pragma unroll
+            for (int k = 0; k < kUnroll; ++k) {
+                u32x4 o = {0u, 0u, 0u, 0u};
+#pragma unroll
+                for (int j = 0; j < 4; ++j) {
+                    const uint32_t u = v[k][j];
+                    if (HIST) account_run<DEEP, kCopies>(u & 0x7FFFFFFFu, p, tbl, lane32, w, amax);
+                    if (STORE) o[j] = quantize_bits<MODE, FTZ>(u, p);
+                }
+                if (STORE) put(i + k * kBlock, o);
+            }
+            if (HIST) {
+                uint32_t flat[4 * kUnroll];
+#pragma unroll
+                for (int k = 0; k < kUnroll; ++k)
+#pragma unroll
+                    for (int j = 0; j < 4; ++j) flat[4 * k + j] = v[k][j];
+                account_run_top(flat, amax, p, w);
+            }
             t += gridDim.x;
-            if (t * kTileVec < nvec) load(t);
+            if (HIST && t * kTileVec < nvec) load(t);
         }
         if (t == full_tiles && full_tiles * kTileVec < nvec) {
             // the ragged last tile, lane by lane
+            if (!HIST) load(t);
 #pragma unroll
             for (int k = 0; k < kUnroll; ++k) {
                 const size_t i = full_tiles * kTileVec + k * kBlock + tid;
@@ -177,41 +181,49 @@ __global__ __launch_bounds__(kBlock) void stream_kernel(const uint32_t *__restri
             }
         }
         if (blockIdx.x == 0 && tid < 64) {
-            account<DEEP, kCopies>(edge_u & 0x7FFFFFFFu, edge, p, tbl, lane32, w);
+            if (HIST) account<DEEP, kCopies>(edge_u & 0x7FFFFFFFu, edge, p, tbl, lane32, w);
             if (STORE && edge) put_one(edge_at, quantize_bits<MODE, FTZ>(edge_u, p));
         }
     } else if constexpr (VEC) {
-        // Without statistics a workgroup has one tile, and what counts is a short kernel (2^23 elements: 10.7 us; 11.4 with the
-        // other branch's loop and leftovers).
+        // Values without statistics: a workgroup has one tile, and what counts is a short kernel (2^23 elements: 11.1 us; 11.5 with
+        // the other branch's loop and leftovers, where codes without statistics are the faster ones: 2^24 16.8 against 17.2).
         const u32x4 *xv = reinterpret_cast<const u32x4 *>(x + head);
         const size_t full_tiles = nvec / kTileVec;
-        for (size_t t = blockIdx.x; t < full_tiles; t += gridDim.x) {
+        u32x4 v[kUnroll];
+        size_t t = blockIdx.x;
+        for (; t < full_tiles; t += gridDim.x) {
             const size_t i = t * kTileVec + tid;
-            u32x4 v[kUnroll];
 #pragma unroll
             for (int k = 0; k < kUnroll; ++k) v[k] = __builtin_nontemporal_load(xv + i + k * kBlock);
-            tile(v, i);
-        }
-        if (blockIdx.x == full_tiles % gridDim.x && full_tiles * kTileVec < nvec) {
 #pragma unroll
             for (int k = 0; k < kUnroll; ++k) {
-                const size_t i = full_tiles * kTileVec + k * kBlock + tid;
-                const bool valid = i < nvec;
-                u32x4 v = {0u, 0u, 0u, 0u};
-                if (valid) v = __builtin_nontemporal_load(xv + i);
-                u32x4 o = do_vec<MODE, STORE, FTZ, HIST, DEEP, kCopies>(v, valid, p, tbl, lane32, w);
-                if (STORE && valid) put(i, o);
+                u32x4 o = {0u, 0u, 0u, 0u};
+#pragma unroll
+                for (int j = 0; j < 4; ++j) o[j] = quantize_bits<MODE, FTZ>(v[k][j], p);
+                put(i + k * kBlock, o);
+            }
+        }
+        if (t == full_tiles && full_tiles * kTileVec < nvec) {
+            const size_t i = full_tiles * kTileVec + tid;
+#pragma unroll
+            for (int k = 0; k < kUnroll; ++k) {
+                v[k] = u32x4{0u, 0u, 0u, 0u};
+                if (i + k * kBlock < nvec) v[k] = __builtin_nontemporal_load(xv + i + k * kBlock);
+            }
+#pragma unroll
+            for (int k = 0; k < kUnroll; ++k) {
+                u32x4 o = do_vec<MODE, STORE, FTZ, HIST, DEEP, kCopies>(v[k], i + k * kBlock < nvec, p, tbl, lane32, w);
+                if (i + k * kBlock < nvec) put(i + k * kBlock, o);
             }
         }
         if (blockIdx.x == 0 && tid < 64 && tid < n - 4 * nvec) {
             const size_t at = tid < head ? tid : 4 * nvec + tid;
             const uint32_t u = x[at];
-            if (STORE) put_one(at, quantize_bits<MODE, FTZ>(u, p));
+            put_one(at, quantize_bits<MODE, FTZ>(u, p));
         }
     } else {
         if (HIST) {
             hist_begin<kCopies, kBlock>(tbl, s_bins, s_cls, tid);
-            hist_clear<kBlock>(sink, blockIdx.x, gridDim.x, tid);
         }
         const size_t stride = (size_t)gridDim.x * kBlock;
         // every lane runs the same number of trips
@@ -225,7 +237,10 @@ __global__ __launch_bounds__(kBlock) void stream_kernel(const uint32_t *__restri
         }
     }
 
-    if (HIST) hist_end<kCopies, kBlock>(tbl, s_bins, s_cls, w, p, sink, blockIdx.x, gridDim.x, tid);
+    if (HIST) {
+        hist_clear<kBlock>(sink, blockIdx.x, gridDim.x, tid);
+        hist_end<kCopies, kBlock>(tbl, s_bins, s_cls, w, p, sink, blockIdx.x, gridDim.x, tid);
+    }
 }
 
 // Sums the shard records into the caller's fmt_hist_t and clears them for the next call (one
@@ -277,6 +292,8 @@ static int launch_variant(const float *x, void *y, size_t n, size_t head, size_t
     auto kern = stream_kernel<MODE, STORE, FTZ, HIST, DEEP, VEC, PACK, kCopiesMost>;
     if constexpr (HIST && STORE && !PACK && VEC)
         if (n >= kLarge) kern = stream_kernel<MODE, STORE, FTZ, HIST, DEEP, VEC, PACK, kCopiesLarge>;
+    if constexpr (HIST && !STORE && VEC)
+        if (n >= kAlone) kern = stream_kernel<MODE, STORE, FTZ, HIST, DEEP, VEC, PACK, kCopiesAlone>;
     int cus = 0;
     int rc = device_cu_count(&cus);
     if (rc != FMT_OK) return rc;
@@ -289,8 +306,8 @@ static int launch_variant(const float *x, void *y, size_t n, size_t head, size_t
     const size_t cap = (size_t)cus * (HIST ? (STORE ? kGridFused : kGridPerCU) : kGridStore);
     size_t g = want;
     if (HIST) {
-        // mid-size tensors: at least four tiles per workgroup (one tile does not pay for the table),
-        // but no fewer workgroups than the four per compute unit that the LDS table lets run at once
+        // mid-size tensors: at least four tiles per workgroup (one tile does not pay for the table), but no fewer workgroups
+        // than four per compute unit (1 to 12 tried on 4 M elements: 8 gain 8 % for statistics alone and lose 10 % fused)
         const size_t resident = (size_t)cus * 4;
         g = (want + 3) / 4;
         if (g < resident) g = want < resident ? want : resident;

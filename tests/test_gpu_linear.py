@@ -383,3 +383,19 @@ def test_rounded_on_the_way_out(fmt, e, m, d, shape):
             got = direct.cpu().numpy()
             assert np.array_equal(np.isnan(got), np.isnan(r))
             assert np.array_equal(got[~np.isnan(r)], r[~np.isnan(r)])
+
+
+def test_statistics_of_a_large_output(fmt):
+    """Outputs of 2^27 elements and more count with more replicas of the table: the counts of fmt_histogram on the rounded sums."""
+    M, N, K = 32800, 4100, 8
+    f = (6, 9, True)
+    X = torch.randn(M, K, device="cuda").mul_(3.0).exp2_()
+    W = torch.randn(N, K, device="cuda").mul_(2.0).exp2_()
+    Y = torch.empty(M, N, device="cuda")
+    h, want = fmt.new_hist().fill_(-1), fmt.new_hist()
+    for rows in (M, 100):                                            # the small tables as well
+        fmt.fmt_linear(X[:rows], W, None, f, out=Y[:rows], hist=h)
+        acc = fmt.fmt_quantize(fmt.fmt_gemm(X[:rows], W, f, transB=True), f)
+        fmt.fmt_histogram(acc, f, hist=want)
+        torch.cuda.synchronize()
+        assert torch.equal(Y[:rows], acc) and torch.equal(h, want)

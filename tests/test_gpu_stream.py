@@ -422,6 +422,33 @@ def test_statistics_in_one_launch(fmt, tiles, rest, offset):
             assert_same_hist(fmt, hist[i], w, "n = %d, pass %d" % (n, i))
 
 
+@pytest.mark.parametrize("n", [(1 << 26) - 1, 1 << 26, (1 << 27) - 4095, (1 << 27) + 4097])
+def test_statistics_of_large_tensors(fmt, n):
+    """Sizes around the lines where a pass takes more replicas of its table: the three passes agree with a count of the classes and of
+    the binades by torch (exponents and thresholds of the patterns), and with one another."""
+    f = (6, 9, True)
+    x = torch.randn(n, device="cuda").mul_(12.0).exp2_()
+    x[::1001] = 0.0
+    x[5::100003] = float("inf")
+    x[7::100003] = float("nan")
+    hist = [fmt.new_hist().fill_(-1) for _ in range(3)]
+    y = fmt.fmt_quantize(x, f, hist=hist[0])
+    fmt.fmt_histogram(x, f, hist=hist[1])
+    fmt.fmt_pack16(x, f, hist=hist[2])
+    torch.cuda.synchronize()
+    assert torch.equal(hist[0], hist[1]) and torch.equal(hist[0], hist[2])
+    h = fmt.hist_to_dict(hist[0])
+    minn = 2.0 ** -30
+    inf, nan, zero = int(torch.isinf(x).sum()), int(torch.isnan(x).sum()), int((x == 0).sum())
+    want = {"total": n, "zero": zero, "inf": inf, "nan": nan, "underflow": int((y == 0).sum()) - zero,
+            "denormal": int(((y > 0) & (y < minn)).sum()), "overflow": int(torch.isinf(y).sum()) - inf,
+            "normal": int(((y >= minn) & torch.isfinite(y)).sum())}
+    assert {k: h[k] for k in want} == want
+    e = ((x.view(torch.int32) >> 23) & 255)[(x != 0) & ~torch.isnan(x)]          # no fp32 denormals among them
+    bins = torch.bincount((e.to(torch.int64) - 127 + 48).clamp_(0, 63), minlength=64)
+    assert np.array_equal(h["bins"], bins.cpu().numpy())
+
+
 def test_statistics_after_records_left_over(fmt):
     """Passes that overlap on one stream's scratch leave counts and arrivals in its partial records.  Here the test leaves them
     there itself (every word of the buffer: seven arrivals and a count), so that nothing races: the first pass of few
