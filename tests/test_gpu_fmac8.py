@@ -196,8 +196,8 @@ def test_against_the_plain_definition(fmt, e, m, d):
 @pytest.mark.parametrize("e,m,d", [(6, 9, True), (6, 9, False), (5, 10, True), (6, 11, False), (2, 11, True), (3, 1, True)])
 def test_forms_of_the_step_by_stage(fmt, e, m, d, M, N):
     """Every tile size of the kernel (1, 4 and 16 outputs per thread), with stages of 32 k on both sides of the bound
-    that decides which form of the fused step a stage takes: products far below it, the largest product just below
-    and just above 2^(Emin-m+52) (or 2^Emax) over the growth of a group, a stage with an overflow, one with an infinity, one of
+    that decides which form of the fused step a stage takes: products far below it, the largest operands the last values of
+    the format whose product is below 2^(Emin-m+52) (or 2^Emax) over the growth of a group and the first above it, a stage with an overflow, one with an infinity, one of
     values around the smallest denormal, and large products that meet a tiny accumulator.  Bit for bit on sampled rows and columns."""
     rng = np.random.default_rng(10 * e + m + M)
     c = oracle.format_constants(e, m)
@@ -210,10 +210,15 @@ def test_forms_of_the_step_by_stage(fmt, e, m, d, M, N):
     def clip(X, hi):
         return np.clip(X, -hi, hi).astype(np.float32)
     A, B = clip(A, top / 16), clip(B, top / 16)
-    for stage, factor in ((1, 0.30), (2, 0.36), (3, 1.5)):        # max|w| max|x| = factor^2 * 2^limit: 0.09, 0.13, 2.25
+    growth = sum((1.0 + 2.0 ** -(m + 1)) ** i for i in range(9))  # of |a + w x| over a group, each step rounded up by half a unit
+    edge = np.sqrt(0.99 * 2.0 ** limit / growth)
+    step = 2.0 ** (max(np.floor(np.log2(edge)), c["Emin"]) - m)   # of the format at the edge
+    below = np.floor(edge / step) * step
+    assert below ** 2 < 0.99 * 2.0 ** limit / growth < (below + step) ** 2
+    for stage, largest in ((1, below), (2, below + step), (3, 1.5 * top)):
         s = slice(32 * stage, 32 * stage + 32)
-        A[:, s] = clip(workloads.log2_normal((M, 32), limit / 2 - 4, 4.0, 0.0, rng), factor * top)
-        B[s, :] = clip(workloads.log2_normal((32, N), limit / 2 - 4, 4.0, 0.0, rng), factor * top)
+        A[:, s] = clip(workloads.log2_normal((M, 32), limit / 2 - 4, 4.0, 0.0, rng), largest)
+        B[s, :] = clip(workloads.log2_normal((32, N), limit / 2 - 4, 4.0, 0.0, rng), largest)
     A[M // 2, 32 * 4 + 3] = np.inf
     s = slice(32 * 5, 32 * 6)
     A[:, s] = workloads.log2_normal((M, 32), (c["Emin"] - m) / 2.0, 1.0, 0.0, rng)
