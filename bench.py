@@ -618,8 +618,8 @@ def main() -> int:
                                                   / (VALU_LANE_INSTR_PER_S / FMAC8_INSTR_PER_MAC), 4),
                                     "note": "vector issue rate 256 CUs x 64 lanes x 2.4 GHz = 39.3 T "
                                             "lane-instructions/s over the 5 instructions of the fused step "
-                                            "in fp64 (5.8 are executed per step with the master additions and "
-                                            "the LDS reads)"}}
+                                            "in fp64 (6.2 are executed per step with the operands' rounding and "
+                                            "the master additions)"}}
     # loss-scale controller on the nine statistics records of configuration 4's gradient tensors
     recs = torch.stack([L["h"][2] for L in layers])
     st = fmt.fmt_dls_init(1024.0)

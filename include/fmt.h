@@ -220,7 +220,9 @@ int fmt_gemm(int transA, int transB, int64_t M, int64_t N, int64_t K,
  *
  *     C[i][j] = sum_k Q(a)[i][k] * Q(b)[j][k]        (exact products, fp32 accumulation: FMACS, Sec. III-B)
  *
- * bit for bit what fmt_gemm returns for the same operands (same kernels, same order of accumulation).
+ * bit for bit what fmt_gemm returns for the same operands (same kernels, same order of accumulation), except for
+ * formats with e == 6 and m == 8 or 9 in products below 1 GFLOP or with K < 128: there fmt_gemm splits its operands
+ * into 16-bit pieces where prepared operands are exponent planes, so the same exact products are accumulated in another order.
  *
  * fmt_operand_bytes  size in bytes of the device buffer a prepared operand of `rows` x `k` needs.
  * fmt_prepare        op(X) is `rows` x `k`: trans == 0: X is rows x k, row-major, ld >= k;

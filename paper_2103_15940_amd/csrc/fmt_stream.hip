@@ -20,7 +20,8 @@
 // (lane l uses replica l modulo that number); the class counts are per-lane compare-and-add counters.  Each workgroup folds its
 // table into 64 bins and adds its 72 counts, with one 64-bit atomic per slot, into one of a few partial records in library
 // scratch; the workgroup that adds last to a slot passes the sum on to the caller's fmt_hist_t (hist_end), so a pass is one
-// launch.  fmt_quantize_static, whose records are shared by all streams, sums them in a second kernel.
+// launch.  fmt_quantize_static, whose records are shared by all streams, and passes recorded into a graph, whose records
+// are the same at every replay, sum them in a second kernel.
 #include <mutex>
 
 #include "fmt_hist.h"
