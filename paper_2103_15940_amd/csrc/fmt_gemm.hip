@@ -40,6 +40,7 @@
 #include <cmath>
 #include <cstdio>
 #include <cstdlib>
+#include <cstring>
 #include <type_traits>
 #include <vector>
 
@@ -1834,7 +1835,7 @@ static Plan make_plan(int M, int N, int kblocks, int cus, int pieces)
         {4, 4, 1, 1.21, 1.21}, {4, 2, 1, 1.0, 1.0}, {2, 4, 1, 1.03, 1.03}, {2, 2, 2, 0.98, 1.11}, {1, 1, 4, 0.53, 0.68}};
     const Shape(&shapes)[5] = pieces == 1 ? single : multi;
     const double wg_cost = pieces == 1 ? 68.0 : 40.0, split_cost = pieces == 1 ? 5.76 : 2.5;
-    if (const char *env = getenv("FMT_GEMM_PLAN")) {      // tuning override: "tm,tn,nsplit[,sched]"
+    if (const char *env = getenv("FMT_GEMM_PLAN")) {      // tuning override: "tm,tn,nsplit[,sched]" (other values leave the plan to the model)
         Plan forced{2, 2, 1, 1};
         if (sscanf(env, "%d,%d,%d,%d", &forced.tm, &forced.tn, &forced.nsplit, &forced.sched) >= 3) {
             for (const auto &sh : shapes)
@@ -2248,8 +2249,8 @@ static int prepare_operands(const OperandSpec &sa, const OperandLayout &la, cons
 static Scheme api_scheme(fmt_format_t f, int64_t K);
 
 // Parts of k of a direct product (fmt_direct.hip), or 0 where the general route is the better one (or forced by a plan).
-// FMT_GEMM_DIRECT=0|1 (tuning, tests): never, or wherever the kernel can.  Both routes' times on the GPU (us), fitted to 664 products
-// of 16 x 40 to 328 x 3256 with k of 32 to 2393 in all layouts, replayed from graphs:
+// FMT_GEMM_PLAN=direct (tests): wherever the kernel can; any other value: nowhere.  Both routes' times on the GPU (us), fitted to 664
+// products of 16 x 40 to 328 x 3256 with k of 32 to 2393 in all layouts, replayed from graphs:
 //   direct   3.2, and per block of 32 k that a wave takes one after the other 1.0 (one piece 0.85), or, with n waves on a SIMD of
 //            the busiest compute unit, 0.72 n while the chip is not full and 0.95 n when it is; more for every operand whose
 //            rows lie along k (a load touches a line per lane); 0.7 per 10^6 results; up to 11 blocks (long chains came out
@@ -2265,7 +2266,8 @@ static Scheme api_scheme(fmt_format_t f, int64_t K);
 static int direct_parts(int M, int N, int K, const OperandSpec &sa, const OperandSpec &sb, const Plan &plan, fmt_format_t f, Scheme sch,
                         int mode, bool layer, int cus)
 {
-    if (getenv("FMT_GEMM_PLAN") != nullptr) return 0;
+    const char *env = getenv("FMT_GEMM_PLAN");
+    if (env != nullptr && strcmp(env, "direct") != 0) return 0;
     // formats whose rounding has the short form of direct_convert
     if (!(mode == kModeMagic && sch.ps <= 2) && !(mode == kModeInteger && sch.ps == 1)) return 0;
     // offsets inside an operand in 32 bits
@@ -2274,14 +2276,14 @@ static int direct_parts(int M, int N, int K, const OperandSpec &sa, const Operan
     const int kblocks = (K + kUnitK - 1) / kUnitK;
     const int64_t tiles = (((int64_t)M + 31) / 32) * (((int64_t)N + 31) / 32);
     int parts = plan.nsplit;
-    if (api_scheme(f, K).scaled) {
+    if (planes_possible(f) && api_scheme(f, K).scaled) {
         // the prepared calls of these formats take the planes, so no other call promises these sums and the parts are
         // free: enough for two waves per SIMD (2048), two blocks each at least
         parts = 1;
         while (parts < kDirectParts && tiles * parts < 2048 && kblocks / (parts * 2) >= 2) parts *= 2;
     }
     if (parts > kDirectParts) return 0;
-    if (const char *env = getenv("FMT_GEMM_DIRECT")) return env[0] == '1' ? parts : 0;
+    if (env != nullptr) return parts;
     const bool one = pieces_of(sch.ps) == 1;
     const double along = (sa.kcontig ? 1.0 : 0.0) + (sb.kcontig ? 1.0 : 0.0);
     const int64_t per_wg = direct_blocks_per_workgroup(parts), wgs = (tiles + per_wg - 1) / per_wg;

@@ -1,5 +1,5 @@
 """Small products of fp32 matrices: fmt_gemm in one launch, operands rounded on the way into the matrix cores, against the CPU
-oracle, against the general route (forced through FMT_GEMM_DIRECT=0) and against the prepared calls."""
+oracle, against the general route (forced through FMT_GEMM_PLAN=general) and against the prepared calls."""
 import ctypes
 
 import numpy as np
@@ -30,7 +30,7 @@ def fmt():
 
 @pytest.fixture(autouse=True)
 def plain_environment(monkeypatch):
-    for name in ("FMT_GEMM_PLAN", "FMT_GEMM_WINDOW", "FMT_GEMM_DIRECT"):
+    for name in ("FMT_GEMM_PLAN", "FMT_GEMM_WINDOW"):
         monkeypatch.delenv(name, raising=False)
 
 
@@ -79,7 +79,7 @@ def bits(t):
 def test_every_layout_and_alignment(fmt, e, m, d, shape, monkeypatch):
     """Integers small enough for every partial sum to be exact: the oracle's bits whatever the order of the sums.  All layouts,
     leading dimensions and base alignments (k-contiguous rows of any alignment, k that ends inside a block of 32 or of 8)."""
-    monkeypatch.setenv("FMT_GEMM_DIRECT", "1")
+    monkeypatch.setenv("FMT_GEMM_PLAN", "direct")
     M, N, K = shape
     rng = np.random.default_rng(M + 10 * N + 100 * K + e)
     top = 3 if m >= 3 else 1
@@ -107,9 +107,9 @@ def test_bits_of_the_general_route_with_k_in_parts(fmt, e, m, d, M, N, K, parts,
         A = torch.randn((K, M) if tA else (M, K), device="cuda", generator=g)
         B = torch.randn((N, K) if tB else (K, N), device="cuda", generator=g)
         C = [torch.full((M, N), float("nan"), device="cuda") for _ in range(3)]
-        monkeypatch.setenv("FMT_GEMM_DIRECT", "1")
+        monkeypatch.setenv("FMT_GEMM_PLAN", "direct")
         assert launches(fmt, lambda: fmt.fmt_gemm(A, B, f, transA=tA, transB=tB, out=C[0])) == 1
-        monkeypatch.setenv("FMT_GEMM_DIRECT", "0")
+        monkeypatch.setenv("FMT_GEMM_PLAN", "general")
         assert launches(fmt, lambda: fmt.fmt_gemm(A, B, f, transA=tA, transB=tB, out=C[1])) == (2 if parts == 1 else 3)
         fmt.fmt_gemm_prepared(fmt.fmt_prepare(A, f, trans=tA), fmt.fmt_prepare(B, f, trans=not tB), out=C[2])
         torch.cuda.synchronize()
@@ -131,7 +131,7 @@ def test_which_route_a_product_takes(fmt):
 def test_values_over_the_whole_range(fmt, e, m, d, monkeypatch):
     """Random operands (normal, denormal and flushed values, zeros): within the accumulation bound of the oracle; the bits
     of the prepared calls where they share the representation; and next to the general route."""
-    monkeypatch.setenv("FMT_GEMM_DIRECT", "1")
+    monkeypatch.setenv("FMT_GEMM_PLAN", "direct")
     rng = np.random.default_rng(50 + e + m)
     c = oracle.format_constants(e, m)
     M, N, K = 96, 70, 128
@@ -147,7 +147,7 @@ def test_values_over_the_whole_range(fmt, e, m, d, monkeypatch):
         pa = fmt.fmt_prepare(torch.from_numpy(A).cuda(), (e, m, d))
         pb = fmt.fmt_prepare(torch.from_numpy(B).cuda(), (e, m, d), trans=True)
         assert np.array_equal(fmt.fmt_gemm_prepared(pa, pb).cpu().numpy().view(np.uint32), got.view(np.uint32))
-    monkeypatch.setenv("FMT_GEMM_DIRECT", "0")
+    monkeypatch.setenv("FMT_GEMM_PLAN", "general")
     general = product(fmt, A, B, (e, m, d), False, False)
     assert np.linalg.norm(got - general) <= 1e-6 * np.linalg.norm(ref)
 
@@ -156,7 +156,7 @@ def test_values_over_the_whole_range(fmt, e, m, d, monkeypatch):
 def test_overflow_infinity_nan(fmt, e, m, d, monkeypatch):
     """Elements that overflow the format, infinities and NaN: non-finite results exactly where the oracle has them, NaN where it
     has NaN, and the other outputs untouched by them."""
-    monkeypatch.setenv("FMT_GEMM_DIRECT", "1")
+    monkeypatch.setenv("FMT_GEMM_PLAN", "direct")
     rng = np.random.default_rng(9)
     M, N, K = 70, 66, 100
     A = rng.integers(-2, 3, (M, K)).astype(np.float32)
