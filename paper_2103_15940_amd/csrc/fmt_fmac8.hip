@@ -11,8 +11,8 @@
 //
 // Three forms of the fused step, all giving the one rounding of the exact sum:
 //   wide    (e <= 6, m <= 11, operands of ordinary size: the common case) fp64 around the hardware's fused
-//           multiply-add, s = fma(w, x, a), and the rounding (s + C) - C with C = 1.5 * 2^(max(E, Emin) + 52 - m):
-//           5 vector instructions (7 with the flush), and the vector units issue fp64 adds and fused multiply-adds
+//           multiply-add, s = fma(w, x, a), and the rounding (C + s) - C with C = t * 2^(52 - m), t about as large as s:
+//           4 vector instructions (6 with the flush), and the vector units issue fp64 adds and fused multiply-adds
 //           at the rate of single fp32 ones.  See fmac_wide for why the rounding to 53 bits on the way does no harm
 //           as long as |s| stays below `wide_limit`; a workgroup takes this form for a stage of 32 k when
 //           the largest operand magnitudes of the stage say that no sum can get there.
@@ -123,18 +123,32 @@ __device__ __forceinline__ float fmac_fix(float tried, float a, float w, float x
 
 // Constants of the wide step.
 struct WideConsts {
-    uint32_t minn_hi;    // hi word of 1.5 * 2^Emin
-    uint32_t exp_mask;   // 0x7FF00000 and 0x80000 in registers: with literals the compiler spends two instructions
-    uint32_t half;       // (and, or) where one (v_and_or_b32, which takes no literal) does
+    uint32_t floor_hi;   // hi word of 1.5 * 2^Emin
     double scale;        // 2^(52 - m)
-    double minn;         // 2^Emin
+    uint32_t flush_hi;   // hi word of 2^Emin - 2^(Emin - m - 1), whose lo word is zero
     float limit;         // the form is used while max|w| * max|x| of a stage stays below this
 };
 
-// The fused step in fp64, for |a + w*x| < wide_limit = 2^(Emin - m + 52).
-//   * s = fma(w, x, a) is the exact sum rounded to 53 bits; r rounds s to the format's grid at s (C is 1.5 times a
-//     power of two whose last place is the grid's step, so s + C rounds to the grid for either sign, ties to the
-//     even multiple, and taking C off again is exact).
+// The larger of |s| and 1.5 * 2^Emin with the lo word cleared, in one instruction: the hi words of two non-negative doubles
+// compare like the singles of the same pattern (a pattern that is a denormal single belongs to a double below 2^-1015,
+// here zero, and loses either way; one that is an infinite or NaN single to a double from 2^1017, far above the limit).
+__device__ __forceinline__ double carrier(double s, const WideConsts &k)
+{
+    float t;
+    asm("v_max_f32 %0, |%1|, %2" : "=v"(t) : "v"(__int_as_float(__double2hiint(s))), "s"(k.floor_hi));
+    return __hiloint2double(__float_as_int(t), 0);
+}
+
+// The fused step in fp64, for |a + w*x| < wide_limit = 2^(Emin - m + 52): 4 instructions (6 with the flush).
+//   * s = fma(w, x, a) is the exact sum rounded to 53 bits; r = (C + s) - C rounds s to the format's grid at s, whose step is
+//     G = 2^(max(E(s), Emin) - m).  C = t * 2^(52 - m), with t in [2^max(E, Emin), 2^(max(E, Emin) + 1)) a value of at most
+//     21 bits (carrier): the last place of C is G, and C is a multiple of 2^32 G, so that C + s, rounded to a multiple of G,
+//     is C plus the multiple nearest to s, ties to the even one, and taking C off again is exact.  C + s stays in C's
+//     binade at the upper end (t is at least 2^(max(E, Emin) - 20) below the next power of two, |s| far less than that times
+//     2^(52 - m)); at the lower end it may leave it for s < 0 and t = 2^E exactly -- then |s| < 2^E (1 + 2^-20), the grid
+//     is the finer G/2, and the nearest multiple is 2^E as on G.  C is formed inside the two additions, exactly.
+//     (With |s| itself in place of its first 21 bits C could be an odd multiple of G, and a sum that crosses into the next
+//     binade, where multiples of 2G are taken, would come out one G off.)
 //   * r is the single rounding of the exact sum: with s exact there is nothing to show.  a is a multiple of
 //     2^(Emin - m), which is at least the last place of s, so only bits of p = w*x can be lost.  p has at most
 //     2m + 2 bits, so a p with bits below the last place of s is smaller than 2^(E(s) - 51 + 2m) <=
@@ -148,12 +162,14 @@ template <bool FTZ, bool FIRST>
 __device__ __forceinline__ double fmac_wide(double a, double w, double x, const WideConsts &k)
 {
     const double s = FIRST ? __dmul_rn(w, x) : __fma_rn(w, x, a);
-    // u = 1.5 * 2^max(E, Emin); C = u * 2^(52 - m) is formed inside the two fused multiply-adds (exactly)
-    const double u = __hiloint2double((int)max(((uint32_t)__double2hiint(s) & k.exp_mask) | k.half, k.minn_hi), 0);
-    const double r = __fma_rn(u, -k.scale, __fma_rn(u, k.scale, s));
+    const double t = carrier(s, k);
+    const double r = __fma_rn(t, -k.scale, __fma_rn(t, k.scale, s));
     if (!FTZ) return r;
-    // r has at most 12 significant bits: its lo word is zero, clearing the hi word makes a zero of it
-    return __hiloint2double(fabs(r) < k.minn ? 0 : __double2hiint(r), __double2loint(r));
+    // The result is below minN exactly where |s| is below minN less half a step (that midpoint goes to minN, the even
+    // multiple), which s's hi word decides while the additions run.  r has at most 12 significant bits: its lo word is zero,
+    // clearing the hi word makes a zero of it.
+    const bool below = fabsf(__int_as_float(__double2hiint(s))) < __uint_as_float(k.flush_hi);
+    return __hiloint2double(below ? 0 : __double2hiint(r), __double2loint(r));
 }
 
 // A stage's operand: a double, or (LOW) a float in the low word.
@@ -171,8 +187,8 @@ enum { kStepSingle = 0, kStepOdd = 1 };     // the form besides the wide one tha
 // what counts is that every SIMD has instructions to issue: for the wide step 16 chains per thread where there are tiles enough
 // to fill the chip, 4 or 1 where there are not; the round-to-odd step, five times as long, fills it with one (see launch).  Operand stages are rounded on the way into LDS, as fp64 (a
 // value converted once instead of once per use); the next stage's loads are in flight while a stage is computed.
-// Measured in 1/6/9: 2048 x 2048 x 1024 takes 0.74 ms (5.8 T fused steps/s; 1.97 ms with the single form alone),
-// 256 x 256 x 256 takes 17 us (224 us with 64 x 64 tiles and the single form alone).
+// Measured in 1/6/9: 2048 x 2048 x 1024 takes 0.63 ms (6.8 T fused steps/s; 0.74 ms with a step of 5 instructions, 1.97 ms with the
+// single form alone), 256 x 256 x 256 takes 13 us (17 us with a step of 5 instructions whose operands were read one by one).
 template <int MODE, bool FTZ, int STEP, int T>
 __global__ __launch_bounds__(256) void fmac8_kernel(const uint32_t *__restrict__ A, int64_t lda, int transA,
                                                     const uint32_t *__restrict__ B, int64_t ldb, int transB,
@@ -223,8 +239,6 @@ __global__ __launch_bounds__(256) void fmac8_kernel(const uint32_t *__restrict__
             if (gc < N && gkb < K) vb[it] = transB ? B[(size_t)gc * ldb + gkb] : B[(size_t)gkb * ldb + gc];
         }
     };
-
-    if (STEP == kStepSingle) asm("" : "+v"(wc.half));      // a vector register: an instruction takes one scalar operand only
 
     // The largest tile, whose thread uses a value four times, stores a stage for the form that the stage before it took: as fp64,
     // or (the single form) as fp32 in the low words.  Converting at each use instead made the single form 4 % slower there
@@ -294,20 +308,29 @@ __global__ __launch_bounds__(256) void fmac8_kernel(const uint32_t *__restrict__
 #pragma unroll 1
             for (int g = 0; g < kFK / 8; ++g) {
                 double a16[T][T];
-#pragma unroll
-                for (int kk = 0; kk < 8; ++kk) {
-                    double w[T], x[T];
+                double w[8][T], x[8][T];
+                auto read = [&](int kk) __attribute__((always_inline)) {
 #pragma unroll
                     for (int i = 0; i < T; ++i) {
-                        w[i] = sa[g * 8 + kk][ty * T + i];
-                        x[i] = sb[g * 8 + kk][tx * T + i];
+                        w[kk][i] = sa[g * 8 + kk][ty * T + i];
+                        x[kk][i] = sb[g * 8 + kk][tx * T + i];
                     }
+                };
+                // few chains per thread: a group's operands are read ahead of its steps, which would wait for them one by one
+                if constexpr (T <= 2) {
+#pragma unroll
+                    for (int kk = 0; kk < 8; ++kk) read(kk);
+                    __builtin_amdgcn_sched_barrier(0);
+                }
+#pragma unroll
+                for (int kk = 0; kk < 8; ++kk) {
+                    if constexpr (T > 2) read(kk);
 #pragma unroll
                     for (int i = 0; i < T; ++i)
 #pragma unroll
                         for (int j = 0; j < T; ++j)
-                            a16[i][j] = kk == 0 ? fmac_wide<FTZ, true>(0.0, w[i], x[j], wc)
-                                                : fmac_wide<FTZ, false>(a16[i][j], w[i], x[j], wc);
+                            a16[i][j] = kk == 0 ? fmac_wide<FTZ, true>(0.0, w[kk][i], x[kk][j], wc)
+                                                : fmac_wide<FTZ, false>(a16[i][j], w[kk][i], x[kk][j], wc);
                 }
 #pragma unroll
                 for (int i = 0; i < T; ++i)
@@ -414,10 +437,11 @@ static int launch(int transA, int transB, int M, int N, int K, const float *A, i
         return FMT_TILE(1);
     } else {
         // `alone` is what one tile on a compute unit takes (the chains' latency with 1, 4 or 16 of them to interleave), `each` the
-        // time per tile of a compute unit with work enough.  Measured in 1/6/9, wide form (us, T = 1 / 2 / 4): N = 64: 16.8 / 28.5 /
-        // 62.6; 384: 24 / 30 / 63; 512: 30 / 30 / 64; 768: 59 / 52 / 66; 1024: 93 / 66 / 67; 1500: 190 / 129 / 153; 2048: 335 / 211 /
-        // 197.  The values decide which form a stage takes, so the rule is the ordinary one's.  Where all stages take the single
-        // form it is off by up to a third (640: 65 / 83 / 228; 1024: 123 / 118 / 228; 1500: 240 / 220 / 448; 2048: 426 / 367 / 497).
+        // time per tile of a compute unit with work enough.  Measured in 1/6/9, wide form (us, T = 1 / 2 / 4): N = 64: 13.1 / 21.4 /
+        // 57.7; 384: 23 / 22 / 58; 512: 29 / 23 / 59; 640: 44 / 32 / 59; 768: 53 / 42 / 59; 1024: 88 / 53 / 61; 1500: 185 / 109 / 127;
+        // 2048: 334 / 187 / 165.  The values decide which form a stage takes; at 384 and 512, where four chains per thread would gain
+        // up to 6 us, the single form loses 35, so the line lies above them.  Where all stages take the single
+        // form the rule is off by up to a third (640: 65 / 83 / 228; 1024: 123 / 118 / 228; 1500: 240 / 220 / 448; 2048: 426 / 367 / 497).
         int cus = 0;
         const int rc = device_cu_count(&cus);
         if (rc != FMT_OK) return rc;
@@ -452,11 +476,9 @@ int launch_gemm_fmac8(int transA, int transB, int64_t M, int64_t N, int64_t K, c
     fp.ftz = f.denorm == 0;
     const bool ftz = f.denorm == 0;
     WideConsts wc;
-    wc.minn_hi = ((uint32_t)(1 - bias + 1023) << 20) | 0x80000u;
-    wc.exp_mask = 0x7FF00000u;
-    wc.half = 0x80000u;
+    wc.floor_hi = ((uint32_t)(1 - bias + 1023) << 20) | 0x80000u;
     wc.scale = ldexp(1.0, 52 - f.m);
-    wc.minn = fp.minn;
+    wc.flush_hi = ((uint32_t)(-bias + 1023) << 20) | (0xFFFFFu & ~((1u << (19 - f.m)) - 1u));     // 1.1...1 (m + 1 ones) * 2^(Emin - 1)
     // Below 2^(Emin - m + 52) the wide step is exact (see fmac_wide), below 2^Emax nothing overflows.  Through the 8
     // steps of a group |a + w*x| grows to at most max|w*x| times the sum of (1 + 2^-(m+1))^i, i = 0..8 (each step's
     // rounding adds at most half a last place): that factor, and a little for the product of the maxima, comes off.

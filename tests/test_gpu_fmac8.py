@@ -237,3 +237,19 @@ def test_forms_of_the_step_by_stage(fmt, e, m, d, M, N):
     nan = np.isnan(ref)
     assert np.array_equal(np.isnan(got), nan)
     assert_bits(np.where(nan, 0, got).astype(np.float32), np.where(nan, 0, ref).astype(np.float32), "stages")
+
+
+@pytest.mark.parametrize("e,m,d", [(6, 9, True), (6, 9, False), (6, 11, True), (6, 3, True)])
+def test_sums_next_to_a_power_of_two(fmt, e, m, d):
+    """A power of two plus a product far below it that fills the last places of the 53-bit sum, on either side: the sum lies next to
+    the end of a binade with its last bit set."""
+    rng = np.random.default_rng(e + m)
+    n = 96
+    A, B = np.zeros((n, 16), np.float32), np.zeros((16, n), np.float32)
+    A[:, 0] = 2.0 ** rng.integers(-6, 7, n)
+    B[0] = rng.choice([-1.0, 1.0], n) * 2.0 ** rng.integers(-6, 7, n)
+    frac = lambda k: 1.0 + (2 * rng.integers(0, 1 << (m - 1), k) + 1) * 2.0 ** -m      # noqa: E731  (last bit set)
+    A[:, 1] = rng.choice([-1.0, 1.0], n) * frac(n) * 2.0 ** rng.integers(-22, -12, n)
+    B[1] = frac(n) * 2.0 ** rng.integers(-22, -12, n)
+    got, ref = run(fmt, A, B, (e, m, d))
+    assert_bits(got, ref, "1/%d/%d" % (e, m))
