@@ -9,7 +9,8 @@
 // ALU work (no matrix cores), bound by the rate at which the vector units issue instructions: one per
 // lane and clock.
 //
-// Three forms of the fused step, all giving the one rounding of the exact sum:
+// Four forms of the fused step, all giving the one rounding of the exact sum:
+//   half    (binary16, 1/5/10) the packed 16-bit fused multiply-add of the vector units: half an instruction (fmac8_half_kernel).
 //   wide    (e <= 6, m <= 11, operands of ordinary size: the common case) fp64 around the hardware's fused
 //           multiply-add, s = fma(w, x, a), and the rounding (C + s) - C with C = t * 2^(52 - m), t about as large as s:
 //           4 vector instructions (6 with the flush), and the vector units issue fp64 adds and fused multiply-adds
@@ -412,6 +413,153 @@ __global__ __launch_bounds__(256) void fmac8_kernel(const uint32_t *__restrict__
     }
 }
 
+// binary16 (1/5/10), bound by the issue of vector instructions (about 1.2 per step with the conversions, the additions to the
+// masters and the staging): 2048 x 2048 x 1024 takes 0.18 ms, 0.20 in 1/5/10/n (0.74 and 0.96 in the wide form of five
+// instructions); a result of up to 512 x 512 x 256 11 us (17 - 29), bound by the latency of its stages.
+// The vector units' own packed fused multiply-add takes two steps per instruction -- v_pk_fma_f16 rounds the
+// exact w*x + a once to binary16, to nearest even, with denormal results and overflow to infinity, which is the step of 1/5/10/d.
+// For 1/5/10/n the kernel runs with denormal inputs of 16-bit operations read as zero and denormal results kept (MODE.FP_DENORM
+// of the 16- and 64-bit operations = 2): a step rounds first, and a result below minN is a zero to the step that follows, and to
+// the end of the group by a selection.
+template <bool FTZ, int T>
+__global__ __launch_bounds__(256) void fmac8_half_kernel(const float *__restrict__ A, int64_t lda, int transA,
+                                                         const float *__restrict__ B, int64_t ldb, int transB,
+                                                         float *__restrict__ C, int64_t ldc, int M, int N, int K, int tiles_n,
+                                                         QuantParams qp)
+{
+    typedef _Float16 f16x2 __attribute__((ext_vector_type(2)));
+    constexpr int kTile = 16 * T;
+    constexpr int kHK = T == 2 ? 64 : 32;           // k per stage
+    constexpr int kLoads = kTile * kHK / 256;      // elements of one operand per thread and stage
+    __shared__ __attribute__((aligned(16))) _Float16 sa[2][kHK][kTile + 4];   // rounded operand values, [k][row]; two stages
+    __shared__ __attribute__((aligned(16))) _Float16 sb[2][kHK][kTile + 4];
+    const int tid = threadIdx.x, tx = tid & 15, ty = tid >> 4;
+    const int row0 = (blockIdx.x / tiles_n) * kTile, col0 = (blockIdx.x % tiles_n) * kTile;
+    if (FTZ) __builtin_amdgcn_s_setreg(1 | (6 << 6) | (1 << 11), 2);         // MODE[7:6]
+
+    float acc32[T][T];
+#pragma unroll
+    for (int i = 0; i < T; ++i)
+#pragma unroll
+        for (int j = 0; j < T; ++j) acc32[i][j] = 0.0f;
+
+    float va[kLoads], vb[kLoads];
+    // element `it` of this thread, as in fmac8_kernel
+    auto at = [&](int it, bool kcontig, int &r, int &k) {
+        const int idx = it * 256 + tid;
+        r = kcontig ? idx / kHK : idx % kTile;
+        k = kcontig ? idx % kHK : idx / kTile;
+    };
+    auto load = [&](int k0) {
+#pragma unroll
+        for (int it = 0; it < kLoads; ++it) {
+            int r, k;
+            at(it, !transA, r, k);
+            va[it] = 0.0f;
+            if (row0 + r < M && k0 + k < K) va[it] = transA ? A[(size_t)(k0 + k) * lda + row0 + r] : A[(size_t)(row0 + r) * lda + k0 + k];
+            at(it, transB != 0, r, k);
+            vb[it] = 0.0f;
+            if (col0 + r < N && k0 + k < K) vb[it] = transB ? B[(size_t)(col0 + r) * ldb + k0 + k] : B[(size_t)(k0 + k) * ldb + col0 + r];
+        }
+    };
+    // the conversion to binary16 is the rounding of 1/5/10/d; 1/5/10/n reads its denormals as zeros
+    auto store = [&](int buf) {
+#pragma unroll
+        for (int it = 0; it < kLoads; ++it) {
+            int r, k;
+            at(it, !transA, r, k);
+            sa[buf][k][r] = static_cast<_Float16>(va[it]);
+            at(it, transB != 0, r, k);
+            sb[buf][k][r] = static_cast<_Float16>(vb[it]);
+        }
+    };
+
+    load(0);
+    store(0);
+    __syncthreads();
+    int buf = 0;
+    for (int k0 = 0; k0 < K; k0 += kHK) {
+        const bool more = k0 + kHK < K;
+        if (more) load(k0 + kHK);                  // in flight while this stage is computed
+#pragma unroll 1
+        for (int g = 0; g < kHK / 8; ++g) {
+            f16x2 a16[T][T / 2], w[8][T / 2], x[8][T / 2];
+            auto read = [&](int kk) __attribute__((always_inline)) {
+#pragma unroll
+                for (int i = 0; i < T / 2; ++i) {
+                    w[kk][i] = *reinterpret_cast<const f16x2 *>(&sa[buf][g * 8 + kk][ty * T + 2 * i]);
+                    x[kk][i] = *reinterpret_cast<const f16x2 *>(&sb[buf][g * 8 + kk][tx * T + 2 * i]);
+                }
+            };
+            if constexpr (T == 2) {
+#pragma unroll
+                for (int kk = 0; kk < 8; ++kk) read(kk);
+                __builtin_amdgcn_sched_barrier(0);
+            }
+#pragma unroll
+            for (int kk = 0; kk < 8; ++kk) {
+                if constexpr (T > 2) read(kk);
+#pragma unroll
+                for (int i = 0; i < T; ++i) {
+                    const f16x2 wi = {w[kk][i / 2][i & 1], w[kk][i / 2][i & 1]};
+#pragma unroll
+                    for (int j = 0; j < T / 2; ++j) a16[i][j] = kk == 0 ? wi * x[kk][j] : __builtin_elementwise_fma(wi, x[kk][j], a16[i][j]);
+                }
+            }
+#pragma unroll
+            for (int i = 0; i < T; ++i)
+#pragma unroll
+                for (int j = 0; j < T; ++j) {
+                    float a = static_cast<float>(a16[i][j / 2][j & 1]);
+                    if (FTZ) a = fabsf(a) < 0x1p-14f ? 0.0f : a;
+                    acc32[i][j] = __fadd_rn(acc32[i][j], a);
+                }
+        }
+        buf ^= 1;
+        if (more) store(buf);                      // the stage before this one was read before the last barrier
+        __syncthreads();
+    }
+#pragma unroll
+    for (int i = 0; i < T; ++i) {
+        const int r = row0 + ty * T + i;
+#pragma unroll
+        for (int j = 0; j < T; ++j) {
+            const int c = col0 + tx * T + j;
+            if (r < M && c < N)
+                C[(size_t)r * ldc + c] = __uint_as_float(quantize_bits<kModeMagic, FTZ>(__float_as_uint(acc32[i][j]), qp));
+        }
+    }
+}
+
+template <bool FTZ, int T>
+static int launch_half_tile(int transA, int transB, int M, int N, int K, const float *A, int64_t lda, const float *B, int64_t ldb,
+                            float *C, int64_t ldc, const QuantParams &qp, hipStream_t stream)
+{
+    const int tiles_m = (M + 16 * T - 1) / (16 * T), tiles_n = (N + 16 * T - 1) / (16 * T);
+    if ((int64_t)tiles_m * tiles_n >= ((int64_t)1 << 31)) return FMT_ERR_SHAPE;
+    hipLaunchKernelGGL((fmac8_half_kernel<FTZ, T>), dim3(tiles_m * tiles_n), dim3(256), 0, stream, A, lda, transA, B, ldb, transB, C,
+                       ldc, M, N, K, tiles_n, qp);
+    FMT_HIP_CHECK(hipGetLastError());
+    return FMT_OK;
+}
+
+template <bool FTZ>
+static int launch_half(int transA, int transB, int M, int N, int K, const float *A, int64_t lda, const float *B, int64_t ldb,
+                       float *C, int64_t ldc, const QuantParams &qp, hipStream_t stream)
+{
+#define FMT_TILE(T) launch_half_tile<FTZ, T>(transA, transB, M, N, K, A, lda, B, ldb, C, ldc, qp, stream)
+    // Measured (us, N x N x 256, T = 2 / 4): N = 64 ... 512: 11 / 25; 768: 16 / 26; 1024: 20 / 26; 1500: 40 / 41; 2048: 66 / 51.
+    int cus = 0;
+    const int rc = device_cu_count(&cus);
+    if (rc != FMT_OK) return rc;
+    auto estimate = [&](int t, double alone, double each) {
+        const int64_t tiles = (((int64_t)M + 16 * t - 1) / (16 * t)) * (((int64_t)N + 16 * t - 1) / (16 * t));
+        return std::max(alone, (double)((tiles + cus - 1) / cus) * each);
+    };
+    return estimate(2, 10.8, 4.2) <= estimate(4, 25.0, 13.2) ? FMT_TILE(2) : FMT_TILE(4);
+#undef FMT_TILE
+}
+
 template <int MODE, bool FTZ, int STEP, int T>
 static int launch_tile(int transA, int transB, int M, int N, int K, const float *A, int64_t lda, const float *B, int64_t ldb,
                        float *C, int64_t ldc, const QuantParams &qp, const Fmac8Params &fp, const WideConsts &wc, hipStream_t stream)
@@ -488,7 +636,10 @@ int launch_gemm_fmac8(int transA, int transB, int64_t M, int64_t N, int64_t K, c
 #define FMT_RUN(MD, STEP)                                                                                             \
     (ftz ? launch<MD, true, STEP>(transA, transB, (int)M, (int)N, (int)K, A, lda, B, ldb, C, ldc, qp, fp, wc, stream) \
          : launch<MD, false, STEP>(transA, transB, (int)M, (int)N, (int)K, A, lda, B, ldb, C, ldc, qp, fp, wc, stream))
-    // wide and single-precision fused steps where they are exact: 1/5/10, 1/6/9 and their neighbours
+    if (f.e == 5 && f.m == 10 && !fmac8_force_f64())
+        return ftz ? launch_half<true>(transA, transB, (int)M, (int)N, (int)K, A, lda, B, ldb, C, ldc, qp, stream)
+                   : launch_half<false>(transA, transB, (int)M, (int)N, (int)K, A, lda, B, ldb, C, ldc, qp, stream);
+    // wide and single-precision fused steps where they are exact: 1/6/9 and its neighbours
     if (f.e <= 6 && f.m <= 11 && !fmac8_force_f64()) return FMT_RUN(kModeMagic, kStepSingle);
     if (qp.mode == kModeMagic) return FMT_RUN(kModeMagic, kStepOdd);
     if (qp.mode == kModeInteger) return FMT_RUN(kModeInteger, kStepOdd);

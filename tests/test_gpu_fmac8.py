@@ -239,6 +239,27 @@ def test_forms_of_the_step_by_stage(fmt, e, m, d, M, N):
     assert_bits(np.where(nan, 0, got).astype(np.float32), np.where(nan, 0, ref).astype(np.float32), "stages")
 
 
+@pytest.mark.parametrize("M,N,K", [(31, 33, 63), (32, 32, 64), (33, 65, 65), (1, 2, 9), (2000, 2010, 45), (2048, 1999, 33)])
+@pytest.mark.parametrize("d", [True, False])
+def test_binary16_tiles(fmt, d, M, N, K):
+    """1/5/10 at the edges of the 32 x 32 and 64 x 64 tiles and of their stages of 64 and 32 k, with accumulators that wander
+    through the denormals and that overflow.  Bit for bit on sampled rows and columns, all layouts."""
+    rng = np.random.default_rng(M + N + K)
+    A = workloads.log2_normal((M, K), -6.0, 4.0, 0.05, rng)
+    B = workloads.log2_normal((K, N), -6.0, 4.0, 0.05, rng)
+    A[M // 2] = workloads.log2_normal((K,), 8.0, 2.0, 0.0, rng)
+    rows = np.unique(np.concatenate([rng.integers(0, M, 24), [0, M // 2, M - 1]]))
+    cols = np.unique(np.concatenate([rng.integers(0, N, 24), [0, N - 1]]))
+    ref = oracle.gemm_fmac8(np.ascontiguousarray(A[rows]), np.ascontiguousarray(B[:, cols]), 5, 10, d)
+    for tA, tB in LAYOUTS:
+        C = fmt.fmt_gemm_fmac8(dev(A.T if tA else A), dev(B.T if tB else B), (5, 10, d), transA=tA, transB=tB)
+        torch.cuda.synchronize()
+        got = np.ascontiguousarray(C.cpu().numpy()[np.ix_(rows, cols)])
+        nan = np.isnan(ref)
+        assert np.array_equal(np.isnan(got), nan)
+        assert_bits(np.where(nan, 0, got).astype(np.float32), np.where(nan, 0, ref).astype(np.float32), "layout %s" % ((tA, tB),))
+
+
 @pytest.mark.parametrize("e,m,d", [(6, 9, True), (6, 9, False), (6, 11, True), (6, 3, True)])
 def test_sums_next_to_a_power_of_two(fmt, e, m, d):
     """A power of two plus a product far below it that fills the last places of the 53-bit sum, on either side: the sum lies next to
