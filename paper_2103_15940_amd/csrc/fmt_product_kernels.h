@@ -1,0 +1,570 @@
+// The product kernels (see fmt_gemm.hip for what they multiply) and their launches, instantiated per piece scheme.
+#pragma once
+
+#include "fmt_internal.h"
+#include "fmt_product.h"
+#include "fmt_quant.h"
+#include "fmt_split.h"
+
+namespace fmt {
+
+// Epilogue of one wave.  The MFMAs are fed operand B's fragment first and A's second, so a 32 x 32 accumulator
+// block holds the TRANSPOSE of the usual layout: register v of lane l holds row l % 32 and column
+// 8*(v/4) + 4*(l/32) + v%4 of the block of C -- four consecutive columns per group of four registers, which
+// leave in one 16-byte store per lane (64 store instructions per wave for a 256 x 256 tile instead of 256;
+// nothing is assumed about alignment beyond 4 bytes).
+// SCALED: out = acc * 2^-(S_row + S_col), exactly; the scale arrays are padded to the tile grid and 16-byte
+// aligned, and all of a lane's scales are fetched together ahead of its stores.
+// img > 0: column = (image, position), element (row, col) goes to out[image][row][position] (NCHW with `img`
+// positions); the four columns of a group go out together when they fall into one image.
+// A wave whose block of C lies inside the matrix (all but the last row and column of tiles) takes a path without
+// per-lane tests, in two phases: first every accumulator is scaled in place, then the stores go out straight
+// from the accumulator registers.  Measured on a 256 x 256 tile (one wave per SIMD): stores interleaved with
+// the arithmetic that refills their data registers take 20 - 25 us per tile when every compute unit stores at
+// once (a store holds its data registers until the memory pipeline has taken them), the two phases 8 us, of
+// which the stores are 5.
+template <int TM, int TN, bool SCALED>
+__device__ __forceinline__ void store_tile(floatx16 (&acc)[TM][TN], float *__restrict__ out, int64_t ld, int M, int N, int img,
+                                           int row_base, int col_base, int lane, const int *__restrict__ Sa,
+                                           const int *__restrict__ Sb)
+{
+    typedef int i32x4 __attribute__((ext_vector_type(4)));
+    typedef float f32x4u __attribute__((ext_vector_type(4), aligned(4)));
+    const int r_in = lane & 31, c_half = (lane >> 5) * 4;
+    int sa[TM];
+    i32x4 sb[TN][4];
+    if constexpr (SCALED) {
+#pragma unroll
+        for (int i = 0; i < TM; ++i) sa[i] = Sa[row_base + i * 32 + r_in];
+#pragma unroll
+        for (int j = 0; j < TN; ++j)
+#pragma unroll
+            for (int g = 0; g < 4; ++g) sb[j][g] = -*reinterpret_cast<const i32x4 *>(Sb + col_base + j * 32 + g * 8 + c_half);
+    }
+    // rows are `rs` elements apart in both output maps
+    const size_t rs = img > 0 ? (size_t)img : (size_t)ld;
+    float *rowp[TM];
+#pragma unroll
+    for (int i = 0; i < TM; ++i) rowp[i] = out + (size_t)(row_base + i * 32 + r_in) * rs;
+
+    if (row_base + 32 * TM <= M && col_base + 32 * TN <= N && (img & 3) == 0) {      // the same in the whole wave
+        if constexpr (SCALED) {
+#pragma unroll
+            for (int i = 0; i < TM; ++i)
+#pragma unroll
+                for (int j = 0; j < TN; ++j)
+#pragma unroll
+                    for (int v = 0; v < 16; ++v) acc[i][j][v] = ldexpf(acc[i][j][v], sb[j][v >> 2][v & 3] - sa[i]);
+            __builtin_amdgcn_sched_barrier(0);
+        }
+        // the four stores that complete the 128-byte lines of a block go out back to back
+#pragma unroll
+        for (int j = 0; j < TN; ++j) {
+            size_t coff[4];
+#pragma unroll
+            for (int g = 0; g < 4; ++g) {
+                const int col0 = col_base + j * 32 + g * 8 + c_half;
+                coff[g] = (size_t)col0;
+                if (img > 0) {                   // img is a multiple of 4 and so is col0: one image holds the four columns
+                    const int image = col0 / img;
+                    coff[g] = (size_t)image * M * img + (col0 - image * img);
+                }
+            }
+#pragma unroll
+            for (int i = 0; i < TM; ++i)
+#pragma unroll
+                for (int g = 0; g < 4; ++g) {
+                    f32x4u v;
+#pragma unroll
+                    for (int c = 0; c < 4; ++c) v[c] = acc[i][j][g * 4 + c];
+                    *reinterpret_cast<f32x4u *>(rowp[i] + coff[g]) = v;
+                }
+        }
+        return;
+    }
+    // the last row or column of tiles, and NCHW maps whose images are not a multiple of 4 positions long
+#pragma unroll
+    for (int j = 0; j < TN; ++j)
+#pragma unroll
+        for (int g = 0; g < 4; ++g) {
+            const int col0 = col_base + j * 32 + g * 8 + c_half;
+            if (col0 >= N) continue;
+            // offset of column col0 within a row of the output map; whether its four columns are adjacent there
+            size_t coff = (size_t)col0;
+            bool together = col0 + 3 < N;
+            if (img > 0) {
+                const int image = col0 / img, pos = col0 - image * img;
+                coff = (size_t)image * M * img + pos;
+                together = together && pos + 3 < img;
+            }
+#pragma unroll
+            for (int i = 0; i < TM; ++i) {
+                if (row_base + i * 32 + r_in >= M) continue;
+                f32x4u v;
+#pragma unroll
+                for (int c = 0; c < 4; ++c) {
+                    v[c] = acc[i][j][g * 4 + c];
+                    if constexpr (SCALED) v[c] = ldexpf(v[c], sb[j][g][c] - sa[i]);
+                }
+                if (together) {
+                    *reinterpret_cast<f32x4u *>(rowp[i] + coff) = v;
+                } else {
+#pragma unroll
+                    for (int c = 0; c < 4; ++c)
+                        if (col0 + c < N) {
+                            size_t off = coff + c;
+                            if (img > 0) {
+                                const int image = (col0 + c) / img;
+                                off = (size_t)image * M * img + (col0 + c - image * img);
+                            }
+                            rowp[i][off] = v[c];
+                        }
+                }
+            }
+        }
+}
+
+// product: Aw / Bw are prepared operands (rows padded to a multiple of kRowPad, k to a multiple
+// of 32).  A workgroup is 2 x 2 waves; each wave owns TM x TN MFMA tiles of 32 x 32, so the
+// workgroup tile is (64*TM) x (64*TN).  Operand stages of KS*16 k go from global memory straight
+// into LDS (global_load_lds, 16 bytes per lane) through a ring of NST stage buffers, one barrier
+// per stage.  With SPLIT the k range is cut into parts and each part writes its own M x N slab
+// of partial sums (summed by reduce_kernel).
+// SCALED (single fp16 piece only): the operands are exponent planes with per-row power-of-two scales
+// (pa.S / pb.S), undone on the way out; this kernel multiplies plane 0 by plane 0, planes_tail_kernel
+// adds the products of the elements that live in the other planes.
+// GATHER: operand B is not a prepared operand but a rounded convolution tensor in pixel-major order (`im`,
+// Bw unused): a lane's 16-byte load of (position, 8 consecutive k) is 8 consecutive channels of one pixel,
+// whose address is a per-lane base (the position's corner pixel) plus a per-stage term (the tap and the
+// channel block), or the zero vector where the tap falls outside the tensor (a per-lane bit mask over
+// the taps).  The stage image in LDS and everything after it are the same.
+// The body is shared by the kernel of one product (bid = blockIdx.x) and the kernel of a group of products
+// (bid = the workgroup's index within its product).
+// LINEAR: the results are a fully connected layer's accumulators; they leave as R(R(acc) + R(b)) (lin).
+template <int PS, int TM, int TN, int KS, int NST, bool SPLIT, bool SCHED, bool SCALED, bool GATHER = false, bool LINEAR = false>
+__device__ __forceinline__ void product_body(const u32x4 *__restrict__ Aw, const u32x4 *__restrict__ Bw,
+                                             float *__restrict__ C, int M, int N, int64_t ldc, int img,
+                                             int kblocks, int tiles_m, int tiles_n, int kb_per_split,
+                                             const Planes &pa, const Planes &pb, const Implicit &im, const unsigned bid,
+                                             const LinearOut &lin = LinearOut{})
+{
+    constexpr int P = pieces_of(PS);
+    constexpr int UA = 2 * TM, UB = 2 * TN;              // 32-row units per operand in the workgroup tile
+    constexpr int kHalf = 64;                            // vectors of one piece of one unit per 16 k
+    constexpr int SV = kHalf * KS;                       // ... per stage
+    constexpr int VA = UA * P * SV, VB = UB * P * SV;    // 16-byte vectors per operand per stage
+    constexpr int LA = (VA + 255) / 256, LB = (VB + 255) / 256;   // loads per lane per stage
+    constexpr int kWaitLanded = ((NST - 2) * (LA + LB));  // stage loads that may still be in flight
+    static_assert(kWaitLanded < 64 && (KS == 1 || KS == 2) && NST >= 2 && NST <= 4, "unsupported pipeline shape");
+    static_assert(NST == 2 || (VA % 256 == 0 && VB % 256 == 0), "the wait for a stage counts the same loads in every wave");
+    // One LDS array per stage buffer, each addressed with a compile-time index: the compiler then knows
+    // which loads-to-LDS an LDS read can depend on and leaves the younger stages in flight.
+    constexpr int STV = VA + VB;
+    __shared__ u32x4 st0[STV];
+    __shared__ u32x4 st1[STV];
+    __shared__ u32x4 st2[NST > 2 ? STV : 1];
+    __shared__ u32x4 st3[NST > 3 ? STV : 1];
+    auto stage = [&](int b) -> u32x4 * { return b == 0 ? st0 : b == 1 ? st1 : b == 2 ? st2 : st3; };
+    typedef __attribute__((address_space(3))) void lds_void;
+    typedef const __attribute__((address_space(1))) void glb_void;
+
+    const int tid = threadIdx.x;
+    const int lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int wm = wave >> 1, wn = wave & 1;
+
+    // Workgroup -> (tile, k part).  Consecutive workgroup ids go to different XCDs (8 of them,
+    // each with its own L2), so ids are remapped to give every XCD a contiguous run of tiles.
+    const int ntiles = tiles_m * tiles_n;
+    const int per_xcd = (ntiles + 7) / 8;
+    const int wg = (int)(bid % (unsigned)(per_xcd * 8));
+    const int split = (int)(bid / (unsigned)(per_xcd * 8));
+    const int tile = (wg % 8) * per_xcd + wg / 8;
+    if (tile >= ntiles) return;
+    // Within the run, tiles are walked in groups of kGroup tile rows, column by column, so that
+    // the 32 tiles an XCD works on at a time cover few distinct operand panels.
+    constexpr int kGroup = 16 / TM;                      // 1024 rows of op(A) per group
+    const int per_group = kGroup * tiles_n;
+    const int group = tile / per_group, in_group = tile % per_group;
+    const int rows_here = min(kGroup, tiles_m - group * kGroup);
+    const int tm = group * kGroup + in_group % rows_here, tn = in_group / rows_here;
+    const int kb0 = SPLIT ? split * kb_per_split : 0;
+    const int kb1 = SPLIT ? min(kblocks, kb0 + kb_per_split) : kblocks;
+    const int steps = (kb1 - kb0) * (2 / KS);            // stages to consume
+
+    // Stage image per operand = [unit row-block][piece][SV vectors]; in the workspace a unit's
+    // piece is 128 vectors (two 16-k halves) and row-blocks are kblocks*P*128 vectors apart.
+    const size_t rb_stride = (size_t)kblocks * P * kUnitVec;
+    const u32x4 *ga[LA], *gb[LB];
+#pragma unroll
+    for (int j = 0; j < LA; ++j) {
+        const int q = min(j * 256 + tid, VA - 1);
+        const int rbl = q / (P * SV), piece = (q % (P * SV)) / SV, v = q % SV;
+        ga[j] = Aw + ((size_t)tm * UA + rbl) * rb_stride + (size_t)kb0 * P * kUnitVec + piece * kUnitVec + v;
+    }
+    int gbase[GATHER ? LB : 1];          // GATHER: vector index of the position's corner pixel (+ piece, + k chunk)
+    uint32_t gmask[GATHER ? LB : 1];     // ... and the taps that fall inside the tensor
+#pragma unroll
+    for (int j = 0; j < LB; ++j) {
+        const int q = min(j * 256 + tid, VB - 1);
+        const int rbl = q / (P * SV), piece = (q % (P * SV)) / SV, v = q % SV;
+        if constexpr (GATHER) {
+            const int row = (tn * UB + rbl) * kUnitRows + v % kUnitRows;
+            int x, t, y, n;
+            divmod(im.r0, min(row, im.rows - 1), t, x);
+            divmod(im.r1, t, n, y);
+            const int by = y * im.mul_y + im.off_y, bx = x * im.mul_x + im.off_x;
+            uint32_t mq = 0u;
+            int tap = 0;
+            for (int r = 0; r < im.R; ++r)
+                for (int s2 = 0; s2 < im.S; ++s2, ++tap) {
+                    const int iy = by + im.tap_sign * r, ix = bx + im.tap_sign * s2;
+                    if ((unsigned)iy < (unsigned)im.th && (unsigned)ix < (unsigned)im.tw) mq |= 1u << tap;
+                }
+            gmask[j] = row < im.rows ? mq : 0u;
+            gbase[j] = piece * im.piece_vec + ((n * im.th + by) * im.tw + bx) * im.c8 + v / kUnitRows;
+            gb[j] = im.T;
+        } else {
+            gb[j] = Bw + ((size_t)tn * UB + rbl) * rb_stride + (size_t)kb0 * P * kUnitVec + piece * kUnitVec + v;
+        }
+    }
+
+    // a layer's bias, loaded ahead of the products: register v of a lane holds column 8*(v/4) + 4*(l/32) + v%4 (see store_tile)
+    uint32_t bias[LINEAR ? TN : 1][LINEAR ? 16 : 1];
+    if constexpr (LINEAR) {
+#pragma unroll
+        for (int j = 0; j < TN; ++j)
+#pragma unroll
+            for (int v = 0; v < 16; ++v)
+                bias[j][v] = linear_bias(lin, (tn * 2 + wn) * (32 * TN) + j * 32 + (v >> 2) * 8 + (lane >> 5) * 4 + (v & 3), N);
+    }
+
+    floatx16 acc[TM][TN];
+#pragma unroll
+    for (int i = 0; i < TM; ++i)
+#pragma unroll
+        for (int j = 0; j < TN; ++j)
+#pragma unroll
+            for (int v = 0; v < 16; ++v) acc[i][j][v] = 0.0f;
+
+    // Loads of stage t (clamped to the last one, so that the number of loads in flight is the
+    // same in every trip; a clamped load lands in a buffer nobody reads any more).
+    auto issue = [&](int t, int buf) {
+        const int tc = min(t, steps - 1);
+        u32x4 *sa = stage(buf), *sb = sa + VA;
+        const size_t off = KS == 2 ? (size_t)tc * P * kUnitVec : (size_t)(tc >> 1) * P * kUnitVec + (tc & 1) * kHalf;
+#pragma unroll
+        for (int j = 0; j < LA; ++j)
+            if (VA % 256 == 0 || j * 256 + wave * 64 < VA)
+                __builtin_amdgcn_global_load_lds((glb_void *)(ga[j] + off), (lds_void *)(sa + j * 256 + wave * 64), 16, 0, 0);
+        if constexpr (GATHER) {
+            // stage number (in stages of 16*KS k) -> tap and channel block: the same in the whole workgroup
+            int tap, cb, r, s2;
+            divmod(im.kc, kb0 * (2 / KS) + tc, tap, cb);
+            divmod(im.ks, tap, r, s2);
+            const int toff = im.tap_sign * (r * im.tw + s2) * im.c8 + cb * (2 * KS);
+#pragma unroll
+            for (int j = 0; j < LB; ++j)
+                if (VB % 256 == 0 || j * 256 + wave * 64 < VB) {
+                    const int at = ((gmask[j] >> tap) & 1u) ? gbase[j] + toff : im.zero;
+                    __builtin_amdgcn_global_load_lds((glb_void *)(im.T + at), (lds_void *)(sb + j * 256 + wave * 64), 16, 0, 0);
+                }
+        } else {
+#pragma unroll
+            for (int j = 0; j < LB; ++j)
+                if (VB % 256 == 0 || j * 256 + wave * 64 < VB)
+                    __builtin_amdgcn_global_load_lds((glb_void *)(gb[j] + off), (lds_void *)(sb + j * 256 + wave * 64), 16, 0, 0);
+        }
+    };
+
+    // Operand fragments live in two register sets: while the MFMAs of stage t run on one, the LDS
+    // reads of stage t + 1 fill the other, so that no MFMA waits for LDS latency (a workgroup tile
+    // of 128 x 128 has one wave per SIMD and nothing else to run meanwhile).
+    bf16x8 fa[2][KS][TM][P], fb[2][KS][TN][P];
+    auto read_frags = [&](int buf, int set) __attribute__((always_inline)) {
+        const u32x4 *sa = stage(buf), *sb = sa + VA;
+#pragma unroll
+        for (int kk = 0; kk < KS; ++kk) {
+#pragma unroll
+            for (int i = 0; i < TM; ++i)
+#pragma unroll
+                for (int q = 0; q < P; ++q)
+                    fa[set][kk][i][q] = __builtin_bit_cast(bf16x8, sa[((wm * TM + i) * P + q) * SV + kk * kHalf + lane]);
+#pragma unroll
+            for (int j = 0; j < TN; ++j)
+#pragma unroll
+                for (int q = 0; q < P; ++q)
+                    fb[set][kk][j][q] = __builtin_bit_cast(bf16x8, sb[((wn * TN + j) * P + q) * SV + kk * kHalf + lane]);
+        }
+    };
+    // The barrier is the bare instruction behind the waits it needs (this wave's LDS reads retired,
+    // its stage landed): __syncthreads() would also wait for every load-to-LDS still in flight.
+    auto barrier = [&]() __attribute__((always_inline)) { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); };
+
+    if (steps > 0) {
+#pragma unroll
+        for (int t = 0; t < NST; ++t) issue(t, t);
+        constexpr int kWaitFirst = (NST - 1) * (LA + LB);
+        __builtin_amdgcn_s_waitcnt(0x0F70 | (kWaitFirst & 0xF) | ((kWaitFirst >> 4) << 14));
+        barrier();
+        read_frags(0, 0);
+    }
+    // Trip t: stage t is in register set `cur`; stage t + 1 (buffer b + 1) is read into the other set
+    // and stage t + NST is loaded into buffer b, which every wave has finished reading once it is past
+    // the barrier.  The trips are unrolled over the ring and the two register sets, so that buffer and
+    // set are compile-time constants, and the loop over whole turns has a single exit (with early
+    // exits the compiler falls back to waiting for all loads at the loop head); the remaining trips
+    // follow it.
+    auto trip = [&](int t, int b, int cur) __attribute__((always_inline)) {
+        // stage t + 1 has landed once at most the loads of the NST-2 younger stages are in flight
+        __builtin_amdgcn_sched_barrier(0);       // MFMAs are not memory operations: without this they drift across the barrier
+        __builtin_amdgcn_s_waitcnt(0x0F70 | (kWaitLanded & 0xF) | ((kWaitLanded >> 4) << 14));
+        barrier();                               // ... for every wave; and every wave holds stage t in registers
+        read_frags((b + 1) % NST, cur ^ 1);
+        issue(t + NST, b);
+#pragma unroll
+        for (int kk = 0; kk < KS; ++kk) {
+#pragma unroll
+            for (int i = 0; i < TM; ++i)
+#pragma unroll
+                for (int j = 0; j < TN; ++j)
+#pragma unroll
+                    for (int qa = 0; qa < P; ++qa)
+#pragma unroll
+                        for (int qb = 0; qb < P; ++qb)
+                            // B's fragment first: the block comes out transposed (see store_tile)
+                            acc[i][j] = PS == 0 ? __builtin_amdgcn_mfma_f32_32x32x16_f16(__builtin_bit_cast(f16x8, fb[cur][kk][j][qb]),
+                                                                                         __builtin_bit_cast(f16x8, fa[cur][kk][i][qa]),
+                                                                                         acc[i][j], 0, 0, 0)
+                                                : __builtin_amdgcn_mfma_f32_32x32x16_bf16(fb[cur][kk][j][qb], fa[cur][kk][i][qa], acc[i][j], 0, 0, 0);
+        }
+        // Issue order inside one trip: the next stage's LDS reads, then its global loads, threaded
+        // between the MFMAs so that they issue in the MFMAs' shadow.
+        if constexpr (SCHED) {
+            constexpr int kMfma = TM * TN * P * P * KS, kReads = (TM + TN) * P * KS, kLoads = LA + LB;
+            constexpr int kDsEach = (kReads + kMfma - 1) / kMfma;            // LDS reads behind each of the first MFMAs
+            constexpr int kPairs = (kReads + kDsEach - 1) / kDsEach;
+#pragma unroll
+            for (int r = 0; r < kPairs; ++r) {
+                __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+                __builtin_amdgcn_sched_group_barrier(0x100, kDsEach, 0);
+            }
+            constexpr int kLeft = kMfma - kPairs;                            // MFMAs left for the global loads
+            if constexpr (kLeft > kLoads) {
+                constexpr int kPer = kLeft / (kLoads + 1);
+#pragma unroll
+                for (int r = 0; r < kLoads; ++r) {
+                    __builtin_amdgcn_sched_group_barrier(0x008, kPer, 0);
+                    __builtin_amdgcn_sched_group_barrier(0x020, 1, 0);
+                }
+            } else if constexpr (kLeft > 0) {
+                constexpr int kEach = (kLoads + kLeft - 1) / kLeft;
+#pragma unroll
+                for (int r = 0; r < kLeft; ++r) {
+                    __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+                    __builtin_amdgcn_sched_group_barrier(0x020, kEach, 0);
+                }
+            } else {
+                __builtin_amdgcn_sched_group_barrier(0x020, kLoads, 0);
+            }
+        }
+    };
+    constexpr int kTurn = NST % 2 == 0 ? NST : 2 * NST;      // trips after which buffer and register set repeat
+    int t0 = 0;
+    for (; t0 + kTurn <= steps; t0 += kTurn) {
+#pragma unroll
+        for (int u = 0; u < kTurn; ++u) trip(t0 + u, u % NST, u & 1);
+    }
+#pragma unroll
+    for (int u = 0; u < kTurn - 1; ++u)
+        if (t0 + u < steps) trip(t0 + u, u % NST, u & 1);
+    // every load-to-LDS of this wave must have landed before the workgroup's LDS is handed back
+    __builtin_amdgcn_s_waitcnt(0x0F70);
+
+    if constexpr (LINEAR)
+        linear_round<TM * TN * 16>(lin, [&](int i) { return acc[i / (TN * 16)][i / 16 % TN][i % 16]; },
+                                   [&](int i, float y) { acc[i / (TN * 16)][i / 16 % TN][i % 16] = y; },
+                                   [&](int i) { return bias[i / 16 % TN][i % 16]; });
+    // plain: C[row][col] with leading dimension ldc; a part of a split k: its own M x N slab; img > 0: NCHW
+    float *out = SPLIT ? C + (size_t)split * M * ldc : C;
+    store_tile<TM, TN, SCALED>(acc, out, ldc, M, N, SPLIT ? 0 : img, (tm * 2 + wm) * (32 * TM), (tn * 2 + wn) * (32 * TN), lane, pa.S,
+                               pb.S);
+}
+
+template <int PS, int TM, int TN, int KS, int NST, bool SPLIT, bool SCHED, bool SCALED, bool GATHER = false>
+__global__ __launch_bounds__(256) void product_kernel(const u32x4 *__restrict__ Aw, const u32x4 *__restrict__ Bw,
+                                                      float *__restrict__ C, int M, int N, int64_t ldc, int img,
+                                                      int kblocks, int tiles_m, int tiles_n, int kb_per_split,
+                                                      Planes pa, Planes pb, Implicit im)
+{
+    product_body<PS, TM, TN, KS, NST, SPLIT, SCHED, SCALED, GATHER>(Aw, Bw, C, M, N, ldc, img, kblocks, tiles_m, tiles_n,
+                                                                  kb_per_split, pa, pb, im, blockIdx.x);
+}
+
+template <int PS, int TM, int TN, int KS, int NST>
+__global__ __launch_bounds__(256) void product_linear_kernel(const u32x4 *__restrict__ Aw, const u32x4 *__restrict__ Bw,
+                                                             float *__restrict__ C, int M, int N, int64_t ldc, int kblocks,
+                                                             int tiles_m, int tiles_n, LinearOut lin)
+{
+    const Planes none{nullptr, nullptr, 0, 0, nullptr, nullptr};
+    product_body<PS, TM, TN, KS, NST, false, true, false, false, true>(Aw, Bw, C, M, N, ldc, 0, kblocks, tiles_m, tiles_n, kblocks, none,
+                                                                     none, Implicit{}, blockIdx.x, lin);
+}
+
+template <int PS, int TM, int TN, int KS, int NST, bool SCHED, bool SCALED>
+__global__ __launch_bounds__(256) void product_group_kernel(Group grp)
+{
+    const GroupItem &it = grp.p[group_member(grp.first, blockIdx.x)];      // the same in the whole workgroup
+    product_body<PS, TM, TN, KS, NST, true, SCHED, SCALED, false>(it.Aw, it.Bw, it.C, it.M, it.N, it.ldc, 0, it.kblocks, it.tiles_m,
+                                                                it.tiles_n, it.kb_per_part, it.pa, it.pb, Implicit{},
+                                                                blockIdx.x - it.first);
+}
+
+template <int PS, int TM, int TN, bool SPLIT, bool SCHED, bool SCALED, bool GATHER = false>
+static int launch_product_v2(const u32x4 *Aw, const u32x4 *Bw, float *out, int M, int N, int64_t ld, int img, int kblocks,
+                            int nsplit, hipStream_t stream, const Planes &pa, const Planes &pb, const Implicit &im = Implicit{})
+{
+    constexpr int KS = Pipe<PS, TM, TN>::ks, NST = Pipe<PS, TM, TN>::nst;
+    if constexpr (lds_bytes(TM, TN, pieces_of(PS), KS, NST) > 160 * 1024) {
+        return FMT_ERR_SHAPE;                            // never planned (make_plan skips such tiles)
+    } else {
+        const int tiles_m = (M + 64 * TM - 1) / (64 * TM), tiles_n = (N + 64 * TN - 1) / (64 * TN);
+        const int64_t per_xcd = ((int64_t)tiles_m * tiles_n + 7) / 8;
+        if (per_xcd * 8 * nsplit >= ((int64_t)1 << 31)) return FMT_ERR_SHAPE;
+        const int kb_per = (kblocks + nsplit - 1) / nsplit;
+        auto kern = product_kernel<PS, TM, TN, KS, NST, SPLIT, SCHED, SCALED, GATHER>;
+        Implicit imk = im;
+        if (GATHER) imk.kc = make_fastdiv(im.c8 * 8 / (16 * KS));   // stages of 16*KS k per tap
+        hipLaunchKernelGGL(kern, dim3((unsigned)(per_xcd * 8 * nsplit)), dim3(256), 0, stream, Aw, Bw, out, M, N, ld, img,
+                           kblocks, tiles_m, tiles_n, kb_per, pa, pb, imk);
+        FMT_HIP_CHECK(hipGetLastError());
+        return FMT_OK;
+    }
+}
+
+template <int PS, int TM, int TN, bool SPLIT, bool SCHED>
+static int launch_product_v(const u32x4 *Aw, const u32x4 *Bw, float *out, int M, int N, int64_t ld, int img, int kblocks,
+                            int nsplit, hipStream_t stream, const Planes &pa, const Planes &pb)
+{
+    if constexpr (PS == 0) {
+        if (pa.S != nullptr)
+            return launch_product_v2<PS, TM, TN, SPLIT, SCHED, true>(Aw, Bw, out, M, N, ld, img, kblocks, nsplit, stream, pa, pb);
+    }
+    return launch_product_v2<PS, TM, TN, SPLIT, SCHED, false>(Aw, Bw, out, M, N, ld, img, kblocks, nsplit, stream, pa, pb);
+}
+
+template <int PS, int TM, int TN>
+static int launch_product(const u32x4 *Aw, const u32x4 *Bw, float *C, int M, int N, int64_t ldc, int img, int kblocks,
+                          const Plan &plan, float *part, hipStream_t stream, const Planes &pa, const Planes &pb,
+                          const Implicit *im = nullptr)
+{
+    if (im != nullptr) {
+        // operand B gathered inside the product kernel (convolutions); no planes, pinned issue order only
+        if (plan.nsplit == 1)
+            return launch_product_v2<PS, TM, TN, false, true, false, true>(Aw, nullptr, C, M, N, ldc, img, kblocks, 1, stream, pa,
+                                                                          pb, *im);
+        int rcg = launch_product_v2<PS, TM, TN, true, true, false, true>(Aw, nullptr, part, M, N, (int64_t)N, 0, kblocks,
+                                                                        plan.nsplit, stream, pa, pb, *im);
+        if (rcg != FMT_OK) return rcg;
+        return launch_reduce(part, plan.nsplit, C, M, N, ldc, img, stream);
+    }
+    // the elements outside plane 0 of exponent-plane operands follow the product (plain row-major results only)
+    auto tail = [&]() -> int {
+        if (PS != 0 || pa.S == nullptr) return FMT_OK;
+        if (img != 0) return FMT_ERR_SHAPE;
+        return launch_planes_tail(Aw, Bw, pa, pb, C, ldc, M, N, kblocks, stream);
+    };
+    if (plan.nsplit == 1) {
+        int rc1 = plan.sched ? launch_product_v<PS, TM, TN, false, true>(Aw, Bw, C, M, N, ldc, img, kblocks, 1, stream, pa, pb)
+                             : launch_product_v<PS, TM, TN, false, false>(Aw, Bw, C, M, N, ldc, img, kblocks, 1, stream, pa, pb);
+        return rc1 != FMT_OK ? rc1 : tail();
+    }
+    int rc = plan.sched
+                 ? launch_product_v<PS, TM, TN, true, true>(Aw, Bw, part, M, N, (int64_t)N, 0, kblocks, plan.nsplit, stream, pa, pb)
+                 : launch_product_v<PS, TM, TN, true, false>(Aw, Bw, part, M, N, (int64_t)N, 0, kblocks, plan.nsplit, stream, pa, pb);
+    if (rc != FMT_OK) return rc;
+    rc = launch_reduce(part, plan.nsplit, C, M, N, ldc, img, stream);
+    return rc != FMT_OK ? rc : tail();
+}
+
+template <int PS, int T>
+static int launch_product_linear(const u32x4 *Aw, const u32x4 *Bw, const OutSpec &out, int M, int N, int kblocks, hipStream_t stream)
+{
+    constexpr int KS = Pipe<PS, T, T>::ks, NST = Pipe<PS, T, T>::nst;
+    const int tiles_m = (M + 64 * T - 1) / (64 * T), tiles_n = (N + 64 * T - 1) / (64 * T);
+    const int64_t per_xcd = ((int64_t)tiles_m * tiles_n + 7) / 8;
+    if (per_xcd * 8 >= ((int64_t)1 << 31)) return FMT_ERR_SHAPE;
+    hipLaunchKernelGGL((product_linear_kernel<PS, T, T, KS, NST>), dim3((unsigned)(per_xcd * 8)), dim3(256), 0, stream, Aw, Bw, out.C, M, N,
+                       out.ldc, kblocks, tiles_m, tiles_n, *out.lin);
+    FMT_HIP_CHECK(hipGetLastError());
+    return FMT_OK;
+}
+
+template <int PS>
+int product_of_views(const OperandView &va, const OperandView &vb, int M, int N, int kblocks, const OutSpec &out,
+                            const Plan &plan, float *part, hipStream_t stream)
+{
+    // A layer's output roundings in the product kernel: where the product leaves whole sums in one launch, and for the tiles of up
+    // to 128 x 128 (two workgroups and more per compute unit, so that the roundings of one run beside the products of
+    // another; a 256 x 256 tile has neither the registers nor the company).  Measured, fmt_linear_prepared in 1/8/7, product and pass
+    // against one kernel: 64 x 128 x 128 8.7 -> 5.4 us, 333 x 4096 x 1024 14.2 -> 9.8, 2048 x 2048 x 512 24.4 -> 18.9,
+    // 4096 x 1024 x 1024 25.1 -> 22.5, 4096 x 3072 x 1024 51.8 -> 51.5.
+    if (out.lin != nullptr && va.pl.S == nullptr && out.img == 0 && plan.nsplit == 1 && plan.tm == plan.tn && plan.tm <= 2) {
+        const int rc = plan.tm == 2 ? launch_product_linear<PS, 2>(va.W, vb.W, out, M, N, kblocks, stream)
+                                    : launch_product_linear<PS, 1>(va.W, vb.W, out, M, N, kblocks, stream);
+        if (rc == FMT_OK) *out.rounded = true;
+        return rc;
+    }
+#define FMT_PRODUCT(TMV, TNV) \
+    launch_product<PS, TMV, TNV>(va.W, vb.W, out.C, M, N, out.ldc, out.img, kblocks, plan, part, stream, va.pl, vb.pl)
+    if (plan.tm == 4 && plan.tn == 4) return FMT_PRODUCT(4, 4);
+    if (plan.tm == 4 && plan.tn == 2) return FMT_PRODUCT(4, 2);
+    if (plan.tm == 2 && plan.tn == 4) return FMT_PRODUCT(2, 4);
+    if (plan.tm == 2 && plan.tn == 2) return FMT_PRODUCT(2, 2);
+    return FMT_PRODUCT(1, 1);
+#undef FMT_PRODUCT
+}
+
+// Convolutions: operand B gathered by the product kernel.
+template <int PS>
+int product_gathered(const OperandView &va, const Implicit &im, int M, int N, int kblocks, const OutSpec &out, const Plan &plan,
+                     float *part, hipStream_t stream)
+{
+    const Planes none{nullptr, nullptr, 0, 0, nullptr, nullptr};
+#define FMT_PRODUCT(TMV, TNV) \
+    launch_product<PS, TMV, TNV>(va.W, nullptr, out.C, M, N, out.ldc, out.img, kblocks, plan, part, stream, none, none, &im)
+    if (plan.tm == 4 && plan.tn == 4) return FMT_PRODUCT(4, 4);
+    if (plan.tm == 4 && plan.tn == 2) return FMT_PRODUCT(4, 2);
+    if (plan.tm == 2 && plan.tn == 4) return FMT_PRODUCT(2, 4);
+    if (plan.tm == 2 && plan.tn == 2) return FMT_PRODUCT(2, 2);
+    return FMT_PRODUCT(1, 1);
+#undef FMT_PRODUCT
+}
+
+template <int PS, bool SCALED, int T>
+static int launch_group_t(const Group &grp, unsigned grid, hipStream_t stream)
+{
+    constexpr int KS = Pipe<PS, T, T>::ks, NST = Pipe<PS, T, T>::nst;
+    if constexpr (lds_bytes(T, T, pieces_of(PS), KS, NST) > 160 * 1024) {
+        return FMT_ERR_SHAPE;                            // never chosen (group_tile checks the same bound)
+    } else {
+        hipLaunchKernelGGL((product_group_kernel<PS, T, T, KS, NST, true, SCALED>), dim3(grid), dim3(256), 0, stream, grp);
+        FMT_HIP_CHECK(hipGetLastError());
+        return FMT_OK;
+    }
+}
+
+template <int PS, bool SCALED>
+int launch_group(const Group &grp, unsigned grid, int t, hipStream_t stream)
+{
+    return t == 4 ? launch_group_t<PS, SCALED, 4>(grp, grid, stream) : launch_group_t<PS, SCALED, 2>(grp, grid, stream);
+}
+
+#define FMT_PRODUCT_INSTANCES(PS)                                                                                            \
+    template int product_of_views<PS>(const OperandView &, const OperandView &, int, int, int, const OutSpec &, const Plan &, \
+                                      float *, hipStream_t);                                                                  \
+    template int product_gathered<PS>(const OperandView &, const Implicit &, int, int, int, const OutSpec &, const Plan &,    \
+                                      float *, hipStream_t);                                                                  \
+    template int launch_group<PS, false>(const Group &, unsigned, int, hipStream_t);
+
+}  // namespace fmt
