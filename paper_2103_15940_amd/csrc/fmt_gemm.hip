@@ -580,23 +580,45 @@ __device__ __forceinline__ uint32_t split_planes(const OP &o, int row, int k0, c
                                                  u32x4 &pb)
 {
     const int S = o.pl.S[row];                   // S covers the padded rows
+    const float f = __uint_as_float((uint32_t)(127 + S) << 23);     // 2^S: -16 <= S <= 15
+    pa = pb = u32x4{0u, 0u, 0u, 0u};
+    uint32_t mine = 0u;
+    // All eight lie in plane 0 if their magnitudes, scaled (exactly), are below 2^16 and the smallest that is not zero has its last
+    // bit at or above binary16's, 2^-24: is at least 2^-15 or, where the plane reaches down to the format's denormals (S >= 6 + m), whatever
+    // it is.  Then the conversion is exact: 2 vector instructions per element (3.5 for the higher planes), where a conversion there
+    // and back and two comparisons per element take 8.
+    float sc[8], top = 0.0f;
+#pragma unroll
+    for (int j = 0; j < 8; ++j) sc[j] = __uint_as_float(r[j]) * f;
+#pragma unroll
+    for (int j = 0; j < 8; j += 2) asm("v_maximum3_f32 %0, |%1|, |%2|, %0" : "+v"(top) : "v"(sc[j]), "v"(sc[j + 1]));
+    bool inside = top < 65536.0f;
+    const bool bottom = S >= 46 - o.pl.w;
+    if (__ballot(!bottom) != 0ull) {             // the same in the whole wave
+        uint32_t least = 0xFFFFFFFFu;            // twice a pattern less one: zeros come last
+#pragma unroll
+        for (int j = 0; j < 8; ++j) least = min(least, (__float_as_uint(sc[j]) << 1) - 1u);
+        inside = inside && (bottom || least >= 2u * 0x38000000u - 1u);
+    }
+    if (inside) {
+#pragma unroll
+        for (int i = 0; i < 4; ++i) p0[i] = __builtin_bit_cast(uint32_t, __builtin_amdgcn_cvt_pkrtz(sc[2 * i], sc[2 * i + 1]));
+        return mine;
+    }
     uint32_t hb[8];
     bool other[8], any = false;
 #pragma unroll
     for (int j = 0; j < 8; ++j) {
-        // r * 2^S (exact: |S| is small) converts to binary16 and back unchanged <=> it is a binary16
+        // r * 2^S converts to binary16 and back unchanged <=> it is a binary16
         // value -- zeros, the normal and the denormal range, infinities.  NaN (neither below nor above its
         // own conversion) stays in plane 0 as well.
-        const float sc = ldexpf(__uint_as_float(r[j]), S);
-        const _Float16 h = static_cast<_Float16>(sc);               // round to nearest even
+        const _Float16 h = static_cast<_Float16>(sc[j]);            // round to nearest even
         const float back = static_cast<float>(h);
-        other[j] = back < sc || back > sc;
+        other[j] = back < sc[j] || back > sc[j];
         any |= other[j];
         hb[j] = (uint32_t)__builtin_bit_cast(uint16_t, h);
     }
-    pa = pb = u32x4{0u, 0u, 0u, 0u};
-    uint32_t mine = 0u;
-    if (any) {                                   // rare: the common case does not pay for it element by element
+    if (any) {  
         const int w = o.pl.w;
 #pragma unroll
         for (int j = 0; j < 8; ++j) {
@@ -687,8 +709,7 @@ __device__ __forceinline__ void prepare_scaled_block(const OP &o, int K, int kbl
     }
     uint32_t r[8];
     u32x4 p0, pa, pb;
-#pragma unroll
-    for (int j = 0; j < 8; ++j) r[j] = quantize_bits<MODE, FTZ>(v[j], p);
+    quantize_run<MODE, FTZ>(v, run_is_rare(v, p), p, round_masks(p), r);
     const uint32_t mine = split_planes(o, row, k0, r, p0, pa, pb);
     __syncthreads();                             // s_planes has been cleared
     if (mine != 0u) atomicOr(&s_planes[u], mine);
@@ -700,9 +721,9 @@ __device__ __forceinline__ void prepare_scaled_block(const OP &o, int K, int kbl
 
 // Both orientations of one tile of a plain matrix X -- 32 rows (32 ty ..) by 64 columns (64 tx ..) -- as scaled
 // exponent planes: o0 is X as stored (its rows are X's, k runs along X's columns), o1 is X transposed.  The
-// tile is one workgroup's share of either operand in prepare_scaled_block, and the threads keep that function's
-// element mappings: the tile is read and rounded once in o0's mapping (a row's eight consecutive columns per
-// thread), the rounded patterns cross over to o1's mapping (a column's eight consecutive rows) through LDS.
+// tile is one workgroup's share of either operand in prepare_scaled_block; it is read and rounded once, and the
+// rounded patterns cross over to that function's mappings (a row's eight consecutive columns per
+// thread, a column's eight consecutive rows) through LDS.
 // A workgroup takes kPairTiles tiles side by side (columns 64 tx0 ..): all their loads are issued before the first
 // is worked on (measured: two tiles 2 - 4 % faster than one, four slower than two).
 constexpr int kPairTiles = 2;
@@ -720,53 +741,72 @@ __device__ __forceinline__ void prepare_pair_tile(const OP &o0, const OP &o1, co
     __shared__ uint32_t s_planes[4 * kPairTiles];       // per tile: o0's two units (halves of k), then o1's two (halves of its rows)
     const int tid = threadIdx.x;
     if (tid < 4 * kPairTiles) s_planes[tid] = 0u;
+    const RoundMasks masks = round_masks(p);
     const int R = o0.rows, C = o1.rows;                 // X is R x C
-    const int xr = ty * 32 + tid / 8;
+    // X is read, and Y written, 16 bytes per lane and side by side: four columns of two rows per thread.  With a row's eight
+    // consecutive columns per thread, as o0 wants them, every instruction covers half lines (12 tensors of 4 M to 16 M elements, ROUND:
+    // 572 -> 545 us with the products).  512 instead of 256 bytes of a row per instruction: 160 -> 167 us for the launch.
+    const int rr = ty * 32 + tid / 16, cc = (tid % 16) * 4;
     uint32_t v[kPairTiles][8];
 #pragma unroll
     for (int n = 0; n < kPairTiles; ++n) {
-        const int xc = (tx0 + n) * 64 + (tid % 8) * 8;
-        if (o0.vec4 && xr < R && xc + 8 <= C) {
-            const u32x4 *src = reinterpret_cast<const u32x4 *>(o0.X + (size_t)xr * o0.ld + xc);
-            const u32x4 lo = __builtin_nontemporal_load(src), hi = __builtin_nontemporal_load(src + 1);
+        const int xc = (tx0 + n) * 64 + cc;
 #pragma unroll
-            for (int j = 0; j < 4; ++j) {
-                v[n][j] = lo[j];
-                v[n][4 + j] = hi[j];
+        for (int h = 0; h < 2; ++h) {
+            const int row = rr + 16 * h;
+            if (o0.vec4 && row < R && xc + 4 <= C) {
+                const u32x4 w4 = __builtin_nontemporal_load(reinterpret_cast<const u32x4 *>(o0.X + (size_t)row * o0.ld + xc));
+#pragma unroll
+                for (int j = 0; j < 4; ++j) v[n][4 * h + j] = w4[j];
+            } else {
+#pragma unroll
+                for (int j = 0; j < 4; ++j) v[n][4 * h + j] = (row < R && xc + j < C) ? o0.X[(size_t)row * o0.ld + xc + j] : 0u;
             }
-        } else {
-#pragma unroll
-            for (int j = 0; j < 8; ++j) v[n][j] = (xr < R && xc + j < C) ? o0.X[(size_t)xr * o0.ld + xc + j] : 0u;
         }
     }
+    const int xr = ty * 32 + tid / 8;                   // o0's mapping
 #pragma unroll
     for (int n = 0; n < kPairTiles; ++n) {
         const int tx = tx0 + n;
         const int xc = tx * 64 + (tid % 8) * 8;
-        uint32_t r[8];
+        {
+            uint32_t q[8];
+            bool rare;
+            if (ROUND && ty * 32 + 32 <= R && tx * 64 + 64 <= C) {       // the whole tile lies in X: the same in the workgroup
+                uint32_t amax = 0u;
 #pragma unroll
-        for (int j = 0; j < 8; ++j) r[j] = quantize_bits<MODE, FTZ>(v[n][j], p);
-        if constexpr (ROUND) {
-            const bool row_ok = xr < R;
-#pragma unroll
-            for (int j = 0; j < 8; ++j)
-                account<DEEP, kPairCopies>(v[n][j] & 0x7FFFFFFFu, row_ok && xc + j < C, p, tbl, (uint32_t)tid % kPairCopies, w);
-            if (row_ok) {
-                uint32_t *dstY = Y + (size_t)xr * ldy + xc;
-                if (xc + 8 <= C && ((reinterpret_cast<uintptr_t>(Y) | (uintptr_t)(ldy * 4)) & 15) == 0) {
-                    __builtin_nontemporal_store(u32x4{r[0], r[1], r[2], r[3]}, reinterpret_cast<u32x4 *>(dstY));
-                    __builtin_nontemporal_store(u32x4{r[4], r[5], r[6], r[7]}, reinterpret_cast<u32x4 *>(dstY) + 1);
-                } else {
+                for (int j = 0; j < 8; ++j) account_run<DEEP, kPairCopies>(v[n][j] & 0x7FFFFFFFu, p, tbl, (uint32_t)tid % kPairCopies, w, amax);
+                account_run_top(v[n], amax, p, w);
+                rare = amax >= p.t_ovf;
+            } else {
+                if constexpr (ROUND) {
 #pragma unroll
                     for (int j = 0; j < 8; ++j)
-                        if (xc + j < C) dstY[j] = r[j];
+                        account<DEEP, kPairCopies>(v[n][j] & 0x7FFFFFFFu, rr + 4 * (j & 4) < R && tx * 64 + cc + (j & 3) < C, p, tbl,
+                                                   (uint32_t)tid % kPairCopies, w);
                 }
+                rare = run_is_rare(v[n], p);
+            }
+            quantize_run<MODE, FTZ>(v[n], rare, p, masks, q);
+            const bool vec = ROUND && ((reinterpret_cast<uintptr_t>(Y) | (uintptr_t)(ldy * 4)) & 15) == 0;
+#pragma unroll
+            for (int h = 0; h < 2; ++h) {
+                const u32x4 q4{q[4 * h], q[4 * h + 1], q[4 * h + 2], q[4 * h + 3]};
+                if constexpr (ROUND) {
+                    const int row = rr + 16 * h, col = tx * 64 + cc;
+                    uint32_t *dst = Y + (size_t)row * ldy + col;
+                    if (row < R && vec && col + 4 <= C) {
+                        __builtin_nontemporal_store(q4, reinterpret_cast<u32x4 *>(dst));
+                    } else if (row < R) {
+#pragma unroll
+                        for (int j = 0; j < 4; ++j)
+                            if (col + j < C) dst[j] = q4[j];
+                    }
+                }
+                // (the reads of the tile before this one ended before that tile's second barrier)
+                *reinterpret_cast<u32x4 *>(&s_r[tid / 16 + 16 * h][cc]) = q4;
             }
         }
-        // (the reads of the tile before this one ended before that tile's second barrier)
-        u32x4 *dst = reinterpret_cast<u32x4 *>(&s_r[tid / 8][(tid % 8) * 8]);
-        dst[0] = u32x4{r[0], r[1], r[2], r[3]};
-        dst[1] = u32x4{r[4], r[5], r[6], r[7]};
         __syncthreads();
         // beyond an operand's k-blocks there is nothing of it to write (the other operand's padded rows lie there)
         const bool do0 = tx < (o0.kblocks + 1) / 2, do1 = ty < o1.kblocks;
@@ -775,8 +815,14 @@ __device__ __forceinline__ void prepare_pair_tile(const OP &o0, const OP &o1, co
         const int u0 = 4 * n + (tid % 8) / 4, u1 = 4 * n + 2 + (tid % 64) / 32;
         // (where an operand has nothing to write the tile holds zeros only and its rows are padded ones, whose
         // scales exist: the split is harmless there and leaves no records)
-        uint32_t t[8];
+        uint32_t r[8], t[8];
         u32x4 p0a, paa, pba, p0b, pab, pbb;
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+            const u32x4 r4 = *reinterpret_cast<const u32x4 *>(&s_r[tid / 8][(tid % 8) * 8 + 4 * h]);
+#pragma unroll
+            for (int j = 0; j < 4; ++j) r[4 * h + j] = r4[j];
+        }
         const uint32_t mine0 = split_planes(o0, xr, xc, r, p0a, paa, pba);
 #pragma unroll
         for (int j = 0; j < 8; ++j) t[j] = s_r[(tid / 64) * 8 + j][tid % 64];
@@ -815,8 +861,10 @@ __global__ __launch_bounds__(256) void prepare_scaled_kernel(PrepOperand a, Prep
 // 2i (X as stored: rows of X, k along its columns) and 2i + 1 (X transposed) belong to matrix i; the table
 // travels by value in the kernel arguments.  A workgroup takes tiles of 32 rows x 64 columns of X and
 // prepares them for both operands (prepare_pair_tile): X is read and rounded once.  Every
-// matrix owns a run of workgroup ids padded to a multiple of 8 (first[] = the runs' first ids, ascending)
-// and remapped XCD by XCD as above.
+// matrix owns a run of workgroup ids padded to a multiple of 8 (first[] = the runs' first ids, ascending).
+// Tiles go to the workgroups in id order, and a workgroup's further steps are a whole run of workgroups on, so that what the chip works
+// on at a time is one stretch of X, Y and the planes: memory takes that at 6.0 TB/s (964 MB in 160 us), and at 4.8 (198) with the
+// ids remapped to give each XCD a stretch of its own and a workgroup consecutive tiles.  No line is used twice here.
 constexpr int kMaxPrepGroup = 32;
 
 struct PrepPlain {
@@ -862,15 +910,14 @@ __global__ __launch_bounds__(256) void prepare_scaled_group_kernel(PrepGroup grp
 {
     __shared__ __align__(16) uint32_t tbl[ROUND ? kHistRows * kPairCopies : 4];
     __shared__ uint32_t s_bins[ROUND ? FMT_NBINS : 1], s_cls[ROUND ? 8 : 1];
-    const int at = run_of(grp.first, blockIdx.x);
+    const int at = __builtin_amdgcn_readfirstlane(run_of(grp.first, blockIdx.x));
     const PrepPlain &o0 = grp.o[2 * at], &o1 = grp.o[2 * at + 1];
     // ROUND: a workgroup takes up to kRoundSteps consecutive steps of kPairTiles tiles, so that clearing and folding
     // its statistics table is paid once per 16 K elements (as in the stream kernels); fewer when the launch is small
     const unsigned kSteps = ROUND ? (unsigned)rg.steps : 1u;
     const unsigned lid = blockIdx.x - grp.first[at], ntiles = grp.tiles[at];
     const unsigned nwg = (ntiles + kSteps - 1u) / kSteps;
-    const unsigned per_xcd = (nwg + 7u) / 8u;
-    const unsigned g = (lid % 8u) * per_xcd + lid / 8u;
+    const unsigned g = lid;
     if (g >= nwg) return;                        // workgroup-uniform: before any barrier
     // rows of X in 32s: o0's units (rows padded to the tile grid) cover o1's k-blocks; columns of X in 64s:
     // pairs of o1's units cover o0's slabs of two k-blocks
@@ -879,7 +926,7 @@ __global__ __launch_bounds__(256) void prepare_scaled_group_kernel(PrepGroup grp
     if constexpr (ROUND) hist_begin<kPairCopies, 256>(tbl, s_bins, s_cls, threadIdx.x);
 #pragma unroll 1
     for (unsigned step = 0; step < kSteps; ++step) {
-        const unsigned t = g * kSteps + step;
+        const unsigned t = g + step * nwg;
         if (t >= ntiles) break;                  // workgroup-uniform
         if (step > 0) __syncthreads();           // the step before has read its words of LDS
         const int ty = (int)(t / (unsigned)ntx), tx = (int)(t % (unsigned)ntx) * kPairTiles;

@@ -39,6 +39,66 @@ __device__ __forceinline__ uint32_t quantize_bits(uint32_t u, const QuantParams 
     return (a > 0x7F800000u) ? 0x7FC00000u : r;
 }
 
+// What programs round is finite and far from overflow.  A run of elements in which every |x| is below t_ovf (a look of one
+// instruction per two elements) takes the short form: 5 vector instructions per element (7 with the flush; e == 8: 3 and 6)
+// where quantize_bits takes 13 to 15.
+
+// Constants in registers: v_and_or_b32 takes no literal, and one scalar operand only.
+struct RoundMasks {
+    uint32_t exponent, half, sign, floor;        // 0x7F800000, 0x00400000, 0x80000000 and the pattern of 1.5 * minN
+};
+
+__device__ __forceinline__ RoundMasks round_masks(const QuantParams &p)
+{
+    RoundMasks k{0x7F800000u, 0x00400000u, 0x80000000u, p.minn_bits | 0x00400000u};
+    asm("" : "+s"(k.exponent), "+v"(k.half), "+s"(k.sign));
+    return k;
+}
+
+// Whether an |x| of a run is at or above t_ovf, infinite or NaN (v_maximum3_f32 hands a NaN on).
+template <int N>
+__device__ __forceinline__ bool run_is_rare(const uint32_t (&u)[N], const QuantParams &p)
+{
+    static_assert(N % 2 == 0, "pairs");
+    float top = 0.0f;
+#pragma unroll
+    for (int j = 0; j < N; j += 2) asm("v_maximum3_f32 %0, |%1|, |%2|, %0" : "+v"(top) : "v"(u[j]), "v"(u[j + 1]));
+    return !(top < __uint_as_float(p.t_ovf));
+}
+
+// Q of one element with |x| < t_ovf.  e < 8: (C + x) - C with C = 1.5 * 2^(max(E, Emin) + 23 - m), whose last place is the format's step
+// for either sign of x; C is formed inside the two fused multiply-adds.  SIGN: the sign of a zero is kept.
+template <int MODE, bool FTZ, bool SIGN = true>
+__device__ __forceinline__ uint32_t quantize_short(uint32_t u, const QuantParams &p, const RoundMasks &k)
+{
+    static_assert(MODE != kModeMixed, "no short form");
+    if constexpr (MODE == kModeMagic) {
+        const float c = __uint_as_float(max((u & k.exponent) | k.half, k.floor)), scale = __uint_as_float((127u + p.shift) << 23);
+        float q = __fmaf_rn(c, -scale, __fmaf_rn(c, scale, __uint_as_float(u)));
+        if (FTZ) q = fabsf(q) < __uint_as_float(p.minn_bits) ? 0.0f : q;
+        return SIGN ? (u & k.sign) | __float_as_uint(q) : __float_as_uint(q);
+    } else {
+        uint32_t r = (u + p.rbias + __builtin_amdgcn_ubfe(u, p.shift, p.lsb_width)) & p.nmask;
+        if (FTZ) r = (u & 0x7FFFFFFFu) < p.t_den ? u & 0x80000000u : r;
+        return r;
+    }
+}
+
+// Q of a run; rare: what run_is_rare says of it.
+template <int MODE, bool FTZ, int N>
+__device__ __forceinline__ void quantize_run(const uint32_t (&u)[N], bool rare, const QuantParams &p, const RoundMasks &k, uint32_t (&r)[N])
+{
+    if constexpr (MODE != kModeMixed) {
+        if (__ballot(rare) == 0ull) {            // the same in the whole wave
+#pragma unroll
+            for (int j = 0; j < N; ++j) r[j] = quantize_short<MODE, FTZ>(u[j], p, k);
+            return;
+        }
+    }
+#pragma unroll
+    for (int j = 0; j < N; ++j) r[j] = quantize_bits<MODE, FTZ>(u[j], p);
+}
+
 // (1+e+m)-bit code (Sec. III) of r, the pattern of a value of the format (quantize_bits' result);
 // needs 1 + e + m <= 16, so MODE is kModeMagic (e < 8) or kModeInteger (e == 8).  At or above minN
 // the code is the fp32 pattern rebased to the format's bias and shifted; below minN the stored
