@@ -1488,11 +1488,15 @@ struct StatOperand {
 // a value that is normal in the format, every T in [hi + 1, lo + wid] keeps all elements seen in plane 0:
 //   - a denormal value was seen: T = 9 - m, the highest choice that keeps the denormals (gradient
 //     tensors live here);
-//   - otherwise up to three binades above hi + 1 (not beyond the middle of [hi + 1, lo + wid]),
+//   - otherwise up to four binades above hi + 1 (not beyond the middle of [hi + 1, lo + wid]),
 //     which leaves room on both sides for the elements the sample did not see; if the row spans
 //     more than a plane, T = lo + wid (the small values stay, the large ones go to the plane above).
 // Any T in [kWinTmin, kWinTmax] is correct -- what does not fit plane 0 goes to another plane -- the
-// choice only decides how often the other planes are needed, which is why a sample suffices.
+// choice only decides how often the other planes are needed, which is why a sample suffices: kStatSlabs * 64 = 128 elements of a
+// row with four binades of room leave no more outside plane 0 than 256 with three (log2|x| ~ N(mu, 3^2 .. 6^2) around the format's
+// middle, rows of 4096: 2e-5 .. 2e-2 either way; normal and uniform rows: none; where denormals are met: the same), and the
+// launch, which reads its sample in pieces of 128 and 256 bytes from all over the tensors, is the shorter.
+constexpr int kStatSlabs = 2;
 __device__ __forceinline__ void window_stats_block(const StatOperand &o, int K, int kstep, int emin, int m, int by)
 {
     __shared__ int s_hi[8][32], s_lo[8][32];
@@ -1511,10 +1515,10 @@ __device__ __forceinline__ void window_stats_block(const StatOperand &o, int K, 
     const int row = by * 32 + (o.kcontig ? tid / 8 : tid % 32);
     const int kl = o.kcontig ? tid % 8 : tid / 32;
     if (row < o.rows) {
-        // at most four slabs are visited (kstep = ceil(slabs / 4)); all their loads are issued first
-        uint32_t u[4][8];
+        // at most kStatSlabs slabs of 64 k are visited (kstep = ceil(slabs / kStatSlabs)); all their loads are issued first
+        uint32_t u[kStatSlabs][8];
 #pragma unroll
-        for (int i = 0; i < 4; ++i) {
+        for (int i = 0; i < kStatSlabs; ++i) {
             const int k0 = min(kl * 8 + i * 64 * kstep, K - 1);
             if (o.kcontig && o.vec4 && k0 + 8 <= K) {      // k0 is a multiple of 8 here
                 const u32x4 *src = reinterpret_cast<const u32x4 *>(o.X + (size_t)row * o.ld + k0);
@@ -1533,7 +1537,7 @@ __device__ __forceinline__ void window_stats_block(const StatOperand &o, int K, 
             }
         }
 #pragma unroll
-        for (int i = 0; i < 4; ++i)
+        for (int i = 0; i < kStatSlabs; ++i)
 #pragma unroll
             for (int j = 0; j < 8; ++j) look(u[i][j]);
     }
@@ -1559,7 +1563,7 @@ __device__ __forceinline__ void window_stats_block(const StatOperand &o, int K, 
     int T = 0;
     if (hi != -1000) {
         const int top = hi + 1, room = lo + wid;
-        T = lo < emin ? 9 - m : (top >= room ? room : top + min(3, (room - top) / 2));
+        T = lo < emin ? 9 - m : (top >= room ? room : top + min(4, (room - top) / 2));
     }
     T = max(kWinTmin, min(kWinTmax, T));
     o.S[row] = 15 - T;
@@ -1651,11 +1655,11 @@ static int prepare_operands(const OperandSpec &sa, const OperandLayout &la, cons
                 return t;
             };
             const StatOperand ta = stat(oa, la, true), tb = stat(ob, sb ? *lb : la, sb != nullptr);
-            // a sample of at most 4 slabs of 64 k per row (256 elements): the scale only has to be a good guess
+            // a sample of the row: the scale only has to be a good guess
             const int slabs = (K + 63) / 64;
             const int bias = (1 << (f.e - 1)) - 1;
             hipLaunchKernelGGL(window_stats_kernel, dim3(ta.nblocks + tb.nblocks), dim3(256), 0, stream, ta, tb, K,
-                               (slabs + 3) / 4, K, (slabs + 3) / 4, 1 - bias, f.m);
+                               (slabs + kStatSlabs - 1) / kStatSlabs, K, (slabs + kStatSlabs - 1) / kStatSlabs, 1 - bias, f.m);
             FMT_HIP_CHECK(hipGetLastError());
             hipLaunchKernelGGL((prepare_scaled_kernel<MODE, FTZ>), dim3(prep_grid), dim3(256), 0, stream, oa, ob, K, kblocks, K,
                                kblocks, p);
@@ -1960,7 +1964,7 @@ int launch_prepare_pair_batch(int64_t count, const PrepPairItem *items, fmt_form
         t.rec_cnt = v.pl.rec_cnt;
         t.nblocks = (unsigned)L.units;
         sg.K[n] = K;
-        sg.kstep[n] = ((K + 63) / 64 + 3) / 4;
+        sg.kstep[n] = ((K + 63) / 64 + kStatSlabs - 1) / kStatSlabs;
         sg.first[n] = stat_ids;
         stat_ids += t.nblocks;
         ++n;
