@@ -399,3 +399,16 @@ def test_statistics_of_a_large_output(fmt):
         fmt.fmt_histogram(acc, f, hist=want)
         torch.cuda.synchronize()
         assert torch.equal(Y[:rows], acc) and torch.equal(h, want)
+
+
+@pytest.mark.parametrize("e,m,d", [(7, 16, False), (7, 20, True), (7, 12, True)])
+def test_layers_of_several_pieces_repeat(fmt, e, m, d):
+    """A layer in a format of two or three bf16 pieces, without statistics: every call gives what the separate calls give."""
+    M, N, K = 1232, 2316, 522
+    g = torch.Generator(device="cuda").manual_seed(5)
+    X, W = torch.randn(M, K, generator=g, device="cuda"), torch.randn(N, K, generator=g, device="cuda") * 0.05
+    b, f = torch.randn(N, generator=g, device="cuda"), (e, m, d)
+    Xp, Wp = fmt.fmt_prepare(X, f), fmt.fmt_prepare(W, f)
+    want = fmt.fmt_quantize(fmt.fmt_quantize(fmt.fmt_gemm_prepared(Xp, Wp), f) + fmt.fmt_quantize(b, f), f)
+    for _ in range(40):
+        assert torch.equal(fmt.fmt_linear_prepared(Xp, Wp, b), want)
