@@ -67,11 +67,16 @@ int launch_stream_static(const float *x, float *y, size_t n, const QuantParams &
                          fmt_hist_t *hist, hipStream_t stream);
 int launch_unpack16(const uint16_t *codes, float *y, size_t n, const QuantParams &p, hipStream_t stream);
 
-// Output roundings of a fully connected layer, y = R(R(acc) + R(b)): the (unrounded) bias, or nullptr, and the format.
+// Output roundings of a fully connected layer, y = R(R(acc) + R(b)): the (unrounded) bias, or nullptr, and the format; the record of
+// the statistics of R(acc) + R(b), or nullptr; where the outputs go as 16-bit codes (leading dimension ldcodes), or nullptr: they
+// take the accumulators' place.
 struct LinearOut {
     const float *bias;
     int32_t ftz;
     QuantParams p;
+    fmt_hist_t *hist;
+    uint16_t *codes;
+    int64_t ldcodes;
 };
 
 // GEMM (fmt_gemm.hip).  lin != nullptr: C is to receive a layer's rounded outputs; *rounded says on return whether it has (where

@@ -1,10 +1,14 @@
 // The product kernels (see fmt_gemm.hip for what they multiply) and their launches, instantiated per piece scheme.
 #pragma once
 
+#include <type_traits>
+
+#include "fmt_hist.h"
 #include "fmt_internal.h"
 #include "fmt_product.h"
 #include "fmt_quant.h"
 #include "fmt_split.h"
+#include "fmt_tail.h"
 
 namespace fmt {
 
@@ -124,6 +128,143 @@ __device__ __forceinline__ void store_tile(floatx16 (&acc)[TM][TN], float *__res
         }
 }
 
+// The scales of exponent planes undone in place (see store_tile).
+template <int TM, int TN>
+__device__ __forceinline__ void unscale_tile(floatx16 (&acc)[TM][TN], int row_base, int col_base, int lane, const int *__restrict__ Sa,
+                                             const int *__restrict__ Sb)
+{
+    typedef int i32x4 __attribute__((ext_vector_type(4)));
+#pragma unroll
+    for (int i = 0; i < TM; ++i) {
+        const int sa = Sa[row_base + i * 32 + (lane & 31)];
+#pragma unroll
+        for (int j = 0; j < TN; ++j)
+#pragma unroll
+            for (int g = 0; g < 4; ++g) {
+                const i32x4 sb = *reinterpret_cast<const i32x4 *>(Sb + col_base + j * 32 + g * 8 + (lane >> 5) * 4);
+#pragma unroll
+                for (int c = 0; c < 4; ++c) acc[i][j][4 * g + c] = ldexpf(acc[i][j][4 * g + c], -(sb[c] + sa));
+            }
+    }
+}
+
+// replicas of the statistics table: as in the stream kernels, as many as fit a stage buffer of the smallest tile
+constexpr int linear_copies(int tm) { return tm == 1 ? 4 : 8; }
+
+// Outputs of a fully connected layer from a workgroup's accumulators, R(t) with t = R(acc) + R(b) (Sec. IV-A), HIST: and the statistics
+// of t (Sec. V), to C or as 16-bit codes.  tbl: LDS that no load is on its way to any more, for the statistics' table.
+// The common case takes the short forms of the rounding on the accumulators: about 20 vector instructions per output, half
+// of them the statistics, four neighbouring columns (a quad of registers) at a time.  Tiles that hold anything else --
+// sums or biases near the format's largest value or beyond, elements outside plane 0 (`outside`, add() adds their products
+// to C), a last quad that N cuts, formats without a short form -- leave their sums in C and take a loop over them, one by one:
+// the code of the common case stays a few kilobytes (unrolled, both together are 40 times the loop over the products, and the
+// workgroups wait for instructions).
+template <int PS, int TM, int TN, bool HIST, class ADD>
+__device__ __forceinline__ void linear_tile(floatx16 (&acc)[TM][TN], float *C, int64_t ldc, int M, int N, int tm, int tn, int wm, int wn, int lane,
+                                            const uint32_t (&bias)[TN][16], const LinearOut &lin, const HistSink &sink, uint32_t *tbl,
+                                            int tile, int ntiles, bool outside, ADD &&add)
+{
+    constexpr int kCopies = linear_copies(TM);
+    __shared__ uint32_t s_bins[HIST ? FMT_NBINS : 1], s_cls[HIST ? 8 : 1];
+    const QuantParams &p = lin.p;
+    const bool has_bias = lin.bias != nullptr;
+    const uint32_t tid = threadIdx.x, copy = tid % kCopies;
+    const int row_base = (tm * 2 + wm) * (32 * TM), col_base = (tn * 2 + wn) * (32 * TN);
+    Counts w;
+
+    // near: |acc| and |b| below a quarter of the smallest magnitude that rounds to infinity keep |t| below it (NaN is not below)
+    float top = 0.0f;
+#pragma unroll
+    for (int j = 0; j < TN; ++j)
+#pragma unroll
+        for (int v = 0; v < 16; ++v) {
+            top = __builtin_elementwise_maximum(fabsf(__uint_as_float(bias[j][v])), top);
+#pragma unroll
+            for (int i = 0; i < TM; ++i) top = __builtin_elementwise_maximum(fabsf(acc[i][j][v]), top);
+        }
+    const bool odd = outside || !(top < 0.25f * __uint_as_float(p.t_ovf)) || (p.mode == kModeMagic && p.shift < 2u) ||
+                     p.mode == kModeMixed || ((N & 3) != 0 && (tn + 1) * (64 * TN) > N);
+    const bool one_by_one = __syncthreads_or(odd ? 1 : 0) != 0;      // every wave is done with the stage buffers as well
+    if constexpr (HIST) hist_begin<kCopies, 256>(tbl, s_bins, s_cls, tid);
+
+    if (!one_by_one) {
+        const RoundMasks masks = round_masks(p);
+        const int row_in = row_base + (lane & 31), col_in = col_base + (lane >> 5) * 4;
+        auto run = [&](auto mode, auto flush) __attribute__((always_inline)) {
+            constexpr int MODE = decltype(mode)::value;
+            constexpr bool FTZ = decltype(flush)::value;
+#pragma unroll
+            for (int j = 0; j < TN; ++j)
+#pragma unroll
+                for (int g = 0; g < 4; ++g) {
+                    const int col = col_in + j * 32 + g * 8;
+                    if (col >= N) continue;                          // N is a multiple of 4 here
+                    uint32_t rb[4];
+#pragma unroll
+                    for (int c = 0; c < 4; ++c) rb[c] = has_bias ? quantize_short<MODE, FTZ>(bias[j][4 * g + c], p, masks) : 0u;
+#pragma unroll
+                    for (int i = 0; i < TM; ++i) {
+                        const int row = row_in + i * 32;
+                        if (row >= M) continue;
+                        uint32_t t[4];
+#pragma unroll
+                        for (int c = 0; c < 4; ++c) {
+                            t[c] = quantize_short<MODE, FTZ>(__float_as_uint(acc[i][j][4 * g + c]), p, masks);
+                            if (has_bias) t[c] = __float_as_uint(__fadd_rn(__uint_as_float(t[c]), __uint_as_float(rb[c])));
+                            if constexpr (HIST) account_below<kCopies>(t[c] & 0x7FFFFFFFu, p, tbl, copy, w);
+                            if (has_bias) t[c] = quantize_short<MODE, FTZ>(t[c], p, masks);     // without one it changes nothing
+                        }
+                        // (kept in the accumulators for a store behind them all, under these tests, they would take twice the registers)
+                        typedef uint32_t u32x4u __attribute__((ext_vector_type(4), aligned(4)));
+                        typedef uint32_t u32x2u __attribute__((ext_vector_type(2), aligned(2)));
+                        if (lin.codes == nullptr) {
+                            *reinterpret_cast<u32x4u *>(C + (size_t)row * ldc + col) = u32x4u{t[0], t[1], t[2], t[3]};
+                        } else {
+#pragma unroll
+                            for (int c = 0; c < 4; ++c) t[c] = MODE == kModeInteger ? t[c] >> p.shift : encode_bits<MODE>(t[c], p);     // e == 8: the upper bits
+                            *reinterpret_cast<u32x2u *>(lin.codes + (size_t)row * lin.ldcodes + col) = u32x2u{t[0] | (t[1] << 16), t[2] | (t[3] << 16)};
+                        }
+                    }
+                }
+        };
+        constexpr std::integral_constant<int, kModeMagic> magic{};
+        constexpr std::integral_constant<int, kModeInteger> integer{};
+        if (PS == 0 || p.mode == kModeMagic) {
+            if (lin.ftz) run(magic, std::true_type{});
+            else run(magic, std::false_type{});
+        } else {
+            if (lin.ftz) run(integer, std::true_type{});
+            else run(integer, std::false_type{});
+        }
+    } else {
+        store_tile<TM, TN, false>(acc, C, ldc, M, N, 0, row_base, col_base, lane, nullptr, nullptr);
+        __syncthreads();
+        if (outside) add();
+#pragma unroll 1
+        for (int at = (int)tid; at < 64 * TM * 64 * TN; at += 256) {
+            const int row = tm * (64 * TM) + at / (64 * TN), col = tn * (64 * TN) + at % (64 * TN);
+            const bool valid = row < M && col < N;
+            uint32_t t = 0u;
+            if (valid) {
+                t = quantize_bits_rt(__float_as_uint(C[(size_t)row * ldc + col]), p, lin.ftz != 0);
+                if (has_bias)
+                    t = __float_as_uint(__fadd_rn(__uint_as_float(t),
+                                                  __uint_as_float(quantize_bits_rt(__float_as_uint(lin.bias[col]), p, lin.ftz != 0))));
+            }
+            if constexpr (HIST) account<false, kCopies>(t & 0x7FFFFFFFu, valid, p, tbl, copy, w);
+            if (valid) {
+                if (has_bias) t = quantize_bits_rt(t, p, lin.ftz != 0);
+                if (lin.codes == nullptr) C[(size_t)row * ldc + col] = __uint_as_float(t);
+                else lin.codes[(size_t)row * lin.ldcodes + col] = (uint16_t)(p.mode == kModeInteger ? encode_bits<kModeInteger>(t, p) : encode_bits<kModeMagic>(t, p));
+            }
+        }
+    }
+    if constexpr (HIST) {
+        hist_clear<256>(sink, (uint32_t)tile, (uint32_t)ntiles, tid);
+        hist_end<kCopies, 256>(tbl, s_bins, s_cls, w, p, sink, (uint32_t)tile, (uint32_t)ntiles, tid);
+    }
+}
+
 // product: Aw / Bw are prepared operands (rows padded to a multiple of kRowPad, k to a multiple
 // of 32).  A workgroup is 2 x 2 waves; each wave owns TM x TN MFMA tiles of 32 x 32, so the
 // workgroup tile is (64*TM) x (64*TN).  Operand stages of KS*16 k go from global memory straight
@@ -140,13 +281,15 @@ __device__ __forceinline__ void store_tile(floatx16 (&acc)[TM][TN], float *__res
 // the taps).  The stage image in LDS and everything after it are the same.
 // The body is shared by the kernel of one product (bid = blockIdx.x) and the kernel of a group of products
 // (bid = the workgroup's index within its product).
-// LINEAR: the results are a fully connected layer's accumulators; they leave as R(R(acc) + R(b)) (lin).
-template <int PS, int TM, int TN, int KS, int NST, bool SPLIT, bool SCHED, bool SCALED, bool GATHER = false, bool LINEAR = false>
+// LINEAR: the results are a fully connected layer's accumulators; they leave as R(R(acc) + R(b)) (lin), HIST: with the
+// statistics of R(acc) + R(b) (sink).
+template <int PS, int TM, int TN, int KS, int NST, bool SPLIT, bool SCHED, bool SCALED, bool GATHER = false, bool LINEAR = false,
+          bool HIST = false>
 __device__ __forceinline__ void product_body(const u32x4 *__restrict__ Aw, const u32x4 *__restrict__ Bw,
                                              float *__restrict__ C, int M, int N, int64_t ldc, int img,
                                              int kblocks, int tiles_m, int tiles_n, int kb_per_split,
                                              const Planes &pa, const Planes &pb, const Implicit &im, const unsigned bid,
-                                             const LinearOut &lin = LinearOut{})
+                                             const LinearOut &lin = LinearOut{}, const HistSink &sink = HistSink{})
 {
     constexpr int P = pieces_of(PS);
     constexpr int UA = 2 * TM, UB = 2 * TN;              // 32-row units per operand in the workgroup tile
@@ -381,10 +524,36 @@ __device__ __forceinline__ void product_body(const u32x4 *__restrict__ Aw, const
     // every load-to-LDS of this wave must have landed before the workgroup's LDS is handed back
     __builtin_amdgcn_s_waitcnt(0x0F70);
 
-    if constexpr (LINEAR)
-        linear_round<TM * TN * 16>(lin, [&](int i) { return acc[i / (TN * 16)][i / 16 % TN][i % 16]; },
-                                   [&](int i, float y) { acc[i / (TN * 16)][i / 16 % TN][i % 16] = y; },
-                                   [&](int i) { return bias[i / 16 % TN][i % 16]; });
+    if constexpr (LINEAR) {
+        // the stage buffers serve again; the smallest tile's do not hold what the additions below need
+        constexpr bool kTailFits = sizeof(st1) >= sizeof(TailLds);
+        static_assert(sizeof(st0) >= kHistRows * linear_copies(TM) * 4, "room for the statistics' table");
+        __shared__ __attribute__((aligned(16))) char s_tail[SCALED && !kTailFits ? sizeof(TailLds) : 16];
+        const int row_base = (tm * 2 + wm) * (32 * TM), col_base = (tn * 2 + wn) * (32 * TN);
+        bool outside = false;
+        if constexpr (SCALED) {
+            unscale_tile<TM, TN>(acc, row_base, col_base, lane, pa.S, pb.S);
+            // Elements outside plane 0 in the rows or columns of the tile: their products have to be added ahead of the
+            // roundings.  Rare in a forward pass.
+            uint32_t count = 0u;
+#pragma unroll
+            for (int u = 0; u < UA; ++u) count |= pa.rec_cnt[tm * UA + u];
+#pragma unroll
+            for (int u = 0; u < UB; ++u) count |= pb.rec_cnt[tn * UB + u];
+            outside = __builtin_amdgcn_readfirstlane((int)count) != 0;
+        }
+        linear_tile<PS, TM, TN, HIST>(acc, C, ldc, M, N, tm, tn, wm, wn, lane, bias, lin, sink, reinterpret_cast<uint32_t *>(st0), tile, ntiles,
+                                      outside, [&]() __attribute__((always_inline)) {
+                                          if constexpr (SCALED)
+                                              for (int u = 0; u < UA; ++u) {
+                                                  planes_tail_body(Aw, Bw, pa, pb, C, ldc, M, N, kblocks, tm * UA + u, tn * UB * kUnitRows,
+                                                                   UB * kUnitRows,
+                                                                   *reinterpret_cast<TailLds *>(kTailFits ? reinterpret_cast<char *>(st1) : s_tail));
+                                                  __syncthreads();
+                                              }
+                                      });
+        return;
+    }
     // plain: C[row][col] with leading dimension ldc; a part of a split k: its own M x N slab; img > 0: NCHW
     float *out = SPLIT ? C + (size_t)split * M * ldc : C;
     store_tile<TM, TN, SCALED>(acc, out, ldc, M, N, SPLIT ? 0 : img, (tm * 2 + wm) * (32 * TM), (tn * 2 + wn) * (32 * TN), lane, pa.S,
@@ -401,14 +570,13 @@ __global__ __launch_bounds__(256) void product_kernel(const u32x4 *__restrict__ 
                                                                   kb_per_split, pa, pb, im, blockIdx.x);
 }
 
-template <int PS, int TM, int TN, int KS, int NST>
-__global__ __launch_bounds__(256) void product_linear_kernel(const u32x4 *__restrict__ Aw, const u32x4 *__restrict__ Bw,
-                                                             float *__restrict__ C, int M, int N, int64_t ldc, int kblocks,
-                                                             int tiles_m, int tiles_n, LinearOut lin)
+template <int PS, int TM, int TN, int KS, int NST, bool SCALED, bool HIST>
+__global__ __launch_bounds__(256, SCALED && TM == 2 ? 2 : 1) void product_linear_kernel(const u32x4 *__restrict__ Aw, const u32x4 *__restrict__ Bw,
+                                                             float *C, int M, int N, int64_t ldc, int kblocks,
+                                                             int tiles_m, int tiles_n, Planes pa, Planes pb, LinearOut lin, HistSink sink)
 {
-    const Planes none{nullptr, nullptr, 0, 0, nullptr, nullptr};
-    product_body<PS, TM, TN, KS, NST, false, true, false, false, true>(Aw, Bw, C, M, N, ldc, 0, kblocks, tiles_m, tiles_n, kblocks, none,
-                                                                     none, Implicit{}, blockIdx.x, lin);
+    product_body<PS, TM, TN, KS, NST, false, true, SCALED, false, true, HIST>(Aw, Bw, C, M, N, ldc, 0, kblocks, tiles_m, tiles_n, kblocks, pa,
+                                                                            pb, Implicit{}, blockIdx.x, lin, sink);
 }
 
 template <int PS, int TM, int TN, int KS, int NST, bool SCHED, bool SCALED>
@@ -487,35 +655,60 @@ static int launch_product(const u32x4 *Aw, const u32x4 *Bw, float *C, int M, int
     return rc != FMT_OK ? rc : tail();
 }
 
-template <int PS, int T>
-static int launch_product_linear(const u32x4 *Aw, const u32x4 *Bw, const OutSpec &out, int M, int N, int kblocks, hipStream_t stream)
+template <int PS, int T, bool SCALED, bool HIST>
+static int launch_product_linear(const OperandView &va, const OperandView &vb, const OutSpec &out, int M, int N, int kblocks, hipStream_t stream)
 {
     constexpr int KS = Pipe<PS, T, T>::ks, NST = Pipe<PS, T, T>::nst;
     const int tiles_m = (M + 64 * T - 1) / (64 * T), tiles_n = (N + 64 * T - 1) / (64 * T);
-    const int64_t per_xcd = ((int64_t)tiles_m * tiles_n + 7) / 8;
+    const int64_t ntiles = (int64_t)tiles_m * tiles_n, per_xcd = (ntiles + 7) / 8;
     if (per_xcd * 8 >= ((int64_t)1 << 31)) return FMT_ERR_SHAPE;
-    hipLaunchKernelGGL((product_linear_kernel<PS, T, T, KS, NST>), dim3((unsigned)(per_xcd * 8)), dim3(256), 0, stream, Aw, Bw, out.C, M, N,
-                       out.ldc, kblocks, tiles_m, tiles_n, *out.lin);
+    HistSink sink{};
+    if (HIST) {
+        HistRecords at;
+        const int rc = get_hist_records(stream, (uint64_t)ntiles, &at);
+        if (rc != FMT_OK) return rc;
+        sink = hist_sink(at, (unsigned long long)M * (unsigned long long)N, out.lin->hist, (uint64_t)ntiles);
+    }
+    hipLaunchKernelGGL((product_linear_kernel<PS, T, T, KS, NST, SCALED, HIST>), dim3((unsigned)(per_xcd * 8)), dim3(256), 0, stream, va.W,
+                       vb.W, out.C, M, N, out.ldc, kblocks, tiles_m, tiles_n, va.pl, vb.pl, *out.lin, sink);
     FMT_HIP_CHECK(hipGetLastError());
+    if (HIST && sink.hist == nullptr) return launch_hist_finalize(sink.records, (size_t)M * (size_t)N, out.lin->hist, stream);
     return FMT_OK;
+}
+
+template <int PS, int T>
+static int launch_product_linear_t(const OperandView &va, const OperandView &vb, const OutSpec &out, int M, int N, int kblocks,
+                                   hipStream_t stream)
+{
+    const bool hist = out.lin->hist != nullptr;
+    if constexpr (PS == 0)
+        if (va.pl.S != nullptr)
+            return hist ? launch_product_linear<PS, T, true, true>(va, vb, out, M, N, kblocks, stream)
+                        : launch_product_linear<PS, T, true, false>(va, vb, out, M, N, kblocks, stream);
+    return hist ? launch_product_linear<PS, T, false, true>(va, vb, out, M, N, kblocks, stream)
+                : launch_product_linear<PS, T, false, false>(va, vb, out, M, N, kblocks, stream);
 }
 
 template <int PS>
 int product_of_views(const OperandView &va, const OperandView &vb, int M, int N, int kblocks, const OutSpec &out,
                             const Plan &plan, float *part, hipStream_t stream)
 {
-    // A layer's output roundings in the product kernel: where the product leaves whole sums in one launch, and for the tiles of up
-    // to 128 x 128 (two workgroups and more per compute unit, so that the roundings of one run beside the products of
-    // another; a 256 x 256 tile has neither the registers nor the company).  Measured, fmt_linear_prepared in 1/8/7, product and pass
-    // against one kernel: 64 x 128 x 128 8.7 -> 5.4 us, 333 x 4096 x 1024 14.2 -> 9.8, 2048 x 2048 x 512 24.4 -> 18.9,
-    // 4096 x 1024 x 1024 25.1 -> 22.5, 4096 x 3072 x 1024 51.8 -> 51.5.
+    // A layer's output roundings, statistics and codes in the product's kernel: where the product leaves whole sums in one launch, and for
+    // the tiles of up to 128 x 128 (two workgroups and more per compute unit, so that the roundings of one run beside the products of
+    // another; a 256 x 256 tile has neither the registers nor the company).  Measured, product (with planes: and the launch that adds
+    // the elements outside plane 0) and pass against one kernel, us: 4096 x 3072 x 1024 in 1/6/9 with statistics 64 -> 55, without 58 -> 46,
+    // in 1/8/7 59 -> 49 and 51 -> 45; 1/8/7 without statistics 64 x 128 x 128 8.7 -> 5.4, 333 x 4096 x 1024 14.2 -> 9.8, 2048 x 2048 x 512
+    // 24.4 -> 18.9.  (4096 x 3072: 768 tiles on 512 slots; both workgroups of a compute unit come to their roundings at the same time.)
     // Not with three pieces: that kernel gave wrong blocks of results in some calls (1232 x 2316 x 522 in 1/7/16: most of them), cause
     // unknown; the product's own kernel with three pieces gives the same sums in every call, so these formats keep the pass.
-    if (PS < 3 && out.lin != nullptr && va.pl.S == nullptr && out.img == 0 && plan.nsplit == 1 && plan.tm == plan.tn && plan.tm <= 2) {
-        const int rc = plan.tm == 2 ? launch_product_linear<PS, 2>(va.W, vb.W, out, M, N, kblocks, stream)
-                                    : launch_product_linear<PS, 1>(va.W, vb.W, out, M, N, kblocks, stream);
-        if (rc == FMT_OK) *out.rounded = true;
-        return rc;
+    if constexpr (PS < 3) {
+        const bool deep = out.lin != nullptr && out.lin->hist != nullptr && out.lin->p.exp_lo < -126;     // rows for fp32 denormals: the pass has them
+        if (out.lin != nullptr && out.img == 0 && plan.nsplit == 1 && plan.tm == plan.tn && plan.tm <= 2 && !deep) {
+            const int rc = plan.tm == 2 ? launch_product_linear_t<PS, 2>(va, vb, out, M, N, kblocks, stream)
+                                        : launch_product_linear_t<PS, 1>(va, vb, out, M, N, kblocks, stream);
+            if (rc == FMT_OK) *out.rounded = true;
+            return rc;
+        }
     }
 #define FMT_PRODUCT(TMV, TNV) \
     launch_product<PS, TMV, TNV>(va.W, vb.W, out.C, M, N, out.ldc, out.img, kblocks, plan, part, stream, va.pl, vb.pl)

@@ -55,14 +55,16 @@ __device__ __forceinline__ RoundMasks round_masks(const QuantParams &p)
     return k;
 }
 
-// Whether an |x| of a run is at or above t_ovf, infinite or NaN (v_maximum3_f32 hands a NaN on).
+// Whether an |x| of a run is at or above t_ovf, infinite or NaN (v_maximum3_f32 hands a NaN on; not as inline assembly: a run may
+// come straight from the matrix cores, whose results the compiler knows when to read).
 template <int N>
 __device__ __forceinline__ bool run_is_rare(const uint32_t (&u)[N], const QuantParams &p)
 {
     static_assert(N % 2 == 0, "pairs");
     float top = 0.0f;
 #pragma unroll
-    for (int j = 0; j < N; j += 2) asm("v_maximum3_f32 %0, |%1|, |%2|, %0" : "+v"(top) : "v"(u[j]), "v"(u[j + 1]));
+    for (int j = 0; j < N; j += 2)
+        top = __builtin_elementwise_maximum(__builtin_elementwise_maximum(fabsf(__uint_as_float(u[j])), fabsf(__uint_as_float(u[j + 1]))), top);
     return !(top < __uint_as_float(p.t_ovf));
 }
 

@@ -401,6 +401,48 @@ def test_statistics_of_a_large_output(fmt):
         assert torch.equal(Y[:rows], acc) and torch.equal(h, want)
 
 
+@pytest.mark.parametrize("M,N,K", [(64, 64, 40), (333, 1030, 256), (520, 1100, 520), (1100, 1300, 96)])
+@pytest.mark.parametrize("e,m,d", [(6, 9, True), (6, 9, False), (6, 8, True), (5, 10, False), (8, 7, True), (8, 7, False), (7, 20, True)])
+def test_statistics_and_codes_on_the_way_out(fmt, e, m, d, M, N, K, monkeypatch):
+    """A layer's output roundings, statistics and 16-bit codes in the product's kernel, with rows and columns that have elements
+    outside plane 0 in some tiles and none in others, infinities, and edges of 64 x 64 and 128 x 128 tiles: bit for bit what the
+    separate calls make of the product's sums."""
+    monkeypatch.setenv("FMT_GEMM_WINDOW", "1")               # 1/6/m: the planes at any size
+    monkeypatch.setenv("FMT_GEMM_PLAN", "%d,%d,1" % ((2, 2) if M * N > 300000 else (1, 1)))
+    f = (e, m, d)
+    rng = np.random.default_rng(M + N + K + e + m)
+    X = rng.standard_normal((M, K)).astype(np.float32)
+    W = (rng.standard_normal((N, K)) * 0.05).astype(np.float32)
+    X[M // 2:M // 2 + 3] = workloads.log2_normal((3, K), -12.0, 8.0, 0.1, rng)       # some rows spread over all the format's binades
+    W[5, ::7] = 2.0 ** -37                                                            # a column with elements below plane 0
+    W[6, ::5] = 3.0e9
+    X[1, 0] = 1e30
+    X, W = torch.from_numpy(X).cuda(), torch.from_numpy(W).cuda()
+    b = torch.from_numpy(rng.standard_normal(N).astype(np.float32)).cuda()
+    b[0] = -1e-30                                                                     # rounds to -0
+    acc = fmt.fmt_gemm(X, W, f, transB=True)
+    for bias in (b, None):
+        t = fmt.fmt_quantize(acc, f)
+        if bias is not None:
+            t = t + fmt.fmt_quantize(bias, f)
+        want, hw = fmt.fmt_quantize(t, f), fmt.fmt_histogram(t, f)
+        h0, h1, h2 = fmt.new_hist(), fmt.new_hist(), fmt.new_hist()
+        Xp, Wp = fmt.fmt_prepare(X, f), fmt.fmt_prepare(W, f)
+        for y, h in ((fmt.fmt_linear(X, W, bias, f, hist=h0), h0), (fmt.fmt_linear(X, W, bias, f), None),
+                     (fmt.fmt_linear_prepared(Xp, Wp, bias, hist=h1), h1)):
+            torch.cuda.synchronize()
+            nan = torch.isnan(want)
+            assert torch.equal(torch.isnan(y), nan)
+            assert torch.equal(y[~nan].view(torch.int32), want[~nan].view(torch.int32))
+            assert h is None or torch.equal(h, hw)
+        if 1 + e + m <= 16:
+            for h in (h2, None):
+                codes = fmt.fmt_linear_pack16(X, W, bias, f, hist=h)
+                torch.cuda.synchronize()
+                assert torch.equal(codes, fmt.fmt_pack16(want, f))
+                assert h is None or torch.equal(h, hw)
+
+
 @pytest.mark.parametrize("e,m,d", [(7, 16, False), (7, 20, True), (7, 12, True)])
 def test_layers_of_several_pieces_repeat(fmt, e, m, d):
     """A layer in a format of two or three bf16 pieces, without statistics: every call gives what the separate calls give."""
