@@ -257,31 +257,30 @@ __global__ __launch_bounds__(256) void round_split_kernel(const uint32_t *__rest
 // by 32 channels: reads run along pixels, the transposition goes through LDS, and a lane writes 8
 // consecutive channels of one pixel as one 16-byte vector.  One vector of zeros follows the last piece.
 template <int MODE, bool FTZ, int PS>
-__global__ __launch_bounds__(256) void nhwc_split_kernel(const uint32_t *__restrict__ x, u32x4 *__restrict__ out, int C,
-                                                         int HW, int npix, QuantParams p)
+__device__ __forceinline__ void nhwc_split_block(const uint32_t *__restrict__ x, u32x4 *__restrict__ out, int C, int HW, int npix,
+                                                 const QuantParams &p, int bx, int cb)
 {
     constexpr int P = pieces_of(PS);
     constexpr int kPitch = 18;                                  // 32-bit words per pixel row (16 + 2: odd multiple of 2)
     __shared__ uint32_t tile[P][64][kPitch];
     const int tid = threadIdx.x;
     const int pix = tid % 64, cg = tid / 64;
-    const int gp = blockIdx.x * 64 + pix, cb = blockIdx.y;
+    const int gp = bx * 64 + pix;
     const bool valid = gp < npix;
     const int n = valid ? gp / HW : 0, hw = valid ? gp - n * HW : 0;
     const uint32_t *src = x + ((size_t)n * C + cb * 32 + cg * 8) * HW + hw;
-    uint32_t pc[8][P];
+    uint32_t u[8];
 #pragma unroll
-    for (int i = 0; i < 8; ++i) {
-        const uint32_t u = valid ? src[(size_t)i * HW] : 0u;
-        round_and_split<MODE, FTZ, PS>(u, p, pc[i]);
-    }
+    for (int i = 0; i < 8; ++i) u[i] = valid ? src[(size_t)i * HW] : 0u;
+    u32x4 pc[P];
+    split8<MODE, FTZ, PS>(u, p, pc);
 #pragma unroll
     for (int q = 0; q < P; ++q)
 #pragma unroll
-        for (int i = 0; i < 4; ++i) tile[q][pix][cg * 4 + i] = pc[2 * i][q] | (pc[2 * i + 1][q] << 16);
+        for (int i = 0; i < 4; ++i) tile[q][pix][cg * 4 + i] = pc[q][i];
     __syncthreads();
     const int opix = tid / 4, part = tid % 4;
-    const int ogp = blockIdx.x * 64 + opix;
+    const int ogp = bx * 64 + opix;
     const size_t piece_vec = (size_t)npix * (C / 8);
     if (ogp < npix) {
 #pragma unroll
@@ -292,7 +291,7 @@ __global__ __launch_bounds__(256) void nhwc_split_kernel(const uint32_t *__restr
             out[q * piece_vec + (size_t)ogp * (C / 8) + cb * 4 + part] = w;
         }
     }
-    if (blockIdx.x == 0 && blockIdx.y == 0 && tid == 0) out[P * piece_vec] = u32x4{0u, 0u, 0u, 0u};
+    if (bx == 0 && cb == 0 && tid == 0) out[P * piece_vec] = u32x4{0u, 0u, 0u, 0u};
 }
 
 // Transposed patches (wgrad: rows = taps (ch, r, s), k = positions (n, y, x)), pre-rounded tensor.
@@ -558,18 +557,10 @@ __device__ __forceinline__ void prepare_block(const PrepOperand &a, const PrepOp
         }
         return;
     }
-    uint32_t pc[8][P];
+    u32x4 w[P];
+    split8<MODE, FTZ, PS>(v, p, w);
 #pragma unroll
-    for (int j = 0; j < 8; ++j) round_and_split<MODE, FTZ, PS>(v[j], p, pc[j]);
-#pragma unroll
-    for (int q = 0; q < P; ++q) {
-        u32x4 w;
-        w[0] = pc[0][q] | (pc[1][q] << 16);
-        w[1] = pc[2][q] | (pc[3][q] << 16);
-        w[2] = pc[4][q] | (pc[5][q] << 16);
-        w[3] = pc[6][q] | (pc[7][q] << 16);
-        o.W[unit_vec_index(rb, kb, kblocks, P, q, c, rr)] = w;
-    }
+    for (int q = 0; q < P; ++q) o.W[unit_vec_index(rb, kb, kblocks, P, q, c, rr)] = w[q];
 }
 
 // Eight rounded values of one thread (fp32 patterns r[], elements k0 .. k0 + 7 of row `row` of operand o) as
@@ -841,6 +832,23 @@ template <int MODE, bool FTZ, int PS, bool TAPS>
 __global__ __launch_bounds__(256) void prepare_kernel(PrepOperand a, PrepOperand b, int K, int kblocks, QuantParams p)
 {
     prepare_block<MODE, FTZ, PS, TAPS>(a, b, K, kblocks, p, blockIdx.x);
+}
+
+// What a product needs that gathers its patches itself, in one launch: the filter as a prepared operand (workgroups below
+// split_first) and the tensor in pixel-major pieces (the others, nx of them along the pixels).  Two launches of 6 and 8 us before.
+template <int MODE, bool FTZ, int PS>
+__global__ __launch_bounds__(256) void prepare_implicit_kernel(PrepOperand a, int K, int kblocks, unsigned split_first, unsigned nx,
+                                                               const uint32_t *__restrict__ x, u32x4 *__restrict__ out, int C, int HW,
+                                                               int npix, QuantParams p)
+{
+    if (blockIdx.x < split_first) {              // workgroup-uniform
+        PrepOperand none = a;
+        none.nblocks = 0u;
+        prepare_block<MODE, FTZ, PS>(a, none, K, kblocks, p, blockIdx.x);
+    } else {
+        const unsigned id = blockIdx.x - split_first;
+        nhwc_split_block<MODE, FTZ, PS>(x, out, C, HW, npix, p, (int)(id % nx), (int)(id / nx));
+    }
 }
 
 template <int MODE, bool FTZ>
@@ -2014,10 +2022,19 @@ static int run_implicit(int M, int N, int K, const OperandSpec &sa, const float 
     const OperandView va = view_of(ws, la);
     u32x4 *T = reinterpret_cast<u32x4 *>(ws + la.bytes);
     float *partp = reinterpret_cast<float *>(ws + la.bytes + nhwc);
-    rc = prepare_operands<MODE, FTZ, PS>(sa, la, va, nullptr, nullptr, nullptr, nullptr, nullptr, K, f, p, stream);
-    if (rc != FMT_OK) return rc;
-    hipLaunchKernelGGL((nhwc_split_kernel<MODE, FTZ, PS>), dim3((unsigned)((npix + 63) / 64), (unsigned)(C / 32)), dim3(256), 0,
-                       stream, reinterpret_cast<const uint32_t *>(tensor), T, C, HW, npix, p);
+    PrepOperand o;
+    o.X = reinterpret_cast<const uint32_t *>(sa.X);
+    o.W = va.W;
+    o.ld = sa.ld;
+    o.rows = la.rows;
+    o.kcontig = sa.kcontig;
+    o.vec4 = 0;
+    o.nblocks = (unsigned)((la.kblocks + 1) / 2) * la.units;
+    o.g = sa.g;
+    o.pl = va.pl;
+    const unsigned split_first = (o.nblocks + 7u) / 8u * 8u, nx = (unsigned)((npix + 63) / 64);
+    hipLaunchKernelGGL((prepare_implicit_kernel<MODE, FTZ, PS>), dim3(split_first + nx * (unsigned)(C / 32)), dim3(256), 0, stream, o, K,
+                       la.kblocks, split_first, nx, reinterpret_cast<const uint32_t *>(tensor), T, C, HW, npix, p);
     FMT_HIP_CHECK(hipGetLastError());
     im.T = T;
     im.piece_vec = (int)piece_vec;
