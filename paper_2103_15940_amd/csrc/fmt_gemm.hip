@@ -1093,14 +1093,15 @@ __global__ void zero_fill_kernel(float *__restrict__ C, int M, int N, int64_t ld
 // the time, and cutting k fills the machine at the price of writing and re-reading partial sums.
 static Plan make_plan(int M, int N, int kblocks, int cus, int pieces)
 {
-    // eff1 / effmax: relative MFMA rate of a compute unit with one / with max_occ resident workgroups
+    // eff1 / effmax: relative MFMA rate of a compute unit with one / with max_occ resident workgroups; 128 x 64 is there for layers
+    // (product_of_views) and to be forced: products of their own gain by it at single sizes only (333 x 4096 x 1024 8.7 -> 7.6 us)
     struct Shape { int tm, tn, max_occ; double eff1, effmax; };
-    static const Shape multi[] = {
-        {4, 4, 1, 1.15, 1.15}, {4, 2, 1, 1.0, 1.0}, {2, 4, 1, 1.03, 1.03}, {2, 2, 2, 0.80, 0.95}, {1, 1, 4, 0.45, 0.78}};
+    static const Shape multi[6] = {
+        {4, 4, 1, 1.15, 1.15}, {4, 2, 1, 1.0, 1.0}, {2, 4, 1, 1.03, 1.03}, {2, 2, 2, 0.80, 0.95}, {1, 1, 4, 0.45, 0.78}, {2, 1, 3, 0.01, 0.01}};
     // one piece: a quarter of the MFMA work per byte, the small tiles lose less
-    static const Shape single[] = {
-        {4, 4, 1, 1.21, 1.21}, {4, 2, 1, 1.0, 1.0}, {2, 4, 1, 1.03, 1.03}, {2, 2, 2, 0.98, 1.11}, {1, 1, 4, 0.53, 0.68}};
-    const Shape(&shapes)[5] = pieces == 1 ? single : multi;
+    static const Shape single[6] = {
+        {4, 4, 1, 1.21, 1.21}, {4, 2, 1, 1.0, 1.0}, {2, 4, 1, 1.03, 1.03}, {2, 2, 2, 0.98, 1.11}, {1, 1, 4, 0.53, 0.68}, {2, 1, 3, 0.01, 0.01}};
+    const Shape(&shapes)[6] = pieces == 1 ? single : multi;
     const double wg_cost = pieces == 1 ? 68.0 : 40.0, split_cost = pieces == 1 ? 5.76 : 2.5;
     if (const char *env = getenv("FMT_GEMM_PLAN")) {      // tuning override: "tm,tn,nsplit[,sched]" (other values leave the plan to the model)
         Plan forced{2, 2, 1, 1};

@@ -82,11 +82,12 @@ __device__ __forceinline__ void account_run_top(const uint32_t (&u)[N], uint32_t
     }
 }
 
-// Statistics of one element below t_ovf, in the lanes that call it.
+// Statistics of one element below t_ovf, in the lanes that call it; not `valid`: it does not count.
 template <int COPIES>
-__device__ __forceinline__ void account_below(uint32_t a, const QuantParams &p, uint32_t *tbl, uint32_t copy, Counts &w)
+__device__ __forceinline__ void account_below(uint32_t a, bool valid, const QuantParams &p, uint32_t *tbl, uint32_t copy, Counts &w)
 {
-    __hip_atomic_fetch_add(&tbl[(a >> 23) * COPIES + copy], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+    __hip_atomic_fetch_add(&tbl[(a >> 23) * COPIES + copy], valid ? 1u : 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+    a = valid ? a : 0xFFFFFFFFu;
     w.z += a == 0u ? 1u : 0u;
     w.zu += a <= p.t_zero ? 1u : 0u;
     w.zud += a < p.t_den ? 1u : 0u;

@@ -126,12 +126,12 @@ constexpr size_t lds_bytes(int tm, int tn, int pieces, int ks, int nst)
 
 // Pipeline shape per piece scheme and tile shape: k16 steps per stage, and as many stage buffers (at
 // most FMT_GEMM_NST, at least two) as fit the tile's share of the 160 KiB of LDS -- all of it for the
-// large tiles, half for 128 x 128 (two resident workgroups), a quarter for 64 x 64.
+// large tiles, half for 128 x 128 (two resident workgroups), a third for 128 x 64, a quarter for 64 x 64.
 constexpr int pipe_ks(int pieces) { return pieces == 1 ? FMT_GEMM_KS : FMT_GEMM_KS_MULTI; }
 constexpr int pipe_nst(int tm, int tn, int pieces, int ks)
 {
     if ((tm * pieces * ks) % 2 || (tn * pieces * ks) % 2) return 2;   // stage not a whole number of loads per wave
-    const size_t budget = (size_t)160 * 1024 / (tm * tn > 4 ? 1 : tm * tn == 4 ? 2 : 4);
+    const size_t budget = (size_t)160 * 1024 / (tm * tn > 4 ? 1 : tm * tn == 4 ? 2 : tm * tn == 2 ? 3 : 4);
     int n = FMT_GEMM_NST;
     while (n > 2 && lds_bytes(tm, tn, pieces, ks, n) > budget) --n;
     return n;

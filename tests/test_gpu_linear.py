@@ -401,14 +401,15 @@ def test_statistics_of_a_large_output(fmt):
         assert torch.equal(Y[:rows], acc) and torch.equal(h, want)
 
 
-@pytest.mark.parametrize("M,N,K", [(64, 64, 40), (333, 1030, 256), (520, 1100, 520), (1100, 1300, 96)])
+@pytest.mark.parametrize("M,N,K,tile", [(64, 64, 40, "1,1,1"), (333, 1030, 256, "1,1,1"), (333, 1031, 256, "2,1,1"), (520, 1100, 520, "2,2,1"),
+                                        (300, 1303, 96, "2,2,1"), (520, 1100, 520, "2,1,1")])
 @pytest.mark.parametrize("e,m,d", [(6, 9, True), (6, 9, False), (6, 8, True), (5, 10, False), (8, 7, True), (8, 7, False), (7, 20, True)])
-def test_statistics_and_codes_on_the_way_out(fmt, e, m, d, M, N, K, monkeypatch):
+def test_statistics_and_codes_on_the_way_out(fmt, e, m, d, M, N, K, tile, monkeypatch):
     """A layer's output roundings, statistics and 16-bit codes in the product's kernel, with rows and columns that have elements
-    outside plane 0 in some tiles and none in others, infinities, and edges of 64 x 64 and 128 x 128 tiles: bit for bit what the
+    outside plane 0 in some tiles and none in others, infinities, and edges of all three tiles: bit for bit what the
     separate calls make of the product's sums."""
     monkeypatch.setenv("FMT_GEMM_WINDOW", "1")               # 1/6/m: the planes at any size
-    monkeypatch.setenv("FMT_GEMM_PLAN", "%d,%d,1" % ((2, 2) if M * N > 300000 else (1, 1)))
+    monkeypatch.setenv("FMT_GEMM_PLAN", tile)
     f = (e, m, d)
     rng = np.random.default_rng(M + N + K + e + m)
     X = rng.standard_normal((M, K)).astype(np.float32)
