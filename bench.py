@@ -50,7 +50,7 @@ BF16_MFMA_PEAK_TFLOPS = 2500.0  # MI355X dense bf16 MFMA, published
 # Vector-ALU issue rate of the chip (one instruction per lane and clock: 256 CUs x 4 SIMDs x 16 lanes x 2.4 GHz)
 # and the vector instructions one FMAC-8 step takes in its fp64 form (from the ISA; operands of ordinary size).
 VALU_LANE_INSTR_PER_S = 256 * 64 * 2.4e9
-FMAC8_INSTR_PER_MAC = 5.0
+FMAC8_INSTR_PER_MAC = 4.0
 MEASURED_TRAFFIC_BYTES = 2157514900   # profiles/stream_kernel_config5_hbm_traffic.md
 
 
@@ -617,8 +617,8 @@ def main() -> int:
                                     "frac": round(2048.0 * 2048 * 1024 / (f8_ms * 1e-3)
                                                   / (VALU_LANE_INSTR_PER_S / FMAC8_INSTR_PER_MAC), 4),
                                     "note": "vector issue rate 256 CUs x 64 lanes x 2.4 GHz = 39.3 T "
-                                            "lane-instructions/s over the 5 instructions of the fused step "
-                                            "in fp64 (6.2 are executed per step with the operands' rounding and "
+                                            "lane-instructions/s over the 4 instructions of the fused step "
+                                            "in fp64 (more are executed per step: the operands' rounding and "
                                             "the master additions)"}}
     # loss-scale controller on the nine statistics records of configuration 4's gradient tensors
     recs = torch.stack([L["h"][2] for L in layers])
