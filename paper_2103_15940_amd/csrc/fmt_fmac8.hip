@@ -30,6 +30,7 @@
 #include <algorithm>
 #include <cmath>
 #include <cstdlib>
+#include <cstring>
 #include <type_traits>
 
 #include "fmt_internal.h"
@@ -626,7 +627,10 @@ int launch_gemm_fmac8(int transA, int transB, int64_t M, int64_t N, int64_t K, c
     WideConsts wc;
     wc.floor_hi = ((uint32_t)(1 - bias + 1023) << 20) | 0x80000u;
     wc.scale = ldexp(1.0, 52 - f.m);
-    wc.flush_hi = ((uint32_t)(-bias + 1023) << 20) | (0xFFFFFu & ~((1u << (19 - f.m)) - 1u));     // 1.1...1 (m + 1 ones) * 2^(Emin - 1)
+    const double flush = ldexp(1.0, 1 - bias) - ldexp(1.0, -bias - f.m);       // half a step below minN: m fractional ones, all in the hi word
+    uint64_t flush_bits = 0;
+    memcpy(&flush_bits, &flush, sizeof(flush_bits));
+    wc.flush_hi = (uint32_t)(flush_bits >> 32);
     // Below 2^(Emin - m + 52) the wide step is exact (see fmac_wide), below 2^Emax nothing overflows.  Through the 8
     // steps of a group |a + w*x| grows to at most max|w*x| times the sum of (1 + 2^-(m+1))^i, i = 0..8 (each step's
     // rounding adds at most half a last place): that factor, and a little for the product of the maxima, comes off.

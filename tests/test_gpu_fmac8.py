@@ -274,3 +274,53 @@ def test_sums_next_to_a_power_of_two(fmt, e, m, d):
     B[1] = frac(n) * 2.0 ** rng.integers(-22, -12, n)
     got, ref = run(fmt, A, B, (e, m, d))
     assert_bits(got, ref, "1/%d/%d" % (e, m))
+
+
+FLUSHING = [(6, 9), (6, 11), (6, 3), (4, 3), (5, 2), (3, 1), (5, 10)]
+
+
+@pytest.mark.parametrize("M,N", [(40, 70), (700, 800), (2000, 2010)])
+@pytest.mark.parametrize("e,m", FLUSHING)
+def test_flush_next_to_the_smallest_normal(fmt, e, m, M, N):
+    """Sums that round to minN or just miss it, at every tile size: products and accumulator-plus-product sums half a step below minN
+    (a tie, which goes to minN), one bit of the product on either side of it, and between there and minN.  Both signs.  A second
+    product that adds nothing but its own bits follows, so that a sum wrongly flushed shows in every later step as well."""
+    rng = np.random.default_rng(10 * e + m)
+    c = oracle.format_constants(e, m)
+    lo = c["Emin"]
+    h = 2.0 ** (lo // 2)                                          # B's values; h * g = 2^Emin
+    g = 2.0 ** (lo - lo // 2)
+    last = 2.0 ** -m
+    # in units of 2^Emin; values of the format times a power of two that the operands' exponents absorb
+    heads = np.array([0.0, 1.0 - last, 1.0 - last / 2, 0.5 * (2.0 - last), 0.5 * (2.0 - 2 * last), 1.0, 1.0 + last, 0.75, 2.0])
+    tails = np.array([0.0, last / 2, last / 4, last / 8, last, -last / 2, -last / 4, -last / 8, -last])
+    A, B = np.zeros((M, 16), np.float32), np.zeros((16, N), np.float32)
+    head, tail = rng.choice(heads, M), rng.choice(tails, M)
+    head[:9], tail[:9] = heads, 0.0
+    A[:, 0], A[:, 1] = head * g, tail * g
+    A[:, 2] = rng.choice([0.0, last / 2, -last / 2], M) * g
+    B[:3] = rng.choice([-h, h], N)
+    B[1:3] *= rng.choice([1.0, 1.0, -1.0], N)
+    A[:, 8:11], B[8:11] = A[:, :3], B[:3]                         # and in a second group
+    C = fmt.fmt_gemm_fmac8(dev(A), dev(B), (e, m, False))
+    torch.cuda.synchronize()
+    rows = np.unique(np.concatenate([np.arange(36), rng.integers(0, M, 120)]))
+    cols = np.unique(np.concatenate([rng.integers(0, N, 24), [0, N - 1]]))
+    ref = oracle.gemm_fmac8(np.ascontiguousarray(A[rows]), np.ascontiguousarray(B[:, cols]), e, m, False)
+    assert_bits(np.ascontiguousarray(C.cpu().numpy()[np.ix_(rows, cols)]), ref, "next to minN")
+
+
+@pytest.mark.parametrize("M,N", [(200, 200), (700, 800), (2000, 2010)])
+@pytest.mark.parametrize("e,m", FLUSHING)
+def test_flush_of_random_sums_around_the_smallest_normal(fmt, e, m, M, N):
+    """Flushing formats with operands around 2^(Emin/2), so that sums wander about minN."""
+    rng = np.random.default_rng(100 * e + m)
+    c = oracle.format_constants(e, m)
+    A = workloads.log2_normal((M, 64), c["Emin"] / 2, 1.0, 0.02, rng)
+    B = workloads.log2_normal((64, N), c["Emin"] / 2, 1.0, 0.02, rng)
+    C = fmt.fmt_gemm_fmac8(dev(A), dev(B), (e, m, False))
+    torch.cuda.synchronize()
+    rows, cols = np.unique(rng.integers(0, M, 150)), np.unique(rng.integers(0, N, 150))
+    ref = oracle.gemm_fmac8(np.ascontiguousarray(A[rows]), np.ascontiguousarray(B[:, cols]), e, m, False)
+    assert (ref == 0.0).any() and (ref != 0.0).any()
+    assert_bits(np.ascontiguousarray(C.cpu().numpy()[np.ix_(rows, cols)]), ref, "around minN")
