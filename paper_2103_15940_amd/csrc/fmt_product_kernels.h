@@ -327,9 +327,13 @@ __device__ __forceinline__ void product_body(const u32x4 *__restrict__ Aw, const
     constexpr int SV = kHalf * KS;                       // ... per stage
     constexpr int VA = UA * P * SV, VB = UB * P * SV;    // 16-byte vectors per operand per stage
     constexpr int LA = (VA + 255) / 256, LB = (VB + 255) / 256;   // loads per lane per stage
-    constexpr int kWaitLanded = ((NST - 2) * (LA + LB));  // stage loads that may still be in flight
-    static_assert(kWaitLanded < 64 && (KS == 1 || KS == 2) && NST >= 2 && NST <= 4, "unsupported pipeline shape");
-    static_assert(NST == 2 || (VA % 256 == 0 && VB % 256 == 0), "the wait for a stage counts the same loads in every wave");
+    // Loads of a wave that may still be in flight when a stage is read, which is the oldest of NST (the first) or NST - 1.  Where an
+    // operand's stage is not a whole number of loads per wave (three pieces: 384 vectors of a 64-row operand), the upper waves issue
+    // fewer than LA + LB; counting those of the last wave for every wave (j * 256 + 192 < VA), no wait ends before the wave's own loads
+    // of the stage have landed.
+    constexpr int kFewest = (VA + 63) / 256 + (VB + 63) / 256;
+    constexpr int kWaitFirst = (NST - 1) * kFewest, kWaitLanded = (NST - 2) * kFewest;
+    static_assert(kWaitFirst < 64 && (KS == 1 || KS == 2) && NST >= 2 && NST <= 4, "unsupported pipeline shape");
     // One LDS array per stage buffer, each addressed with a compile-time index: the compiler then knows
     // which loads-to-LDS an LDS read can depend on and leaves the younger stages in flight.
     constexpr int STV = VA + VB;
@@ -477,7 +481,6 @@ __device__ __forceinline__ void product_body(const u32x4 *__restrict__ Aw, const
     if (steps > 0) {
 #pragma unroll
         for (int t = 0; t < NST; ++t) issue(t, t);
-        constexpr int kWaitFirst = (NST - 1) * (LA + LB);
         __builtin_amdgcn_s_waitcnt(0x0F70 | (kWaitFirst & 0xF) | ((kWaitFirst >> 4) << 14));
         barrier();
         read_frags(0, 0);
@@ -729,8 +732,7 @@ int product_of_views(const OperandView &va, const OperandView &vb, int M, int N,
     // the elements outside plane 0) and pass against one kernel, us: 4096 x 3072 x 1024 in 1/6/9 with statistics 64 -> 55, without 58 -> 46,
     // in 1/8/7 59 -> 49 and 51 -> 45; 1/8/7 without statistics 64 x 128 x 128 8.7 -> 5.4, 333 x 4096 x 1024 14.2 -> 9.8, 2048 x 2048 x 512
     // 24.4 -> 18.9.  (4096 x 3072: 768 tiles on 512 slots; both workgroups of a compute unit come to their roundings at the same time.)
-    // Not with three pieces: that kernel gave wrong blocks of results in some calls (1232 x 2316 x 522 in 1/7/16: most of them), cause
-    // unknown; the product's own kernel with three pieces gives the same sums in every call, so these formats keep the pass.
+    // Formats of three pieces keep the pass.
     if constexpr (PS < 3) {
         const bool deep = out.lin != nullptr && out.lin->hist != nullptr && out.lin->p.exp_lo < -126;     // rows for fp32 denormals: the pass has them
         if (out.lin != nullptr && out.img == 0 && plan.nsplit == 1 && !deep) {

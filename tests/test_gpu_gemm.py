@@ -479,3 +479,38 @@ def test_seeded_random_cases(fmt, seed, monkeypatch):
         assert np.array_equal(got[:, :N], ref), what
     else:
         assert rel_fro(got[:, :N], ref) <= TOL, what
+
+
+@pytest.mark.parametrize("plan", ["1,1,1", "1,1,4", "2,1,1", "2,2,1"])
+@pytest.mark.parametrize("e,m,d", [(7, 16, False), (7, 20, True), (8, 23, True)])
+def test_three_pieces_on_small_tiles_repeat(fmt, e, m, d, plan, monkeypatch):
+    """Formats of three bf16 pieces, where the four waves of a 64-row tile load different numbers of vectors per stage: products,
+    products of prepared operands, layers and convolutions of integers with all of the format's bits, a few per sum, so
+    that every sum is exact.  The first stage of k is met by every workgroup, so a stage read too early shows in some of the calls."""
+    monkeypatch.setenv("FMT_GEMM_PLAN", plan)
+    f, top = (e, m, d), 1 << (min(m, 20) + 1)
+    rng = np.random.default_rng(m)
+    M, N, K = 300, 520, 522
+    A = (2 * rng.integers(-top // 2, top // 2, (M, K)) + 1).astype(np.float32)
+    B = np.zeros((N, K), np.float32)
+    B[np.arange(N)[:, None], rng.integers(0, K, (N, 5))] = rng.choice([-1.0, 1.0], (N, 5))
+    B[:, :2] = 1.0                                                # the first stage of k counts in every sum
+    want = torch.from_numpy((A.astype(np.float64) @ B.T.astype(np.float64)).astype(np.float32)).cuda()
+    Ad, Bd = dev(A), dev(B)
+    bias = torch.randn(N, generator=torch.Generator(device="cuda").manual_seed(m), device="cuda") * 1000.0
+    y = fmt.fmt_quantize(fmt.fmt_quantize(want, f) + fmt.fmt_quantize(bias, f), f)
+    Ap, Bp = fmt.fmt_prepare(Ad, f), fmt.fmt_prepare(Bd, f)
+    for _ in range(12):
+        assert torch.equal(fmt.fmt_gemm(Ad, Bd, f, transB=True), want)
+        assert torch.equal(fmt.fmt_gemm(Bd, Ad, f, transB=True), want.T)
+        assert torch.equal(fmt.fmt_gemm_prepared(Ap, Bp), want)
+        assert torch.equal(fmt.fmt_linear_prepared(Ap, Bp, bias), y)
+    # 3 x 3 convolution, 32 to 64 channels (patches gathered by the product's kernel), five taps per filter
+    X = (2 * rng.integers(-top // 2, top // 2, (4, 32, 12, 12)) + 1).astype(np.float32)
+    W = np.zeros((64, 32 * 9), np.float32)
+    W[np.arange(64)[:, None], rng.integers(0, 32 * 9, (64, 5))] = rng.choice([-1.0, 1.0], (64, 5))
+    W = W.reshape(64, 32, 3, 3)
+    wantc = torch.nn.functional.conv2d(torch.from_numpy(X).double(), torch.from_numpy(W).double(), padding=1).float().cuda()
+    Xd, Wd = dev(X), dev(W)
+    for _ in range(12):
+        assert torch.equal(fmt.fmt_conv2d_fwd(Xd, Wd, f), wantc)
