@@ -153,18 +153,19 @@ __device__ __forceinline__ void unscale_tile(floatx16 (&acc)[TM][TN], int row_ba
 constexpr int linear_copies(int tiles) { return tiles == 1 ? 4 : 8; }
 
 // Outputs of a fully connected layer from a workgroup's accumulators, R(t) with t = R(acc) + R(b) (Sec. IV-A), HIST: and the statistics
-// of t (Sec. V), to C or as 16-bit codes.  tbl: LDS that no load is on its way to any more, for the statistics' table.
+// of t (Sec. V), to C or as 16-bit codes.  tbl: LDS that holds the statistics' table once every wave is done with its stages.
 // The common case takes the short forms of the rounding on the accumulators: about 20 vector instructions per output, half
-// of them the statistics, four neighbouring columns (a quad of registers) at a time.  Tiles that hold anything else --
-// sums or biases near the format's largest value or beyond, elements outside plane 0 (`outside`, add() adds their products
-// to C), in 128 x 128 tiles a last quad that N cuts, formats without a short form -- leave their sums in C and take a loop over them, one by one:
-// the code of the common case stays a few kilobytes (unrolled, both together are 40 times the loop over the products, and the
-// workgroups wait for instructions).
-template <int PS, int TM, int TN, bool HIST, class ADD>
-__device__ __forceinline__ void linear_tile(floatx16 (&acc)[TM][TN], float *C, int64_t ldc, int M, int N, int tm, int tn, int wm, int wn, int lane,
+// of them the statistics, four neighbouring columns (a quad of registers) at a time.  A wave that holds sums or biases near the
+// format's largest value or beyond leaves its sums in C and takes a loop over them: the code of the common case
+// stays a few kilobytes (with both forms unrolled it is ten times that, and the workgroups wait for instructions).
+// Formats without a short form never come here, nor do 128 x 128 tiles that cut a quad (product_of_views).
+template <int PS, int TM, int TN, bool HIST>
+__device__ __forceinline__ void linear_tile(floatx16 (&acc)[TM][TN], float *C, int64_t ldc, int M, int N, int row_base, int col_base, int lane,
                                             const uint32_t (&bias)[TN][16], const LinearOut &lin, const HistSink &sink, uint32_t *tbl,
-                                            int tile, int ntiles, bool outside, ADD &&add)
+                                            int tile, int ntiles)
 {
+    typedef uint32_t u32x4u __attribute__((ext_vector_type(4), aligned(4)));
+    typedef uint32_t u32x2u __attribute__((ext_vector_type(2), aligned(2)));
     constexpr int kCopies = linear_copies(TM * TN);
     // quads that N cuts among the common ones: 40 % more code in a 128 x 128 tile with planes (107 -> 148 KB, more registers spilled;
     // 4096 x 3072 x 1024 in 1/6/9 with statistics and no such quad 53 -> 69 us and more), so not there
@@ -173,25 +174,26 @@ __device__ __forceinline__ void linear_tile(floatx16 (&acc)[TM][TN], float *C, i
     const QuantParams &p = lin.p;
     const bool has_bias = lin.bias != nullptr;
     const uint32_t tid = threadIdx.x, copy = tid % kCopies;
-    const int row_base = (tm * 2 + wm) * (32 * TM), col_base = (tn * 2 + wn) * (32 * TN);
     Counts w;
 
-    // near: |acc| and |b| below a quarter of the smallest magnitude that rounds to infinity keep |t| below it (NaN is not below)
-    float top = 0.0f;
+    // |acc| + |b| below half of the smallest magnitude that rounds to infinity keeps |t| below it: either rounding adds at most half a
+    // step, an eighth of the largest power of two at that height (NaN is not below)
+    float top = 0.0f, topb = 0.0f;
 #pragma unroll
     for (int j = 0; j < TN; ++j)
 #pragma unroll
         for (int v = 0; v < 16; ++v) {
-            top = __builtin_elementwise_maximum(fabsf(__uint_as_float(bias[j][v])), top);
+            topb = __builtin_elementwise_maximum(fabsf(__uint_as_float(bias[j][v])), topb);
 #pragma unroll
             for (int i = 0; i < TM; ++i) top = __builtin_elementwise_maximum(fabsf(acc[i][j][v]), top);
         }
-    const bool odd = outside || !(top < 0.25f * __uint_as_float(p.t_ovf)) || (p.mode == kModeMagic && p.shift < 2u) ||
-                     p.mode == kModeMixed || (!kCut && (N & 3) != 0 && (tn + 1) * (64 * TN) > N);
-    const bool one_by_one = __syncthreads_or(odd ? 1 : 0) != 0;      // every wave is done with the stage buffers as well
-    if constexpr (HIST) hist_begin<kCopies, 256>(tbl, s_bins, s_cls, tid);
+    const bool rare = __ballot(!(top + topb < 0.5f * __uint_as_float(p.t_ovf))) != 0ull;     // the same in the whole wave
+    if constexpr (HIST) {
+        __syncthreads();                         // every wave is done with the stage buffers
+        hist_begin<kCopies, 256>(tbl, s_bins, s_cls, tid);
+    }
 
-    if (!one_by_one) {
+    if (!rare) {
         const RoundMasks masks = round_masks(p);
         const int row_in = row_base + (lane & 31), col_in = col_base + (lane >> 5) * 4;
         auto run = [&](auto mode, auto flush) __attribute__((always_inline)) {
@@ -220,8 +222,6 @@ __device__ __forceinline__ void linear_tile(floatx16 (&acc)[TM][TN], float *C, i
                             if (has_bias) t[c] = quantize_short<MODE, FTZ>(t[c], p, masks);     // without one it changes nothing
                         }
                         // (kept in the accumulators for a store behind them all, under these tests, they would take twice the registers)
-                        typedef uint32_t u32x4u __attribute__((ext_vector_type(4), aligned(4)));
-                        typedef uint32_t u32x2u __attribute__((ext_vector_type(2), aligned(2)));
                         if (lin.codes == nullptr) {
                             float *dst = C + (size_t)row * ldc + col;
                             if (!kCut || left >= 4) {
@@ -256,37 +256,73 @@ __device__ __forceinline__ void linear_tile(floatx16 (&acc)[TM][TN], float *C, i
             else run(integer, std::false_type{});
         }
     } else {
+        // The wave's own block: a lane takes the same four columns of every kRows-th row, kAhead rows at a time.  A layer whose
+        // outputs are all NaN, 4096 x 3072 x 1024 in 1/8/7: 47 us (others 40; 81 with one element and one load at a time).
         store_tile<TM, TN, false>(acc, C, ldc, M, N, 0, row_base, col_base, lane, nullptr, nullptr);
-        __syncthreads();
-        if (outside) add();
-        // four loads at a time where the registers have room (128 x 128 tiles with planes: anything more here is paid for by the
-        // common case, whose values are what gets spilled)
-        constexpr int kAhead = kCut ? 4 : 1;
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "workgroup");
+        constexpr int kRows = 64 / (8 * TN), kAhead = 4;
+        const int col = col_base + lane % (8 * TN) * 4, left = N - col;
+        auto run = [&](auto mode, auto flush) __attribute__((always_inline)) {
+            constexpr int MODE = decltype(mode)::value;
+            constexpr bool FTZ = decltype(flush)::value;
+            uint32_t rb[4];
+#pragma unroll
+            for (int c = 0; c < 4; ++c) rb[c] = has_bias && c < left ? quantize_bits<MODE, FTZ>(__float_as_uint(lin.bias[col + c]), p) : 0u;
 #pragma unroll 1
-        for (int at0 = (int)tid; at0 < 64 * TM * 64 * TN; at0 += 256 * kAhead) {
-            float u[kAhead];
+            for (int r0 = row_base + lane / (8 * TN); r0 < row_base + 32 * TM; r0 += kRows * kAhead) {
+                u32x4u u[kAhead];
 #pragma unroll
-            for (int q = 0; q < kAhead; ++q) {
-                const int at = at0 + q * 256, row = tm * (64 * TM) + at / (64 * TN), col = tn * (64 * TN) + at % (64 * TN);
-                u[q] = row < M && col < N ? C[(size_t)row * ldc + col] : 0.0f;
-            }
-#pragma unroll
-            for (int q = 0; q < kAhead; ++q) {
-                const int at = at0 + q * 256, row = tm * (64 * TM) + at / (64 * TN), col = tn * (64 * TN) + at % (64 * TN);
-                const bool valid = row < M && col < N;
-                uint32_t t = 0u;
-                if (valid) {
-                    t = quantize_bits_rt(__float_as_uint(u[q]), p, lin.ftz != 0);
-                    if (has_bias)
-                        t = __float_as_uint(__fadd_rn(__uint_as_float(t),
-                                                      __uint_as_float(quantize_bits_rt(__float_as_uint(lin.bias[col]), p, lin.ftz != 0))));
+                for (int q = 0; q < kAhead; ++q) {
+                    const uint32_t *src = reinterpret_cast<const uint32_t *>(C) + (size_t)(r0 + q * kRows) * ldc + col;
+                    const bool in = r0 + q * kRows < M;
+                    u[q] = u32x4u{0u, 0u, 0u, 0u};
+                    if (in && left >= 4) {
+                        u[q] = *reinterpret_cast<const u32x4u *>(src);
+                    } else if (in) {
+                        if (left > 0) u[q][0] = src[0];
+                        if (left > 1) u[q][1] = src[1];
+                        if (left > 2) u[q][2] = src[2];
+                    }
                 }
-                if constexpr (HIST) account<false, kCopies>(t & 0x7FFFFFFFu, valid, p, tbl, copy, w);
-                if (!valid) continue;
-                if (has_bias) t = quantize_bits_rt(t, p, lin.ftz != 0);
-                if (lin.codes == nullptr) C[(size_t)row * ldc + col] = __uint_as_float(t);
-                else lin.codes[(size_t)row * lin.ldcodes + col] = (uint16_t)(p.mode == kModeInteger ? encode_bits<kModeInteger>(t, p) : encode_bits<kModeMagic>(t, p));
+#pragma unroll 1
+                for (int q = 0; q < kAhead; ++q) {
+                    const int row = r0 + q * kRows;
+                    uint32_t t[4];
+#pragma unroll
+                    for (int c = 0; c < 4; ++c) {
+                        t[c] = quantize_bits<MODE, FTZ>(u[0][c], p);
+                        if (has_bias) t[c] = __float_as_uint(__fadd_rn(__uint_as_float(t[c]), __uint_as_float(rb[c])));
+                        if constexpr (HIST) account<false, kCopies>(t[c] & 0x7FFFFFFFu, row < M && c < left, p, tbl, copy, w);
+                        if (has_bias) t[c] = quantize_bits<MODE, FTZ>(t[c], p);
+                    }
+                    u[0] = u[1], u[1] = u[2], u[2] = u[3];
+                    if (row >= M) continue;
+                    if (lin.codes == nullptr) {
+                        uint32_t *dst = reinterpret_cast<uint32_t *>(C) + (size_t)row * ldc + col;
+                        if (left >= 4) {
+                            *reinterpret_cast<u32x4u *>(dst) = u32x4u{t[0], t[1], t[2], t[3]};
+                        } else {
+                            if (left > 0) dst[0] = t[0];
+                            if (left > 1) dst[1] = t[1];
+                            if (left > 2) dst[2] = t[2];
+                        }
+                    } else {
+                        uint16_t *dst = lin.codes + (size_t)row * lin.ldcodes + col;
+#pragma unroll
+                        for (int c = 0; c < 4; ++c)
+                            if (c < left) dst[c] = (uint16_t)encode_bits<MODE>(t[c], p);
+                    }
+                }
             }
+        };
+        constexpr std::integral_constant<int, kModeMagic> magic{};
+        constexpr std::integral_constant<int, kModeInteger> integer{};
+        if (PS == 0 || p.mode == kModeMagic) {
+            if (lin.ftz) run(magic, std::true_type{});
+            else run(magic, std::false_type{});
+        } else {
+            if (lin.ftz) run(integer, std::true_type{});
+            else run(integer, std::false_type{});
         }
     }
     if constexpr (HIST) {
@@ -408,13 +444,16 @@ __device__ __forceinline__ void product_body(const u32x4 *__restrict__ Aw, const
 
     // a layer's bias, loaded ahead of the products: register v of a lane holds column 8*(v/4) + 4*(l/32) + v%4 (see store_tile)
     uint32_t bias[LINEAR ? TN : 1][LINEAR ? 16 : 1];
-    if constexpr (LINEAR) {
+    auto load_bias = [&]() __attribute__((always_inline)) {
+        if constexpr (LINEAR) {
 #pragma unroll
-        for (int j = 0; j < TN; ++j)
+            for (int j = 0; j < TN; ++j)
 #pragma unroll
-            for (int v = 0; v < 16; ++v)
-                bias[j][v] = linear_bias(lin, (tn * 2 + wn) * (32 * TN) + j * 32 + (v >> 2) * 8 + (lane >> 5) * 4 + (v & 3), N);
-    }
+                for (int v = 0; v < 16; ++v)
+                    bias[j][v] = linear_bias(lin, (tn * 2 + wn) * (32 * TN) + j * 32 + (v >> 2) * 8 + (lane >> 5) * 4 + (v & 3), N);
+        }
+    };
+    load_bias();
 
     floatx16 acc[TM][TN];
 #pragma unroll
@@ -558,33 +597,51 @@ __device__ __forceinline__ void product_body(const u32x4 *__restrict__ Aw, const
     __builtin_amdgcn_s_waitcnt(0x0F70);
 
     if constexpr (LINEAR) {
-        // the stage buffers serve again; the smallest tile's do not hold what the additions below need
-        constexpr bool kTailFits = sizeof(st1) >= sizeof(TailLds);
         static_assert(sizeof(st0) >= kHistRows * linear_copies(TM * TN) * 4, "room for the statistics' table");
-        __shared__ __attribute__((aligned(16))) char s_tail[SCALED && !kTailFits ? sizeof(TailLds) : 16];
         const int row_base = (tm * 2 + wm) * (32 * TM), col_base = (tn * 2 + wn) * (32 * TN);
-        bool outside = false;
         if constexpr (SCALED) {
             unscale_tile<TM, TN>(acc, row_base, col_base, lane, pa.S, pb.S);
-            // Elements outside plane 0 in the rows or columns of the tile: their products have to be added ahead of the
-            // roundings.  Rare in a forward pass.
-            uint32_t count = 0u;
+            // Elements outside plane 0 in the rows or columns of the tile: their products are added ahead of the roundings.
+            uint32_t any = 0u;
 #pragma unroll
-            for (int u = 0; u < UA; ++u) count |= pa.rec_cnt[tm * UA + u];
+            for (int u = 0; u < UA; ++u) any |= pa.rec_cnt[tm * UA + u];
 #pragma unroll
-            for (int u = 0; u < UB; ++u) count |= pb.rec_cnt[tn * UB + u];
-            outside = __builtin_amdgcn_readfirstlane((int)count) != 0;
+            for (int u = 0; u < UB; ++u) any |= pb.rec_cnt[tn * UB + u];
+            if (__builtin_amdgcn_readfirstlane((int)any) != 0) {
+                // The stage buffers serve again: the sums take the last ones, kRows rows each; the records take the first where it is
+                // left and holds them.
+                constexpr int kRows = STV * 16 / (64 * TN * 4), kUsed = (64 * TM + kRows - 1) / kRows;
+                static_assert(kUsed <= NST && NST > 2, "room for the sums");
+                constexpr bool kFits = kUsed < NST && sizeof(st0) >= sizeof(TailLds);
+                __shared__ __attribute__((aligned(16))) char s_tail[kFits ? 16 : sizeof(TailLds)];
+                typedef float f32x4 __attribute__((ext_vector_type(4)));
+                TailTile<TM, TN, kRows> tile_sums;
+#pragma unroll
+                for (int q = 0; q < 4; ++q) tile_sums.s[q] = (lds_ptr<float>)reinterpret_cast<char *>(stage(q < kUsed ? NST - kUsed + q : 0));
+                auto quads = [&](auto &&move) __attribute__((always_inline)) {
+#pragma unroll
+                    for (int i = 0; i < TM; ++i)
+#pragma unroll
+                        for (int j = 0; j < TN; ++j)
+#pragma unroll
+                            for (int g = 0; g < 4; ++g)
+                                move(i, j, g, (lds_ptr<f32x4>)tile_sums.at((wm * TM + i) * 32 + (lane & 31), (wn * TN + j) * 32 + g * 8 + (lane >> 5) * 4));
+                };
+                __syncthreads();                 // every wave is done with the stage buffers
+                quads([&](int i, int j, int g, lds_ptr<f32x4> at) __attribute__((always_inline)) {
+                    *at = f32x4{acc[i][j][4 * g], acc[i][j][4 * g + 1], acc[i][j][4 * g + 2], acc[i][j][4 * g + 3]};
+                });
+                __syncthreads();
+                tail_tile<TM, TN, kRows>(Aw, Bw, pa, pb, kblocks, tm, tn, tile_sums, (lds_ptr<TailLds>)(kFits ? reinterpret_cast<char *>(st0) : s_tail));
+                quads([&](int i, int j, int g, lds_ptr<f32x4> at) __attribute__((always_inline)) {
+                    const f32x4 v = *at;
+#pragma unroll
+                    for (int c = 0; c < 4; ++c) acc[i][j][4 * g + c] = v[c];
+                });
+                load_bias();                     // again: nothing is kept in registers over the call
+            }
         }
-        linear_tile<PS, TM, TN, HIST>(acc, C, ldc, M, N, tm, tn, wm, wn, lane, bias, lin, sink, reinterpret_cast<uint32_t *>(st0), tile, ntiles,
-                                      outside, [&]() __attribute__((always_inline)) {
-                                          if constexpr (SCALED)
-                                              for (int u = 0; u < UA; ++u) {
-                                                  planes_tail_body(Aw, Bw, pa, pb, C, ldc, M, N, kblocks, tm * UA + u, tn * UB * kUnitRows,
-                                                                   UB * kUnitRows,
-                                                                   *reinterpret_cast<TailLds *>(kTailFits ? reinterpret_cast<char *>(st1) : s_tail));
-                                                  __syncthreads();
-                                              }
-                                      });
+        linear_tile<PS, TM, TN, HIST>(acc, C, ldc, M, N, row_base, col_base, lane, bias, lin, sink, reinterpret_cast<uint32_t *>(st0), tile, ntiles);
         return;
     }
     // plain: C[row][col] with leading dimension ldc; a part of a split k: its own M x N slab; img > 0: NCHW
@@ -604,7 +661,7 @@ __global__ __launch_bounds__(256) void product_kernel(const u32x4 *__restrict__ 
 }
 
 template <int PS, int TM, int TN, int KS, int NST, bool SCALED, bool HIST>
-__global__ __launch_bounds__(256, SCALED && TM * TN == 4 ? 2 : 1) void product_linear_kernel(const u32x4 *__restrict__ Aw, const u32x4 *__restrict__ Bw,
+__global__ __launch_bounds__(256, SCALED ? (TM * TN == 4 ? 2 : 3) : 1) void product_linear_kernel(const u32x4 *__restrict__ Aw, const u32x4 *__restrict__ Bw,
                                                              float *C, int M, int N, int64_t ldc, int kblocks,
                                                              int tiles_m, int tiles_n, Planes pa, Planes pb, LinearOut lin, HistSink sink)
 {

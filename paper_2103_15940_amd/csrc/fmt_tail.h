@@ -2,6 +2,8 @@
 // that rounds a layer's outputs in the product itself.
 #pragma once
 
+#include <type_traits>
+
 #include "fmt_product.h"
 #include "fmt_split.h"
 
@@ -53,45 +55,54 @@ struct TailLds {
     int cnt[4];
 };
 
-// The block of C of row unit rb and the columns [col0, col0 + cols); 256 threads, col0 and cols multiples of 32.
-__device__ __forceinline__ void planes_tail_body(const u32x4 *__restrict__ Aw, const u32x4 *__restrict__ Bw, const Planes &pa,
-                                                 const Planes &pb, float *__restrict__ C, int64_t ldc, int M, int N, int kblocks,
-                                                 int rb, int col0, int cols, TailLds &lds)
+// Records of the rows of units [unit0, unit0 + U) of an operand (count[]: how many each has) that fit their lists (kRecCap each), one row after the other in
+// lds.rec and lds.val, each row's in the order (k, row): the prepare pass appends them in whatever order its workgroups run, and
+// the additions must not depend on that.  256 threads, a wave per row of units; the record arrays are free before, and filled behind the
+// last barrier.
+template <int U>
+__device__ __forceinline__ void tail_lists(const Planes &pl, size_t unit0, const uint32_t (&count)[U], TailLds &lds)
 {
-    uint32_t(&s_rec)[kTailRecs] = lds.rec;
-    float(&s_val)[kTailRecs] = lds.val;
-    uint32_t(&s_list)[256] = lds.list;
-    int(&s_cnt)[4] = lds.cnt;
+    static_assert(U <= 4 && kRecCap == 64, "a wave per list");
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
+    int n = 0, first = 0;
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+        const int have = count[u] <= (uint32_t)kRecCap ? (int)count[u] : 0;
+        first += u < wave ? have : 0;
+        n = u == wave ? have : n;
+    }
+    uint32_t key = 0u, val = 0u;
+    if (lane < n) {
+        const uint32_t *rec = pl.recs + ((unit0 + wave) * kRecCap + lane) * 2;
+        key = rec[0];
+        val = rec[1];
+        lds.list[wave * 64 + lane] = key;
+    }
+    __syncthreads();
+    if (lane < n) {
+        int rank = 0;
+        for (int i = 0; i < n; ++i) rank += lds.list[wave * 64 + i] < key ? 1 : 0;
+        lds.rec[first + rank] = key;
+        lds.val[first + rank] = __uint_as_float(val);
+    }
+    __syncthreads();
+}
+
+// Where the walk through a row of units is.
+struct TailWalk {
+    int base = 0, total = -1;    // the blocks of k [base, base + 256): how many of them have other planes (-1: not looked at yet)
+    int at = 0, part = 0;        // the group of four of these that comes next; of its parts (see tail_group) the next one
+};
+
+// The next records of row of units urow of operand W / pl (row scales S32) whose list does not hold them: walks the units that have
+// other planes, k ascending, four units at a time.  The two other planes of a unit are 256 vectors, one per thread (threads 0..127
+// the plane above, vector tid: k-chunk tid / 32, row tid % 32; threads 128..255 the plane below), all four units' loads are issued
+// together, their non-zero elements become records (row in the unit, k, TRUE value: the pattern with the plane's and the
+// row's scale undone) in lds.rec and lds.val, in a fixed order (thread, unit, position).  Returns how many (0: no more).  256
+// threads; a barrier lies between the use of the records and the next call.
+__device__ __forceinline__ int tail_group(const u32x4 *__restrict__ W, const Planes &pl, size_t urow, int kblocks, TailLds &lds, TailWalk &w)
+{
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int ub0 = col0 / kUnitRows;                // first unit of B of this block
-    const int nub = min(cols / kUnitRows, (N + kRowPad - 1) / kRowPad * (kRowPad / kUnitRows) - ub0);   // B is padded to whole groups of 8 units
-
-    // how many elements outside plane 0 A's row of units and B's rows of units hold (counted by the prepare pass)
-    const uint32_t cnt_a = pa.rec_cnt[rb];
-    const bool do_a = cnt_a != 0u;
-    const bool do_b = __syncthreads_or(tid < nub && pb.rec_cnt[ub0 + tid] != 0u ? 1 : 0) != 0;
-    if (!do_a && !do_b) return;
-
-    // The records of a row of units whose count fits its list: read, and put into the order (k, row) -- the
-    // prepare pass appends them in whatever order its workgroups run, and the additions below must not depend
-    // on that.  One barrier before (the record arrays are free), one after.
-    auto take_list = [&](const Planes &pl, size_t urow, int n) __attribute__((always_inline)) {
-        uint32_t key = 0u, val = 0u;
-        if (tid < n) {
-            key = pl.recs[(urow * kRecCap + tid) * 2];
-            val = pl.recs[(urow * kRecCap + tid) * 2 + 1];
-            s_list[tid] = key;
-        }
-        __syncthreads();
-        if (tid < n) {
-            int rank = 0;
-            for (int i = 0; i < n; ++i) rank += s_list[i] < key ? 1 : 0;
-            s_rec[rank] = key;
-            s_val[rank] = __uint_as_float(val);
-        }
-        __syncthreads();
-    };
-
     // Ordered compaction over the workgroup: thread t contributes `have` items; returns the index of its
     // first one and, in total, the number of items.  Two barriers.
     auto place = [&](int have, int &total) __attribute__((always_inline)) {
@@ -101,87 +112,122 @@ __device__ __forceinline__ void planes_tail_body(const u32x4 *__restrict__ Aw, c
             const int up = __shfl_up(incl, off, 64);
             if (lane >= off) incl += up;
         }
-        __syncthreads();                                   // s_cnt is free again
-        if (lane == 63) s_cnt[wave] = incl;
+        __syncthreads();                                   // lds.cnt is free again
+        if (lane == 63) lds.cnt[wave] = incl;
         __syncthreads();
         int before = 0;
         total = 0;
 #pragma unroll
         for (int q = 0; q < 4; ++q) {
-            before += q < wave ? s_cnt[q] : 0;
-            total += s_cnt[q];
+            before += q < wave ? lds.cnt[q] : 0;
+            total += lds.cnt[q];
         }
+        total = __builtin_amdgcn_readfirstlane(total);
         return before + incl - have;
     };
-
-    // Walks the units of one row of units (mask row urow of operand W / pl, row scales S32) that have
-    // other planes, k ascending, four units at a time: the two other planes of a unit are 256 vectors, one
-    // per thread (threads 0..127 the plane above, vector tid: k-chunk tid / 32, row tid % 32; threads
-    // 128..255 the plane below), all four units' loads are issued together, their non-zero elements become
-    // records (row in the unit, k, TRUE value: the pattern with the plane's and the row's scale undone) in a
-    // fixed order (thread, unit, position), and `apply(n)` uses up the n records of the group.
-    auto walk = [&](const u32x4 *__restrict__ W, const Planes &pl, size_t urow, const int *S32, uint32_t first, bool have_first,
-                    auto &&apply) {
-        const int q = tid < kUnitVec ? 1 : 2, vec = tid & (kUnitVec - 1);
-        const int r = vec & 31, c = vec >> 5;
-        const int undo = -(S32[r] + (q == 1 ? -pl.w : pl.w));   // the plane above carries 2^(S - w), the one below 2^(S + w)
-        for (int base = 0; base < kblocks; base += 256) {
-            const int kb = base + tid;
-            const uint32_t m = base == 0 && have_first ? first : (kb < kblocks ? (uint32_t)pl.mask[urow * kblocks + kb] & 6u : 0u);
-            int total;
-            const int at = place(m != 0u ? 1 : 0, total);
-            if (m != 0u) s_list[at] = (uint32_t)tid | (m << 16);
+    const int q = tid < kUnitVec ? 1 : 2, vec = tid & (kUnitVec - 1);
+    const int r = vec & 31, c = vec >> 5;
+    const int undo = -(pl.S[urow * kUnitRows + r] + (q == 1 ? -pl.w : pl.w));   // the plane above carries 2^(S - w), the one below 2^(S + w)
+    for (;;) {
+        if (w.total < 0) {
+            if (w.base >= kblocks) return 0;
+            const int kb = w.base + tid;
+            const uint32_t m = kb < kblocks ? (uint32_t)pl.mask[urow * kblocks + kb] & 6u : 0u;
+            const int at = place(m != 0u ? 1 : 0, w.total);
+            if (m != 0u) lds.list[at] = (uint32_t)tid | (m << 16);
             __syncthreads();
-            for (int n0 = 0; n0 < total; n0 += 4) {
-                u32x4 v[4];
-                int kbn[4];
-#pragma unroll
-                for (int u = 0; u < 4; ++u) {
-                    const uint32_t e = n0 + u < total ? s_list[n0 + u] : 0u;
-                    kbn[u] = base + (int)(e & 0xFFFFu);
-                    v[u] = u32x4{0u, 0u, 0u, 0u};
-                    if ((e >> (16 + q)) & 1u) v[u] = W[(size_t)q * pl.plane + (urow * kblocks + kbn[u]) * kUnitVec + vec];
-                }
-                // records of unit u (all four: u < 0) and plane qq (both: qq == 0) of this group, then their use
-                auto emit = [&](int only_u, int only_q) {
-                    const bool mine = only_q == 0 || only_q == q;
-                    int cnt = 0;
-#pragma unroll
-                    for (int u = 0; u < 4; ++u)
-                        if (mine && (only_u < 0 || only_u == u)) {
-#pragma unroll
-                            for (int t = 0; t < 8; ++t) cnt += (((t & 1) ? v[u][t >> 1] >> 16 : v[u][t >> 1]) & 0x7FFFu) != 0u ? 1 : 0;
-                        }
-                    int nrec;
-                    int at2 = place(cnt, nrec);
-                    if (nrec > kTailRecs) return nrec;       // workgroup-uniform: the caller splits the group
-                    if (cnt) {
-#pragma unroll
-                        for (int u = 0; u < 4; ++u)
-                            if (only_u < 0 || only_u == u) {
-#pragma unroll
-                                for (int t = 0; t < 8; ++t) {
-                                    const uint32_t hp = ((t & 1) ? v[u][t >> 1] >> 16 : v[u][t >> 1]) & 0xFFFFu;
-                                    if (hp & 0x7FFFu) {
-                                        s_rec[at2] = (uint32_t)r | ((uint32_t)(kbn[u] * kUnitK + c * 8 + t) << 5);
-                                        s_val[at2] = ldexpf(static_cast<float>(__builtin_bit_cast(_Float16, (uint16_t)hp)), undo);
-                                        ++at2;
-                                    }
-                                }
-                            }
-                    }
-                    __syncthreads();
-                    apply(nrec);
-                    __syncthreads();                         // the records are free again
-                    return nrec;
-                };
-                if (emit(-1, 0) > kTailRecs) {               // rare: many elements outside plane 0 -- one plane of one unit at a time
-                    for (int u = 0; u < 4; ++u)
-                        for (int qq = 1; qq <= 2; ++qq) (void)emit(u, qq);
-                }
-            }
+            w.at = 0;
         }
-    };
+        if (w.at >= w.total) {
+            w.base += 256;
+            w.total = -1;
+            continue;
+        }
+        u32x4 v[4];
+        int kbn[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            const uint32_t e = w.at + u < w.total ? lds.list[w.at + u] : 0u;
+            kbn[u] = w.base + (int)(e & 0xFFFFu);
+            v[u] = u32x4{0u, 0u, 0u, 0u};
+            if ((e >> (16 + q)) & 1u) v[u] = W[(size_t)q * pl.plane + (urow * kblocks + kbn[u]) * kUnitVec + vec];
+        }
+        // part 0: the whole group; where that does not fit (rare: many elements outside plane 0), parts 1 to 8: one plane of one unit each
+        const int only_u = w.part == 0 ? -1 : (w.part - 1) >> 1;
+        const bool mine = w.part == 0 || 1 + ((w.part - 1) & 1) == q;
+        int cnt = 0;
+#pragma unroll
+        for (int u = 0; u < 4; ++u)
+            if (mine && (only_u < 0 || only_u == u)) {
+#pragma unroll
+                for (int t = 0; t < 8; ++t) cnt += (((t & 1) ? v[u][t >> 1] >> 16 : v[u][t >> 1]) & 0x7FFFu) != 0u ? 1 : 0;
+            }
+        int n;
+        int to = place(cnt, n);
+        if (n > kTailRecs) {                                 // the same in the workgroup
+            w.part = 1;
+            continue;
+        }
+        w.part = w.part == 0 || w.part == 8 ? 0 : w.part + 1;
+        if (w.part == 0) w.at += 4;
+        if (n == 0) continue;
+        if (cnt) {
+#pragma unroll
+            for (int u = 0; u < 4; ++u)
+                if (only_u < 0 || only_u == u) {
+#pragma unroll
+                    for (int t = 0; t < 8; ++t) {
+                        const uint32_t hp = ((t & 1) ? v[u][t >> 1] >> 16 : v[u][t >> 1]) & 0xFFFFu;
+                        if (hp & 0x7FFFu) {
+                            lds.rec[to] = (uint32_t)r | ((uint32_t)(kbn[u] * kUnitK + c * 8 + t) << 5);
+                            lds.val[to] = ldexpf(static_cast<float>(__builtin_bit_cast(_Float16, (uint16_t)hp)), undo);
+                            ++to;
+                        }
+                    }
+                }
+        }
+        __syncthreads();
+        return n;
+    }
+}
+
+// Hands the `count` (not zero) elements outside plane 0 of row of units urow to apply(n), n records at a time.
+template <class APPLY>
+__device__ __forceinline__ void tail_records(const u32x4 *__restrict__ W, const Planes &pl, size_t urow, int kblocks, uint32_t count,
+                                             TailLds &lds, APPLY &&apply)
+{
+    if (count <= (uint32_t)kRecCap) {
+        const uint32_t counts[1] = {count};
+        tail_lists<1>(pl, urow, counts, lds);
+        apply((int)count);
+        __syncthreads();                                     // the records are free again
+        return;
+    }
+    TailWalk w;
+    for (;;) {
+        const int n = tail_group(W, pl, urow, kblocks, lds, w);
+        if (n == 0) return;
+        apply(n);
+        __syncthreads();
+    }
+}
+
+// The block of C of row unit rb and the columns [col0, col0 + cols); 256 threads, col0 and cols multiples of 32.
+__device__ __forceinline__ void planes_tail_body(const u32x4 *__restrict__ Aw, const u32x4 *__restrict__ Bw, const Planes &pa,
+                                                 const Planes &pb, float *__restrict__ C, int64_t ldc, int M, int N, int kblocks,
+                                                 int rb, int col0, int cols, TailLds &lds)
+{
+    uint32_t(&s_rec)[kTailRecs] = lds.rec;
+    float(&s_val)[kTailRecs] = lds.val;
+    const int tid = threadIdx.x;
+    const int ub0 = col0 / kUnitRows;                // first unit of B of this block
+    const int nub = min(cols / kUnitRows, (N + kRowPad - 1) / kRowPad * (kRowPad / kUnitRows) - ub0);   // B is padded to whole groups of 8 units
+
+    // how many elements outside plane 0 A's row of units and B's rows of units hold (counted by the prepare pass)
+    const uint32_t cnt_a = pa.rec_cnt[rb];
+    const bool do_a = cnt_a != 0u;
+    const bool do_b = __syncthreads_or(tid < nub && pb.rec_cnt[ub0 + tid] != 0u ? 1 : 0) != 0;
+    if (!do_a && !do_b) return;
 
     if (do_a) {
         // 1. this block's columns of thread tid, one after the other: C[row][col] += a * b(k, col) for the
@@ -240,13 +286,7 @@ __device__ __forceinline__ void planes_tail_body(const u32x4 *__restrict__ Aw, c
             }
           }
         };
-        if (cnt_a <= (uint32_t)kRecCap) {
-            take_list(pa, (size_t)rb, (int)cnt_a);
-            apply_a((int)cnt_a);
-            __syncthreads();                                 // the records are free again
-        } else {
-            walk(Aw, pa, (size_t)rb, pa.S + rb * kUnitRows, 0u, false, apply_a);
-        }
+        tail_records(Aw, pa, (size_t)rb, kblocks, cnt_a, lds, apply_a);
     }
     if (do_b) {
         // 2. the rows of this block, one per lane of the first half-wave: C[row][col0] += a0(row, k) * b
@@ -269,15 +309,137 @@ __device__ __forceinline__ void planes_tail_body(const u32x4 *__restrict__ Aw, c
                     *dst = __fmaf_rn(a, s_val[i], *dst);
                 }
             };
-            if (cnt_b <= (uint32_t)kRecCap) {
-                take_list(pb, (size_t)ub, (int)cnt_b);
-                apply_b((int)cnt_b);
-                __syncthreads();
-            } else {
-                walk(Bw, pb, (size_t)ub, pb.S + ub * kUnitRows, 0u, false, apply_b);
-            }
+            tail_records(Bw, pb, (size_t)ub, kblocks, cnt_b, lds, apply_b);
         }
     }
+}
+
+// The same products for a workgroup's tile whose sums (scales undone) wait in LDS: the same additions to every element in the same
+// order.  A thread owns the tile's elements of one column (A's records) or one row (B's) and of every second or fourth row or
+// column, and takes eight records at a time, the loads of what they meet side by side.
+// A function that is called, with the sums in LDS meanwhile: inlined beside the accumulators it takes the registers of the common case
+// (128 x 128 with statistics: 800 spills; 4096 x 3072 x 1024 in 1/6/9 74 us instead of 49), and handed the accumulators it
+// passes them through memory.  That layer with 0.05 / 1 % of X outside plane 0: 101 / 810 us; 210 / 1320 where they were added to
+// sums in C, which were then rounded one by one; 82 / 490 with product, tail kernel and pass, which find the records of a row of
+// units once per 256 columns and more, not once per 128.  Other tiles, 2048 x 2048 x 512: 36 / 190, 56 / 320, 41 / 130.
+template <class T> using lds_ptr = __attribute__((address_space(3))) T *;
+
+// A 64 TM x 64 TN tile of sums in LDS, R rows in each of up to four arrays; columns in groups of four, which move with the row so that
+// a column's elements lie in 16 different groups of banks.
+template <int TM, int TN, int R> struct TailTile {
+    lds_ptr<float> s[4];
+    __device__ __forceinline__ lds_ptr<float> at(int row, int col) const
+    {
+        const int i = row / R;
+        const lds_ptr<float> base = i == 0 ? s[0] : i == 1 ? s[1] : i == 2 ? s[2] : s[3];
+        return base + (row - i * R) * (64 * TN) + (col ^ ((row & 15) << 2));
+    }
+};
+
+template <int TM, int TN, int R>
+__device__ __attribute__((noinline)) void tail_tile(const u32x4 *__restrict__ Aw, const u32x4 *__restrict__ Bw, Planes pa, Planes pb, int kblocks,
+                                                    int tm, int tn, TailTile<TM, TN, R> tile, lds_ptr<TailLds> ldsp)
+{
+    constexpr int UA = 2 * TM, UB = 2 * TN, kA = 64 * TM, kB = 64 * TN, kU = 8;
+    TailLds &lds = *(TailLds *)ldsp;
+    const int tid = threadIdx.x;
+    uint32_t count_a[UA], count_b[UB];               // (read again: as arguments they cost the common case 1 us of 40)
+#pragma unroll
+    for (int u = 0; u < UA; ++u) count_a[u] = pa.rec_cnt[tm * UA + u];
+#pragma unroll
+    for (int u = 0; u < UB; ++u) count_b[u] = pb.rec_cnt[tn * UB + u];
+
+    // apply(n, unit_of): n records in lds, unit_of(i) the row of units of the i-th; first those of all rows of units whose lists hold
+    // them, then the others', one row after the other
+    auto records = [&](const u32x4 *__restrict__ W, const Planes &pl, int unit0, const auto &count, auto &&apply) __attribute__((always_inline)) {
+        constexpr int U = sizeof(count) / sizeof(count[0]);
+        int first[U + 1];                            // of the listed records, the first of each row of units
+        uint32_t many = 0u;                          // rows of units with more than their lists hold, a bit each
+        first[0] = 0;
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const bool listed = count[u] <= (uint32_t)kRecCap;
+            first[u + 1] = __builtin_amdgcn_readfirstlane(first[u] + (listed ? (int)count[u] : 0));
+            many |= listed ? 0u : 1u << u;
+        }
+        many = (uint32_t)__builtin_amdgcn_readfirstlane((int)many);
+#pragma unroll 1
+        for (int turn = -1; turn < U; ++turn) {
+            if (turn < 0 ? first[U] == 0 : ((many >> turn) & 1u) == 0u) continue;
+            TailWalk w;
+            for (;;) {
+                int n = first[U];
+                if (turn < 0) tail_lists(pl, (size_t)unit0, count, lds);
+                else n = tail_group(W, pl, (size_t)(unit0 + turn), kblocks, lds, w);
+                if (n == 0) break;
+                apply(n, [&](int i) __attribute__((always_inline)) {
+                    int unit = 0;
+#pragma unroll
+                    for (int u = 1; u < U; ++u) unit += i >= first[u] ? 1 : 0;
+                    return turn < 0 ? unit : turn;
+                });
+                __syncthreads();                     // the records are free again
+                if (turn < 0) break;
+            }
+        }
+    };
+    // pattern of the binary16 value of plane 0 at (row of the operand's rows from unit0, k)
+    auto plane0 = [&](const u32x4 *__restrict__ W, size_t uidx, int row, int k) __attribute__((always_inline)) {
+        return reinterpret_cast<const uint16_t *>(W + uidx * kUnitVec + (size_t)(k % kUnitK / 8 * kUnitRows + row % kUnitRows))[k % 8];
+    };
+
+    records(Aw, pa, tm * UA, count_a, [&](int n, auto &&unit_of) __attribute__((always_inline)) {
+        constexpr int kParts = 256 / kB;
+        const int col = tid % kB, part = tid / kB, sb = pb.S[tn * kB + col];
+        const size_t unit = (size_t)(tn * UB + col / kUnitRows) * kblocks;
+#pragma unroll 1
+        for (int i0 = 0; i0 < n; i0 += kU) {
+            uint32_t rec[kU], x[kU], mk[kU];
+#pragma unroll
+            for (int q = 0; q < kU; ++q) {
+                rec[q] = lds.rec[min(i0 + q, n - 1)];
+                x[q] = mk[q] = 0u;
+                if ((int)(rec[q] % kParts) == part) {
+                    const int k = (int)(rec[q] >> 5);
+                    x[q] = plane0(Bw, unit + k / kUnitK, col, k);
+                    mk[q] = pb.mask[unit + k / kUnitK];
+                }
+            }
+#pragma unroll
+            for (int q = 0; q < kU; ++q) {
+                if (i0 + q >= n || (int)(rec[q] % kParts) != part) continue;
+                const int k = (int)(rec[q] >> 5);
+                float y = static_cast<float>(__builtin_bit_cast(_Float16, (uint16_t)x[q]));
+                if (mk[q] & 6u) y = unit_value(Bw, (unit + k / kUnitK) * kUnitVec, pb, mk[q], k % kUnitK / 8, col % kUnitRows, k % 8);
+                const lds_ptr<float> sum = tile.at(unit_of(i0 + q) * kUnitRows + (int)(rec[q] & 31u), col);
+                *sum = __fmaf_rn(lds.val[i0 + q], ldexpf(y, -sb), *sum);
+            }
+        }
+    });
+    // an element of A outside plane 0 has met B's above: plane 0 only
+    records(Bw, pb, tn * UB, count_b, [&](int n, auto &&unit_of) __attribute__((always_inline)) {
+        constexpr int kParts = 256 / kA;
+        const int row = tid % kA, part = tid / kA, sa = pa.S[tm * kA + row];
+        const size_t unit = (size_t)(tm * UA + row / kUnitRows) * kblocks;
+#pragma unroll 1
+        for (int i0 = 0; i0 < n; i0 += kU) {
+            uint32_t rec[kU], x[kU];
+#pragma unroll
+            for (int q = 0; q < kU; ++q) {
+                rec[q] = lds.rec[min(i0 + q, n - 1)];
+                const int k = (int)(rec[q] >> 5);
+                x[q] = 0u;
+                if ((int)(rec[q] % kParts) == part) x[q] = plane0(Aw, unit + k / kUnitK, row, k);
+            }
+#pragma unroll
+            for (int q = 0; q < kU; ++q) {
+                if (i0 + q >= n || (int)(rec[q] % kParts) != part) continue;
+                const float y = ldexpf(static_cast<float>(__builtin_bit_cast(_Float16, (uint16_t)x[q])), -sa);
+                const lds_ptr<float> sum = tile.at(row, unit_of(i0 + q) * kUnitRows + (int)(rec[q] & 31u));
+                *sum = __fmaf_rn(y, lds.val[i0 + q], *sum);
+            }
+        }
+    });
 }
 
 }  // namespace fmt

@@ -455,3 +455,64 @@ def test_layers_of_several_pieces_repeat(fmt, e, m, d):
     want = fmt.fmt_quantize(fmt.fmt_quantize(fmt.fmt_gemm_prepared(Xp, Wp), f) + fmt.fmt_quantize(b, f), f)
     for _ in range(40):
         assert torch.equal(fmt.fmt_linear_prepared(Xp, Wp, b), want)
+
+
+@pytest.mark.parametrize("tile", ["1,1,1", "2,1,1", "2,2,1"])
+@pytest.mark.parametrize("m,d", [(9, True), (8, False)])
+def test_layers_with_many_elements_outside_plane_0(fmt, m, d, tile, monkeypatch):
+    """Rows of units of both operands whose elements outside plane 0 fill part of their list, all of it, more than it holds, and more
+    than are taken at a time, beside ones that have none: the outputs of the separate calls bit for bit, in both directions
+    (the operands swapped), with outputs near the format's largest value in some waves."""
+    monkeypatch.setenv("FMT_GEMM_WINDOW", "1")
+    monkeypatch.setenv("FMT_GEMM_PLAN", tile)
+    f = (6, m, d)
+    M, N, K = 300, 392, 328
+    rng = np.random.default_rng(m)
+
+    def operand(rows, scale):
+        X = (rng.standard_normal((rows, K)) * scale).astype(np.float32)
+        X[:70] = workloads.log2_normal((70, K), -12.0, 9.0, 0.05, rng)            # two full rows of units: thousands, a third per unit of k
+        X[97] = workloads.log2_normal((K,), -12.0, 9.0, 0.0, rng)                 # one row: more than the list
+        X[130, ::5] = 2.0 ** -36                                                  # the list and a few more, or just below
+        X[161, 3], X[170, 40] = 2.0 ** -38, 3.0e8                                 # a few
+        return X
+
+    X, W = operand(M, 1.0), operand(N, 0.05)
+    X[200:210, 0] = 3.0e9
+    W[300:310, 0] = 1.2
+    b = torch.from_numpy(rng.standard_normal(N).astype(np.float32)).cuda()
+    for x, w, bias in ((X, W, b), (W, X, None)):
+        x, w = torch.from_numpy(x).cuda(), torch.from_numpy(w).cuda()
+        xp, wp = fmt.fmt_prepare(x, f), fmt.fmt_prepare(w, f)
+        t = fmt.fmt_quantize(fmt.fmt_gemm_prepared(xp, wp), f)
+        if bias is not None:
+            t = t + fmt.fmt_quantize(bias, f)
+        want, hw, h = fmt.fmt_quantize(t, f), fmt.fmt_histogram(t, f), fmt.new_hist()
+        for _ in range(3):
+            for y in (fmt.fmt_linear_prepared(xp, wp, bias, hist=h), fmt.fmt_linear_prepared(xp, wp, bias)):
+                torch.cuda.synchronize()
+                nan = torch.isnan(want)
+                assert torch.equal(torch.isnan(y), nan)
+                assert torch.equal(y[~nan].view(torch.int32), want[~nan].view(torch.int32))
+            assert torch.equal(h, hw)
+
+
+@pytest.mark.parametrize("tile", ["1,1,1", "2,1,1", "2,2,1"])
+@pytest.mark.parametrize("e,m,d", [(5, 10, True), (6, 9, True), (8, 7, False), (7, 12, True)])
+def test_layers_repeat(fmt, e, m, d, tile, monkeypatch):
+    """The layer's kernels on every tile, with one and two pieces and with planes, with and without statistics: the same outputs and
+    counts in every call, those of the separate calls.  k leaves every remainder of the turns of the stage ring."""
+    monkeypatch.setenv("FMT_GEMM_WINDOW", "1")
+    monkeypatch.setenv("FMT_GEMM_PLAN", tile)
+    f = (e, m, d)
+    M, N = 1100, 1204
+    g = torch.Generator(device="cuda").manual_seed(5)
+    for K in (488, 520, 552, 584):
+        X, W = torch.randn(M, K, generator=g, device="cuda"), torch.randn(N, K, generator=g, device="cuda") * 0.05
+        b = torch.randn(N, generator=g, device="cuda")
+        Xp, Wp = fmt.fmt_prepare(X, f), fmt.fmt_prepare(W, f)
+        t = fmt.fmt_quantize(fmt.fmt_gemm_prepared(Xp, Wp), f) + fmt.fmt_quantize(b, f)
+        want, hw, h = fmt.fmt_quantize(t, f), fmt.fmt_histogram(t, f), fmt.new_hist()
+        for i in range(12):
+            assert torch.equal(fmt.fmt_linear_prepared(Xp, Wp, b), want), (K, i)
+            assert torch.equal(fmt.fmt_linear_prepared(Xp, Wp, b, hist=h), want) and torch.equal(h, hw), (K, i)
