@@ -318,15 +318,17 @@ __global__ __launch_bounds__(256) void fmac8_kernel(const uint32_t *__restrict__
                         x[kk][i] = sb[g * 8 + kk][tx * T + i];
                     }
                 };
-                // few chains per thread: a group's operands are read ahead of its steps, which would wait for them one by one
-                if constexpr (T <= 2) {
-#pragma unroll
-                    for (int kk = 0; kk < 8; ++kk) read(kk);
-                    __builtin_amdgcn_sched_barrier(0);
-                }
+                // few chains per thread: operands are read ahead of the steps, which would wait for them one by one; with four chains half a
+                // group's at a time (a whole group's take the registers of a fifth wave per SIMD, from the single form as well: 1500 x 1500 x
+                // 256 in 1/6/9 240 us instead of 229; wide form 107 and 106)
+                constexpr int kAhead = T == 1 ? 8 : T == 2 ? 4 : 1;
 #pragma unroll
                 for (int kk = 0; kk < 8; ++kk) {
-                    if constexpr (T > 2) read(kk);
+                    if (kk % kAhead == 0) {
+#pragma unroll
+                        for (int k2 = 0; k2 < kAhead; ++k2) read(kk + k2);
+                        if (T <= 2) __builtin_amdgcn_sched_barrier(0);
+                    }
 #pragma unroll
                     for (int i = 0; i < T; ++i)
 #pragma unroll
@@ -589,7 +591,8 @@ static int launch(int transA, int transB, int M, int N, int K, const float *A, i
         // time per tile of a compute unit with work enough.  Measured in 1/6/9, wide form (us, T = 1 / 2 / 4): N = 64: 13.1 / 21.4 /
         // 57.7; 384: 23 / 22 / 58; 512: 29 / 23 / 59; 640: 44 / 32 / 59; 768: 53 / 42 / 59; 1024: 88 / 53 / 61; 1500: 185 / 109 / 127;
         // 2048: 334 / 187 / 165.  The values decide which form a stage takes; at 384 and 512, where four chains per thread would gain
-        // up to 6 us, the single form loses 35, so the line lies above them.  Where all stages take the single
+        // up to 6 us, the single form loses 35, so the line lies above them: the constants are a little above the wide form's times (with
+        // those, 13.4 / 5.4, 21.6 / 12.5 and 58 / 41, N = 448 to 576 would take four chains, and nothing else would change).  Where all stages take the single
         // form the rule is off by up to a third (640: 65 / 83 / 228; 1024: 123 / 118 / 228; 1500: 240 / 220 / 448; 2048: 426 / 367 / 497).
         int cus = 0;
         const int rc = device_cu_count(&cus);
