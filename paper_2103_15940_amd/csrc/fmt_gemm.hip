@@ -1093,26 +1093,26 @@ __global__ void zero_fill_kernel(float *__restrict__ C, int M, int N, int64_t ld
 // the time, and cutting k fills the machine at the price of writing and re-reading partial sums.
 static Plan make_plan(int M, int N, int kblocks, int cus, int pieces)
 {
-    // eff1 / effmax: relative MFMA rate of a compute unit with one / with max_occ resident workgroups; 128 x 64 is there for layers
-    // (product_of_views) and to be forced: products of their own gain by it at single sizes only (333 x 4096 x 1024 8.7 -> 7.6 us)
+    // eff1 / effmax: relative MFMA rate of a compute unit with one / with max_occ resident workgroups
     struct Shape { int tm, tn, max_occ; double eff1, effmax; };
-    static const Shape multi[6] = {
-        {4, 4, 1, 1.15, 1.15}, {4, 2, 1, 1.0, 1.0}, {2, 4, 1, 1.03, 1.03}, {2, 2, 2, 0.80, 0.95}, {1, 1, 4, 0.45, 0.78}, {2, 1, 3, 0.01, 0.01}};
+    static const Shape multi[5] = {
+        {4, 4, 1, 1.15, 1.15}, {4, 2, 1, 1.0, 1.0}, {2, 4, 1, 1.03, 1.03}, {2, 2, 2, 0.80, 0.95}, {1, 1, 4, 0.45, 0.78}};
     // one piece: a quarter of the MFMA work per byte, the small tiles lose less
-    static const Shape single[6] = {
-        {4, 4, 1, 1.21, 1.21}, {4, 2, 1, 1.0, 1.0}, {2, 4, 1, 1.03, 1.03}, {2, 2, 2, 0.98, 1.11}, {1, 1, 4, 0.53, 0.68}, {2, 1, 3, 0.01, 0.01}};
-    const Shape(&shapes)[6] = pieces == 1 ? single : multi;
+    static const Shape single[5] = {
+        {4, 4, 1, 1.21, 1.21}, {4, 2, 1, 1.0, 1.0}, {2, 4, 1, 1.03, 1.03}, {2, 2, 2, 0.98, 1.11}, {1, 1, 4, 0.53, 0.68}};
+    const Shape(&shapes)[5] = pieces == 1 ? single : multi;
     const double wg_cost = pieces == 1 ? 68.0 : 40.0, split_cost = pieces == 1 ? 5.76 : 2.5;
     if (const char *env = getenv("FMT_GEMM_PLAN")) {      // tuning override: "tm,tn,nsplit[,sched]" (other values leave the plan to the model)
-        Plan forced{2, 2, 1, 1};
+        Plan forced{2, 2, 1, 1, cus, true};
         if (sscanf(env, "%d,%d,%d,%d", &forced.tm, &forced.tn, &forced.nsplit, &forced.sched) >= 3) {
-            for (const auto &sh : shapes)
-                if (sh.tm == forced.tm && sh.tn == forced.tn && forced.nsplit >= 1 && forced.nsplit <= 64 &&
-                    lds_bytes(sh.tm, sh.tn, pieces, pipe_ks(pieces), 2) <= 160 * 1024)
-                    return forced;
+            bool known = forced.tm == 2 && forced.tn == 1;        // layers only (layer_plan); other products take 64 x 64 then
+            for (const auto &sh : shapes) known = known || (sh.tm == forced.tm && sh.tn == forced.tn);
+            if (known && forced.nsplit >= 1 && forced.nsplit <= 64 &&
+                lds_bytes(forced.tm, forced.tn, pieces, pipe_ks(pieces), 2) <= 160 * 1024)
+                return forced;
         }
     }
-    Plan best{2, 2, 1, 1};
+    Plan best{2, 2, 1, 1, cus};
     double best_t = 1e300;
     for (const auto &sh : shapes) {
         if (lds_bytes(sh.tm, sh.tn, pieces, pipe_ks(pieces), 2) > 160 * 1024) continue;
@@ -1128,7 +1128,7 @@ static Plan make_plan(int M, int N, int kblocks, int cus, int pieces)
             // MFMA time on that compute unit (arbitrary units) + start-up / epilogue cost per workgroup
             double t = per_cu * ((double)bm * bn * kb_per / eff + wg_cost * bm * bn / 128.0);
             if (ns > 1) t += split_cost * (double)M * N * (ns + 1) / cus * 8.0;   // partial sums out and back
-            if (t < best_t) { best_t = t; best = Plan{sh.tm, sh.tn, ns, 1}; }
+            if (t < best_t) { best_t = t; best = Plan{sh.tm, sh.tn, ns, 1, cus}; }
         }
     }
     return best;

@@ -117,6 +117,8 @@ struct Plan {
     int tm, tn;      // wave tile in MFMA tiles; workgroup tile = 64*tm x 64*tn
     int nsplit;      // k parts
     int sched;       // 1: pin the issue order inside a trip (sched_group_barrier), 0: leave it to the compiler
+    int cus = 256;   // compute units it was made for
+    bool forced = false;     // by FMT_GEMM_PLAN
 };
 
 constexpr size_t lds_bytes(int tm, int tn, int pieces, int ks, int nst)

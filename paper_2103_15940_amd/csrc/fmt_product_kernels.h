@@ -827,7 +827,6 @@ int product_of_views(const OperandView &va, const OperandView &vb, int M, int N,
     if (plan.tm == 4 && plan.tn == 2) return FMT_PRODUCT(4, 2);
     if (plan.tm == 2 && plan.tn == 4) return FMT_PRODUCT(2, 4);
     if (plan.tm == 2 && plan.tn == 2) return FMT_PRODUCT(2, 2);
-    if (plan.tm == 2 && plan.tn == 1) return FMT_PRODUCT(2, 1);
     return FMT_PRODUCT(1, 1);
 #undef FMT_PRODUCT
 }
