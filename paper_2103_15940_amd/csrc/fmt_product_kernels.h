@@ -779,6 +779,58 @@ static int launch_product_linear_t(const OperandView &va, const OperandView &vb,
                 : launch_product_linear<PS, TM, TN, false, false>(va, vb, out, M, N, kblocks, stream);
 }
 
+// Whether a layer's roundings have the short forms and statistics that the product's kernel knows: not where statistics reach below
+// 2^-126 (rows for fp32 denormals).
+template <int PS>
+static bool layer_in_product(const LinearOut &lin)
+{
+    if (lin.hist != nullptr && lin.p.exp_lo < -126) return false;
+    return PS < 3;               // formats of three pieces keep the pass
+}
+
+// The tile of a layer that ends in the product's kernel, from the plan of its product.  The roundings behind the sums gain by
+// company on the compute unit, the sums by large tiles, so the line goes by k.  (Tiles per compute unit: of 128 x 128.)
+template <int PS>
+static Plan layer_plan(const Plan &plan, const LinearOut &lin, int M, int N, int kblocks)
+{
+    Plan p = plan;
+    if (p.forced || PS == 3) return p;               // three pieces: 128 x 128 is the best of the tiles that round (9 products per value)
+    const bool hist = lin.hist != nullptr;
+    const int64_t tiles_m = ((int64_t)M + 127) / 128, tiles_n = ((int64_t)N + 127) / 128, tiles = tiles_m * tiles_n, cus = plan.cus;
+    const int64_t outputs = (int64_t)M * N;
+    if (p.tm * p.tn > 4 && kblocks <= 48) {
+        // 128 x 128 instead of 256 x 256 (or 128 x 256) and a pass, up to k = 1536 (us, with statistics, 1/6/9: 4096 x 4096 x 1024 71 / 61;
+        // 8192 x 4096 x 1536 154 / 143; k = 2048: alike, 4096: 256 x 256 is better).  From 2^26 outputs the chip's reads and stores
+        // count as well.  Where the XCDs' runs of tiles are whole groups of tile rows, or whole groups whole runs, they walk in step,
+        // a power of two of bytes apart, and 128 x 128 loses from k = 512 with 8192 columns and more (8192 x 8192 x 1024 in 1/5/10
+        // 266 / 299, x 512 218 / 222; 8320 x 8192 x 1024, not in step, 287 / 254), from k = 1024 with fewer (32768 x 2048 x 1024
+        // 258 / 261, x 1536 309 / 342; 33000 x 2048 x 1536 349 / 341).  From 2^27 outputs k = 1536 is too long in any case, from 2^28
+        // being in step counts no more (16384 x 16384 x 512 1050 / 846, x 1024 1205 / 1113).
+        const int64_t per_xcd = tiles / 8, group = 8 * tiles_n;
+        const bool in_step = tiles % 8 == 0 && (per_xcd % group == 0 || group % per_xcd == 0);
+        const int most = outputs < ((int64_t)1 << 26)              ? 48
+                         : in_step && outputs < ((int64_t)1 << 28) ? (N > 4096 ? (hist ? 8 : 16) : 32)
+                         : outputs < ((int64_t)1 << 27)            ? 48
+                                                                   : 32;
+        if (kblocks <= most) p.tm = p.tn = 2;
+    } else if (p.tm == 2 && p.tn == 2) {
+        // 128 x 64 instead of 128 x 128: three workgroups per compute unit instead of two share the roundings.  Times of 128 x 64 over
+        // 128 x 128 with one piece, with statistics / without:
+        //   k up to 256    0.86 - 0.97 / 0.78 - 0.90 at 0.75 to 9 tiles per compute unit, 1 at 24
+        //   k = 512        0.88 - 1.02 / 0.83 - 0.98 at 0.75 to 9, 1.05 / 1.1 at 24
+        //   k = 1024       0.92 - 0.99 / 0.90 - 1.0 up to 1.5 tiles, 0.92 / 0.94 at 2.25, 1.03 / 1.02 at 3, 1.07 / 1.06 at 9
+        //   k = 1536       0.96 - 1.01 / 0.95 - 1.06 up to 1.5 tiles, 1.08 / 1.1 at 3
+        // and two pieces as half as long a k.  Between 1.5 and 2 tiles, which 128 x 128 takes in one round, with statistics 1.01 - 1.07.
+        const int one = PS == 2 ? kblocks * 2 : kblocks;     // as if of one piece
+        const bool few = 2 * tiles < 5 * cus, one_round = hist && tiles <= 2 * cus && 2 * tiles > 3 * cus;
+        if (!one_round && (one <= 8 || (one <= 16 && tiles <= 12 * cus) || (few && one <= (hist ? 48 : 32)))) p.tn = 1;
+    }
+    // a quad that N cuts is in the common case of the smaller tiles only (as 128 x 128 / 128 x 64, with statistics, us:
+    // 4096 x 3003 x 1024 in 1/6/9 86 / 59; 1001 x 3003 x 2500 62 / 33)
+    if (p.tm == 2 && p.tn == 2 && (N & 3) != 0) p.tn = 1;
+    return p;
+}
+
 template <int PS>
 int product_of_views(const OperandView &va, const OperandView &vb, int M, int N, int kblocks, const OutSpec &out,
                             const Plan &plan, float *part, hipStream_t stream)
@@ -786,39 +838,16 @@ int product_of_views(const OperandView &va, const OperandView &vb, int M, int N,
     // A layer's output roundings, statistics and codes in the product's kernel: where the product leaves whole sums in one launch, and for
     // tiles of up to 128 x 128 (two workgroups and more per compute unit, so that the roundings of one run beside the products of
     // another; a 256 x 256 tile has neither the registers nor the company).  Measured, product (with planes: and the launch that adds
-    // the elements outside plane 0) and pass against one kernel, us: 4096 x 3072 x 1024 in 1/6/9 with statistics 64 -> 55, without 58 -> 46,
-    // in 1/8/7 59 -> 49 and 51 -> 45; 1/8/7 without statistics 64 x 128 x 128 8.7 -> 5.4, 333 x 4096 x 1024 14.2 -> 9.8, 2048 x 2048 x 512
-    // 24.4 -> 18.9.  (4096 x 3072: 768 tiles on 512 slots; both workgroups of a compute unit come to their roundings at the same time.)
-    // Formats of three pieces keep the pass.
-    if constexpr (PS < 3) {
-        const bool deep = out.lin != nullptr && out.lin->hist != nullptr && out.lin->p.exp_lo < -126;     // rows for fp32 denormals: the pass has them
-        if (out.lin != nullptr && out.img == 0 && plan.nsplit == 1 && !deep) {
-            // The tile, where the sums do not take so long that the roundings behind them are a small part (k up to 1536).  128 x 64
-            // instead of 128 x 128: three workgroups per compute unit instead of two share the roundings, up to two 128 x 128 tiles per
-            // compute unit with planes, at any size without (us, 128 x 128 / 128 x 64: 2048 x 2048 x 512 with statistics 23.4 / 18.4
-            // in 1/6/9, 19.6 / 17.4 in 1/8/7; 4096 x 1024 x 1024 27.5 / 23.3 and 23.4 / 21.9; 4096 x 3072 x 1024 in 1/8/7 52.3 / 50.1,
-            // without statistics 48.3 / 45.3; not: with planes and statistics 52.8 / 61.6, 4096 x 1024 x 4096 42.5 / 46.0).
-            // 128 x 128 instead of 256 x 256 and a pass (4096 x 4096 x 1024: with statistics 72.9 -> 64.7 in 1/6/9 and 68.8 -> 60.2
-            // in 1/8/7; without 68.5 -> 56.1 and 63.0 -> 55.3).
-            Plan p = plan;
-            if (kblocks <= 48 && getenv("FMT_GEMM_PLAN") == nullptr) {
-                int cus = 0;
-                const int rcc = device_cu_count(&cus);
-                if (rcc != FMT_OK) return rcc;
-                const int64_t tiles = (((int64_t)M + 127) / 128) * (((int64_t)N + 127) / 128);
-                if (p.tm * p.tn > 4) p.tm = p.tn = 2;
-                else if (p.tm == 2 && p.tn == 2 && (va.pl.S == nullptr || tiles <= 2 * (int64_t)cus)) p.tn = 1;
-            }
-            // a last quad cut by N is in the common case of the smaller tiles only (as 128 x 128 / 128 x 64, with statistics, us:
-            // 4096 x 3003 x 1024 in 1/6/9 86 / 59; 1001 x 3003 x 2500 62 / 33)
-            if (p.tm == 2 && p.tn == 2 && (N & 3) != 0) p.tn = 1;
-            if (p.tm <= 2 && p.tn <= 2) {
-                const int rc = p.tm == 2 ? (p.tn == 2 ? launch_product_linear_t<PS, 2, 2>(va, vb, out, M, N, kblocks, stream)
-                                                      : launch_product_linear_t<PS, 2, 1>(va, vb, out, M, N, kblocks, stream))
-                                         : launch_product_linear_t<PS, 1, 1>(va, vb, out, M, N, kblocks, stream);
-                if (rc == FMT_OK) *out.rounded = true;
-                return rc;
-            }
+    // the elements outside plane 0) and pass against one kernel, us: 4096 x 3072 x 1024 in 1/6/9 with statistics 59 -> 49, without 54 -> 40,
+    // in 1/8/7 55 -> 46 and 46 -> 39; 333 x 4096 x 1024 in 1/6/9 22.0 -> 13.5 and 15.6 -> 9.7.
+    if (out.lin != nullptr && out.img == 0 && plan.nsplit == 1 && layer_in_product<PS>(*out.lin)) {
+        const Plan p = layer_plan<PS>(plan, *out.lin, M, N, kblocks);
+        if (p.tm <= 2 && p.tn <= 2 && (p.tn == 1 || (N & 3) == 0)) {
+            const int rc = p.tm == 2 ? (p.tn == 2 ? launch_product_linear_t<PS, 2, 2>(va, vb, out, M, N, kblocks, stream)
+                                                  : launch_product_linear_t<PS, 2, 1>(va, vb, out, M, N, kblocks, stream))
+                                     : launch_product_linear_t<PS, 1, 1>(va, vb, out, M, N, kblocks, stream);
+            if (rc == FMT_OK) *out.rounded = true;
+            return rc;
         }
     }
 #define FMT_PRODUCT(TMV, TNV) \
