@@ -780,12 +780,12 @@ static int launch_product_linear_t(const OperandView &va, const OperandView &vb,
 }
 
 // Whether a layer's roundings have the short forms and statistics that the product's kernel knows: not where statistics reach below
-// 2^-126 (rows for fp32 denormals).
+// 2^-126 (rows for fp32 denormals), and not with 23 and more bits of significand in formats with e < 8.
 template <int PS>
 static bool layer_in_product(const LinearOut &lin)
 {
     if (lin.hist != nullptr && lin.p.exp_lo < -126) return false;
-    return PS < 3;               // formats of three pieces keep the pass
+    return PS < 3 || lin.p.mode == kModeInteger || (lin.p.mode == kModeMagic && lin.p.shift >= 2u);
 }
 
 // The tile of a layer that ends in the product's kernel, from the plan of its product.  The roundings behind the sums gain by
@@ -839,7 +839,7 @@ int product_of_views(const OperandView &va, const OperandView &vb, int M, int N,
     // tiles of up to 128 x 128 (two workgroups and more per compute unit, so that the roundings of one run beside the products of
     // another; a 256 x 256 tile has neither the registers nor the company).  Measured, product (with planes: and the launch that adds
     // the elements outside plane 0) and pass against one kernel, us: 4096 x 3072 x 1024 in 1/6/9 with statistics 59 -> 49, without 54 -> 40,
-    // in 1/8/7 55 -> 46 and 46 -> 39; 333 x 4096 x 1024 in 1/6/9 22.0 -> 13.5 and 15.6 -> 9.7.
+    // in 1/8/7 55 -> 46 and 46 -> 39, in 1/7/20 179 -> 166 and 173 -> 158; 333 x 4096 x 1024 in 1/6/9 22.0 -> 13.5 and 15.6 -> 9.7.
     if (out.lin != nullptr && out.img == 0 && plan.nsplit == 1 && layer_in_product<PS>(*out.lin)) {
         const Plan p = layer_plan<PS>(plan, *out.lin, M, N, kblocks);
         if (p.tm <= 2 && p.tn <= 2 && (p.tn == 1 || (N & 3) == 0)) {
