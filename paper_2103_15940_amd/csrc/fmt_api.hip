@@ -497,7 +497,7 @@ int fmt_linear_prepared(const fmt_operand_t *X, const fmt_operand_t *W, const fl
     }
     hipStream_t s = static_cast<hipStream_t>(stream);
     // the product may round its sums on the way out
-    const LinearOut lin{b, X->format.denorm == 0, p, hist, nullptr, 0};
+    const LinearOut lin{{b, X->format.denorm == 0, p}, hist, nullptr, 0};
     bool rounded = false;
     rc = launch_gemm_prepared(X->data, W->data, X->rows, W->rows, X->k, X->scheme, X->format, Y, ldy, s, &lin, &rounded);
     if (rc != FMT_OK || rounded) return rc;
@@ -536,7 +536,7 @@ int fmt_linear(int64_t M, int64_t N, int64_t K,
         if (!aligned(b, 4)) return FMT_ERR_ALIGN;
         if (overlap(Y, 4 * (size_t)((M - 1) * ldy + N), b, 4 * (size_t)N)) return FMT_ERR_ALIAS;
     }
-    const LinearOut lin{b, f.denorm == 0, p, hist, nullptr, 0};
+    const LinearOut lin{{b, f.denorm == 0, p}, hist, nullptr, 0};
     bool rounded = false;
     rc = launch_gemm(0, 1, M, N, K, X, ldx, W, ldw, Y, ldy, f, p, s, &lin, &rounded);
     if (rc != FMT_OK || rounded) return rc;
@@ -599,7 +599,7 @@ int fmt_linear_pack16(int64_t M, int64_t N, int64_t K,
     float *acc = nullptr;
     rc = get_acc_scratch(s, (size_t)M * (size_t)N * sizeof(float), &acc);
     if (rc != FMT_OK) return rc;
-    const LinearOut lin{b, f.denorm == 0, p, hist, Y16, ldy};
+    const LinearOut lin{{b, f.denorm == 0, p}, hist, Y16, ldy};
     bool rounded = false;
     rc = launch_gemm(0, 1, M, N, K, X, ldx, W, ldw, acc, N, f, p, s, &lin, &rounded);
     if (rc != FMT_OK || rounded) return rc;

@@ -29,7 +29,7 @@ struct DirectOperand {
 template <int MODE, bool FTZ, int PS, bool AVEC, bool BVEC>
 __global__ __launch_bounds__(512) void direct_product_kernel(DirectOperand a, DirectOperand b, float *__restrict__ C, int64_t ldc,
                                                               int M, int N, int K, int kblocks, int tiles_m, int ntiles, int parts,
-                                                              int kb_per, int tiles_per_wg, QuantParams p, LinearOut lin, int linear)
+                                                              int kb_per, int tiles_per_wg, QuantParams p, LinearRound lin, int linear)
 {
     constexpr int P = pieces_of(PS);
     extern __shared__ float s_part[];            // parts > 1: [wave][16][64]
@@ -197,7 +197,7 @@ __global__ __launch_bounds__(512) void direct_product_kernel(DirectOperand a, Di
 
 template <int MODE, bool FTZ, int PS>
 static int launch(int M, int N, int K, const MatrixOperand &A, const MatrixOperand &B, float *C, int64_t ldc, int parts,
-                  const QuantParams &p, const LinearOut *lin, hipStream_t stream)
+                  const QuantParams &p, const LinearRound *lin, hipStream_t stream)
 {
     auto operand = [](const MatrixOperand &m, int rows) {
         return DirectOperand{reinterpret_cast<const uint32_t *>(m.X), m.kcontig ? (uint32_t)m.ld : 1u, m.kcontig ? 1u : (uint32_t)m.ld, rows};
@@ -211,14 +211,14 @@ static int launch(int M, int N, int K, const MatrixOperand &A, const MatrixOpera
                           : (B.kcontig ? direct_product_kernel<MODE, FTZ, PS, false, true> : direct_product_kernel<MODE, FTZ, PS, false, false>);
     hipLaunchKernelGGL(kern, dim3((unsigned)((tiles + per_wg - 1) / per_wg)), dim3(64 * waves), lds, stream, operand(A, M), operand(B, N), C,
                        ldc, M, N, K, kblocks, tiles_m, tiles, parts, (kblocks + parts - 1) / parts, per_wg, p,
-                       lin != nullptr ? *lin : LinearOut{}, lin != nullptr ? 1 : 0);
+                       lin != nullptr ? *lin : LinearRound{}, lin != nullptr ? 1 : 0);
     FMT_HIP_CHECK(hipGetLastError());
     return FMT_OK;
 }
 
 // C (M x N) = Q(A) Q(B)^T; K >= 1, 1 <= parts <= kDirectParts, fewer than 2^31 blocks of 32 x 32 (the caller's size limit).
 int launch_direct_product(int M, int N, int K, const MatrixOperand &A, const MatrixOperand &B, float *C, int64_t ldc, int parts, int ps,
-                          bool ftz, const QuantParams &p, const LinearOut *lin, hipStream_t stream)
+                          bool ftz, const QuantParams &p, const LinearRound *lin, hipStream_t stream)
 {
     if (parts < 1 || parts > kDirectParts) return FMT_ERR_SHAPE;
 #define FMT_RUN(MD, PSV)                                                                      \

@@ -67,13 +67,18 @@ int launch_stream_static(const float *x, float *y, size_t n, const QuantParams &
                          fmt_hist_t *hist, hipStream_t stream);
 int launch_unpack16(const uint16_t *codes, float *y, size_t n, const QuantParams &p, hipStream_t stream);
 
-// Output roundings of a fully connected layer, y = R(R(acc) + R(b)): the (unrounded) bias, or nullptr, and the format; the record of
-// the statistics of R(acc) + R(b), or nullptr; where the outputs go as 16-bit codes (leading dimension ldcodes), or nullptr: they
-// take the accumulators' place.
-struct LinearOut {
+// Output roundings of a fully connected layer, y = R(R(acc) + R(b)): the (unrounded) bias, or nullptr, and the format.
+// (What the small products' kernel takes: its arguments fill 4 cache lines of host memory, with the words of LinearOut a fifth, which
+// cost every product 0.2 of 10 us.)
+struct LinearRound {
     const float *bias;
     int32_t ftz;
     QuantParams p;
+};
+
+// And the record of the statistics of R(acc) + R(b), or nullptr; where the outputs go as 16-bit codes (leading dimension ldcodes), or
+// nullptr: they take the accumulators' place.
+struct LinearOut : LinearRound {
     fmt_hist_t *hist;
     uint16_t *codes;
     int64_t ldcodes;
@@ -95,7 +100,7 @@ struct MatrixOperand {
 constexpr int kDirectParts = 8;      // most parts of k (waves of a workgroup)
 constexpr int direct_blocks_per_workgroup(int parts) { return parts >= 4 ? 1 : 4 / parts; }   // blocks of 32 x 32 results
 int launch_direct_product(int M, int N, int K, const MatrixOperand &A, const MatrixOperand &B, float *C, int64_t ldc, int parts, int ps,
-                          bool ftz, const QuantParams &p, const LinearOut *lin, hipStream_t stream);
+                          bool ftz, const QuantParams &p, const LinearRound *lin, hipStream_t stream);
 
 // Prepared operands in caller-owned memory (fmt_gemm.hip).  scheme: opaque tag of the representation.
 int prepared_operand_bytes(int64_t rows, int64_t K, fmt_format_t f, size_t *bytes, int *scheme);

@@ -152,7 +152,7 @@ __device__ __forceinline__ uint32_t quantize_bits_rt(uint32_t u, const QuantPara
 // bias(i): its column's unrounded bias (the caller loads them early: they come from memory).  The variant of the rounding is
 // chosen once for all of them.
 template <int N, class GET, class SET, class BIAS>
-__device__ __forceinline__ void linear_round(const LinearOut &lin, GET &&get, SET &&set, BIAS &&bias)
+__device__ __forceinline__ void linear_round(const LinearRound &lin, GET &&get, SET &&set, BIAS &&bias)
 {
     const bool has_bias = lin.bias != nullptr;
     auto run = [&](auto round) __attribute__((always_inline)) {
@@ -177,7 +177,7 @@ __device__ __forceinline__ void linear_round(const LinearOut &lin, GET &&get, SE
 }
 
 // Unrounded bias of a column (0 without a bias or beyond the columns).
-__device__ __forceinline__ uint32_t linear_bias(const LinearOut &lin, int col, int N)
+__device__ __forceinline__ uint32_t linear_bias(const LinearRound &lin, int col, int N)
 {
     return lin.bias != nullptr && col < N ? __float_as_uint(lin.bias[col]) : 0u;
 }
