@@ -45,7 +45,7 @@ __global__ __launch_bounds__(512) void direct_product_kernel(DirectOperand a, Di
         for (int v = 0; v < 16; ++v) bias[v] = linear_bias(lin, col0 + (v >> 2) * 8 + (lane >> 5) * 4 + (v & 3), N);
     }
 
-    const DirectMasks masks = direct_masks(p);
+    const RoundMasks masks = round_masks(p);
 
     // Rows beyond the operand read its last row: their results are not stored.  A load's address is one that is the same in
     // the whole wave plus a lane's offset.

@@ -51,7 +51,8 @@ struct RoundMasks {
 __device__ __forceinline__ RoundMasks round_masks(const QuantParams &p)
 {
     RoundMasks k{0x7F800000u, 0x00400000u, 0x80000000u, p.minn_bits | 0x00400000u};
-    asm("" : "+s"(k.exponent), "+v"(k.half), "+s"(k.sign));
+    asm("" : "+s"(k.exponent), "+v"(k.half));
+    asm("" : "+s"(k.sign));
     return k;
 }
 
@@ -69,7 +70,7 @@ __device__ __forceinline__ bool run_is_rare(const uint32_t (&u)[N], const QuantP
 }
 
 // Q of one element with |x| < t_ovf.  e < 8: (C + x) - C with C = 1.5 * 2^(max(E, Emin) + 23 - m), whose last place is the format's step
-// for either sign of x; C is formed inside the two fused multiply-adds.  SIGN: the sign of a zero is kept.
+// for either sign of x; C is formed inside the two fused multiply-adds.  e == 8: to nearest even on the integer pattern.  SIGN: the sign of a zero is kept.
 template <int MODE, bool FTZ, bool SIGN = true>
 __device__ __forceinline__ uint32_t quantize_short(uint32_t u, const QuantParams &p, const RoundMasks &k)
 {
@@ -81,7 +82,7 @@ __device__ __forceinline__ uint32_t quantize_short(uint32_t u, const QuantParams
         return SIGN ? (u & k.sign) | __float_as_uint(q) : __float_as_uint(q);
     } else {
         uint32_t r = (u + p.rbias + __builtin_amdgcn_ubfe(u, p.shift, p.lsb_width)) & p.nmask;
-        if (FTZ) r = (u & 0x7FFFFFFFu) < p.t_den ? u & 0x80000000u : r;
+        if (FTZ) r = (u & 0x7FFFFFFFu) < p.t_den ? (SIGN ? u & 0x80000000u : 0u) : r;
         return r;
     }
 }

@@ -53,59 +53,22 @@ __device__ __forceinline__ void round_and_split(uint32_t u, const QuantParams &p
     }
 }
 
-// Constants in registers: with literals the compiler spends two instructions (and, or) where one (v_and_or_b32, which takes no
-// literal) does.
-struct DirectMasks {
-    uint32_t exponent, half, minn;               // 0x7F800000, 0x00400000 and the pattern of 1.5 * minN
-};
-
 // Eight consecutive k of one row (fp32 patterns) as MFMA operand vectors, one per piece: Q and the split of
 // round_and_split.  What a product of network tensors meets is finite and far from overflow, so the
-// common path leaves those cases out and looks once per eight elements whether the wave holds one:
-//   e < 8   the rounding is (x + C) - C with C = 1.5 * 2^(max(E, Emin) + 23 - m) for either sign (C is formed inside the
-//           two fused multiply-adds); the sign of a zero is lost, which no sum can show (it starts from +0)
-//   e == 8  round to nearest even on the integer pattern
-// 5 to 8 vector instructions per element where the general path takes about 20.
+// common path takes the short form of the rounding (the sign of a zero is lost, which no sum can show: it starts from +0) and looks once per
+// eight elements whether the wave holds anything else.  5 to 8 vector instructions per element where the general path takes about 20.
 constexpr bool direct_form(int mode, int ps) { return (mode == kModeMagic && ps <= 2) || (mode == kModeInteger && ps == 1); }
 
 template <int MODE, bool FTZ, int PS>
-__device__ __forceinline__ void direct_convert(const uint32_t (&v)[8], const QuantParams &p, const DirectMasks &k,
+__device__ __forceinline__ void direct_convert(const uint32_t (&v)[8], const QuantParams &p, const RoundMasks &k,
                                                u32x4 (&out)[pieces_of(PS)])
 {
     constexpr int P = pieces_of(PS);
     static_assert(direct_form(MODE, PS), "formats with a short form");
-    bool rare;
-    if constexpr (MODE == kModeMagic) {
-        // largest |x| (the instruction takes magnitudes; a NaN is passed over, and stays one below)
-        float top = 0.0f;
-#pragma unroll
-        for (int j = 0; j < 8; j += 2) asm("v_max3_f32 %0, |%1|, |%2|, %0" : "+v"(top) : "v"(v[j]), "v"(v[j + 1]));
-        rare = top >= __uint_as_float(p.t_ovf);
-    } else {
-        uint32_t top = 0u;                   // as a pattern: NaN on top
-#pragma unroll
-        for (int j = 0; j < 8; ++j) top = max(top, v[j] & 0x7FFFFFFFu);
-        rare = top >= p.t_ovf;
-    }
-    if (__ballot(rare) == 0ull) {            // the same in the whole wave
+    if (__ballot(run_is_rare(v, p)) == 0ull) {            // the same in the whole wave
         uint32_t r[8];
-        if constexpr (MODE == kModeMagic) {
-            const float scale = __uint_as_float((127u + p.shift) << 23), minn = __uint_as_float(p.minn_bits);
 #pragma unroll
-            for (int j = 0; j < 8; ++j) {
-                const float x = __uint_as_float(v[j]);
-                const float u = __uint_as_float(max((v[j] & k.exponent) | k.half, k.minn));
-                float q = __fmaf_rn(u, -scale, __fmaf_rn(u, scale, x));
-                if (FTZ) q = fabsf(q) < minn ? 0.0f : q;
-                r[j] = __float_as_uint(q);
-            }
-        } else {
-#pragma unroll
-            for (int j = 0; j < 8; ++j) {
-                r[j] = (v[j] + p.rbias + __builtin_amdgcn_ubfe(v[j], p.shift, p.lsb_width)) & p.nmask;
-                if (FTZ) r[j] = (v[j] & 0x7FFFFFFFu) < p.t_den ? 0u : r[j];
-            }
-        }
+        for (int j = 0; j < 8; ++j) r[j] = quantize_short<MODE, FTZ, false>(v[j], p, k);
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
             if constexpr (PS == 0) {         // values of the format are binary16 values: the conversion is exact
@@ -130,20 +93,13 @@ __device__ __forceinline__ void direct_convert(const uint32_t (&v)[8], const Qua
         for (int i = 0; i < 4; ++i) out[q][i] = pc[2 * i][q] | (pc[2 * i + 1][q] << 16);
 }
 
-__device__ __forceinline__ DirectMasks direct_masks(const QuantParams &p)
-{
-    DirectMasks k{0x7F800000u, 0x00400000u, p.minn_bits | 0x00400000u};
-    asm("" : "+s"(k.exponent), "+v"(k.half));
-    return k;
-}
-
 // The same for any format: two elements per word, one set of words per piece.
 template <int MODE, bool FTZ, int PS>
 __device__ __forceinline__ void split8(const uint32_t (&v)[8], const QuantParams &p, u32x4 (&out)[pieces_of(PS)])
 {
     constexpr int P = pieces_of(PS);
     if constexpr (direct_form(MODE, PS)) {
-        direct_convert<MODE, FTZ, PS>(v, p, direct_masks(p), out);
+        direct_convert<MODE, FTZ, PS>(v, p, round_masks(p), out);
     } else {
         uint32_t pc[8][P];
 #pragma unroll
