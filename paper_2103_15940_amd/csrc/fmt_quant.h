@@ -82,7 +82,10 @@ __device__ __forceinline__ uint32_t quantize_short(uint32_t u, const QuantParams
         return SIGN ? (u & k.sign) | __float_as_uint(q) : __float_as_uint(q);
     } else {
         uint32_t r = (u + p.rbias + __builtin_amdgcn_ubfe(u, p.shift, p.lsb_width)) & p.nmask;
-        if (FTZ) r = (u & 0x7FFFFFFFu) < p.t_den ? (SIGN ? u & 0x80000000u : 0u) : r;
+        // On its way to the matrix cores as floats, denormal ones among them: the magnitude costs that comparison nothing (64 x 256 x 784 in
+        // 1/8/7/n in one launch 11.9 -> 10.6 us).  Not where statistics need the magnitude's pattern anyway (a layer 48.6 -> 50.1).
+        if (FTZ && SIGN) r = (u & 0x7FFFFFFFu) < p.t_den ? u & 0x80000000u : r;
+        if (FTZ && !SIGN) r = fabsf(__uint_as_float(u)) < __uint_as_float(p.t_den) ? 0u : r;
         return r;
     }
 }
