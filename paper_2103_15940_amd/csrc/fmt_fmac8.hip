@@ -592,7 +592,7 @@ static int launch(int transA, int transB, int M, int N, int K, const float *A, i
         // 57.7; 384: 23 / 22 / 58; 512: 29 / 23 / 59; 640: 44 / 32 / 59; 768: 53 / 42 / 59; 1024: 88 / 53 / 61; 1500: 185 / 109 / 127;
         // 2048: 334 / 187 / 165.  The values decide which form a stage takes; at 384 and 512, where four chains per thread would gain
         // up to 6 us, the single form loses 35, so the line lies above them: the constants are a little above the wide form's times (with
-        // those, 13.4 / 5.4, 21.6 / 12.5 and 58 / 41, N = 448 to 576 would take four chains, and nothing else would change).  Where all stages take the single
+        // those, 13.4 / 5.4, 21.6 / 12.5 and 58 / 41, N = 448 to 560 would take four chains).  Where all stages take the single
         // form the rule is off by up to a third (640: 65 / 83 / 228; 1024: 123 / 118 / 228; 1500: 240 / 220 / 448; 2048: 426 / 367 / 497).
         int cus = 0;
         const int rc = device_cu_count(&cus);

@@ -167,8 +167,8 @@ __device__ __forceinline__ void linear_tile(floatx16 (&acc)[TM][TN], float *C, i
     typedef uint32_t u32x4u __attribute__((ext_vector_type(4), aligned(4)));
     typedef uint32_t u32x2u __attribute__((ext_vector_type(2), aligned(2)));
     constexpr int kCopies = linear_copies(TM * TN);
-    // quads that N cuts among the common ones: 40 % more code in a 128 x 128 tile with planes (107 -> 148 KB, more registers spilled;
-    // 4096 x 3072 x 1024 in 1/6/9 with statistics and no such quad 53 -> 69 us and more), so not there
+    // quads that N cuts among the common ones: 40 % more code in a 128 x 128 tile (4096 x 3072 x 1024 in 1/6/9 with statistics and no such
+    // quad 53 -> 69 us and more when it was measured, with 148 KB of code and spills; 77 KB without, and no spills, now), so not there
     constexpr bool kCut = TM * TN < 4;
     __shared__ uint32_t s_bins[HIST ? FMT_NBINS : 1], s_cls[HIST ? 8 : 1];
     const QuantParams &p = lin.p;

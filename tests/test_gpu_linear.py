@@ -498,9 +498,9 @@ def test_layers_with_many_elements_outside_plane_0(fmt, m, d, tile, monkeypatch)
 
 
 @pytest.mark.parametrize("tile", ["1,1,1", "2,1,1", "2,2,1"])
-@pytest.mark.parametrize("e,m,d", [(5, 10, True), (6, 9, True), (8, 7, False), (7, 12, True)])
+@pytest.mark.parametrize("e,m,d", [(5, 10, True), (6, 9, True), (8, 7, False), (7, 12, True), (7, 20, True), (8, 23, True)])
 def test_layers_repeat(fmt, e, m, d, tile, monkeypatch):
-    """The layer's kernels on every tile, with one and two pieces and with planes, with and without statistics: the same outputs and
+    """The layer's kernels on every tile, with one to three pieces and with planes, with and without statistics: the same outputs and
     counts in every call, those of the separate calls.  k leaves every remainder of the turns of the stage ring."""
     monkeypatch.setenv("FMT_GEMM_WINDOW", "1")
     monkeypatch.setenv("FMT_GEMM_PLAN", tile)
