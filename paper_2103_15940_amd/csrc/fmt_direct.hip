@@ -17,14 +17,28 @@ struct DirectOperand {
     int rows;
 };
 
+// LDS of a wave, in bytes: per staged operand and piece 4 chunks of 8 k x 32 rows of 16 bytes; the 32 bytes between chunks put the 16 lanes that
+// write at a time (two rows, 32 k) on different banks.  The sums of a part take the place of the operands.
+constexpr int kDirectChunk = 32 * 16 + 32, kDirectPiece = 4 * kDirectChunk;
+constexpr int direct_lds_at(int operand, int piece, int P, int k4, int row)     // k4: k / 4
+{
+    return (operand * P + piece) * kDirectPiece + k4 / 2 * kDirectChunk + row * 16 + k4 % 2 * 8;
+}
+constexpr int direct_lds_bytes(int P, bool avec, bool bvec)
+{
+    const int staged = ((avec ? 1 : 0) + (bvec ? 1 : 0)) * P * kDirectPiece;
+    return staged > 16 * 64 * 4 ? staged : 16 * 64 * 4;
+}
+
 // C = Q(A) Q(B)^T of two fp32 matrices in one launch, for products so small that the three launches of the general route
 // (prepare, product, sum of the k parts: 5 - 6 us each on the GPU and 3 us each on the host) are what they cost.
-// A wave owns a block of 32 x 32 results and one of `parts` ranges of k; it loads its operands straight into
-// the layout of the MFMA fragments (lane l: row l % 32, eight consecutive k), rounds and splits them in
-// registers and multiplies: no LDS, no barrier, the next 32 k in flight meanwhile.  The parts of a block
+// A wave owns a block of 32 x 32 results and one of `parts` ranges of k; it loads its operands, rounds and splits them in
+// registers and multiplies: no barrier, four blocks of 32 k in flight meanwhile.  The parts of a block
 // meet in LDS and are summed in order.  Every element is rounded once per block of its row or column instead of
-// once, which is what bounds it (vector instructions) and why larger products keep the general route
-// (direct_parts).  The sums are those of the general route bit for bit when `parts` is its plan's: same pieces, same
+// once, which is what bounds it (vector instructions: 0.6 us per block of 32 k and wave in 1/6/9, of it 0.1 the matrix cores) and why larger
+// products keep the general route (direct_parts).  256 x 1024 x 1024 in 1/6/9 takes 9.5 - 10.0 us in a graph (rows along k
+// loaded straight into the fragments' layout, and every XCD all of the larger operand: 11.1 - 12.7), 256 x 10 x 1024 8.5 (9.8),
+// 128 x 512 x 512 in 1/8/7 8.0 (11.9; with the conversion in the vector units alone 8.9 -> 8.0).  The sums are those of the general route bit for bit when `parts` is its plan's: same pieces, same
 // steps of 16 k, same order.
 template <int MODE, bool FTZ, int PS, bool AVEC, bool BVEC>
 __global__ __launch_bounds__(512) void direct_product_kernel(DirectOperand a, DirectOperand b, float *__restrict__ C, int64_t ldc,
@@ -32,9 +46,13 @@ __global__ __launch_bounds__(512) void direct_product_kernel(DirectOperand a, Di
                                                               int kb_per, int tiles_per_wg, QuantParams p, LinearRound lin, int linear)
 {
     constexpr int P = pieces_of(PS);
-    extern __shared__ float s_part[];            // parts > 1: [wave][16][64]
+    extern __shared__ u32x4 s_mem[];             // a stretch per wave: its operands' pieces, then (parts > 1) its sums [16][64]
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int part = wave % parts, tile = blockIdx.x * tiles_per_wg + wave / parts;
+    constexpr int kOwn = direct_lds_bytes(P, AVEC, BVEC);
+    char *const own = reinterpret_cast<char *>(s_mem) + wave * kOwn;
+    // Workgroups go to the XCDs in turn: every XCD gets a run of tiles, so that its L2 holds few of the larger operand's rows
+    const int per_xcd = gridDim.x / 8, wg = (int)(blockIdx.x % 8) * per_xcd + (int)(blockIdx.x / 8);
+    const int part = wave % parts, tile = wg * tiles_per_wg + wave / parts;
     const bool live = tile < ntiles;
     const int row0 = (tile % tiles_m) * 32, col0 = (tile / tiles_m) * 32;
     const int kb0 = part * kb_per, kb1 = live ? min(kblocks, kb0 + kb_per) : 0;
@@ -48,77 +66,164 @@ __global__ __launch_bounds__(512) void direct_product_kernel(DirectOperand a, Di
     const RoundMasks masks = round_masks(p);
 
     // Rows beyond the operand read its last row: their results are not stored.  A load's address is one that is the same in
-    // the whole wave plus a lane's offset.
-    const int half = lane >> 5;
-    const uint32_t off_a = (uint32_t)min(row0 + (lane & 31), a.rows - 1) * a.row_step + (uint32_t)half * 8u * a.k_step;
-    const uint32_t off_b = (uint32_t)min(col0 + (lane & 31), b.rows - 1) * b.row_step + (uint32_t)half * 8u * b.k_step;
+    // the whole wave plus a lane's offset.  Sixteen elements of an operand's 32 rows x 32 k to a lane:
+    //   rows along k (VEC)   8 lanes take the 128 bytes of a row, four k each: rows 8 i + l / 8, i = 0 .. 3, k 4 (l % 8) + j at raw[4 i + j].  They
+    //                        reach the fragments' layout through LDS, as pieces, in a stretch of the wave's own.  Loaded straight into
+    //                        the fragments' layout, 32 rows to an instruction, a load touches 64 pieces of lines.
+    //   rows side by side    the fragments' layout: row l % 32, k 16 kk + 8 (l / 32) + j at raw[8 kk + j]; 32 lanes take 128 bytes
+    const int half = lane >> 5, part_row = lane >> 3, part_k = (lane & 7) * 4;
+    uint32_t off_a[AVEC ? 4 : 1], off_b[BVEC ? 4 : 1];
+    auto offsets = [&](auto vec, const DirectOperand &o, int first, auto &off) __attribute__((always_inline)) {
+        if constexpr (decltype(vec)::value) {
+#pragma unroll
+            for (int i = 0; i < 4; ++i) off[i] = (uint32_t)min(first + 8 * i + part_row, o.rows - 1) * o.row_step;
+        } else {
+            off[0] = (uint32_t)min(first + (lane & 31), o.rows - 1) * o.row_step + (uint32_t)half * 8u * o.k_step;
+        }
+    };
+    constexpr std::integral_constant<bool, AVEC> avec{};
+    constexpr std::integral_constant<bool, BVEC> bvec{};
+    offsets(avec, a, row0, off_a);
+    offsets(bvec, b, col0, off_b);
     // no branch in here: the compiler keeps the loads of several blocks in flight
-    auto load_one = [&](auto vec, const DirectOperand &o, uint32_t off, int kb, uint32_t (&raw)[2][8]) __attribute__((always_inline)) {
+    auto load_one = [&](auto vec, const DirectOperand &o, const auto &off, int kb, uint32_t (&raw)[16]) __attribute__((always_inline)) {
+        if constexpr (decltype(vec)::value) {
+            const uint32_t *src = o.X + (uint32_t)(kb * kUnitK);
 #pragma unroll
-        for (int kk = 0; kk < 2; ++kk) {
-            const uint32_t *src = o.X + (size_t)(uint32_t)(kb * kUnitK + kk * 16) * o.k_step;
-            if constexpr (decltype(vec)::value) {
-                const u32x4u lo = *reinterpret_cast<const u32x4u *>(src + off), hi = *reinterpret_cast<const u32x4u *>(src + off + 4);
+            for (int i = 0; i < 4; ++i) {
+                const u32x4u w = *reinterpret_cast<const u32x4u *>(src + (off[i] + (uint32_t)part_k));
 #pragma unroll
-                for (int j = 0; j < 4; ++j) {
-                    raw[kk][j] = lo[j];
-                    raw[kk][4 + j] = hi[j];
-                }
-            } else {
+                for (int j = 0; j < 4; ++j) raw[4 * i + j] = w[j];
+            }
+        } else {
 #pragma unroll
-                for (int j = 0; j < 8; ++j, src += o.k_step) raw[kk][j] = src[off];
+            for (int kk = 0; kk < 2; ++kk) {
+                const uint32_t *src = o.X + (size_t)(uint32_t)(kb * kUnitK + kk * 16) * o.k_step;
+#pragma unroll
+                for (int j = 0; j < 8; ++j, src += o.k_step) raw[8 * kk + j] = src[off[0]];
             }
         }
     };
-    auto load = [&](int kb, uint32_t (&raw)[2][2][8]) __attribute__((always_inline)) {
-        load_one(std::integral_constant<bool, AVEC>{}, a, off_a, kb, raw[0]);
-        load_one(std::integral_constant<bool, BVEC>{}, b, off_b, kb, raw[1]);
+    auto load = [&](int kb, uint32_t (&raw)[2][16]) __attribute__((always_inline)) {
+        load_one(avec, a, off_a, kb, raw[0]);
+        load_one(bvec, b, off_b, kb, raw[1]);
     };
-    // The block that K ends in, zero beyond K.  A lane's eight k that K cuts are loaded as the last eight of the row and
-    // moved down; single elements (and rows shorter than eight) beyond K read the last k: no load waits behind a test of its own.
-    auto load_last = [&](auto vec, const DirectOperand &o, uint32_t off, int kb, uint32_t (&raw)[2][8]) __attribute__((always_inline)) {
-        const uint32_t *row = o.X + (off - (uint32_t)half * 8u * o.k_step);
-        if (decltype(vec)::value && K >= 8) {
-            int skip[2];
+    // The block that K ends in, zero beyond K.  A lane's four k that K cuts are loaded as the last four of the row and
+    // moved down; single elements (and rows shorter than four) beyond K read the last k: no load waits behind a test of its own.
+    auto load_last = [&](auto vec, const DirectOperand &o, const auto &off, int kb, uint32_t (&raw)[16]) __attribute__((always_inline)) {
+        if constexpr (decltype(vec)::value) {
+            const uint32_t at = (uint32_t)min(kb * kUnitK + part_k, K - 4);      // K >= 4 (launch)
 #pragma unroll
-            for (int kk = 0; kk < 2; ++kk) {
-                const int k0 = kb * kUnitK + kk * 16 + half * 8, at = min(k0, K - 8);
-                const u32x4 lo = *reinterpret_cast<const u32x4u *>(row + at), hi = *reinterpret_cast<const u32x4u *>(row + at + 4);
-                skip[kk] = k0 - at;
+            for (int i = 0; i < 4; ++i) {
+                const u32x4u w = *reinterpret_cast<const u32x4u *>(o.X + (off[i] + at));
 #pragma unroll
-                for (int j = 0; j < 4; ++j) {
-                    raw[kk][j] = lo[j];
-                    raw[kk][4 + j] = hi[j];
-                }
+                for (int j = 0; j < 4; ++j) raw[4 * i + j] = w[j];
             }
-#pragma unroll
-            for (int kk = 0; kk < 2; ++kk)
-#pragma unroll
-                for (int by = 1; by <= 8; by *= 2) {
-                    const bool move = by < 8 ? (skip[kk] & by) != 0 : skip[kk] >= 8;
-#pragma unroll
-                    for (int j = 0; j < 8; ++j) raw[kk][j] = !move ? raw[kk][j] : j + by < 8 ? raw[kk][j + by < 8 ? j + by : 7] : 0u;
-                }
         } else {
 #pragma unroll
             for (int kk = 0; kk < 2; ++kk)
 #pragma unroll
                 for (int j = 0; j < 8; ++j) {
                     const int k = kb * kUnitK + kk * 16 + half * 8 + j;
-                    const uint32_t v = row[(size_t)(uint32_t)min(k, K - 1) * o.k_step];
-                    raw[kk][j] = k < K ? v : 0u;
+                    raw[8 * kk + j] = o.X[off[0] - (uint32_t)half * 8u * o.k_step + (size_t)(uint32_t)min(k, K - 1) * o.k_step];
                 }
+        }
+    };
+    auto cut_last = [&](auto vec, int kb, uint32_t (&raw)[16]) __attribute__((always_inline)) {
+        if constexpr (decltype(vec)::value) {
+            const int k0 = kb * kUnitK + part_k, skip = k0 - min(k0, K - 4);
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                uint32_t v[4];
+#pragma unroll
+                for (int j = 0; j < 4; ++j) v[j] = (skip & 1) != 0 ? raw[4 * i + (j < 3 ? j + 1 : 3)] : raw[4 * i + j];
+#pragma unroll
+                for (int j = 0; j < 4; ++j) {
+                    const uint32_t moved = (skip & 2) != 0 ? v[j < 2 ? j + 2 : 3] : v[j];
+                    raw[4 * i + j] = k0 + j < K ? moved : 0u;
+                }
+            }
+        } else {
+#pragma unroll
+            for (int kk = 0; kk < 2; ++kk)
+#pragma unroll
+                for (int j = 0; j < 8; ++j) raw[8 * kk + j] = kb * kUnitK + kk * 16 + half * 8 + j < K ? raw[8 * kk + j] : 0u;
         }
     };
     floatx16 acc;
 #pragma unroll
     for (int v = 0; v < 16; ++v) acc[v] = 0.0f;
-    auto multiply = [&](const uint32_t (&raw)[2][2][8]) __attribute__((always_inline)) {
+    typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
+    // A lane's sixteen elements as pieces.  Elements near overflow or beyond go through the general conversion in a loop over
+    // LDS: it stands in the code once per block of the ring, and code that runs but a few times per wave has to be short.
+    auto convert = [&](const uint32_t (&raw)[16], u32x4 (&pc)[2][P]) __attribute__((always_inline)) {
+        auto eights = [&](auto &&one) __attribute__((always_inline)) {
+#pragma unroll
+            for (int i = 0; i < 2; ++i) {
+                uint32_t v[8];
+#pragma unroll
+                for (int j = 0; j < 8; ++j) v[j] = raw[8 * i + j];
+                one(v, pc[i]);
+            }
+        };
+        if constexpr (hardware_scheme(MODE, PS)) {
+            if (hardware_format<MODE, PS>(p)) {
+                eights([&](const uint32_t (&v)[8], u32x4 (&out)[P]) __attribute__((always_inline)) { hardware_convert<FTZ, PS>(v, p, out); });
+                return;
+            }
+        }
+        if (__ballot(run_is_rare(raw, p)) == 0ull) {
+            eights([&](const uint32_t (&v)[8], u32x4 (&out)[P]) __attribute__((always_inline)) { short_convert<MODE, FTZ, PS>(v, p, masks, out); });
+            return;
+        }
+        uint32_t *words = reinterpret_cast<uint32_t *>(own) + lane;
+#pragma unroll
+        for (int j = 0; j < 16; ++j) words[j * 64] = raw[j];
+#pragma unroll 1
+        for (int j = 0; j < 16; ++j) {
+            uint32_t piece[P];
+            round_and_split<MODE, FTZ, PS>(words[j * 64], p, piece);
+            words[j * 64] = piece[0] | (P >= 2 ? piece[P >= 2 ? 1 : 0] << 16 : 0u);
+        }
+#pragma unroll
+        for (int i = 0; i < 2; ++i)
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                const uint32_t lo = words[(8 * i + 2 * j) * 64], hi = words[(8 * i + 2 * j + 1) * 64];
+                pc[i][0][j] = __builtin_amdgcn_perm(hi, lo, 0x05040100u);
+                if constexpr (P >= 2) pc[i][P >= 2 ? 1 : 0][j] = __builtin_amdgcn_perm(hi, lo, 0x07060302u);
+            }
+    };
+    auto multiply = [&](const uint32_t (&raw)[2][16]) __attribute__((always_inline)) {
         u32x4 f[2][2][P];                                            // [operand][16 k][piece]
+        convert(raw[0], f[0]);
+        convert(raw[1], f[1]);
+        if constexpr (AVEC || BVEC) {
+            // LDS takes a wave's accesses in order
+            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+            auto staged = [&](auto &&move) __attribute__((always_inline)) {
 #pragma unroll
-        for (int o = 0; o < 2; ++o)
+                for (int o = 0; o < 2; ++o)
+                    if (o == 0 ? AVEC : BVEC) move(o, o == 1 && AVEC ? 1 : 0);
+            };
+            staged([&](int o, int place) __attribute__((always_inline)) {
 #pragma unroll
-            for (int kk = 0; kk < 2; ++kk) direct_convert<MODE, FTZ, PS>(raw[o][kk], p, masks, f[o][kk]);
+                for (int i = 0; i < 4; ++i)
+#pragma unroll
+                    for (int q = 0; q < P; ++q)
+                        *reinterpret_cast<u32x2 *>(own + direct_lds_at(place, q, P, lane & 7, 8 * i + part_row)) =
+                            u32x2{f[o][i / 2][q][i % 2 * 2], f[o][i / 2][q][i % 2 * 2 + 1]};
+            });
+            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+            staged([&](int o, int place) __attribute__((always_inline)) {
+#pragma unroll
+                for (int kk = 0; kk < 2; ++kk)
+#pragma unroll
+                    for (int q = 0; q < P; ++q)
+                        f[o][kk][q] = *reinterpret_cast<const u32x4 *>(own + direct_lds_at(place, q, P, 2 * (2 * kk + half), lane & 31));
+            });
+            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        }
 #pragma unroll
         for (int kk = 0; kk < 2; ++kk)
 #pragma unroll
@@ -133,7 +238,12 @@ __global__ __launch_bounds__(512) void direct_product_kernel(DirectOperand a, Di
     // kDepth blocks of 32 k are in flight: a block takes 0.4 us of rounding and multiplying, a load up to three times that
     constexpr int kDepth = 4;
     const int whole = min(kb1, K / kUnitK);                          // blocks [kb0, whole) lie inside K; at most one more follows
-    uint32_t raw[kDepth][2][2][8];
+    const bool cut = kb0 <= whole && whole < kb1;                    // the block that K ends in is this part's
+    uint32_t raw[kDepth][2][16], raw_cut[2][16];
+    if (cut) {
+        load_last(avec, a, off_a, whole, raw_cut[0]);
+        load_last(bvec, b, off_b, whole, raw_cut[1]);
+    }
 #pragma unroll
     for (int u = 0; u < kDepth; ++u)
         if (kb0 + u < whole) load(kb0 + u, raw[u]);
@@ -145,10 +255,10 @@ __global__ __launch_bounds__(512) void direct_product_kernel(DirectOperand a, Di
             if (kb + u + kDepth < whole) load(kb + u + kDepth, raw[u]);
         }
     }
-    if (kb0 <= whole && whole < kb1) {                                // the block that K ends in, if it is this part's
-        load_last(std::integral_constant<bool, AVEC>{}, a, off_a, whole, raw[0][0]);
-        load_last(std::integral_constant<bool, BVEC>{}, b, off_b, whole, raw[0][1]);
-        multiply(raw[0]);
+    if (cut) {
+        cut_last(avec, whole, raw_cut[0]);
+        cut_last(bvec, whole, raw_cut[1]);
+        multiply(raw_cut);
     }
 
     // register 4g + c of lane l: row l % 32, column 8g + 4 (l / 32) + c of the block
@@ -178,7 +288,7 @@ __global__ __launch_bounds__(512) void direct_product_kernel(DirectOperand a, Di
         return;
     }
 #pragma unroll
-    for (int v = 0; v < 16; ++v) s_part[(wave * 16 + v) * 64 + lane] = acc[v];
+    for (int v = 0; v < 16; ++v) reinterpret_cast<float *>(own)[v * 64 + lane] = acc[v];
     __syncthreads();
     if (!live) return;
     const int w0 = wave - part;                                      // the block's first wave
@@ -189,7 +299,8 @@ __global__ __launch_bounds__(512) void direct_product_kernel(DirectOperand a, Di
 #pragma unroll
         for (int c = 0; c < 4; ++c) {
             sum[c] = 0.0f;
-            for (int q = 0; q < parts; ++q) sum[c] += s_part[((w0 + q) * 16 + 4 * g + c) * 64 + lane];
+            for (int q = 0; q < parts; ++q)
+                sum[c] += reinterpret_cast<const float *>(reinterpret_cast<const char *>(s_mem) + (w0 + q) * kOwn)[(4 * g + c) * 64 + lane];
         }
         put(g, sum[0], sum[1], sum[2], sum[3]);
     }
@@ -204,12 +315,14 @@ static int launch(int M, int N, int K, const MatrixOperand &A, const MatrixOpera
     };
     const int kblocks = (K + kUnitK - 1) / kUnitK;
     const int tiles_m = (M + 31) / 32, tiles = tiles_m * ((N + 31) / 32);
+    const bool avec = A.kcontig && K >= 4, bvec = B.kcontig && K >= 4;       // 16-byte vectors of a row
     const int per_wg = direct_blocks_per_workgroup(parts);
     const int waves = parts * per_wg;
-    const size_t lds = parts > 1 ? (size_t)waves * 16 * 64 * sizeof(float) : 0;
-    auto kern = A.kcontig ? (B.kcontig ? direct_product_kernel<MODE, FTZ, PS, true, true> : direct_product_kernel<MODE, FTZ, PS, true, false>)
-                          : (B.kcontig ? direct_product_kernel<MODE, FTZ, PS, false, true> : direct_product_kernel<MODE, FTZ, PS, false, false>);
-    hipLaunchKernelGGL(kern, dim3((unsigned)((tiles + per_wg - 1) / per_wg)), dim3(64 * waves), lds, stream, operand(A, M), operand(B, N), C,
+    const size_t lds = (size_t)waves * direct_lds_bytes(pieces_of(PS), avec, bvec);
+    const unsigned wgs = (unsigned)((tiles + per_wg - 1) / per_wg);
+    auto kern = avec ? (bvec ? direct_product_kernel<MODE, FTZ, PS, true, true> : direct_product_kernel<MODE, FTZ, PS, true, false>)
+                     : (bvec ? direct_product_kernel<MODE, FTZ, PS, false, true> : direct_product_kernel<MODE, FTZ, PS, false, false>);
+    hipLaunchKernelGGL(kern, dim3((wgs + 7u) / 8u * 8u), dim3(64 * waves), lds, stream, operand(A, M), operand(B, N), C,
                        ldc, M, N, K, kblocks, tiles_m, tiles, parts, (kblocks + parts - 1) / parts, per_wg, p,
                        lin != nullptr ? *lin : LinearRound{}, lin != nullptr ? 1 : 0);
     FMT_HIP_CHECK(hipGetLastError());

@@ -1426,20 +1426,19 @@ static int prepare_operands(const OperandSpec &sa, const OperandLayout &la, cons
 static Scheme api_scheme(fmt_format_t f, int64_t K);
 
 // Parts of k of a direct product (fmt_direct.hip), or 0 where the general route is the better one (or forced by a plan).
-// FMT_GEMM_PLAN=direct (tests): wherever the kernel can; any other value: nowhere.  Both routes' times on the GPU (us), fitted to 664
-// products of 16 x 40 to 328 x 3256 with k of 32 to 2393 in all layouts, replayed from graphs:
-//   direct   3.2, and per block of 32 k that a wave takes one after the other 1.0 (one piece 0.85), or, with n waves on a SIMD of
-//            the busiest compute unit, 0.72 n while the chip is not full and 0.95 n when it is; more for every operand whose
-//            rows lie along k (a load touches a line per lane); 0.7 per 10^6 results; up to 11 blocks (long chains came out
-//            slower than this: 224 x 440 x 2944 30 us in 12 blocks against 22)
+// FMT_GEMM_PLAN=direct (tests): wherever the kernel can; any other value: nowhere.  Both routes' times on the GPU (us), fitted to 900
+// products of 8 x 8 to 2048 x 1200 with k of 8 to 3000 in all layouts, replayed from graphs (both fits within 6 to 10 %):
+//   direct   2.7, and per block of 32 k that a wave takes one after the other, with n waves on a SIMD of the busiest compute unit,
+//            0.62 + 0.38 n (one piece 0.22 + 0.16 n; 0.18 more with the flush); 4.4 per further round of workgroups (a SIMD holds two
+//            waves); 1.3 per 10^6 results and 0.65 per 10^6 operand elements; up to 11 blocks (long chains come out slower)
 //   general  two launches: 5.8, 0.23 (one piece 0.07) per block of k, 2.05 per 10^6 operand elements, 1.06 (0.69) per 10^6
 //            results; three where the plan splits k: 6.7, 0.37 (0.25) per block of a part, 3.3 (1.9) and 0.9 (1.9)
 //            per part and 10^6 results; a layer's output roundings are then a launch of their own, 4
 // A launch less also saves the host 2.5 - 3 us (from Python 7.2, 9.7 and 12.2 us with one, two and three), so a direct product may
-// take 1 us more than two launches, and 2 more than three: with that, the 664 take 6.7 ms one after the other from Python and
-// 5.9 ms from graphs; 7.7 and 6.1 without the direct kernel.  Measured (us in a graph, general / direct): 64 x 64 x 32 in 1/6/9 5.9 / 3.4;
-// 256 x 256 x 511 10.9 / 6.3 - 7.7; 256 x 1024 x 1024 14.4 / 10.7 - 13.0; 1000 x 1000 x 80 8.0 / 6.6 - 7.1; not taken: 1000 x 1000
-// x 256 9.8 / 13.4, 256 x 256 x 2048 14.1 / 15 - 20, 64 x 64 x 2048 11.0 / 15 - 20, 256 x 1024 x 256 in 1/8/7 6.7 / 11.8.
+// take 1.2 us more than three launches: with that, the 900 take 5.90 ms from graphs (6.19 before operands
+// whose rows lie along k came through LDS; 5.84 with the better route each time).  Measured (us in a graph, general / direct): 256 x 256 x
+// 511 in 1/6/9 10.9 / 6.5; 256 x 1024 x 1024 14.4 / 9.5 - 10.0; 300 x 300 x 333 in 1/5/10 8 / 7.2; not taken: 559 x 489 x 1289 in
+// 1/6/9 18.1 / 23.9, 973 x 608 x 1264 in 1/8/7 14.9 / 32.1.
 static int direct_parts(int M, int N, int K, const OperandSpec &sa, const OperandSpec &sb, const Plan &plan, fmt_format_t f, Scheme sch,
                         int mode, bool layer, int cus)
 {
@@ -1462,19 +1461,19 @@ static int direct_parts(int M, int N, int K, const OperandSpec &sa, const Operan
     if (parts > kDirectParts) return 0;
     if (env != nullptr) return parts;
     const bool one = pieces_of(sch.ps) == 1;
-    const double along = (sa.kcontig ? 1.0 : 0.0) + (sb.kcontig ? 1.0 : 0.0);
     const int64_t per_wg = direct_blocks_per_workgroup(parts), wgs = (tiles + per_wg - 1) / per_wg;
     const double n = (double)((wgs + cus - 1) / cus) * (double)(parts * per_wg) / 4.0;
-    const double shared = tiles * parts >= 4 * (int64_t)cus ? 0.95 + 0.125 * along : 0.72 * (1.0 + 0.05 * along);
+    const double rounds = std::max(0.0, std::ceil(n / 2.0) - 1.0);
     const double blocks = (double)((kblocks + parts - 1) / parts);
     if (blocks > 11.0) return 0;
     const double operands = ((double)M + N) * K * 1e-6, results = (double)M * N * 1e-6;
-    const double direct = 3.2 + blocks * std::max((one ? 0.85 : 1.0) * (1.0 + 0.05 * along), shared * n) + 0.7 * results;
+    const double each = (one ? 0.22 + 0.16 * n : 0.62 + 0.38 * n) + (f.denorm == 0 ? 0.18 : 0.0);
+    const double direct = 2.7 + blocks * each + 4.4 * rounds + 1.3 * results + 0.65 * operands;
     const double kb_per = (double)((kblocks + plan.nsplit - 1) / plan.nsplit);
     const double general = plan.nsplit == 1
-                               ? 5.8 + (one ? 0.07 : 0.23) * kb_per + 2.05 * operands + (one ? 0.69 : 1.06) * results + 1.0
+                               ? 5.8 + (one ? 0.07 : 0.23) * kb_per + 2.05 * operands + (one ? 0.69 : 1.06) * results
                                : 6.7 + (one ? 0.25 : 0.365) * kb_per + (one ? 1.9 : 3.3) * operands +
-                                     (one ? 1.9 : 0.9) * plan.nsplit * results + 2.0 + (layer ? 4.0 : 0.0);
+                                     (one ? 1.9 : 0.9) * plan.nsplit * results + 1.2 + (layer ? 4.0 : 0.0);
     return direct < general ? parts : 0;
 }
 

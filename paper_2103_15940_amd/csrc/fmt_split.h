@@ -2,6 +2,8 @@
 // them on the way in.
 #pragma once
 
+#include <type_traits>
+
 #include "fmt_internal.h"
 #include "fmt_quant.h"
 
@@ -53,6 +55,32 @@ __device__ __forceinline__ void round_and_split(uint32_t u, const QuantParams &p
     }
 }
 
+// binary16 and bfloat16 themselves: the conversion of the vector units, two elements per instruction, is the rounding with denormals
+// kept -- equal to round_and_split over all 2^32 patterns, infinities included (NaN stay NaN) -- so nothing is rare.
+constexpr bool hardware_scheme(int mode, int ps) { return (mode == kModeMagic && ps == 0) || (mode == kModeInteger && ps == 1); }
+template <int MODE, int PS>
+__device__ __forceinline__ bool hardware_format(const QuantParams &p)
+{
+    if constexpr (!hardware_scheme(MODE, PS)) return false;
+    return PS == 0 ? p.shift == 13u && p.minn_bits == 0x38800000u : p.shift == 16u;
+}
+
+template <bool FTZ, int PS>
+__device__ __forceinline__ void hardware_convert(const uint32_t (&v)[8], const QuantParams &p, u32x4 (&out)[1])
+{
+    typedef float f32x2 __attribute__((ext_vector_type(2)));
+    typedef typename std::conditional<PS == 0, _Float16, __bf16>::type half_t;
+    typedef half_t half2_t __attribute__((ext_vector_type(2)));
+    float x[8];
+#pragma unroll
+    for (int j = 0; j < 8; ++j) {
+        x[j] = __uint_as_float(v[j]);
+        if (FTZ) x[j] = fabsf(x[j]) < __uint_as_float(p.t_den) ? 0.0f : x[j];
+    }
+#pragma unroll
+    for (int i = 0; i < 4; ++i) out[0][i] = __builtin_bit_cast(uint32_t, __builtin_convertvector((f32x2{x[2 * i], x[2 * i + 1]}), half2_t));
+}
+
 // Eight consecutive k of one row (fp32 patterns) as MFMA operand vectors, one per piece: Q and the split of
 // round_and_split.  What a product of network tensors meets is finite and far from overflow, so the
 // common path takes the short form of the rounding (the sign of a zero is lost, which no sum can show: it starts from +0) and looks once per
@@ -60,28 +88,41 @@ __device__ __forceinline__ void round_and_split(uint32_t u, const QuantParams &p
 constexpr bool direct_form(int mode, int ps) { return (mode == kModeMagic && ps <= 2) || (mode == kModeInteger && ps == 1); }
 
 template <int MODE, bool FTZ, int PS>
+__device__ __forceinline__ void short_convert(const uint32_t (&v)[8], const QuantParams &p, const RoundMasks &k, u32x4 (&out)[pieces_of(PS)])
+{
+    constexpr int P = pieces_of(PS);
+    static_assert(direct_form(MODE, PS), "formats with a short form");
+    uint32_t r[8];
+#pragma unroll
+    for (int j = 0; j < 8; ++j) r[j] = quantize_short<MODE, FTZ, false>(v[j], p, k);
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        if constexpr (PS == 0) {         // values of the format are binary16 values: the conversion is exact
+            out[0][i] = __builtin_bit_cast(uint32_t, __builtin_amdgcn_cvt_pkrtz(__uint_as_float(r[2 * i]), __uint_as_float(r[2 * i + 1])));
+        } else {
+            out[0][i] = __builtin_amdgcn_perm(r[2 * i + 1], r[2 * i], 0x07060302u);
+            if constexpr (P >= 2) {
+                const float l0 = __uint_as_float(r[2 * i]) - __uint_as_float(r[2 * i] & 0xFFFF0000u);              // exact
+                const float l1 = __uint_as_float(r[2 * i + 1]) - __uint_as_float(r[2 * i + 1] & 0xFFFF0000u);
+                out[P >= 2 ? 1 : 0][i] = __builtin_amdgcn_perm(__float_as_uint(l1), __float_as_uint(l0), 0x07060302u);
+            }
+        }
+    }
+}
+
+template <int MODE, bool FTZ, int PS>
 __device__ __forceinline__ void direct_convert(const uint32_t (&v)[8], const QuantParams &p, const RoundMasks &k,
                                                u32x4 (&out)[pieces_of(PS)])
 {
     constexpr int P = pieces_of(PS);
-    static_assert(direct_form(MODE, PS), "formats with a short form");
-    if (__ballot(run_is_rare(v, p)) == 0ull) {            // the same in the whole wave
-        uint32_t r[8];
-#pragma unroll
-        for (int j = 0; j < 8; ++j) r[j] = quantize_short<MODE, FTZ, false>(v[j], p, k);
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            if constexpr (PS == 0) {         // values of the format are binary16 values: the conversion is exact
-                out[0][i] = __builtin_bit_cast(uint32_t, __builtin_amdgcn_cvt_pkrtz(__uint_as_float(r[2 * i]), __uint_as_float(r[2 * i + 1])));
-            } else {
-                out[0][i] = __builtin_amdgcn_perm(r[2 * i + 1], r[2 * i], 0x07060302u);
-                if constexpr (P >= 2) {
-                    const float l0 = __uint_as_float(r[2 * i]) - __uint_as_float(r[2 * i] & 0xFFFF0000u);              // exact
-                    const float l1 = __uint_as_float(r[2 * i + 1]) - __uint_as_float(r[2 * i + 1] & 0xFFFF0000u);
-                    out[P >= 2 ? 1 : 0][i] = __builtin_amdgcn_perm(__float_as_uint(l1), __float_as_uint(l0), 0x07060302u);
-                }
-            }
+    if constexpr (hardware_scheme(MODE, PS)) {
+        if (hardware_format<MODE, PS>(p)) {
+            hardware_convert<FTZ, PS>(v, p, out);
+            return;
         }
+    }
+    if (__ballot(run_is_rare(v, p)) == 0ull) {            // the same in the whole wave
+        short_convert<MODE, FTZ, PS>(v, p, k, out);
         return;
     }
     uint32_t pc[8][P];

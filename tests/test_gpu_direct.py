@@ -171,3 +171,36 @@ def test_overflow_infinity_nan(fmt, e, m, d, monkeypatch):
         assert ((got[inf] == want[inf]) | np.isnan(got[inf])).all()
         fin = np.isfinite(want)
         assert np.array_equal(got[fin], want[fin])
+
+
+@pytest.mark.parametrize("e,m,d", [(5, 10, True), (5, 10, False), (8, 7, True), (8, 7, False)])
+@pytest.mark.parametrize("K", [1, 5])
+def test_conversion_of_binary16_and_bfloat16(fmt, e, m, d, K, monkeypatch):
+    """The vector units' own conversions: every exponent with ties, their neighbours and random mantissas, both signs, and the
+    patterns around the thresholds of overflow and flush, times 1 and 2^20 (K = 1: loaded singly, K = 5: in vectors), in one launch
+    and as prepared operands: the oracle's roundings, exactly (both factors are powers of two)."""
+    rng = np.random.default_rng(e + K)
+    half = 1 << (22 - m)
+    mant = np.concatenate([[0, 1, half - 1, half, half + 1, 3 * half - 1, 3 * half, 3 * half + 1, 0x7FFFFF], rng.integers(0, 1 << 23, 7)])
+    u = (np.arange(255, dtype=np.uint32)[:, None] << 23 | mant.astype(np.uint32)[None, :]).ravel()
+    c = oracle.format_constants(e, m)
+    edges = np.array([c["minN"], c["minD"], c["minD"] / 2, c["minN"] - c["minD"] / 2, c["maxN"]], dtype=np.float64).astype(np.float32).view(np.uint32)
+    u = np.concatenate([u] + [edges + np.uint32(j) for j in (0, 1)] + [edges - np.uint32(1)])
+    x = np.concatenate([u, u | np.uint32(0x80000000)]).view(np.float32)
+    q = oracle.quantize(x, e, m, d).astype(np.float64)
+    A = np.zeros((x.size, K), dtype=np.float32)
+    A[:, K - 1] = x
+    B = np.zeros((K, 2), dtype=np.float32)
+    B[K - 1] = 1.0, 2.0 ** (10 if e == 5 else 20)
+    want = q[:, None] * B[K - 1].astype(np.float64)[None, :]
+    monkeypatch.setenv("FMT_GEMM_PLAN", "direct")
+    got = [product(fmt, A, B, (e, m, d), False, False)]
+    monkeypatch.delenv("FMT_GEMM_PLAN")
+    pa, pb = fmt.fmt_prepare(torch.from_numpy(A).cuda(), (e, m, d)), fmt.fmt_prepare(torch.from_numpy(B).cuda(), (e, m, d), trans=True)
+    got.append(fmt.fmt_gemm_prepared(pa, pb).cpu().numpy())
+    plain = np.isfinite(want) & ((want == 0) | (np.abs(want) >= 2.0 ** -126)) & (np.abs(want) < 2.0 ** 127)
+    inf = np.isinf(want[:, 0])
+    assert plain.sum() > 6000 and (inf.any() or e == 8)
+    for g in got:
+        assert np.array_equal(g[plain], want[plain].astype(np.float32))
+        assert np.array_equal(g[inf, 0], want[inf, 0].astype(np.float32)) or K > 1        # K > 1: infinity times a zero of the padding
