@@ -134,11 +134,15 @@ struct WideConsts {
 // The larger of |s| and 1.5 * 2^Emin with the lo word cleared, in one instruction: the hi words of two non-negative doubles
 // compare like the singles of the same pattern (a pattern that is a denormal single belongs to a double below 2^-1015,
 // here zero, and loses either way; one that is an infinite or NaN single to a double from 2^1017, far above the limit).
-__device__ __forceinline__ double carrier(double s, const WideConsts &k)
+// pair: the registers it comes in, the lower one zero from the kernel's start on (the compiler does not know that it is, and so does not
+// set it to zero before every step or every few).
+typedef float hi_lo __attribute__((ext_vector_type(2)));
+__device__ __forceinline__ double carrier(double s, const WideConsts &k, hi_lo &pair)
 {
     float t;
     asm("v_max_f32 %0, |%1|, %2" : "=v"(t) : "v"(__int_as_float(__double2hiint(s))), "s"(k.floor_hi));
-    return __hiloint2double(__float_as_int(t), 0);
+    pair.y = t;
+    return __builtin_bit_cast(double, pair);
 }
 
 // The fused step in fp64, for |a + w*x| < wide_limit = 2^(Emin - m + 52): 4 instructions (6 with the flush).
@@ -161,10 +165,10 @@ __device__ __forceinline__ double carrier(double s, const WideConsts &k)
 //     zero of either sign is added.
 // Results do not overflow below the limit (the caller's bound is below the format's overflow threshold as well).
 template <bool FTZ, bool FIRST>
-__device__ __forceinline__ double fmac_wide(double a, double w, double x, const WideConsts &k)
+__device__ __forceinline__ double fmac_wide(double a, double w, double x, const WideConsts &k, hi_lo &pair)
 {
     const double s = FIRST ? __dmul_rn(w, x) : __fma_rn(w, x, a);
-    const double t = carrier(s, k);
+    const double t = carrier(s, k, pair);
     const double r = __fma_rn(t, -k.scale, __fma_rn(t, k.scale, s));
     if (!FTZ) return r;
     // The result is below minN exactly where |s| is below minN less half a step (that midpoint goes to minN, the even
@@ -182,6 +186,44 @@ __device__ __forceinline__ A operand(double v)
     else return (A)v;
 }
 
+// A thread's elements of an operand's stages of KS k x 16 T rows, element `it` a fixed step from the one before it: consecutive lanes
+// walk whichever of k and row is contiguous in memory.  PITCH: of a stage in LDS, [k][row].
+template <int T, int KS, int PITCH = 16 * T + 2>
+struct StageOperand {
+    static constexpr int kRows = 16 * T, kCount = kRows * KS / 256;
+    const uint32_t *first;           // element 0 of the stage that begins at k = 0
+    int64_t step, stage;             // from element to element, from k to k
+    int row, k, row_step, k_step, rows;
+    bool inside;                     // the tile's rows are inside the operand
+    __device__ __forceinline__ StageOperand(const uint32_t *X, int64_t ld, bool kcontig, int row0, int rows_, int tid)
+    {
+        row = kcontig ? tid / KS : tid % kRows;
+        k = kcontig ? tid % KS : tid / kRows;
+        row_step = kcontig ? 256 / KS : 0;
+        k_step = kcontig ? 0 : 256 / kRows;
+        first = X + (kcontig ? (int64_t)(row0 + row) * ld + k : (int64_t)k * ld + row0 + row);
+        step = kcontig ? (int64_t)row_step * ld : (int64_t)k_step * ld;
+        stage = kcontig ? 1 : ld;
+        rows = rows_ - row0;
+        inside = row0 + kRows <= rows_;
+    }
+    __device__ __forceinline__ void load(uint32_t (&v)[kCount], int k0, int K) const
+    {
+        const uint32_t *src = first + (int64_t)k0 * stage;
+        if (inside && k0 + KS <= K) {            // the same in the whole workgroup
+#pragma unroll
+            for (int it = 0; it < kCount; ++it) v[it] = src[it * step];
+        } else {
+#pragma unroll
+            for (int it = 0; it < kCount; ++it) {
+                v[it] = 0u;
+                if (row + it * row_step < rows && k0 + k + it * k_step < K) v[it] = src[it * step];
+            }
+        }
+    }
+    __device__ __forceinline__ int place(int it) const { return (k + it * k_step) * PITCH + row + it * row_step; }
+};
+
 constexpr int kFK = 32;        // k per LDS stage (a multiple of 8: FMAC-8 groups never straddle stages)
 enum { kStepSingle = 0, kStepOdd = 1 };     // the form besides the wide one that an instantiation holds
 
@@ -189,10 +231,15 @@ enum { kStepSingle = 0, kStepOdd = 1 };     // the form besides the wide one tha
 // what counts is that every SIMD has instructions to issue: for the wide step 16 chains per thread where there are tiles enough
 // to fill the chip, 4 or 1 where there are not; the round-to-odd step, five times as long, fills it with one (see launch).  Operand stages are rounded on the way into LDS, as fp64 (a
 // value converted once instead of once per use); the next stage's loads are in flight while a stage is computed.
-// Measured in 1/6/9: 2048 x 2048 x 1024 takes 0.63 ms (6.8 T fused steps/s; 0.74 ms with a step of 5 instructions, 1.97 ms with the
-// single form alone), 256 x 256 x 256 takes 13 us (17 us with a step of 5 instructions whose operands were read one by one).
+// Bound by the vector units: the four instructions of the steps alone, in registers, take 0.46 to 0.49 ms of the 0.58 below (the chip answers
+// fp64 with its clock), the rest is the rounding of the operands, the additions to the masters and LDS.  Four workgroups per compute
+// unit (128 registers; the few that spill belong to the loads of tiles at an edge) are all of the 1024 tiles of 2048 x 2048: with
+// three, the fourth ran alone.
+// Measured in 1/6/9: 2048 x 2048 x 1024 takes 0.58 ms (7.4 T fused steps/s; 0.63 ms with three workgroups per compute unit, the general
+// rounding of the operands and 64 registers of addresses, 0.74 ms with a step of 5 instructions, 1.97 ms with the
+// single form alone; the single form at 2048 x 2048 x 256 0.39 ms, 0.49 before), 256 x 256 x 256 takes 12.5 us (17 us with a step of 5 instructions whose operands were read one by one).
 template <int MODE, bool FTZ, int STEP, int T>
-__global__ __launch_bounds__(256) void fmac8_kernel(const uint32_t *__restrict__ A, int64_t lda, int transA,
+__global__ __launch_bounds__(256, T > 2 ? 4 : 1) void fmac8_kernel(const uint32_t *__restrict__ A, int64_t lda, int transA,
                                                     const uint32_t *__restrict__ B, int64_t ldb, int transB,
                                                     float *__restrict__ C, int64_t ldc, int M, int N, int K,
                                                     int tiles_n, QuantParams qp, Fmac8Params fp, WideConsts wc)
@@ -214,32 +261,10 @@ __global__ __launch_bounds__(256) void fmac8_kernel(const uint32_t *__restrict__
                           __uint_as_float((qp.t_ovf & 0x7F800000u) + 0x00800000u)};   // t_ovf lies in the top binade
 
     uint32_t va[kLoads], vb[kLoads];
-    // element `it` of this thread: (row or column in the tile, k in the stage); consecutive lanes walk whichever
-    // of the two is contiguous in memory
-    auto a_at = [&](int it, int &r, int &k) {
-        const int idx = it * 256 + tid;
-        r = transA ? idx % kTile : idx / kFK;
-        k = transA ? idx / kTile : idx % kFK;
-    };
-    auto b_at = [&](int it, int &c, int &k) {
-        const int idx = it * 256 + tid;
-        c = transB ? idx / kFK : idx % kTile;
-        k = transB ? idx % kFK : idx / kTile;
-    };
+    const StageOperand<T, kFK> oa(A, lda, !transA, row0, M, tid), ob(B, ldb, transB != 0, col0, N, tid);
     auto load = [&](int k0) {
-#pragma unroll
-        for (int it = 0; it < kLoads; ++it) {
-            int r, k;
-            a_at(it, r, k);
-            const int gr = row0 + r, gk = k0 + k;
-            va[it] = 0u;
-            if (gr < M && gk < K) va[it] = transA ? A[(size_t)gk * lda + gr] : A[(size_t)gr * lda + gk];
-            int c;
-            b_at(it, c, k);
-            const int gc = col0 + c, gkb = k0 + k;
-            vb[it] = 0u;
-            if (gc < N && gkb < K) vb[it] = transB ? B[(size_t)gc * ldb + gkb] : B[(size_t)gkb * ldb + gc];
-        }
+        oa.load(va, k0, K);
+        ob.load(vb, k0, K);
     };
 
     // The largest tile, whose thread uses a value four times, stores a stage for the form that the stage before it took: as fp64,
@@ -247,25 +272,45 @@ __global__ __launch_bounds__(256) void fmac8_kernel(const uint32_t *__restrict__
     // (2048 x 2048 x 256 in 1/6/9: 512 us; 496 now); the smaller tiles, which gain nothing, are 2 us faster without the
     // code for it (1024 x 1024 x 256, wide form: 66 us against 68).
     constexpr bool kLow = STEP == kStepSingle && T > 2;
+    hi_lo pair = {0.0f, 0.0f};
+    asm("" : "+v"(pair));
     bool wide = true;
     load(0);
     for (int k0 = 0; k0 < K; k0 += kFK) {
+        // Rounding in the short form unless a wave holds something near overflow or beyond (13 instructions per element otherwise, a sixth of
+        // the steps').  The largest magnitudes are taken of the unrounded elements, two per instruction, and rounded where they are used: the
+        // rounding is monotonic.  NaN come out as the largest pattern.
         uint32_t ma = 0u, mb = 0u;
+        auto top = [](const uint32_t (&v)[kLoads]) {
+            float m = fabsf(__uint_as_float(v[0]));
 #pragma unroll
-        for (int it = 0; it < kLoads; ++it) {
-            va[it] = quantize_bits<MODE, FTZ>(va[it], qp);
-            vb[it] = quantize_bits<MODE, FTZ>(vb[it], qp);
-            ma = max(ma, va[it] & 0x7FFFFFFFu);
-            mb = max(mb, vb[it] & 0x7FFFFFFFu);
+            for (int it = 1; it + 1 < kLoads; it += 2)
+                m = __builtin_elementwise_maximum(__builtin_elementwise_maximum(fabsf(__uint_as_float(v[it])), fabsf(__uint_as_float(v[it + 1]))), m);
+            if (kLoads % 2 == 0) m = __builtin_elementwise_maximum(fabsf(__uint_as_float(v[kLoads - 1])), m);
+            return __float_as_uint(m) & 0x7FFFFFFFu;
+        };
+        ma = top(va), mb = top(vb);
+        if (MODE != kModeMixed && __ballot(max(ma, mb) >= qp.t_ovf) == 0ull) {        // the same in the whole wave
+            const RoundMasks masks = round_masks(qp);
+#pragma unroll
+            for (int it = 0; it < kLoads; ++it) {
+                if constexpr (MODE != kModeMixed) {
+                    va[it] = quantize_short<MODE, FTZ, false>(va[it], qp, masks);     // the sign of a zero changes nothing
+                    vb[it] = quantize_short<MODE, FTZ, false>(vb[it], qp, masks);
+                }
+            }
+        } else {
+#pragma unroll
+            for (int it = 0; it < kLoads; ++it) {
+                va[it] = quantize_bits<MODE, FTZ>(va[it], qp);
+                vb[it] = quantize_bits<MODE, FTZ>(vb[it], qp);
+            }
         }
         auto store = [&](auto place) __attribute__((always_inline)) {
 #pragma unroll
             for (int it = 0; it < kLoads; ++it) {
-                int r, k;
-                a_at(it, r, k);
-                sa[k][r] = place(va[it]);
-                b_at(it, r, k);
-                sb[k][r] = place(vb[it]);
+                (&sa[0][0])[oa.place(it)] = place(va[it]);
+                (&sb[0][0])[ob.place(it)] = place(vb[it]);
             }
         };
         if (!kLow || wide) store([](uint32_t q) { return (double)__uint_as_float(q); });
@@ -284,8 +329,8 @@ __global__ __launch_bounds__(256) void fmac8_kernel(const uint32_t *__restrict__
         __syncthreads();
         if (k0 + kFK < K) load(k0 + kFK);          // in flight while this stage is computed
         if (STEP == kStepSingle) {
-            const uint32_t wa = max(max(s_max[0][0], s_max[0][1]), max(s_max[0][2], s_max[0][3]));
-            const uint32_t wb = max(max(s_max[1][0], s_max[1][1]), max(s_max[1][2], s_max[1][3]));
+            const uint32_t wa = quantize_bits<MODE, FTZ>(max(max(s_max[0][0], s_max[0][1]), max(s_max[0][2], s_max[0][3])), qp);
+            const uint32_t wb = quantize_bits<MODE, FTZ>(max(max(s_max[1][0], s_max[1][1]), max(s_max[1][2], s_max[1][3])), qp);
             // infinities and NaN (patterns from 0x7F800000) are left to the other form
             const bool fits = wa < 0x7F800000u && wb < 0x7F800000u && __fmul_rn(__uint_as_float(wa), __uint_as_float(wb)) < wc.limit;
             const bool next = __builtin_amdgcn_readfirstlane(fits ? 1 : 0) != 0;      // the same in the whole workgroup
@@ -295,11 +340,9 @@ __global__ __launch_bounds__(256) void fmac8_kernel(const uint32_t *__restrict__
                 };
 #pragma unroll
                 for (int it = 0; it < kLoads; ++it) {
-                    int r, k;
-                    a_at(it, r, k);
-                    sa[k][r] = other(sa[k][r]);
-                    b_at(it, r, k);
-                    sb[k][r] = other(sb[k][r]);
+                    double &at = (&sa[0][0])[oa.place(it)], &bt = (&sb[0][0])[ob.place(it)];
+                    at = other(at);
+                    bt = other(bt);
                 }
                 __syncthreads();
             }
@@ -333,8 +376,8 @@ __global__ __launch_bounds__(256) void fmac8_kernel(const uint32_t *__restrict__
                     for (int i = 0; i < T; ++i)
 #pragma unroll
                         for (int j = 0; j < T; ++j)
-                            a16[i][j] = kk == 0 ? fmac_wide<FTZ, true>(0.0, w[kk][i], x[kk][j], wc)
-                                                : fmac_wide<FTZ, false>(a16[i][j], w[kk][i], x[kk][j], wc);
+                            a16[i][j] = kk == 0 ? fmac_wide<FTZ, true>(0.0, w[kk][i], x[kk][j], wc, pair)
+                                                : fmac_wide<FTZ, false>(a16[i][j], w[kk][i], x[kk][j], wc, pair);
                 }
 #pragma unroll
                 for (int i = 0; i < T; ++i)
