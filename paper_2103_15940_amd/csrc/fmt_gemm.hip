@@ -64,6 +64,70 @@ __device__ __forceinline__ size_t unit_vec_index(int rb, int kb, int kblocks, in
 constexpr int kWinTmin = 0, kWinTmax = 31;              // range of plane 0's top binade T (S = 15 - T): with
                                                         // three planes every value of a 1/6/m format, m <= 9, fits
 
+constexpr int kNoBinade = -1000;
+
+// The binades of a sample of elements (fp32 patterns): the largest, and the smallest of a value that is normal in the format, emin - 1
+// standing for one in its denormal range.  Zeros, what rounds to zero, infinities and NaN do not count.
+__device__ __forceinline__ void window_look(uint32_t u, int emin, int m, int &hi, int &lo)
+{
+    const uint32_t ab = u & 0x7FFFFFFFu;
+    const int E = (int)(ab >> 23) - 127;
+    if (ab < 0x7F800000u && E >= emin - m - 1) {
+        hi = max(hi, E);
+        lo = min(lo, max(E, emin - 1));
+    }
+}
+
+// The scale exponent S of exponent planes that suits what a sample showed (the rule and its reasons: window_stats_block).
+__device__ __forceinline__ int window_scale(int hi, int lo, int emin, int m)
+{
+    const int wid = 39 - m;                       // binades below the top one that a plane holds with m + 1 significant bits
+    int T = 0;
+    if (hi != kNoBinade) {
+        const int top = hi + 1, room = lo + wid;
+        T = lo < emin ? 9 - m : (top >= room ? room : top + min(4, (room - top) / 2));
+    }
+    return 15 - max(kWinTmin, min(kWinTmax, T));
+}
+
+// The same for a tensor of n > 0 elements with one scale, by a workgroup of 256: 32 runs of 16 elements spread over it.  Every workgroup of
+// the pass that needs S does this for itself, beside its own loads, and all come to the same S: a launch less than with a kernel ahead.
+__device__ __forceinline__ int tensor_scale(const uint32_t *__restrict__ x, uint32_t n, int emin, int m)
+{
+    __shared__ int s_hi[4], s_lo[4];
+    const uint32_t lane = threadIdx.x & 63u, wave = threadIdx.x >> 6;
+    const uint32_t step = n > 512u ? (n - 16u) / 31u : 16u;
+    uint32_t u[2];
+#pragma unroll
+    for (uint32_t i = 0; i < 2; ++i) u[i] = x[min((wave * 8u + i * 4u + lane / 16u) * step + lane % 16u, n - 1u)];
+    int hi = kNoBinade, lo = 1000;
+#pragma unroll
+    for (int i = 0; i < 2; ++i) window_look(u[i], emin, m, hi, lo);
+#pragma unroll
+    for (int off = 1; off < 64; off <<= 1) {
+        hi = max(hi, __shfl_xor(hi, off, 64));
+        lo = min(lo, __shfl_xor(lo, off, 64));
+    }
+    if (lane == 0u) {
+        s_hi[wave] = hi;
+        s_lo[wave] = lo;
+    }
+    __syncthreads();
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        hi = max(hi, s_hi[i]);
+        lo = min(lo, s_lo[i]);
+    }
+    return __builtin_amdgcn_readfirstlane(window_scale(hi, lo, emin, m));
+}
+
+// What a pass that makes such planes knows of the tensor.
+struct WindowTensor {
+    const uint32_t *x;
+    uint32_t n;
+    int emin, m;
+};
+
 // How element (row, k) of an operand is found in memory.
 enum {
     kSrcMatrix = 0,     // X[row*ld + k] (kcontig) or X[k*ld + row]
@@ -251,6 +315,48 @@ __global__ __launch_bounds__(256) void round_split_kernel(const uint32_t *__rest
     }
 }
 
+// The same for exponent planes with one scale: a word holds the element's binary16 pattern and, in its upper half, the plane that it
+// belongs to (0, 1 above, 2 below).
+template <int MODE, bool FTZ>
+__global__ __launch_bounds__(256) void round_window_kernel(WindowTensor t, uint32_t *__restrict__ out, int w, int *__restrict__ S_out, QuantParams p)
+{
+    constexpr int kEach = 4;
+    uint32_t u[kEach];
+    auto load = [&](uint32_t first) __attribute__((always_inline)) {
+#pragma unroll
+        for (uint32_t j = 0; j < kEach; ++j) u[j] = t.x[min(first + threadIdx.x + j * 256u, t.n - 1u)];
+    };
+    uint32_t first = blockIdx.x * (256u * kEach);
+    load(first);
+    const int S = tensor_scale(t.x, t.n, t.emin, t.m);
+    if (blockIdx.x == 0 && threadIdx.x == 0) {
+        out[t.n] = 0u;
+        S_out[0] = S;
+    }
+    const float f = __uint_as_float((uint32_t)(127 + S) << 23);
+    for (;;) {
+        uint32_t r[kEach];
+        quantize_run<MODE, FTZ>(u, run_is_rare(u, p), p, round_masks(p), r);
+#pragma unroll
+        for (uint32_t j = 0; j < kEach; ++j) {
+            const float sc = __uint_as_float(r[j]) * f;
+            _Float16 h = static_cast<_Float16>(sc);
+            const float back = static_cast<float>(h);
+            uint32_t plane = 0u;
+            if (back < sc || back > sc) {         // as split_planes has it
+                const bool up = fabsf(sc) >= 65536.0f;
+                h = static_cast<_Float16>(ldexpf(__uint_as_float(r[j]), up ? S - w : S + w));
+                plane = up ? 1u : 2u;
+            }
+            const uint32_t i = first + threadIdx.x + j * 256u;
+            if (i < t.n) out[i] = (uint32_t)__builtin_bit_cast(uint16_t, h) | (plane << 16);
+        }
+        if (t.n - first <= gridDim.x * (256u * kEach)) break;
+        first += gridDim.x * (256u * kEach);
+        load(first);
+    }
+}
+
 // Rounds an NCHW tensor (C a multiple of 32) to the format, splits it, and writes the pieces in
 // pixel-major order out[piece][pixel][channel] (16 bits per element) -- the operand the product kernel
 // gathers convolution patches from.  A workgroup takes 64 consecutive pixels (of the flattened n*h*w)
@@ -300,9 +406,12 @@ __device__ __forceinline__ void nhwc_split_block(const uint32_t *__restrict__ x,
 // the forward gather; what differs is the output, which wants 8 consecutive positions of ONE tap in
 // a lane.  Each wave therefore passes its 8 taps x 64 positions through a tile of its own in LDS and
 // reads them back transposed (rows padded to 72 words against bank conflicts).
-template <int P>
+// WINDOW: the words are round_window_kernel's.  Plane 0 is written in a first turn over the taps, and only if the workgroup met elements of
+// the other planes are these written, in a second, for the units that hold any.
+template <int P, bool WINDOW = false>
 __device__ __forceinline__ void gather_taps(const PrepOperand &o, unsigned bid, int K, int kblocks)
 {
+    static_assert(!WINDOW || P == 1, "one piece");
     constexpr int NW = (P + 1) / 2;                    // 32-bit word planes per element
     __shared__ uint32_t tile[4][NW][8][72];
     const Gather &g = o.g;
@@ -329,6 +438,18 @@ __device__ __forceinline__ void gather_taps(const PrepOperand &o, unsigned bid, 
     const int gi = lane >> 3, li = lane & 7;           // after the transpose: positions gi*8 .. gi*8+7 of tap li
     const int pb = pg * 256 + wave * 64 + gi * 8;       // first of this lane's 8 positions
     const int kb = pb / kUnitK, c = (pb % kUnitK) / 8;
+    uint32_t have = 1u;                                // WINDOW: planes met
+#pragma unroll 1
+    for (int turn = 0; turn < (WINDOW ? 2 : 1); ++turn) {
+    if constexpr (WINDOW) {
+        if (turn == 1) {
+            // of the unit: the lanes of one half of the wave
+#pragma unroll
+            for (int off = 1; off < 32; off <<= 1) have |= (uint32_t)__shfl_xor((int)have, off, 64);
+            if (kb < kblocks && (lane & 31) == 0) o.pl.mask[(size_t)rb * kblocks + kb] = (uint8_t)have;
+            if (!__syncthreads_or((have & 6u) != 0u)) break;
+        }
+    }
     for (int pass = 0; pass < 4; ++pass) {
         const int tap0 = rb * 32 + pass * 8;           // the same in the whole workgroup
         int s, t2, r, ch;
@@ -366,8 +487,35 @@ __device__ __forceinline__ void gather_taps(const PrepOperand &o, unsigned bid, 
         for (int q = 0; q < NW; ++q)
 #pragma unroll
             for (int m = 0; m < 8; ++m) v[q][m] = tile[wave][q][li][gi * 8 + m];
-        if (kb < kblocks) {
-            const int rr = pass * 8 + li;
+        const int rr = pass * 8 + li;
+        if constexpr (WINDOW) {
+            uint32_t planes = 0u;
+#pragma unroll
+            for (int m = 0; m < 8; ++m) planes |= v[0][m] >> 16;             // 1 above, 2 below, 3 both
+            if (turn == 0) {
+                have |= planes << 1;
+                if (__ballot(planes != 0u) != 0ull) {                        // the same in the whole wave
+#pragma unroll
+                    for (int m = 0; m < 8; ++m) v[0][m] = v[0][m] < 0x10000u ? v[0][m] : 0u;
+                }
+                if (kb < kblocks) {
+                    u32x4 out;
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) out[i] = __builtin_amdgcn_perm(v[0][2 * i + 1], v[0][2 * i], 0x05040100u);
+                    o.W[unit_vec_index(rb, kb, kblocks, 1, 0, c, rr)] = out;
+                }
+            } else if (kb < kblocks) {
+#pragma unroll
+                for (uint32_t q = 1; q < 3; ++q)
+                    if ((have >> q) & 1u) {
+                        u32x4 out;
+#pragma unroll
+                        for (int i = 0; i < 4; ++i)
+                            out[i] = (v[0][2 * i] >> 16 == q ? v[0][2 * i] & 0xFFFFu : 0u) | (v[0][2 * i + 1] >> 16 == q ? v[0][2 * i + 1] << 16 : 0u);
+                        o.W[q * o.pl.plane + unit_vec_index(rb, kb, kblocks, 1, 0, c, rr)] = out;
+                    }
+            }
+        } else if (kb < kblocks) {
 #pragma unroll
             for (int pc = 0; pc < P; ++pc) {
                 u32x4 out;
@@ -379,6 +527,7 @@ __device__ __forceinline__ void gather_taps(const PrepOperand &o, unsigned bid, 
                 o.W[unit_vec_index(rb, kb, kblocks, P, pc, c, rr)] = out;
             }
         }
+    }
     }
 }
 
@@ -566,12 +715,12 @@ __device__ __forceinline__ void prepare_block(const PrepOperand &a, const PrepOp
 // Eight rounded values of one thread (fp32 patterns r[], elements k0 .. k0 + 7 of row `row` of operand o) as
 // binary16 patterns, two per word: p0 = plane 0, pa / pb = the planes above / below (zero where an element
 // does not belong to the plane).  Elements outside plane 0 also leave a record in the list of their row of
-// units for the kernel that adds their products.  Returns 2 / 4 if any element went above / below.
-template <class OP>
-__device__ __forceinline__ uint32_t split_planes(const OP &o, int row, int k0, const uint32_t (&r)[8], u32x4 &p0, u32x4 &pa,
+// units for the kernel that adds their products (not where one scale S serves the whole tensor: RECORDS false, and row and k0 unused).
+// Returns 2 / 4 if any element went above / below.
+template <bool RECORDS = true>
+__device__ __forceinline__ uint32_t split_planes(const Planes &pl, int S, int row, int k0, const uint32_t (&r)[8], u32x4 &p0, u32x4 &pa,
                                                  u32x4 &pb)
 {
-    const int S = o.pl.S[row];                   // S covers the padded rows
     const float f = __uint_as_float((uint32_t)(127 + S) << 23);     // 2^S: -16 <= S <= 15
     pa = pb = u32x4{0u, 0u, 0u, 0u};
     uint32_t mine = 0u;
@@ -585,7 +734,7 @@ __device__ __forceinline__ uint32_t split_planes(const OP &o, int row, int k0, c
 #pragma unroll
     for (int j = 0; j < 8; j += 2) top = __builtin_elementwise_maximum(__builtin_elementwise_maximum(fabsf(sc[j]), fabsf(sc[j + 1])), top);
     bool inside = top < 65536.0f;
-    const bool bottom = S >= 46 - o.pl.w;
+    const bool bottom = S >= 46 - pl.w;
     if (__ballot(!bottom) != 0ull) {             // the same in the whole wave
         uint32_t least = 0xFFFFFFFFu;            // twice a pattern less one: zeros come last
 #pragma unroll
@@ -611,7 +760,7 @@ __device__ __forceinline__ uint32_t split_planes(const OP &o, int row, int k0, c
         hb[j] = (uint32_t)__builtin_bit_cast(uint16_t, h);
     }
     if (any) {  
-        const int w = o.pl.w;
+        const int w = pl.w;
 #pragma unroll
         for (int j = 0; j < 8; ++j) {
             if (other[j]) {
@@ -624,11 +773,13 @@ __device__ __forceinline__ uint32_t split_planes(const OP &o, int row, int k0, c
                 pb[j / 2] |= up ? 0u : gb;
                 mine |= up ? 2u : 4u;
                 hb[j] = 0u;
-                const uint32_t slot = atomicAdd(&o.pl.rec_cnt[row / kUnitRows], 1u);
-                if (slot < (uint32_t)kRecCap) {
-                    uint32_t *rec = o.pl.recs + ((size_t)(row / kUnitRows) * kRecCap + slot) * 2;
-                    rec[0] = ((uint32_t)(k0 + j) << 5) | (uint32_t)(row % kUnitRows);
-                    rec[1] = r[j];
+                if constexpr (RECORDS) {
+                    const uint32_t slot = atomicAdd(&pl.rec_cnt[row / kUnitRows], 1u);
+                    if (slot < (uint32_t)kRecCap) {
+                        uint32_t *rec = pl.recs + ((size_t)(row / kUnitRows) * kRecCap + slot) * 2;
+                        rec[0] = ((uint32_t)(k0 + j) << 5) | (uint32_t)(row % kUnitRows);
+                        rec[1] = r[j];
+                    }
                 }
             }
         }
@@ -702,7 +853,7 @@ __device__ __forceinline__ void prepare_scaled_block(const OP &o, int K, int kbl
     uint32_t r[8];
     u32x4 p0, pa, pb;
     quantize_run<MODE, FTZ>(v, run_is_rare(v, p), p, round_masks(p), r);
-    const uint32_t mine = split_planes(o, row, k0, r, p0, pa, pb);
+    const uint32_t mine = split_planes(o.pl, o.pl.S[row], row, k0, r, p0, pa, pb);      // S covers the padded rows
     __syncthreads();                             // s_planes has been cleared
     if (mine != 0u) atomicOr(&s_planes[u], mine);
     __syncthreads();
@@ -815,10 +966,10 @@ __device__ __forceinline__ void prepare_pair_tile(const OP &o0, const OP &o1, co
 #pragma unroll
             for (int j = 0; j < 4; ++j) r[4 * h + j] = r4[j];
         }
-        const uint32_t mine0 = split_planes(o0, xr, xc, r, p0a, paa, pba);
+        const uint32_t mine0 = split_planes(o0.pl, o0.pl.S[xr], xr, xc, r, p0a, paa, pba);
 #pragma unroll
         for (int j = 0; j < 8; ++j) t[j] = s_r[(tid / 64) * 8 + j][tid % 64];
-        const uint32_t mine1 = split_planes(o1, row1, k1, t, p0b, pab, pbb);
+        const uint32_t mine1 = split_planes(o1.pl, o1.pl.S[row1], row1, k1, t, p0b, pab, pbb);
         if (mine0 != 0u) atomicOr(&s_planes[u0], mine0);
         if (mine1 != 0u) atomicOr(&s_planes[u1], mine1);
         __syncthreads();
@@ -849,6 +1000,117 @@ __global__ __launch_bounds__(256) void prepare_implicit_kernel(PrepOperand a, in
         const unsigned id = blockIdx.x - split_first;
         nhwc_split_block<MODE, FTZ, PS>(x, out, C, HW, npix, p, (int)(id % nx), (int)(id / nx));
     }
+}
+
+// The two for exponent planes with one scale per tensor: an operand whose elements gather8 finds (k along the lanes), in the layout that
+// prepare_scaled_block writes, ...
+template <int MODE, bool FTZ>
+__device__ __forceinline__ void prepare_window_block(const PrepOperand &o, const WindowTensor &t, int K, int kblocks, const QuantParams &p, unsigned bid)
+{
+    __shared__ uint32_t s_planes[2];
+    const int tid = threadIdx.x;
+    if (tid < 2) s_planes[tid] = 0u;
+    const int nslabs = (kblocks + 1) / 2;
+    const int row = (int)(bid / (unsigned)nslabs) * 32 + tid / 8, k0 = (int)(bid % (unsigned)nslabs) * 64 + (tid % 8) * 8;
+    const int u = (tid % 8) / 4;                 // which of the workgroup's two units
+    int idx[8];
+    uint32_t v[8], r[8];
+    gather8(o, row, k0, K, idx);
+#pragma unroll
+    for (int j = 0; j < 8; ++j) v[j] = idx[j] >= 0 ? o.X[(uint32_t)idx[j]] : 0u;
+    const int S = tensor_scale(t.x, t.n, t.emin, t.m);       // its barrier: s_planes has been cleared
+    if (bid == 0u && tid == 0) o.pl.S[0] = S;
+    u32x4 p0, pa, pb;
+    quantize_run<MODE, FTZ>(v, run_is_rare(v, p), p, round_masks(p), r);
+    const uint32_t mine = split_planes<false>(o.pl, S, row, k0, r, p0, pa, pb);
+    if (mine != 0u) atomicOr(&s_planes[u], mine);
+    __syncthreads();
+    if (k0 < kblocks * kUnitK) store_planes(o, row, k0, kblocks, p0, pa, pb, s_planes[u], tid / 8 == 0 && tid % 4 == 0);
+}
+
+// ... and a tensor in pixel-major order, out[plane][pixel][channel] (nhwc_split_block), with the masks of 64 pixels x 32 channels.
+// Planes above and below are written where these are not zero.
+template <int MODE, bool FTZ>
+__device__ __forceinline__ void nhwc_window_block(const WindowTensor &t, u32x4 *__restrict__ out, const Planes &pl, int C, int HW, int npix,
+                                                  const QuantParams &p, int bx, int cb)
+{
+    constexpr int kPitch = 18;
+    __shared__ uint32_t tile[64][kPitch];
+    __shared__ unsigned long long s_have[2];
+    const int tid = threadIdx.x;
+    if (tid < 2) s_have[tid] = 0ull;
+    const int pix = tid % 64, cg = tid / 64;
+    const int gp = bx * 64 + pix;
+    const bool valid = gp < npix;
+    const int n = valid ? gp / HW : 0, hw = valid ? gp - n * HW : 0;
+    const uint32_t *src = t.x + ((size_t)n * C + cb * 32 + cg * 8) * HW + hw;
+    uint32_t u[8], r[8];
+#pragma unroll
+    for (int i = 0; i < 8; ++i) u[i] = valid ? src[(size_t)i * HW] : 0u;
+    const int S = tensor_scale(t.x, t.n, t.emin, t.m);       // its barrier: s_have has been cleared
+    u32x4 pc[3];
+    quantize_run<MODE, FTZ>(u, run_is_rare(u, p), p, round_masks(p), r);
+    const uint32_t mine = split_planes<false>(pl, S, 0, 0, r, pc[0], pc[1], pc[2]);
+    if (__ballot(mine != 0u) != 0ull) {
+        const unsigned long long above = __ballot((mine & 2u) != 0u), below = __ballot((mine & 4u) != 0u);      // a lane per pixel
+        if (pix == 0) {
+            atomicOr(&s_have[0], above);
+            atomicOr(&s_have[1], below);
+        }
+    }
+    const int opix = tid / 4, part = tid % 4;
+    const int ogp = bx * 64 + opix;
+    const size_t piece_vec = (size_t)npix * (C / 8);
+    uint32_t have = 1u;
+#pragma unroll
+    for (int q = 0; q < 3; ++q) {
+        if (!((have >> q) & 1u)) continue;       // the same in the whole workgroup
+        if (q > 0) __syncthreads();              // the plane before has been read
+#pragma unroll
+        for (int i = 0; i < 4; ++i) tile[pix][cg * 4 + i] = pc[q][i];
+        __syncthreads();
+        if (q == 0) have = 1u | (s_have[0] != 0ull ? 2u : 0u) | (s_have[1] != 0ull ? 4u : 0u);
+        if (ogp < npix) {
+            u32x4 w;
+#pragma unroll
+            for (int i = 0; i < 4; ++i) w[i] = tile[opix][part * 4 + i];
+            out[q * piece_vec + (size_t)ogp * (C / 8) + cb * 4 + part] = w;
+        }
+    }
+    if (tid < 2) reinterpret_cast<unsigned long long *>(pl.mask)[((size_t)bx * (C / 32) + cb) * 2 + tid] = s_have[tid];
+    if (bx == 0 && cb == 0 && tid == 0) {
+        pl.S[0] = S;
+        out[3 * piece_vec] = u32x4{0u, 0u, 0u, 0u};
+    }
+}
+
+template <int MODE, bool FTZ>
+__global__ __launch_bounds__(256) void prepare_implicit_window_kernel(PrepOperand a, WindowTensor ta, int K, int kblocks, unsigned split_first,
+                                                                      unsigned nx, WindowTensor tb, u32x4 *__restrict__ out, Planes pl, int C,
+                                                                      int HW, int npix, QuantParams p)
+{
+    if (blockIdx.x < split_first) {              // workgroup-uniform, as are the returns
+        const unsigned per_xcd = split_first / 8u, bid = (blockIdx.x % 8u) * per_xcd + blockIdx.x / 8u;
+        if (bid < a.nblocks) prepare_window_block<MODE, FTZ>(a, ta, K, kblocks, p, bid);
+    } else {
+        const unsigned id = blockIdx.x - split_first;
+        nhwc_window_block<MODE, FTZ>(tb, out, pl, C, HW, npix, p, (int)(id % nx), (int)(id / nx));
+    }
+}
+
+// The operands of the weight gradient: a as above, b gathered from a tensor of words (round_window_kernel).
+template <int MODE, bool FTZ>
+__global__ __launch_bounds__(256) void prepare_taps_window_kernel(PrepOperand a, WindowTensor ta, PrepOperand b, int K, int kblocks, QuantParams p)
+{
+    const unsigned a_ids = (a.nblocks + 7u) / 8u * 8u;
+    const bool second = blockIdx.x >= a_ids;
+    const unsigned lid = blockIdx.x - (second ? a_ids : 0u), nblocks = second ? b.nblocks : a.nblocks;
+    const unsigned bid = (lid % 8u) * ((nblocks + 7u) / 8u) + lid / 8u;
+    if (bid >= nblocks) return;                  // workgroup-uniform: before any barrier
+    if (second)
+        gather_taps<1, true>(b, bid, K, kblocks);
+    else
+        prepare_window_block<MODE, FTZ>(a, ta, K, kblocks, p, bid);
 }
 
 template <int MODE, bool FTZ>
@@ -1249,16 +1511,8 @@ __device__ __forceinline__ void window_stats_block(const StatOperand &o, int K, 
 {
     __shared__ int s_hi[8][32], s_lo[8][32];
     const int tid = threadIdx.x;
-    const int wid = 39 - m;                       // binades below the top one that a plane holds with m + 1 significant bits
-    int hi = -1000, lo = 1000;
-    auto look = [&](uint32_t u) {
-        const uint32_t ab = u & 0x7FFFFFFFu;
-        const int E = (int)(ab >> 23) - 127;
-        if (ab < 0x7F800000u && E >= emin - m - 1) {
-            hi = max(hi, E);
-            lo = min(lo, max(E, emin - 1));           // emin - 1: a value in the format's denormal range
-        }
-    };
+    int hi = kNoBinade, lo = 1000;
+    auto look = [&](uint32_t u) { window_look(u, emin, m, hi, lo); };
     // 32 rows per workgroup, 8 lanes per row; eight loads are issued before any is looked at
     const int row = by * 32 + (o.kcontig ? tid / 8 : tid % 32);
     const int kl = o.kcontig ? tid % 8 : tid / 32;
@@ -1308,13 +1562,7 @@ __device__ __forceinline__ void window_stats_block(const StatOperand &o, int K, 
         }
     }
     if (row >= o.rows_pad) return;
-    int T = 0;
-    if (hi != -1000) {
-        const int top = hi + 1, room = lo + wid;
-        T = lo < emin ? 9 - m : (top >= room ? room : top + min(4, (room - top) / 2));
-    }
-    T = max(kWinTmin, min(kWinTmax, T));
-    o.S[row] = 15 - T;
+    o.S[row] = window_scale(hi, lo, emin, m);
     if (row % kUnitRows == 0) o.rec_cnt[row / kUnitRows] = 0u;
 }
 
@@ -2042,6 +2290,122 @@ static int run_implicit(int M, int N, int K, const OperandSpec &sa, const float 
     return product_gathered<PS>(va, im, M, N, la.kblocks, out, plan, partp, stream);
 }
 
+// Convolutions in 1/6/8 and 1/6/9 on exponent planes with one scale per tensor: one fp16 MFMA product per multiply instead of the four of
+// two bf16 pieces (forward, dgrad and wgrad, 256 -> 256 channels of 14 x 14, 3 x 3 taps, batch 64, us: 79 -> 43, 75 -> 57, 95 -> 73).
+// Below `least` products the scale's sample and the tail cost more than they save.  us, bf16 pieces / planes: forward and dgrad, which
+// gather in the product, 8 to 96 channels, 0.25 - 0.5 x 10^8 products 9.5 / 10.3, 11.2 / 14.5, 2.6 x 10^8 14.8 / 14.0, 3.5 x 10^8 18.8 / 14.1,
+// 8.5 x 10^8 29 / 22; wgrad, whose operands are prepared as patches, 1.2 x 10^8 34 / 36, 3.5 x 10^8 23.8 / 23.7, 8.5 x 10^8 27.1 / 26.2,
+// 1.5 x 10^9 41.2 / 37.3.
+static bool conv_planes(fmt_format_t f, const QuantParams &p, double mults, double least)
+{
+    const int wmode = window_mode();
+    return planes_possible(f) && p.mode == kModeMagic && (wmode == 1 || (wmode == 2 && mults >= least));
+}
+
+static WindowTensor window_tensor(const float *x, int64_t n, fmt_format_t f)
+{
+    return WindowTensor{reinterpret_cast<const uint32_t *>(x), (uint32_t)n, 2 - (1 << (f.e - 1)), f.m};
+}
+
+// run_implicit for these.  The tensor's planes above and below are held whole and written where they are not empty.
+static int run_implicit_window(int M, int N, int K, const OperandSpec &sa, int64_t filter_elems, const float *tensor, int64_t tensor_elems, int HW,
+                               Implicit im, const OutSpec &out, fmt_format_t f, const QuantParams &p, hipStream_t stream)
+{
+    OperandLayout la;
+    int rc = operand_layout(M, K, Scheme{0, true}, f.m, &la);
+    if (rc != FMT_OK) return rc;
+    int cus = 0;
+    rc = device_cu_count(&cus);
+    if (rc != FMT_OK) return rc;
+    const Plan plan = make_plan(M, N, la.kblocks, cus, 1);
+    auto up256 = [](size_t b) { return (b + 255) / 256 * 256; };
+    const int C = im.c8 * 8;
+    const int npix = (int)(tensor_elems / C);
+    const unsigned nx = (unsigned)((npix + 63) / 64);
+    const size_t piece_vec = (size_t)npix * im.c8;
+    const size_t nhwc = up256((3 * piece_vec + 1) * sizeof(u32x4)), masks = up256((size_t)nx * (C / 32) * 2 * sizeof(uint64_t));
+    const size_t part = part_bytes_of(plan, M, N);
+    Scratch s;
+    rc = get_scratch(stream, 0, la.bytes + nhwc + masks + 256 + part, &s);
+    if (rc != FMT_OK) return rc;
+    char *ws = static_cast<char *>(s.gemm_ws);
+    const OperandView va = view_of(ws, la);
+    OperandView vb{reinterpret_cast<u32x4 *>(ws + la.bytes), Planes{nullptr, nullptr, piece_vec, la.w, nullptr, nullptr}};
+    vb.pl.mask = reinterpret_cast<uint8_t *>(ws + la.bytes + nhwc);
+    vb.pl.S = reinterpret_cast<int *>(ws + la.bytes + nhwc + masks);
+    float *partp = reinterpret_cast<float *>(ws + la.bytes + nhwc + masks + 256);
+    PrepOperand o{};
+    o.X = reinterpret_cast<const uint32_t *>(sa.X);
+    o.W = va.W;
+    o.rows = la.rows;
+    o.kcontig = 1;
+    o.nblocks = (unsigned)((la.kblocks + 1) / 2) * la.units;
+    o.g = sa.g;
+    o.pl = va.pl;
+    const unsigned split_first = (o.nblocks + 7u) / 8u * 8u;
+    const WindowTensor ta = window_tensor(sa.X, filter_elems, f), tb = window_tensor(tensor, tensor_elems, f);
+    auto kern = f.denorm == 0 ? prepare_implicit_window_kernel<kModeMagic, true> : prepare_implicit_window_kernel<kModeMagic, false>;
+    hipLaunchKernelGGL(kern, dim3(split_first + nx * (unsigned)(C / 32)), dim3(256), 0, stream, o, ta, K, la.kblocks, split_first, nx, tb, vb.W,
+                       vb.pl, C, HW, npix, p);
+    FMT_HIP_CHECK(hipGetLastError());
+    im.T = vb.W;
+    im.piece_vec = (int)piece_vec;
+    im.zero = (int)(3 * piece_vec);
+    return product_window<true>(va, vb, im, M, N, la.kblocks, out, plan, partp, stream);
+}
+
+// The weight gradient on these planes: dY as the matrix [K][n*P*Q], the patches of X through gather_taps (at most 32 taps).
+static int run_wgrad_window(int M, int N, int K, const OperandSpec &sa, int64_t grad_elems, const OperandSpec &sb, const OutSpec &out,
+                            fmt_format_t f, const QuantParams &p, hipStream_t stream)
+{
+    OperandLayout la, lb;
+    int rc = operand_layout(M, K, Scheme{0, true}, f.m, &la);
+    if (rc != FMT_OK) return rc;
+    rc = operand_layout(N, K, Scheme{0, true}, f.m, &lb);
+    if (rc != FMT_OK) return rc;
+    int cus = 0;
+    rc = device_cu_count(&cus);
+    if (rc != FMT_OK) return rc;
+    const Plan plan = make_plan(M, N, la.kblocks, cus, 1);
+    const size_t part = part_bytes_of(plan, M, N);
+    const int n = (int)sb.pre_elems;
+    Scratch s;
+    rc = get_scratch(stream, 0, la.bytes + lb.bytes + part + ((size_t)n + 1) * sizeof(uint32_t), &s);
+    if (rc != FMT_OK) return rc;
+    char *ws = static_cast<char *>(s.gemm_ws);
+    const OperandView va = view_of(ws, la), vb = view_of(ws + la.bytes, lb);
+    float *partp = reinterpret_cast<float *>(ws + la.bytes + lb.bytes);
+    uint32_t *words = reinterpret_cast<uint32_t *>(ws + la.bytes + lb.bytes + part);
+    const bool ftz = f.denorm == 0;
+    const int grid = n / 1024 < 4096 ? (n + 1023) / 1024 : 4096;
+    hipLaunchKernelGGL((ftz ? round_window_kernel<kModeMagic, true> : round_window_kernel<kModeMagic, false>), dim3(grid), dim3(256), 0, stream,
+                       window_tensor(sb.X, n, f), words, lb.w, vb.pl.S, p);
+    FMT_HIP_CHECK(hipGetLastError());
+    PrepOperand a{}, b{};
+    a.X = reinterpret_cast<const uint32_t *>(sa.X);
+    a.W = va.W;
+    a.rows = la.rows;
+    a.kcontig = 1;
+    a.nblocks = (unsigned)((la.kblocks + 1) / 2) * la.units;
+    a.g = sa.g;
+    a.pl = va.pl;
+    b.X = words;
+    b.W = vb.W;
+    b.rows = lb.rows;
+    b.kcontig = 1;
+    b.nblocks = (unsigned)((lb.kblocks + 7) / 8) * lb.units;
+    b.g = sb.g;
+    b.g.pre = 1;
+    b.g.plane = n + 1;
+    b.g.fast = 2;
+    b.pl = vb.pl;
+    hipLaunchKernelGGL((ftz ? prepare_taps_window_kernel<kModeMagic, true> : prepare_taps_window_kernel<kModeMagic, false>),
+                       dim3((a.nblocks + 7u) / 8u * 8u + (b.nblocks + 7u) / 8u * 8u), dim3(256), 0, stream, a,
+                       window_tensor(sa.X, grad_elems, f), b, K, la.kblocks, p);
+    FMT_HIP_CHECK(hipGetLastError());
+    return product_window<false>(va, vb, Implicit{}, M, N, la.kblocks, out, plan, partp, stream);
+}
+
 // In-kernel gather for forward (which == 0) and dgrad (which == 1): returns FMT_OK after launching, or 1 when
 // the geometry is not covered (channels of the gathered tensor not a multiple of 32, more than 32 taps, dgrad
 // with a stride, index ranges), in which case the caller takes the route through a gathered operand.
@@ -2079,6 +2443,9 @@ static int conv_implicit(int which, const fmt_conv2d_t &g, int64_t P, int64_t Q,
     ft.tw = which == 0 ? rs : g.c * rs;
     const OperandSpec sa{filt, 0, true, ft, 0};
     const OutSpec os{out, 0, (int)(gy * gx)};
+    const bool planes = conv_planes(f, p, (double)g.n * gy * gx * g.k * g.c * rs, 1.5e8) && elems > 0 && (elems / 8) * 3 + (int64_t)(g.r * tw + g.s) * (tc / 8) < ((int64_t)1 << 31);
+    if (planes)
+        return run_implicit_window((int)M, (int)N, (int)K, sa, (int64_t)g.k * g.c * rs, tensor, elems, (int)(th * tw), im, os, f, p, stream);
     const bool ftz = f.denorm == 0;
 #define FMT_IMPL2(MD, FZ)                                                                                                     \
     (sch.ps == 0   ? run_implicit<MD, FZ, 0>((int)M, (int)N, (int)K, sa, tensor, elems, (int)(th * tw), im, os, f, p, stream) \
@@ -2103,7 +2470,8 @@ static int conv_implicit(int which, const fmt_conv2d_t &g, int64_t P, int64_t Q,
 // Forward and (stride 1) dgrad with a channel count that is a multiple of 32 and at most 32 taps gather
 // the patches inside the product kernel from the once-rounded tensor (conv_implicit: scratch is 2P bytes
 // per TENSOR element); the other cases, and wgrad, go through a prepare pass that gathers from the once
-// rounded tensor into a patch-sized 16-bit prepared operand.
+// rounded tensor into a patch-sized 16-bit prepared operand.  1/6/8 and 1/6/9 take exponent planes where conv_planes says so (6 bytes
+// instead of 4 per element of scratch).
 int launch_conv2d(int which, const fmt_conv2d_t &g, const float *a, const float *b, float *out, fmt_format_t f,
                   const QuantParams &p, hipStream_t stream)
 {
@@ -2170,6 +2538,8 @@ int launch_conv2d(int which, const fmt_conv2d_t &g, const float *a, const float 
     patch.k0 = make_fastdiv(patch.gx); patch.k1 = make_fastdiv(patch.gy);
     const OperandSpec sa{a, 0, true, ch, 0};                       // dY as [K][n*P*Q]
     const OperandSpec sb{b, 0, true, patch, (int64_t)g.n * g.c * g.h * g.w};      // patches of X, k along positions
+    if (conv_planes(f, p, (double)M * N * K, 7e8) && g.r * g.s <= 32 && sb.pre_elems > 0)
+        return run_wgrad_window((int)M, (int)N, (int)K, sa, M * K, sb, OutSpec{out, N, 0}, f, p, stream);
     return run_product((int)M, (int)N, (int)K, sa, sb, OutSpec{out, N, 0}, f, p, stream);
 }
 

@@ -35,6 +35,9 @@ struct Planes {
     uint32_t *recs;      // pairs of words, kRecCap pairs per row of units
 };
 constexpr int kRecCap = 64;
+// Convolutions (product_window) use planes with one scale for the whole tensor: S[0] alone, no records.  A tensor whose patches the
+// product kernel gathers has, per 64 pixels x 32 channels, two words of 64 bits in the mask's place, a bit per pixel: what has elements in the plane
+// above, and below.
 
 // Division of a 31-bit dividend by a divisor fixed at launch, as a multiply-high and a shift
 // (m = floor(2^(31+l) / d) + 1 with l = ceil(log2 d) gives floor(a / d) for every 0 <= a < 2^31).
@@ -174,6 +177,10 @@ int product_of_views(const OperandView &va, const OperandView &vb, int M, int N,
 template <int PS>
 int product_gathered(const OperandView &va, const Implicit &im, int M, int N, int kblocks, const OutSpec &out, const Plan &plan,
                      float *part, hipStream_t stream);
+// fmt_product_window.hip
+template <bool GATHER>
+int product_window(const OperandView &va, const OperandView &vb, const Implicit &im, int M, int N, int kblocks, const OutSpec &out,
+                   const Plan &plan, float *part, hipStream_t stream);
 template <int PS, bool SCALED>
 int launch_group(const Group &grp, unsigned grid, int t, hipStream_t stream);
 

@@ -331,6 +331,180 @@ __device__ __forceinline__ void linear_tile(floatx16 (&acc)[TM][TN], float *C, i
     }
 }
 
+// Convolutions on exponent planes with one scale per tensor (formats with e == 6, m = 8 or 9): the products that meet an element outside
+// plane 0 are added to the sums of plane 0, block of 32 k by block, by the wave that owns the results.  Which blocks those are is read
+// from the operands' masks, a lane per block, for the first kWindowChunks * 64 blocks under the first stages' loads.  Of 3.2 M gradients with
+// log2|x| ~ N(-20, 5^2) 43 lie outside, of activations and weights none, so the loops here are short and wait for memory: what bounds them
+// is the wave that has most to do.  Each pair of planes has a scale of its own; the sums take it while the pair's products are added (kInPlace), which is
+// exact: they are multiples of 2^-48 below 2^32 K, and the factors lie within 2^-62 .. 2^62.  The order is fixed, so the results are the
+// same on every run.  256 -> 256 channels of 14 x 14, 3 x 3 taps, batch 64: the
+// dgrad kernel takes 30 us on gradients without such elements, 36 with one and 45 with 43 (the code is met for the first time then, so
+// larger batches or fewer instructions on the common path did not help; reading the masks after the products cost 2 more).
+constexpr int kWindowChunks = 2;
+
+// Bits 1 and 2: operand A has elements of the planes above / below in this wave's rows and block kb; bits 9 and 10: operand B.
+template <int TM, int TN, bool GATHER>
+__device__ __forceinline__ uint32_t window_masks(const Planes &pa, const Planes &pb, const Implicit &im, int kblocks, int kb, int kb1, int unit_a,
+                                                 int unit_b)
+{
+    if (kb >= kb1) return 0u;
+    uint32_t ma = 0u, mb = 0u;
+#pragma unroll
+    for (int i = 0; i < TM; ++i) ma |= pa.mask[(size_t)(unit_a + i) * kblocks + kb];
+    if constexpr (GATHER) {
+        if (unit_b * kUnitRows >= im.rows) return 0u;                // no positions: nothing is stored
+        const unsigned long long *pixels = reinterpret_cast<const unsigned long long *>(pb.mask);
+        int t, x, n0, n1, y0, y1, tap, cb, r, s2;
+        divmod(im.r0, unit_b * kUnitRows, t, x);
+        divmod(im.r1, t, n0, y0);
+        divmod(im.r0, min((unit_b + TN) * kUnitRows, im.rows) - 1, t, x);
+        divmod(im.r1, t, n1, y1);
+        divmod(im.kc, kb, tap, cb);
+        divmod(im.ks, tap, r, s2);
+        y0 = y0 * im.mul_y + im.off_y + im.tap_sign * r;
+        y1 = y1 * im.mul_y + im.off_y + im.tap_sign * r;
+        // the pixels that the positions reach lie between the first of the first one's row and the last of the last one's
+        const int lo = (n0 * im.th + min(max(y0, 0), im.th - 1)) * im.tw, hi = (n1 * im.th + min(max(y1, 0), im.th - 1)) * im.tw + im.tw - 1;
+        for (int q0 = lo / 64; q0 <= hi / 64; q0 += 3) {
+            unsigned long long w[3][2];
+#pragma unroll
+            for (int i = 0; i < 3; ++i)
+#pragma unroll
+                for (int b = 0; b < 2; ++b) w[i][b] = pixels[((size_t)min(q0 + i, hi / 64) * (im.c8 / 4) + cb) * 2 + b];
+#pragma unroll
+            for (int i = 0; i < 3; ++i) {
+                const int q = min(q0 + i, hi / 64);
+                const unsigned long long within = (~0ull << max(lo - q * 64, 0)) & (~0ull >> max(q * 64 + 63 - hi, 0));
+                mb |= ((w[i][0] & within) != 0ull ? 2u : 0u) | ((w[i][1] & within) != 0ull ? 4u : 0u);
+            }
+        }
+    } else {
+#pragma unroll
+        for (int j = 0; j < TN; ++j) mb |= pb.mask[(size_t)(unit_b + j) * kblocks + kb];
+    }
+    return (ma & 6u) | ((mb & 6u) << 8);
+}
+
+template <int TM, int TN, bool GATHER>
+__device__ __forceinline__ void window_tail(floatx16 (&acc)[TM][TN], const uint32_t (&early)[kWindowChunks], const u32x4 *__restrict__ Aw,
+                                            const u32x4 *__restrict__ Bw, const Planes &pa, const Planes &pb, const Implicit &im, int kblocks,
+                                            int kb0, int kb1, int unit_a, int unit_b, int lane)
+{
+    // blocks loaded together: an element outside plane 0 of a gathered tensor is met by every tap (as many as leave the
+    // 64 x 64 and 128 x 128 tiles their four and two workgroups per compute unit)
+    constexpr int kAhead = TM * TN <= 4 ? 4 : TM * TN == 8 ? 2 : 1;
+    // Larger tiles sum a batch apart (in place they spill up to 2 KB per lane, and it is 128 x 128 that convolutions mostly take).
+    constexpr bool kInPlace = TM * TN <= 4;
+    const unsigned long long *pixels = reinterpret_cast<const unsigned long long *>(pb.mask);      // GATHER (see fmt_product.h)
+    auto times = [&](float f) __attribute__((always_inline)) {
+#pragma unroll
+        for (int i = 0; i < TM; ++i)
+#pragma unroll
+            for (int j = 0; j < TN; ++j)
+#pragma unroll
+                for (int v = 0; v < 16; ++v) acc[i][j][v] *= f;
+    };
+#pragma unroll 1
+    for (int first = kb0; first < kb1; first += 64) {
+        const int mine = first + lane, chunk = (first - kb0) / 64;
+        uint32_t masks = chunk == 0 ? early[0] : early[1];
+        static_assert(kWindowChunks == 2, "early");
+        if (chunk >= kWindowChunks) masks = window_masks<TM, TN, GATHER>(pa, pb, im, kblocks, mine, kb1, unit_a, unit_b);
+        if (__ballot(masks != 0u) == 0ull) continue;
+        const uint32_t ma = (masks & 255u) | 1u, mb = (masks >> 8) | 1u;
+        int pn[TN], py[TN], px[TN];                                  // GATHER: corner pixels (columns beyond the matrix are not stored)
+        if constexpr (GATHER) {
+#pragma unroll
+            for (int j = 0; j < TN; ++j) {
+                int t, x;
+                divmod(im.r0, min((unit_b + j) * kUnitRows + (lane & 31), im.rows - 1), t, x);
+                divmod(im.r1, t, pn[j], py[j]);
+                py[j] = py[j] * im.mul_y + im.off_y;
+                px[j] = x * im.mul_x + im.off_x;
+            }
+        }
+#pragma unroll 1
+        for (int pair = 1; pair < 9; ++pair) {                       // (0, 0) is in the sums
+            const int qa = pair / 3, qb = pair % 3;                  // planes: 0, above, below
+            unsigned long long todo = __ballot(mine < kb1 && ((ma >> qa) & (mb >> qb) & 1u) != 0u);
+            if (todo == 0ull) continue;
+            // scales above and below plane 0's: 2^-w, 2^w
+            const int up = (qa == 0 ? 0 : qa == 1 ? -pa.w : pa.w) + (qb == 0 ? 0 : qb == 1 ? -pb.w : pb.w);
+            if constexpr (kInPlace) times(ldexpf(1.0f, up));
+#pragma unroll 1
+            while (todo != 0ull) {
+                int block = 0;
+                u32x4 fa[kAhead][2][TM], fb[kAhead][2][TN];
+#pragma unroll
+                for (int d = 0; d < kAhead; ++d) {
+                    const bool some = d == 0 || todo != 0ull;        // the same in the whole wave; without: the block before again, times zero
+                    if (some) block = first + __builtin_ctzll(todo);
+                    todo &= todo - 1ull;
+                    // what is not in the plane is loaded all the same, beside the mask, and left out
+#pragma unroll
+                    for (int i = 0; i < TM; ++i) {
+                        const size_t unit = (size_t)(unit_a + i) * kblocks + block;
+#pragma unroll
+                        for (int kk = 0; kk < 2; ++kk) fa[d][kk][i] = Aw[qa * pa.plane + unit * kUnitVec + kk * 64 + lane];
+                        if (qa != 0 && !((pa.mask[unit] >> qa) & 1u)) fa[d][0][i] = fa[d][1][i] = u32x4{0u, 0u, 0u, 0u};
+                    }
+                    int tap = 0, cb = 0, r = 0, s2 = 0;
+                    if constexpr (GATHER) {
+                        divmod(im.kc, block, tap, cb);
+                        divmod(im.ks, tap, r, s2);
+                    }
+#pragma unroll
+                    for (int j = 0; j < TN; ++j) {
+                        if constexpr (GATHER) {
+                            const int iy = py[j] + im.tap_sign * r, ix = px[j] + im.tap_sign * s2, pix = (pn[j] * im.th + iy) * im.tw + ix;
+                            const bool in = (unsigned)iy < (unsigned)im.th && (unsigned)ix < (unsigned)im.tw;
+#pragma unroll
+                            for (int kk = 0; kk < 2; ++kk)
+                                fb[d][kk][j] = im.T[in ? qb * im.piece_vec + pix * im.c8 + cb * 4 + kk * 2 + (lane >> 5) : im.zero];
+                            if (!some || (qb != 0 && in && !((pixels[((size_t)(pix / 64) * (im.c8 / 4) + cb) * 2 + (qb - 1)] >> (pix % 64)) & 1ull)))
+                                fb[d][0][j] = fb[d][1][j] = u32x4{0u, 0u, 0u, 0u};
+                        } else {
+                            const size_t unit = (size_t)(unit_b + j) * kblocks + block;
+#pragma unroll
+                            for (int kk = 0; kk < 2; ++kk) fb[d][kk][j] = Bw[qb * pb.plane + unit * kUnitVec + kk * 64 + lane];
+                            if (!some || (qb != 0 && !((pb.mask[unit] >> qb) & 1u))) fb[d][0][j] = fb[d][1][j] = u32x4{0u, 0u, 0u, 0u};
+                        }
+                    }
+                }
+                auto add = [&](floatx16 t, int i, int j, int d, int kk) __attribute__((always_inline)) {
+                    return __builtin_amdgcn_mfma_f32_32x32x16_f16(__builtin_bit_cast(f16x8, fb[d][kk][j]), __builtin_bit_cast(f16x8, fa[d][kk][i]), t,
+                                                                  0, 0, 0);
+                };
+                if constexpr (kInPlace) {
+#pragma unroll
+                    for (int d = 0; d < kAhead; ++d)
+#pragma unroll
+                        for (int kk = 0; kk < 2; ++kk)
+#pragma unroll
+                            for (int i = 0; i < TM; ++i)
+#pragma unroll
+                                for (int j = 0; j < TN; ++j) acc[i][j] = add(acc[i][j], i, j, d, kk);
+                } else {
+#pragma unroll
+                    for (int i = 0; i < TM; ++i)
+#pragma unroll
+                        for (int j = 0; j < TN; ++j) {
+                            floatx16 t = {};
+#pragma unroll
+                            for (int d = 0; d < kAhead; ++d)
+#pragma unroll
+                                for (int kk = 0; kk < 2; ++kk) t = add(t, i, j, d, kk);
+#pragma unroll
+                            for (int v = 0; v < 16; ++v) acc[i][j][v] = fmaf(t[v], ldexpf(1.0f, -up), acc[i][j][v]);
+                        }
+                }
+            }
+            if constexpr (kInPlace) times(ldexpf(1.0f, -up));
+        }
+    }
+    times(ldexpf(1.0f, -(pa.S[0] + pb.S[0])));
+}
+
 // product: Aw / Bw are prepared operands (rows padded to a multiple of kRowPad, k to a multiple
 // of 32).  A workgroup is 2 x 2 waves; each wave owns TM x TN MFMA tiles of 32 x 32, so the
 // workgroup tile is (64*TM) x (64*TN).  Operand stages of KS*16 k go from global memory straight
@@ -347,10 +521,11 @@ __device__ __forceinline__ void linear_tile(floatx16 (&acc)[TM][TN], float *C, i
 // the taps).  The stage image in LDS and everything after it are the same.
 // The body is shared by the kernel of one product (bid = blockIdx.x) and the kernel of a group of products
 // (bid = the workgroup's index within its product).
+// WINDOW (single fp16 piece, plain or GATHER): exponent planes with one scale per operand (window_tail).
 // LINEAR: the results are a fully connected layer's accumulators; they leave as R(R(acc) + R(b)) (lin), HIST: with the
 // statistics of R(acc) + R(b) (sink).
 template <int PS, int TM, int TN, int KS, int NST, bool SPLIT, bool SCHED, bool SCALED, bool GATHER = false, bool LINEAR = false,
-          bool HIST = false>
+          bool HIST = false, bool WINDOW = false>
 __device__ __forceinline__ void product_body(const u32x4 *__restrict__ Aw, const u32x4 *__restrict__ Bw,
                                              float *__restrict__ C, int M, int N, int64_t ldc, int img,
                                              int kblocks, int tiles_m, int tiles_n, int kb_per_split,
@@ -517,9 +692,15 @@ __device__ __forceinline__ void product_body(const u32x4 *__restrict__ Aw, const
     // its stage landed): __syncthreads() would also wait for every load-to-LDS still in flight.
     auto barrier = [&]() __attribute__((always_inline)) { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); };
 
+    [[maybe_unused]] uint32_t early[kWindowChunks] = {0u, 0u};
     if (steps > 0) {
 #pragma unroll
         for (int t = 0; t < NST; ++t) issue(t, t);
+        if constexpr (WINDOW) {
+#pragma unroll
+            for (int c = 0; c < kWindowChunks; ++c)
+                early[c] = window_masks<TM, TN, GATHER>(pa, pb, im, kblocks, kb0 + c * 64 + lane, kb1, tm * UA + wm * TM, tn * UB + wn * TN);
+        }
         __builtin_amdgcn_s_waitcnt(0x0F70 | (kWaitFirst & 0xF) | ((kWaitFirst >> 4) << 14));
         barrier();
         read_frags(0, 0);
@@ -644,20 +825,24 @@ __device__ __forceinline__ void product_body(const u32x4 *__restrict__ Aw, const
         linear_tile<PS, TM, TN, HIST>(acc, C, ldc, M, N, row_base, col_base, lane, bias, lin, sink, reinterpret_cast<uint32_t *>(st0), tile, ntiles);
         return;
     }
+    if constexpr (WINDOW) {
+        static_assert(PS == 0 && KS == 2 && !SCALED, "one fp16 plane, a block of 32 k per stage");
+        window_tail<TM, TN, GATHER>(acc, early, Aw, Bw, pa, pb, im, kblocks, kb0, kb1, tm * UA + wm * TM, tn * UB + wn * TN, lane);
+    }
     // plain: C[row][col] with leading dimension ldc; a part of a split k: its own M x N slab; img > 0: NCHW
     float *out = SPLIT ? C + (size_t)split * M * ldc : C;
     store_tile<TM, TN, SCALED>(acc, out, ldc, M, N, SPLIT ? 0 : img, (tm * 2 + wm) * (32 * TM), (tn * 2 + wn) * (32 * TN), lane, pa.S,
                                pb.S);
 }
 
-template <int PS, int TM, int TN, int KS, int NST, bool SPLIT, bool SCHED, bool SCALED, bool GATHER = false>
+template <int PS, int TM, int TN, int KS, int NST, bool SPLIT, bool SCHED, bool SCALED, bool GATHER = false, bool WINDOW = false>
 __global__ __launch_bounds__(256) void product_kernel(const u32x4 *__restrict__ Aw, const u32x4 *__restrict__ Bw,
                                                       float *__restrict__ C, int M, int N, int64_t ldc, int img,
                                                       int kblocks, int tiles_m, int tiles_n, int kb_per_split,
                                                       Planes pa, Planes pb, Implicit im)
 {
-    product_body<PS, TM, TN, KS, NST, SPLIT, SCHED, SCALED, GATHER>(Aw, Bw, C, M, N, ldc, img, kblocks, tiles_m, tiles_n,
-                                                                  kb_per_split, pa, pb, im, blockIdx.x);
+    product_body<PS, TM, TN, KS, NST, SPLIT, SCHED, SCALED, GATHER, false, false, WINDOW>(Aw, Bw, C, M, N, ldc, img, kblocks, tiles_m, tiles_n,
+                                                                                        kb_per_split, pa, pb, im, blockIdx.x);
 }
 
 template <int PS, int TM, int TN, int KS, int NST, bool SCALED, bool HIST>
@@ -678,7 +863,7 @@ __global__ __launch_bounds__(256) void product_group_kernel(Group grp)
                                                                 blockIdx.x - it.first);
 }
 
-template <int PS, int TM, int TN, bool SPLIT, bool SCHED, bool SCALED, bool GATHER = false>
+template <int PS, int TM, int TN, bool SPLIT, bool SCHED, bool SCALED, bool GATHER = false, bool WINDOW = false>
 static int launch_product_v2(const u32x4 *Aw, const u32x4 *Bw, float *out, int M, int N, int64_t ld, int img, int kblocks,
                             int nsplit, hipStream_t stream, const Planes &pa, const Planes &pb, const Implicit &im = Implicit{})
 {
@@ -690,7 +875,7 @@ static int launch_product_v2(const u32x4 *Aw, const u32x4 *Bw, float *out, int M
         const int64_t per_xcd = ((int64_t)tiles_m * tiles_n + 7) / 8;
         if (per_xcd * 8 * nsplit >= ((int64_t)1 << 31)) return FMT_ERR_SHAPE;
         const int kb_per = (kblocks + nsplit - 1) / nsplit;
-        auto kern = product_kernel<PS, TM, TN, KS, NST, SPLIT, SCHED, SCALED, GATHER>;
+        auto kern = product_kernel<PS, TM, TN, KS, NST, SPLIT, SCHED, SCALED, GATHER, WINDOW>;
         Implicit imk = im;
         if (GATHER) imk.kc = make_fastdiv(im.c8 * 8 / (16 * KS));   // stages of 16*KS k per tap
         hipLaunchKernelGGL(kern, dim3((unsigned)(per_xcd * 8 * nsplit)), dim3(256), 0, stream, Aw, Bw, out, M, N, ld, img,
@@ -868,6 +1053,33 @@ int product_gathered(const OperandView &va, const Implicit &im, int M, int N, in
     const Planes none{nullptr, nullptr, 0, 0, nullptr, nullptr};
 #define FMT_PRODUCT(TMV, TNV) \
     launch_product<PS, TMV, TNV>(va.W, nullptr, out.C, M, N, out.ldc, out.img, kblocks, plan, part, stream, none, none, &im)
+    if (plan.tm == 4 && plan.tn == 4) return FMT_PRODUCT(4, 4);
+    if (plan.tm == 4 && plan.tn == 2) return FMT_PRODUCT(4, 2);
+    if (plan.tm == 2 && plan.tn == 4) return FMT_PRODUCT(2, 4);
+    if (plan.tm == 2 && plan.tn == 2) return FMT_PRODUCT(2, 2);
+    return FMT_PRODUCT(1, 1);
+#undef FMT_PRODUCT
+}
+
+// Convolutions on exponent planes with one scale per operand: operand B prepared or gathered (im; vb.pl has
+// its scale and masks).
+template <int TM, int TN, bool GATHER>
+static int launch_window(const OperandView &va, const OperandView &vb, const Implicit &im, int M, int N, int kblocks, const OutSpec &out,
+                         const Plan &plan, float *part, hipStream_t stream)
+{
+    if (plan.nsplit == 1)
+        return launch_product_v2<0, TM, TN, false, true, false, GATHER, true>(va.W, vb.W, out.C, M, N, out.ldc, out.img, kblocks, 1, stream, va.pl,
+                                                                             vb.pl, im);
+    const int rc = launch_product_v2<0, TM, TN, true, true, false, GATHER, true>(va.W, vb.W, part, M, N, (int64_t)N, 0, kblocks, plan.nsplit,
+                                                                               stream, va.pl, vb.pl, im);
+    return rc != FMT_OK ? rc : launch_reduce(part, plan.nsplit, out.C, M, N, out.ldc, out.img, stream);
+}
+
+template <bool GATHER>
+int product_window(const OperandView &va, const OperandView &vb, const Implicit &im, int M, int N, int kblocks, const OutSpec &out,
+                   const Plan &plan, float *part, hipStream_t stream)
+{
+#define FMT_PRODUCT(TMV, TNV) launch_window<TMV, TNV, GATHER>(va, vb, im, M, N, kblocks, out, plan, part, stream)
     if (plan.tm == 4 && plan.tn == 4) return FMT_PRODUCT(4, 4);
     if (plan.tm == 4 && plan.tn == 2) return FMT_PRODUCT(4, 2);
     if (plan.tm == 2 && plan.tn == 4) return FMT_PRODUCT(2, 4);

@@ -333,3 +333,68 @@ def test_config3_full_size_every_element(fmt):
                            ("dW", dW, oracle.conv2d_wgrad(dY, X, W.shape, e, m, d))):
         assert got.shape == ref.shape and np.all(np.isfinite(got)), name
         assert rel_err(got, ref) <= TOL, "%s: %.3g" % (name, rel_err(got, ref))
+
+
+def in_64_bits(X, W, dY, pad, stride):
+    """The three products in 64 bits, of values and of magnitudes: (Y, dX, dW), (|Y|, |dX|, |dW|)."""
+    def three(x, w, dy):
+        x, w = torch.from_numpy(x).double().requires_grad_(), torch.from_numpy(w).double().requires_grad_()
+        y = torch.nn.functional.conv2d(x, w, padding=pad, stride=stride)
+        y.backward(torch.from_numpy(dy).double())
+        return y.detach().numpy(), x.grad.numpy(), w.grad.numpy()
+    return three(X, W, dY), three(np.abs(X), np.abs(W), np.abs(dY))
+
+
+@pytest.mark.parametrize("plan", [None, "1,1,1", "2,2,2", "4,2,1", "2,4,1", "4,4,1"])
+@pytest.mark.parametrize("spread", ["images", "elements", "single", "gradient"])
+def test_elements_outside_plane_0(fmt, spread, plan, monkeypatch):
+    """1/6/8 and 1/6/9 on exponent planes with one scale per tensor: operands that fill all three planes, images and channels of their own
+    magnitudes (where whole outputs live in the planes above and below), and single elements outside plane 0, at the edges of
+    tiles, images and blocks of 64 pixels.  |sum in fp32 - sum in 64 bits| <= (K + 2) 2^-24 sum|a b| for products that are exact, in any order."""
+    if plan is not None:
+        monkeypatch.setenv("FMT_GEMM_PLAN", plan)
+    monkeypatch.setenv("FMT_GEMM_WINDOW", "1")           # by size these take two bf16 pieces
+    rng = np.random.default_rng(len(spread))
+    for e, m, d, (n, c, h, w, k, r, s, pad, stride) in (
+            (6, 9, True, (5, 64, 9, 8, 96, 3, 3, (1, 1), (1, 1))), (6, 9, False, (3, 32, 13, 11, 40, 2, 4, (0, 3), (1, 2))),
+            (6, 8, True, (2, 96, 17, 5, 32, 5, 3, (2, 1), (1, 1))), (6, 9, True, (4, 33, 8, 7, 65, 3, 3, (1, 1), (2, 2)))):
+        P, Q = oracle.conv_out_size(h, w, r, s, pad, stride)
+        X, W, dY = (rng.standard_normal(shape) for shape in ((n, c, h, w), (k, c, r, s), (n, k, P, Q)))
+        if spread == "images":          # 2^-36 .. 2^26
+            X *= 2.0 ** (rng.integers(-30, 21, (n, 1, 1, 1)) + rng.integers(-6, 6, (1, c, 1, 1)))
+            W *= 2.0 ** rng.integers(-20, 11, (k, c, 1, 1))
+            dY *= 2.0 ** (rng.integers(-30, 21, (n, 1, 1, 1)) + rng.integers(-6, 6, (1, k, 1, 1)))
+        elif spread == "elements":
+            X, W, dY = (t * 2.0 ** np.clip(rng.normal(-4, 12, t.shape), -36, 26) for t in (X, W, dY))
+        elif spread == "single":
+            for t in (X, W, dY):
+                flat = t.reshape(-1)
+                at = np.concatenate([[0, flat.size - 1], rng.integers(0, flat.size, 6)])
+                flat[at] = np.where(rng.random(at.size) < 0.5, 2.0 ** 24, 2.0 ** -33) * 1.5
+        else:
+            dY = workloads.log2_normal(dY.shape, -20.0, 5.0, 0.0, rng)
+            dY.reshape(-1)[rng.integers(0, dY.size, 5)] = 6.0
+        X, W, dY = (oracle.quantize(np.ascontiguousarray(t.astype(np.float32)), e, m, d) for t in (X, W, dY))
+        got = run_all(fmt, X, W, dY, (e, m, d), pad, stride)
+        want, size = in_64_bits(X, W, dY, pad, stride)
+        for name, g_, w_, z_, K in zip(("Y", "dX", "dW"), got, want, size, (c * r * s, k * r * s, n * P * Q)):
+            bad = np.abs(g_ - w_) > (K + 2) * 2.0 ** -24 * z_ + 2.0 ** -149
+            assert not bad.any(), "%s 1/%d/%d: %d of %d" % (name, e, m, bad.sum(), bad.size)
+
+
+def test_infinities_on_exponent_planes(fmt, monkeypatch):
+    """An infinite element makes the outputs that meet it non-finite and leaves the others as they are, also where other elements
+    lie outside plane 0."""
+    monkeypatch.setenv("FMT_GEMM_WINDOW", "1")
+    n, c, h, w, k = 2, 32, 9, 8, 40
+    rng = np.random.default_rng(2)
+    X = rng.integers(-4, 5, (n, c, h, w)).astype(np.float32)
+    W = (rng.integers(1, 5, (k, c, 3, 3)) * 0.25).astype(np.float32)
+    X[1, 3, 0, 0] = 2.0 ** -37
+    clean = fmt.fmt_conv2d_fwd(dev(X), dev(W), (6, 9, True)).cpu().numpy()
+    X[0, 5, 4, 4] = np.inf
+    Y = fmt.fmt_conv2d_fwd(dev(X), dev(W), (6, 9, True)).cpu().numpy()
+    met = np.zeros(Y.shape, bool)
+    met[0, :, 3:6, 3:6] = True
+    assert not np.isfinite(Y[met]).any()
+    assert np.array_equal(Y[~met].view(np.uint32), clean[~met].view(np.uint32))
