@@ -398,3 +398,53 @@ def test_infinities_on_exponent_planes(fmt, monkeypatch):
     met[0, :, 3:6, 3:6] = True
     assert not np.isfinite(Y[met]).any()
     assert np.array_equal(Y[~met].view(np.uint32), clean[~met].view(np.uint32))
+
+
+@pytest.mark.parametrize("seed", [s for s in range(36) if s % 6 in (0, 3)])
+def test_seeded_random_geometries_on_exponent_planes(fmt, seed, monkeypatch):
+    """The drawn geometries in 1/6/9, which by size take two bf16 pieces, on exponent planes."""
+    monkeypatch.setenv("FMT_GEMM_WINDOW", "1")
+    test_seeded_random_geometries(fmt, seed)
+    if seed < 30:
+        test_seeded_random_geometries_with_channel_multiples_of_32(fmt, seed)
+
+
+def test_exponent_planes_under_capture(fmt):
+    """The three calls recorded into a graph at a size that takes exponent planes: every replay, on inputs that change in between (with and
+    without elements outside plane 0), gives the bits of the eager calls."""
+    f, g = (6, 9, True), {"pad": (1, 1), "stride": (1, 1)}
+    gen = torch.Generator(device="cuda").manual_seed(1)
+    draw = lambda *s: torch.randn(s, generator=gen, device="cuda")  # noqa: E731
+    X, W, dY = draw(16, 96, 14, 14), draw(96, 96, 3, 3) * 0.05, draw(16, 96, 14, 14) * 1e-3
+    Y, dX, dW = torch.empty_like(dY), torch.empty_like(X), torch.empty_like(W)
+
+    def three(y, dx, dw):
+        fmt.fmt_conv2d_fwd(X, W, f, out=y, **g)
+        fmt.fmt_conv2d_dgrad(dY, W, X.shape, f, out=dx, **g)
+        fmt.fmt_conv2d_wgrad(dY, X, W.shape, f, out=dw, **g)
+
+    stream = torch.cuda.Stream()
+    with torch.cuda.stream(stream):
+        three(Y, dX, dW)                                 # scratch of the stream
+        stream.synchronize()
+        graph = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(graph, stream=stream):
+            three(Y, dX, dW)
+    torch.cuda.synchronize()
+    for turn in range(4):
+        X.copy_(draw(*X.shape) * 2.0 ** (8 * turn))
+        dY.copy_(draw(*dY.shape) * 2.0 ** (-12 * turn))
+        if turn % 2:
+            X[3, 5, 0, :] = 2.0 ** -36
+            dY[1, 7, 3, 3] = 2.0 ** 25
+        eager = [torch.empty_like(t) for t in (Y, dX, dW)]
+        three(*eager)
+        torch.cuda.synchronize()
+        for t in (Y, dX, dW):
+            t.fill_(float("nan"))
+        torch.cuda.synchronize()
+        with torch.cuda.stream(stream):
+            graph.replay()
+        torch.cuda.synchronize()
+        for a, b in zip((Y, dX, dW), eager):
+            assert torch.equal(a, b)
