@@ -335,12 +335,17 @@ __device__ __forceinline__ void linear_tile(floatx16 (&acc)[TM][TN], float *C, i
 // plane 0 are added to the sums of plane 0, block of 32 k by block, by the wave that owns the results.  Which blocks those are is read
 // from the operands' masks, a lane per block, for the first kWindowChunks * 64 blocks under the first stages' loads.  Of 3.2 M gradients with
 // log2|x| ~ N(-20, 5^2) 43 lie outside, of activations and weights none, so the loops here are short and wait for memory: what bounds them
-// is the wave that has most to do.  Each pair of planes has a scale of its own; the sums take it while the pair's products are added (kInPlace), which is
-// exact: they are multiples of 2^-48 below 2^32 K, and the factors lie within 2^-62 .. 2^62.  The order is fixed, so the results are the
+// is the wave that has most to do.  Each pair of planes has a scale of its own, 2^up, and a batch of blocks of one pair is summed apart and
+// then added as 2^-up of it.  (The running sums cannot be brought to the pair's scale instead: up reaches 2 w = 64 with m = 8, and sums that
+// another pair has raised to 2^64 and more in plane 0's units would overflow on the way.)  Nothing overflows or is lost on this one: a batch is a
+// multiple of 2^-48 below 2^32 * 32 kAhead, so 2^-up of it lies between 2^-112 and 2^104, and the sums are at most 2^64 K in the values' own
+// units, 2^94 K in plane 0's.  The order is fixed, so the results are the
 // same on every run.  256 -> 256 channels of 14 x 14, 3 x 3 taps, batch 64: the
 // dgrad kernel takes 30 us on gradients without such elements, 36 with one and 45 with 43 (the code is met for the first time then, so
 // larger batches or fewer instructions on the common path did not help; reading the masks after the products cost 2 more).
 constexpr int kWindowChunks = 2;
+// Workgroups that a compute unit takes: LDS leaves room for two of 128 x 128 and four of 64 x 64, and the tail's registers must not take it.
+constexpr int window_workgroups(int tiles) { return tiles == 4 ? 2 : tiles == 1 ? 4 : 1; }
 
 // Bits 1 and 2: operand A has elements of the planes above / below in this wave's rows and block kb; bits 9 and 10: operand B.
 template <int TM, int TN, bool GATHER>
@@ -393,17 +398,7 @@ __device__ __forceinline__ void window_tail(floatx16 (&acc)[TM][TN], const uint3
     // blocks loaded together: an element outside plane 0 of a gathered tensor is met by every tap (as many as leave the
     // 64 x 64 and 128 x 128 tiles their four and two workgroups per compute unit)
     constexpr int kAhead = TM * TN <= 4 ? 4 : TM * TN == 8 ? 2 : 1;
-    // Larger tiles sum a batch apart (in place they spill up to 2 KB per lane, and it is 128 x 128 that convolutions mostly take).
-    constexpr bool kInPlace = TM * TN <= 4;
     const unsigned long long *pixels = reinterpret_cast<const unsigned long long *>(pb.mask);      // GATHER (see fmt_product.h)
-    auto times = [&](float f) __attribute__((always_inline)) {
-#pragma unroll
-        for (int i = 0; i < TM; ++i)
-#pragma unroll
-            for (int j = 0; j < TN; ++j)
-#pragma unroll
-                for (int v = 0; v < 16; ++v) acc[i][j][v] *= f;
-    };
 #pragma unroll 1
     for (int first = kb0; first < kb1; first += 64) {
         const int mine = first + lane, chunk = (first - kb0) / 64;
@@ -430,7 +425,7 @@ __device__ __forceinline__ void window_tail(floatx16 (&acc)[TM][TN], const uint3
             if (todo == 0ull) continue;
             // scales above and below plane 0's: 2^-w, 2^w
             const int up = (qa == 0 ? 0 : qa == 1 ? -pa.w : pa.w) + (qb == 0 ? 0 : qb == 1 ? -pb.w : pb.w);
-            if constexpr (kInPlace) times(ldexpf(1.0f, up));
+            const float down = ldexpf(1.0f, -up);
 #pragma unroll 1
             while (todo != 0ull) {
                 int block = 0;
@@ -471,38 +466,30 @@ __device__ __forceinline__ void window_tail(floatx16 (&acc)[TM][TN], const uint3
                         }
                     }
                 }
-                auto add = [&](floatx16 t, int i, int j, int d, int kk) __attribute__((always_inline)) {
-                    return __builtin_amdgcn_mfma_f32_32x32x16_f16(__builtin_bit_cast(f16x8, fb[d][kk][j]), __builtin_bit_cast(f16x8, fa[d][kk][i]), t,
-                                                                  0, 0, 0);
-                };
-                if constexpr (kInPlace) {
 #pragma unroll
-                    for (int d = 0; d < kAhead; ++d)
+                for (int i = 0; i < TM; ++i)
 #pragma unroll
-                        for (int kk = 0; kk < 2; ++kk)
+                    for (int j = 0; j < TN; ++j) {
+                        floatx16 t = {};
 #pragma unroll
-                            for (int i = 0; i < TM; ++i)
+                        for (int d = 0; d < kAhead; ++d)
 #pragma unroll
-                                for (int j = 0; j < TN; ++j) acc[i][j] = add(acc[i][j], i, j, d, kk);
-                } else {
+                            for (int kk = 0; kk < 2; ++kk)
+                                t = __builtin_amdgcn_mfma_f32_32x32x16_f16(__builtin_bit_cast(f16x8, fb[d][kk][j]),
+                                                                           __builtin_bit_cast(f16x8, fa[d][kk][i]), t, 0, 0, 0);
 #pragma unroll
-                    for (int i = 0; i < TM; ++i)
-#pragma unroll
-                        for (int j = 0; j < TN; ++j) {
-                            floatx16 t = {};
-#pragma unroll
-                            for (int d = 0; d < kAhead; ++d)
-#pragma unroll
-                                for (int kk = 0; kk < 2; ++kk) t = add(t, i, j, d, kk);
-#pragma unroll
-                            for (int v = 0; v < 16; ++v) acc[i][j][v] = fmaf(t[v], ldexpf(1.0f, -up), acc[i][j][v]);
-                        }
-                }
+                        for (int v = 0; v < 16; ++v) acc[i][j][v] = fmaf(t[v], down, acc[i][j][v]);
+                    }
             }
-            if constexpr (kInPlace) times(ldexpf(1.0f, -up));
         }
     }
-    times(ldexpf(1.0f, -(pa.S[0] + pb.S[0])));
+    const float unit = ldexpf(1.0f, -(pa.S[0] + pb.S[0]));
+#pragma unroll
+    for (int i = 0; i < TM; ++i)
+#pragma unroll
+        for (int j = 0; j < TN; ++j)
+#pragma unroll
+            for (int v = 0; v < 16; ++v) acc[i][j][v] *= unit;
 }
 
 // product: Aw / Bw are prepared operands (rows padded to a multiple of kRowPad, k to a multiple
@@ -836,7 +823,7 @@ __device__ __forceinline__ void product_body(const u32x4 *__restrict__ Aw, const
 }
 
 template <int PS, int TM, int TN, int KS, int NST, bool SPLIT, bool SCHED, bool SCALED, bool GATHER = false, bool WINDOW = false>
-__global__ __launch_bounds__(256) void product_kernel(const u32x4 *__restrict__ Aw, const u32x4 *__restrict__ Bw,
+__global__ __launch_bounds__(256, WINDOW ? window_workgroups(TM * TN) : 1) void product_kernel(const u32x4 *__restrict__ Aw, const u32x4 *__restrict__ Bw,
                                                       float *__restrict__ C, int M, int N, int64_t ldc, int img,
                                                       int kblocks, int tiles_m, int tiles_n, int kb_per_split,
                                                       Planes pa, Planes pb, Implicit im)

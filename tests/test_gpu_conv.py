@@ -348,9 +348,9 @@ def in_64_bits(X, W, dY, pad, stride):
 @pytest.mark.parametrize("plan", [None, "1,1,1", "2,2,2", "4,2,1", "2,4,1", "4,4,1"])
 @pytest.mark.parametrize("spread", ["images", "elements", "single", "gradient"])
 def test_elements_outside_plane_0(fmt, spread, plan, monkeypatch):
-    """1/6/8 and 1/6/9 on exponent planes with one scale per tensor: operands that fill all three planes, images and channels of their own
-    magnitudes (where whole outputs live in the planes above and below), and single elements outside plane 0, at the edges of
-    tiles, images and blocks of 64 pixels.  |sum in fp32 - sum in 64 bits| <= (K + 2) 2^-24 sum|a b| for products that are exact, in any order."""
+    """1/6/8 and 1/6/9 on exponent planes with one scale per tensor: operands of which much lies in a second plane, images and channels of their
+    own magnitudes (where whole outputs live outside plane 0), and a few elements outside plane 0 (operands with elements both above and
+    below: test_all_pairs_of_planes_meet).  |sum in fp32 - sum in 64 bits| <= (K + 2) 2^-24 sum|a b| for products that are exact, in any order."""
     if plan is not None:
         monkeypatch.setenv("FMT_GEMM_PLAN", plan)
     monkeypatch.setenv("FMT_GEMM_WINDOW", "1")           # by size these take two bf16 pieces
@@ -380,6 +380,117 @@ def test_elements_outside_plane_0(fmt, spread, plan, monkeypatch):
         for name, g_, w_, z_, K in zip(("Y", "dX", "dW"), got, want, size, (c * r * s, k * r * s, n * P * Q)):
             bad = np.abs(g_ - w_) > (K + 2) * 2.0 ** -24 * z_ + 2.0 ** -149
             assert not bad.any(), "%s 1/%d/%d: %d of %d" % (name, e, m, bad.sum(), bad.size)
+
+
+SAMPLE_RUNS = 32
+
+
+def sampled(n):
+    """The elements that a tensor's scale is chosen from: SAMPLE_RUNS runs of 16 spread over it."""
+    step = (n - 16) // (SAMPLE_RUNS - 1) if n > 16 * SAMPLE_RUNS else 16
+    return np.unique(np.minimum((np.arange(SAMPLE_RUNS)[:, None] * step + np.arange(16)).ravel(), n - 1))
+
+
+def planes_of(x, m):
+    """The plane of every element of a tensor in 1/6/m: 0, 1 above, 2 below (zeros: 0)."""
+    emin, wid = -30, 39 - m
+    flat = x.ravel()
+    a = np.abs(flat[sampled(flat.size)].astype(np.float64))
+    E = np.frexp(a[a > 0])[1] - 1
+    hi, lo = int(E.max()), int(max(E.min(), emin - 1))
+    top, room = hi + 1, lo + wid
+    T = 9 - m if lo < emin else room if top >= room else top + min(4, (room - top) // 2)
+    sc = x.astype(np.float64) * 2.0 ** (15 - min(max(T, 0), 31))
+    above = np.abs(sc) >= 65536.0
+    return np.where(above, 1, np.where(np.where(above, 0, sc).astype(np.float16) != sc, 2, 0) * ~above)
+
+
+def place(x, at, value):
+    """x[at] = value, or in the first element after it that the scale does not look at."""
+    i, seen = int(np.ravel_multi_index(at, x.shape)), set(sampled(x.size).tolist())
+    while i % x.size in seen:
+        i += 1
+    x.ravel()[i % x.size] = value
+
+
+def check_three(fmt, X, W, dY, f, pad, stride):
+    """|sum in fp32 - sum in 64 bits| <= (K + 2) 2^-24 sum|a b| for products that are exact, in any order; nothing overflows."""
+    for t in (X, W, dY):
+        assert np.array_equal(t, oracle.quantize(t, *f))
+    got = run_all(fmt, X, W, dY, f, pad, stride)
+    want, size = in_64_bits(X, W, dY, pad, stride)
+    n, _, P, Q = dY.shape
+    k, c, r, s = W.shape
+    for name, g_, w_, z_, K in zip(("Y", "dX", "dW"), got, want, size, (c * r * s, k * r * s, n * P * Q)):
+        assert np.isfinite(g_).all(), "%s 1/%d/%d: %d not finite" % (name, f[0], f[1], (~np.isfinite(g_)).sum())
+        bad = np.abs(g_ - w_) > (K + 2) * 2.0 ** -24 * z_ + 2.0 ** -149
+        assert not bad.any(), "%s 1/%d/%d: %d of %d" % (name, f[0], f[1], bad.sum(), bad.size)
+
+
+def normal_clipped(rng, shape, f):
+    """N(0, 1) of which nothing is below 2^-8: a scale in the middle of its range, with planes above and below."""
+    x = rng.standard_normal(shape)
+    return oracle.quantize(np.ascontiguousarray((np.sign(x) * np.maximum(np.abs(x), 2.0 ** -8)).astype(np.float32)), *f)
+
+
+@pytest.mark.parametrize("m", [8, 9])
+@pytest.mark.parametrize("plan", [None, "1,1,1", "2,2,1", "4,2,1", "2,4,1", "4,4,1", "1,1,3", "2,2,2"])
+def test_all_pairs_of_planes_meet(fmt, m, plan, monkeypatch):
+    """Elements above and below plane 0 in both operands of all three products, large ones that meet large ones in the outputs of
+    waves where small ones meet small ones: the sums reach 2^(2 (26 + S)) in plane 0's units, and the pair of the planes below has a
+    scale of 2^62 (2^64 with m = 8) in them."""
+    if plan is not None:
+        monkeypatch.setenv("FMT_GEMM_PLAN", plan)
+    monkeypatch.setenv("FMT_GEMM_WINDOW", "1")
+    f, rng = (6, m, True), np.random.default_rng(m)
+    for n, c, h, w, k, pad in ((2, 64, 9, 8, 96, (1, 1)), (3, 96, 14, 14, 64, (1, 1))):
+        X, W, dY = (normal_clipped(rng, shape, f) for shape in ((n, c, h, w), (k, c, 3, 3), (n, k, h, w)))
+        big, small = 2.0 ** 26, 1.5 * 2.0 ** -33
+        # the large ones meet in Y[., 5], dX[., 3] and dW[5, 3], the small ones in the channels beside them
+        for t, at in ((X, (0, 3, 4, 4)), (X, (1, 3, 0, 1)), (X, (n - 1, c - 1, h - 1, w - 2)), (W, (5, 3, 1, 1)), (W, (5, 7, 0, 2)), (W, (k - 1, c - 1, 2, 1)),
+                      (dY, (0, 5, 4, 4)), (dY, (1, 5, 0, 2)), (dY, (n - 1, k - 1, h - 1, w - 2))):
+            place(t, at, big)
+        for t, at in ((X, (0, 4, 4, 6)), (X, (1, 9, 2, 2)), (X, (n - 1, c - 2, h - 2, 1)), (W, (6, 4, 1, 1)), (W, (9, 3, 0, 0)), (W, (k - 2, c - 2, 1, 2)),
+                      (dY, (0, 6, 4, 6)), (dY, (1, 9, 3, 2)), (dY, (n - 1, k - 2, 1, 1))):
+            place(t, at, small)
+        for t in (X, W, dY):
+            assert np.array_equal(np.bincount(planes_of(t, m).ravel(), minlength=3)[1:], [3, 3])
+        check_three(fmt, X, W, dY, f, pad, (1, 1))
+
+
+@pytest.mark.parametrize("plan", ["1,1,1", "2,2,1", "4,4,1", "2,2,2", "1,1,3"])
+def test_elements_outside_plane_0_in_long_sums(fmt, plan, monkeypatch):
+    """Sums of more than 128 blocks of 32 k, whose masks are looked at in several steps of 64 blocks (in one part, and in parts that are
+    no multiple of 64 blocks long), with elements above and below plane 0 in the first, the last, and the blocks on both sides of a step."""
+    monkeypatch.setenv("FMT_GEMM_PLAN", plan)
+    monkeypatch.setenv("FMT_GEMM_WINDOW", "1")
+    f, rng = (6, 9, True), np.random.default_rng(7)
+    big, small = 2.0 ** 26, 1.5 * 2.0 ** -33
+    blocks = (0, 63, 64, 127, 128, 143)
+    # 512 channels, 3 x 3 taps: block b is tap b / 16, channels 32 (b % 16) on, for the forward product of X and the input gradient of dY
+    n, c, h, w, k = 1, 512, 6, 5, 40
+    for which in ("fwd", "dgrad"):
+        T, O = normal_clipped(rng, (n, c, h, w), f), normal_clipped(rng, (n, k, h, w), f)
+        F = normal_clipped(rng, (k, c, 3, 3) if which == "fwd" else (c, k, 3, 3), f)
+        for i, b in enumerate(blocks):
+            ch, tap = 32 * (b % 16), (b // 16 // 3, b // 16 % 3)
+            for j, v in enumerate((big, small)):
+                place(T, (0, ch + 5 + 9 * j, i % h, (i + j) % w), v)
+                place(F, ((3 + i + 17 * j, ch + 5 + 9 * j) if which == "fwd" else (ch + 5 + 9 * j, 3 + i + 17 * j)) + tap, v)
+        for t in (T, F):
+            assert (np.bincount(planes_of(t, 9).ravel(), minlength=3)[1:] >= 4).all()
+        check_three(fmt, *((T, F, O) if which == "fwd" else (O, F, T)), f, (1, 1), (1, 1))
+    # 3 images of 40 x 40: block b of the weight gradient is positions 32 b on
+    n, c, h, w, k = 3, 24, 40, 40, 40
+    X, W, dY = normal_clipped(rng, (n, c, h, w), f), normal_clipped(rng, (k, c, 3, 3), f), normal_clipped(rng, (n, k, h, w), f)
+    for i, b in enumerate(blocks + (149,)):
+        for j, v in enumerate((big, small)):
+            image, at = divmod(32 * b + 3 + 8 * j, h * w)
+            place(dY, (image, 3 + i + 20 * j, at // w, at % w), v)
+            place(X, (image, 2 + i + 11 * j, at // w, at % w), v)
+    for t in (X, dY):
+        assert (np.bincount(planes_of(t, 9).ravel(), minlength=3)[1:] >= 4).all()
+    check_three(fmt, X, W, dY, f, (1, 1), (1, 1))
 
 
 def test_infinities_on_exponent_planes(fmt, monkeypatch):
