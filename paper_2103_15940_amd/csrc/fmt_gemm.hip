@@ -1687,8 +1687,14 @@ static Scheme api_scheme(fmt_format_t f, int64_t K);
 // whose rows lie along k came through LDS; 5.84 with the better route each time).  Measured (us in a graph, general / direct): 256 x 256 x
 // 511 in 1/6/9 10.9 / 6.5; 256 x 1024 x 1024 14.4 / 9.5 - 10.0; 300 x 300 x 333 in 1/5/10 8 / 7.2; not taken: 559 x 489 x 1289 in
 // 1/6/9 18.1 / 23.9, 973 x 608 x 1264 in 1/8/7 14.9 / 32.1.
+// Of a layer with nsplit == 1 the general route ends in its product's kernel, statistics and codes included, which the direct one has to
+// leave to a pass of 4 - 10 us: more than it saves (general / direct and pass, from Python: 192 x 101 x 192 in 1/5/10 with statistics
+// 12.0 / 18.2, 752 x 552 x 192 with codes and statistics 12.7 / 18.0, 276 x 1210 x 194 in 1/8/7 with codes 10.7 / 12.0).  So such layers take
+// the general route (in_product) -- where its sums are the direct one's.  1/6/8 and 1/6/9 have parts of their own, and a layer's outputs
+// depend neither on whether statistics are asked for nor on which of fmt_gemm and fmt_linear makes the sums: there the product alone
+// decides, and a pass follows (general / direct and pass, 390 x 1142 x 314: 15.3 / 22.1 with statistics, 11.9 / 10.7 without).
 static int direct_parts(int M, int N, int K, const OperandSpec &sa, const OperandSpec &sb, const Plan &plan, fmt_format_t f, Scheme sch,
-                        int mode, bool layer, int cus)
+                        int mode, const LinearOut *lin, int cus)
 {
     const char *env = getenv("FMT_GEMM_PLAN");
     if (env != nullptr && strcmp(env, "direct") != 0) return 0;
@@ -1700,7 +1706,8 @@ static int direct_parts(int M, int N, int K, const OperandSpec &sa, const Operan
     const int kblocks = (K + kUnitK - 1) / kUnitK;
     const int64_t tiles = (((int64_t)M + 31) / 32) * (((int64_t)N + 31) / 32);
     int parts = plan.nsplit;
-    if (planes_possible(f) && api_scheme(f, K).scaled) {
+    const bool own_parts = planes_possible(f) && api_scheme(f, K).scaled;
+    if (own_parts) {
         // the prepared calls of these formats take the planes, so no other call promises these sums and the parts are
         // free: enough for two waves per SIMD (2048), two blocks each at least
         parts = 1;
@@ -1708,6 +1715,9 @@ static int direct_parts(int M, int N, int K, const OperandSpec &sa, const Operan
     }
     if (parts > kDirectParts) return 0;
     if (env != nullptr) return parts;
+    const bool layer = lin != nullptr && lin->hist == nullptr && lin->codes == nullptr;     // rounded by the direct kernel
+    const bool in_product = lin != nullptr && plan.nsplit == 1 && (lin->hist == nullptr || lin->p.exp_lo >= -126);
+    if (in_product && !layer && !own_parts) return 0;
     const bool one = pieces_of(sch.ps) == 1;
     const int64_t per_wg = direct_blocks_per_workgroup(parts), wgs = (tiles + per_wg - 1) / per_wg;
     const double n = (double)((wgs + cus - 1) / cus) * (double)(parts * per_wg) / 4.0;
@@ -1769,7 +1779,7 @@ static int run(int M, int N, int K, const OperandSpec &sa, const OperandSpec &sb
     // recorded into a graph, does not depend on the route)
     if (!scaled && sa.g.kind == kSrcMatrix && sb.g.kind == kSrcMatrix && out.img == 0) {
         const bool plain = out.lin != nullptr && out.lin->hist == nullptr && out.lin->codes == nullptr;   // a layer's fp32 outputs without statistics
-        const int parts = direct_parts(M, N, K, sa, sb, plan, f, sch, p.mode, plain, cus);
+        const int parts = direct_parts(M, N, K, sa, sb, plan, f, sch, p.mode, out.lin, cus);
         if (parts > 0) {
             const int rcd = launch_direct_product(M, N, K, MatrixOperand{sa.X, sa.ld, sa.kcontig}, MatrixOperand{sb.X, sb.ld, sb.kcontig},
                                                   out.C, out.ldc, parts, PS, FTZ, p, plain ? out.lin : nullptr, stream);
