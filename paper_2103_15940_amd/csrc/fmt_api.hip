@@ -100,6 +100,23 @@ int get_scratch(hipStream_t stream, size_t hist_bytes, size_t gemm_bytes, Scratc
     return FMT_OK;
 }
 
+bool scratch_has_room(hipStream_t stream, size_t gemm_bytes)
+{
+    int dev = 0;
+    if (hipGetDevice(&dev) != hipSuccess) return false;
+    std::lock_guard<std::mutex> lk(g_mu);
+    const Scratch &s = g_scratch[std::make_pair(dev, stream)];
+    if (gemm_bytes <= s.gemm_bytes) return true;
+    hipStreamCaptureStatus capturing = hipStreamCaptureStatusNone;       // (the default stream cannot be captured: get_hist_records)
+    if (stream != nullptr && stream != hipStreamLegacy && hipStreamIsCapturing(stream, &capturing) != hipSuccess) {
+        (void)hipGetLastError();
+        return false;
+    }
+    size_t free_bytes = 0, total = 0;
+    return capturing == hipStreamCaptureStatusNone && hipMemGetInfo(&free_bytes, &total) == hipSuccess &&
+           gemm_bytes + 4096 <= free_bytes + s.gemm_bytes;
+}
+
 int get_hist_records(hipStream_t stream, uint64_t nwg, HistRecords *out)
 {
     int dev = 0;

@@ -2317,7 +2317,8 @@ static WindowTensor window_tensor(const float *x, int64_t n, fmt_format_t f)
     return WindowTensor{reinterpret_cast<const uint32_t *>(x), (uint32_t)n, 2 - (1 << (f.e - 1)), f.m};
 }
 
-// run_implicit for these.  The tensor's planes above and below are held whole and written where they are not empty.
+// run_implicit for these.  The tensor's planes above and below are held whole and written where they are not empty; where there is no
+// scratch for them, 1 comes back and nothing has been launched: two bf16 pieces take a third less.
 static int run_implicit_window(int M, int N, int K, const OperandSpec &sa, int64_t filter_elems, const float *tensor, int64_t tensor_elems, int HW,
                                Implicit im, const OutSpec &out, fmt_format_t f, const QuantParams &p, hipStream_t stream)
 {
@@ -2336,8 +2337,8 @@ static int run_implicit_window(int M, int N, int K, const OperandSpec &sa, int64
     const size_t nhwc = up256((3 * piece_vec + 1) * sizeof(u32x4)), masks = up256((size_t)nx * (C / 32) * 2 * sizeof(uint64_t));
     const size_t part = part_bytes_of(plan, M, N);
     Scratch s;
-    rc = get_scratch(stream, 0, la.bytes + nhwc + masks + 256 + part, &s);
-    if (rc != FMT_OK) return rc;
+    const size_t need = la.bytes + nhwc + masks + 256 + part;
+    if (!scratch_has_room(stream, need) || get_scratch(stream, 0, need, &s) != FMT_OK) return 1;
     char *ws = static_cast<char *>(s.gemm_ws);
     const OperandView va = view_of(ws, la);
     OperandView vb{reinterpret_cast<u32x4 *>(ws + la.bytes), Planes{nullptr, nullptr, piece_vec, la.w, nullptr, nullptr}};
@@ -2364,7 +2365,7 @@ static int run_implicit_window(int M, int N, int K, const OperandSpec &sa, int64
     return product_window<true>(va, vb, im, M, N, la.kblocks, out, plan, partp, stream);
 }
 
-// The weight gradient on these planes: dY as the matrix [K][n*P*Q], the patches of X through gather_taps (at most 32 taps).
+// The weight gradient on these planes: dY as the matrix [K][n*P*Q], the patches of X through gather_taps (at most 32 taps).  1: no scratch.
 static int run_wgrad_window(int M, int N, int K, const OperandSpec &sa, int64_t grad_elems, const OperandSpec &sb, const OutSpec &out,
                             fmt_format_t f, const QuantParams &p, hipStream_t stream)
 {
@@ -2380,8 +2381,8 @@ static int run_wgrad_window(int M, int N, int K, const OperandSpec &sa, int64_t 
     const size_t part = part_bytes_of(plan, M, N);
     const int n = (int)sb.pre_elems;
     Scratch s;
-    rc = get_scratch(stream, 0, la.bytes + lb.bytes + part + ((size_t)n + 1) * sizeof(uint32_t), &s);
-    if (rc != FMT_OK) return rc;
+    const size_t need = la.bytes + lb.bytes + part + ((size_t)n + 1) * sizeof(uint32_t);
+    if (!scratch_has_room(stream, need) || get_scratch(stream, 0, need, &s) != FMT_OK) return 1;
     char *ws = static_cast<char *>(s.gemm_ws);
     const OperandView va = view_of(ws, la), vb = view_of(ws + la.bytes, lb);
     float *partp = reinterpret_cast<float *>(ws + la.bytes + lb.bytes);
@@ -2454,8 +2455,10 @@ static int conv_implicit(int which, const fmt_conv2d_t &g, int64_t P, int64_t Q,
     const OperandSpec sa{filt, 0, true, ft, 0};
     const OutSpec os{out, 0, (int)(gy * gx)};
     const bool planes = conv_planes(f, p, (double)g.n * gy * gx * g.k * g.c * rs, 1.5e8) && elems > 0 && (elems / 8) * 3 + (int64_t)(g.r * tw + g.s) * (tc / 8) < ((int64_t)1 << 31);
-    if (planes)
-        return run_implicit_window((int)M, (int)N, (int)K, sa, (int64_t)g.k * g.c * rs, tensor, elems, (int)(th * tw), im, os, f, p, stream);
+    if (planes) {
+        const int rc = run_implicit_window((int)M, (int)N, (int)K, sa, (int64_t)g.k * g.c * rs, tensor, elems, (int)(th * tw), im, os, f, p, stream);
+        if (rc <= 0) return rc;
+    }
     const bool ftz = f.denorm == 0;
 #define FMT_IMPL2(MD, FZ)                                                                                                     \
     (sch.ps == 0   ? run_implicit<MD, FZ, 0>((int)M, (int)N, (int)K, sa, tensor, elems, (int)(th * tw), im, os, f, p, stream) \
@@ -2548,8 +2551,10 @@ int launch_conv2d(int which, const fmt_conv2d_t &g, const float *a, const float 
     patch.k0 = make_fastdiv(patch.gx); patch.k1 = make_fastdiv(patch.gy);
     const OperandSpec sa{a, 0, true, ch, 0};                       // dY as [K][n*P*Q]
     const OperandSpec sb{b, 0, true, patch, (int64_t)g.n * g.c * g.h * g.w};      // patches of X, k along positions
-    if (conv_planes(f, p, (double)M * N * K, 7e8) && g.r * g.s <= 32 && sb.pre_elems > 0)
-        return run_wgrad_window((int)M, (int)N, (int)K, sa, M * K, sb, OutSpec{out, N, 0}, f, p, stream);
+    if (conv_planes(f, p, (double)M * N * K, 7e8) && g.r * g.s <= 32 && sb.pre_elems > 0) {
+        const int rc = run_wgrad_window((int)M, (int)N, (int)K, sa, M * K, sb, OutSpec{out, N, 0}, f, p, stream);
+        if (rc <= 0) return rc;
+    }
     return run_product((int)M, (int)N, (int)K, sa, sb, OutSpec{out, N, 0}, f, p, stream);
 }
 

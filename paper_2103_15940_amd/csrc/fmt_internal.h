@@ -45,6 +45,9 @@ struct Scratch {
 
 // Returns the scratch record for (current device, stream), growing the requested buffers.
 int get_scratch(hipStream_t stream, size_t hist_bytes, size_t gemm_bytes, Scratch *out);
+// Whether get_scratch would have gemm_bytes: they are there, or can be made (memory is left, and the stream is not being captured).  For
+// routes that need more than another one of the same call.
+bool scratch_has_room(hipStream_t stream, size_t gemm_bytes);
 
 // Room for the partial records of one statistics pass of nwg workgroups on `stream` (fmt_hist.h): the records it adds into, and
 // what the pass clears meanwhile for the pass after it (nullptr: the pass is being captured, and its records are summed

@@ -559,3 +559,36 @@ def test_exponent_planes_under_capture(fmt):
         torch.cuda.synchronize()
         for a, b in zip((Y, dX, dW), eager):
             assert torch.equal(a, b)
+
+
+def test_capture_in_the_scratch_of_two_pieces(fmt, monkeypatch):
+    """Exponent planes take half as much scratch again as two bf16 pieces.  A stream that is being captured, whose scratch cannot grow,
+    records the calls on the pieces if there is room for these only: every replay gives their bits."""
+    f, g = (6, 9, True), {"pad": (1, 1), "stride": (1, 1)}
+    X, W, dY = torch.randn(8, 64, 14, 14, device="cuda"), torch.randn(64, 64, 3, 3, device="cuda") * 0.05, torch.randn(8, 64, 14, 14, device="cuda")
+    Y, dX, dW = torch.empty_like(dY), torch.empty_like(X), torch.empty_like(W)
+    calls = ((lambda o: fmt.fmt_conv2d_fwd(X, W, f, out=o, **g), Y), (lambda o: fmt.fmt_conv2d_dgrad(dY, W, X.shape, f, out=o, **g), dX),
+             (lambda o: fmt.fmt_conv2d_wgrad(dY, X, W.shape, f, out=o, **g), dW))
+    for call, out in calls:
+        fmt.fmt_release_scratch()
+        stream = torch.cuda.Stream()
+        with torch.cuda.stream(stream):
+            monkeypatch.setenv("FMT_GEMM_WINDOW", "0")
+            call(out)
+            stream.synchronize()
+            want, had = out.clone(), fmt.fmt_scratch_bytes()["products"]
+            monkeypatch.setenv("FMT_GEMM_WINDOW", "1")
+            graph = torch.cuda.CUDAGraph()
+            with torch.cuda.graph(graph, stream=stream):
+                call(out)
+            assert fmt.fmt_scratch_bytes()["products"] == had
+            for _ in range(3):
+                out.fill_(float("nan"))
+                stream.synchronize()
+                graph.replay()
+                stream.synchronize()
+                assert torch.equal(out, want)
+            call(out)                                    # not captured: the scratch grows
+            stream.synchronize()
+            assert fmt.fmt_scratch_bytes()["products"] > had
+    fmt.fmt_release_scratch()
