@@ -37,7 +37,7 @@ struct Planes {
 constexpr int kRecCap = 64;
 // Convolutions (product_window) use planes with one scale for the whole tensor: S[0] alone, no records.  A tensor whose patches the
 // product kernel gathers has, per 64 pixels x 32 channels, two words of 64 bits in the mask's place, a bit per pixel: what has elements in the plane
-// above, and below.
+// above, and below.  S[1] of operand A is 1 where both operands are two bf16 pieces instead (window_pair).
 
 // Division of a 31-bit dividend by a divisor fixed at launch, as a multiply-high and a shift
 // (m = floor(2^(31+l) / d) + 1 with l = ceil(log2 d) gives floor(a / d) for every 0 <= a < 2^31).
@@ -83,6 +83,7 @@ struct Implicit {
     FastDiv r0, r1;     // row -> (n, y, x): by gx, then by gy
     FastDiv kc;         // stage number -> (tap, channel block): by channels / (k per stage)
     FastDiv ks;         // tap -> (r, s): by S
+    FastDiv kc_pieces;  // planes (product_window): kc of the stages of two bf16 pieces
 };
 
 // A group of independent products in one launch (fmt_gemm_prepared_batch): workgroup ids [first, next first)

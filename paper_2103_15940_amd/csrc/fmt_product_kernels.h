@@ -492,6 +492,14 @@ __device__ __forceinline__ void window_tail(floatx16 (&acc)[TM][TN], const uint3
             for (int v = 0; v < 16; ++v) acc[i][j][v] *= unit;
 }
 
+// A stage buffer, by its place in the ring: the two bodies of a kernel that holds planes and pieces (product_kernel) have theirs in common.
+template <int PLACE, int VECTORS>
+__device__ __forceinline__ auto stage_buffer() -> u32x4 (&)[VECTORS]
+{
+    __shared__ u32x4 vectors[VECTORS];
+    return vectors;
+}
+
 // product: Aw / Bw are prepared operands (rows padded to a multiple of kRowPad, k to a multiple
 // of 32).  A workgroup is 2 x 2 waves; each wave owns TM x TN MFMA tiles of 32 x 32, so the
 // workgroup tile is (64*TM) x (64*TN).  Operand stages of KS*16 k go from global memory straight
@@ -535,10 +543,10 @@ __device__ __forceinline__ void product_body(const u32x4 *__restrict__ Aw, const
     // One LDS array per stage buffer, each addressed with a compile-time index: the compiler then knows
     // which loads-to-LDS an LDS read can depend on and leaves the younger stages in flight.
     constexpr int STV = VA + VB;
-    __shared__ u32x4 st0[STV];
-    __shared__ u32x4 st1[STV];
-    __shared__ u32x4 st2[NST > 2 ? STV : 1];
-    __shared__ u32x4 st3[NST > 3 ? STV : 1];
+    u32x4(&st0)[STV] = stage_buffer<0, STV>();
+    u32x4(&st1)[STV] = stage_buffer<1, STV>();
+    u32x4(&st2)[NST > 2 ? STV : 1] = stage_buffer<2, (NST > 2 ? STV : 1)>();
+    u32x4(&st3)[NST > 3 ? STV : 1] = stage_buffer<3, (NST > 3 ? STV : 1)>();
     auto stage = [&](int b) -> u32x4 * { return b == 0 ? st0 : b == 1 ? st1 : b == 2 ? st2 : st3; };
     typedef __attribute__((address_space(3))) void lds_void;
     typedef const __attribute__((address_space(1))) void glb_void;
@@ -680,6 +688,10 @@ __device__ __forceinline__ void product_body(const u32x4 *__restrict__ Aw, const
     auto barrier = [&]() __attribute__((always_inline)) { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); };
 
     [[maybe_unused]] uint32_t early[kWindowChunks] = {0u, 0u};
+    // Tensors that span more than a plane have been prepared as two bf16 pieces (window_pair).  The first stages' loads are issued before
+    // that is known: S comes out of the memory behind another XCD's L2.
+    [[maybe_unused]] int in_pieces = 0;
+    if constexpr (WINDOW) in_pieces = pa.S[1];
     if (steps > 0) {
 #pragma unroll
         for (int t = 0; t < NST; ++t) issue(t, t);
@@ -687,6 +699,18 @@ __device__ __forceinline__ void product_body(const u32x4 *__restrict__ Aw, const
 #pragma unroll
             for (int c = 0; c < kWindowChunks; ++c)
                 early[c] = window_masks<TM, TN, GATHER>(pa, pb, im, kblocks, kb0 + c * 64 + lane, kb1, tm * UA + wm * TM, tn * UB + wn * TN);
+            if (__builtin_amdgcn_readfirstlane(in_pieces) != 0) {    // the same in the whole launch
+                // twice the bytes per k, so the same stages in half as many k; the buffers are the same
+                typedef Pipe<2, TM, TN> Pieces;
+                static_assert(Pieces::nst == NST && 2 * Pieces::ks == KS, "stages of the same bytes");
+                __builtin_amdgcn_s_waitcnt(0x0F70);
+                barrier();
+                Implicit imp = im;
+                imp.kc = im.kc_pieces;
+                product_body<2, TM, TN, Pieces::ks, Pieces::nst, SPLIT, SCHED, false, GATHER>(Aw, Bw, C, M, N, ldc, img, kblocks, tiles_m, tiles_n,
+                                                                                           kb_per_split, pa, pb, imp, bid);
+                return;
+            }
         }
         __builtin_amdgcn_s_waitcnt(0x0F70 | (kWaitFirst & 0xF) | ((kWaitFirst >> 4) << 14));
         barrier();
@@ -865,6 +889,7 @@ static int launch_product_v2(const u32x4 *Aw, const u32x4 *Bw, float *out, int M
         auto kern = product_kernel<PS, TM, TN, KS, NST, SPLIT, SCHED, SCALED, GATHER, WINDOW>;
         Implicit imk = im;
         if (GATHER) imk.kc = make_fastdiv(im.c8 * 8 / (16 * KS));   // stages of 16*KS k per tap
+        if (GATHER && WINDOW) imk.kc_pieces = make_fastdiv(im.c8 * 8 / (16 * Pipe<2, TM, TN>::ks));
         hipLaunchKernelGGL(kern, dim3((unsigned)(per_xcd * 8 * nsplit)), dim3(256), 0, stream, Aw, Bw, out, M, N, ld, img,
                            kblocks, tiles_m, tiles_n, kb_per, pa, pb, imk);
         FMT_HIP_CHECK(hipGetLastError());

@@ -382,13 +382,12 @@ def test_elements_outside_plane_0(fmt, spread, plan, monkeypatch):
             assert not bad.any(), "%s 1/%d/%d: %d of %d" % (name, e, m, bad.sum(), bad.size)
 
 
-SAMPLE_RUNS = 32
-
-
-def sampled(n):
-    """The elements that a tensor's scale is chosen from: SAMPLE_RUNS runs of 16 spread over it."""
-    step = (n - 16) // (SAMPLE_RUNS - 1) if n > 16 * SAMPLE_RUNS else 16
-    return np.unique(np.minimum((np.arange(SAMPLE_RUNS)[:, None] * step + np.arange(16)).ravel(), n - 1))
+def sampled(n, runs=64):
+    """The elements that a tensor's scale is chosen from: 32 or 64 runs of 32, an odd number of runs apart (tensors that start at a line)."""
+    if n < 32 * runs + 32:
+        return np.arange(min(n, 32 * runs))
+    step = (((n - 32) // (runs - 1) // 32 - 1) | 1) * 32
+    return (np.arange(runs)[:, None] * step + np.arange(32)).ravel()
 
 
 def planes_of(x, m):
@@ -407,7 +406,7 @@ def planes_of(x, m):
 
 def place(x, at, value):
     """x[at] = value, or in the first element after it that the scale does not look at."""
-    i, seen = int(np.ravel_multi_index(at, x.shape)), set(sampled(x.size).tolist())
+    i, seen = int(np.ravel_multi_index(at, x.shape)), set(sampled(x.size).tolist()) | set(sampled(x.size, 32).tolist())
     while i % x.size in seen:
         i += 1
     x.ravel()[i % x.size] = value
@@ -443,7 +442,7 @@ def test_all_pairs_of_planes_meet(fmt, m, plan, monkeypatch):
         monkeypatch.setenv("FMT_GEMM_PLAN", plan)
     monkeypatch.setenv("FMT_GEMM_WINDOW", "1")
     f, rng = (6, m, True), np.random.default_rng(m)
-    for n, c, h, w, k, pad in ((2, 64, 9, 8, 96, (1, 1)), (3, 96, 14, 14, 64, (1, 1))):
+    for n, c, h, w, k, pad in ((4, 64, 12, 10, 96, (1, 1)), (3, 96, 14, 14, 64, (1, 1))):
         X, W, dY = (normal_clipped(rng, shape, f) for shape in ((n, c, h, w), (k, c, 3, 3), (n, k, h, w)))
         big, small = 2.0 ** 26, 1.5 * 2.0 ** -33
         # the large ones meet in Y[., 5], dX[., 3] and dW[5, 3], the small ones in the channels beside them
@@ -493,6 +492,55 @@ def test_elements_outside_plane_0_in_long_sums(fmt, plan, monkeypatch):
     check_three(fmt, X, W, dY, f, (1, 1), (1, 1))
 
 
+def spread_over(rng, shape, mean, sigma, f):
+    """log2|x| ~ N(mean, sigma^2), random signs."""
+    x = np.where(rng.random(shape) < 0.5, -1.0, 1.0) * 2.0 ** np.clip(rng.normal(mean, sigma, shape), -60, 30)
+    return oracle.quantize(np.ascontiguousarray(x.astype(np.float32)), *f)
+
+
+WIDE = {"high": (-10.0, 7.0), "low": (-5.0, 6.0), "all": (-6.0, 12.0), "top": (28.0, 2.0)}
+# with denormals; without; most of the format; not wide, at the format's top
+
+
+@pytest.mark.parametrize("plan", ["1,1,1", "2,2,1", "4,2,1", "2,4,1", "4,4,1", "1,1,3", "2,2,2"])
+@pytest.mark.parametrize("f", [(6, 9, True), (6, 9, False), (6, 8, True)])
+def test_tensors_wider_than_a_plane(fmt, f, plan, monkeypatch):
+    """Tensors that span more than a plane take two bf16 pieces: the bits of these where either operand is such a tensor, the
+    bits of planes where none is."""
+    monkeypatch.setenv("FMT_GEMM_PLAN", plan)
+    rng = np.random.default_rng(len(plan))
+    n, c, h, w, k = 3, 64, 14, 14, 96
+    for wide in ("none", "high", "low", "all", "top"):
+        for which in ((), ) if wide == "none" else ((0,), (1,), (2,), (0, 1, 2)):
+            X, W, dY = (spread_over(rng, shape, *(WIDE[wide] if i in which else (-3.0, 1.5)), f)
+                        for i, shape in enumerate(((n, c, h, w), (k, c, 3, 3), (n, k, h, w))))
+            got = {}
+            for mode in "013":
+                monkeypatch.setenv("FMT_GEMM_WINDOW", mode)
+                got[mode] = run_all(fmt, X, W, dY, f, (1, 1), (1, 1))
+            for i, operands in enumerate(((0, 1), (1, 2), (0, 2))):
+                pieces = wide != "top" and bool(set(operands) & set(which))
+                assert not np.array_equal(got["0"][i], got["1"][i]), "the test cannot tell"
+                assert np.array_equal(got["3"][i], got["0" if pieces else "1"][i]), (wide, which, i)
+
+
+def test_wide_tensors_by_default(fmt, monkeypatch):
+    """The same at sizes that take planes by default."""
+    f, rng = (6, 9, True), np.random.default_rng(3)
+    n, c, h, w, k = 64, 96, 14, 14, 96
+    monkeypatch.setenv("FMT_GEMM_PLAN", "2,2,1")
+    X, W = spread_over(rng, (n, c, h, w), -3.0, 1.5, f), spread_over(rng, (k, c, 3, 3), -3.0, 1.5, f)
+    for wide in (False, True):
+        dY = spread_over(rng, (n, k, h, w), *(WIDE["high"] if wide else (-3.0, 1.5)), f)
+        monkeypatch.delenv("FMT_GEMM_WINDOW", raising=False)
+        got = run_all(fmt, X, W, dY, f, (1, 1), (1, 1))
+        for mode in "01":
+            monkeypatch.setenv("FMT_GEMM_WINDOW", mode)
+            other = run_all(fmt, X, W, dY, f, (1, 1), (1, 1))
+            for i in range(3):
+                assert np.array_equal(got[i], other[i]) == ((mode == "0") == (wide and i > 0)), (wide, mode, i)
+
+
 def test_infinities_on_exponent_planes(fmt, monkeypatch):
     """An infinite element makes the outputs that meet it non-finite and leaves the others as they are, also where other elements
     lie outside plane 0."""
@@ -520,9 +568,10 @@ def test_seeded_random_geometries_on_exponent_planes(fmt, seed, monkeypatch):
         test_seeded_random_geometries_with_channel_multiples_of_32(fmt, seed)
 
 
-def test_exponent_planes_under_capture(fmt):
-    """The three calls recorded into a graph at a size that takes exponent planes: every replay, on inputs that change in between (with and
-    without elements outside plane 0), gives the bits of the eager calls."""
+def test_exponent_planes_under_capture(fmt, monkeypatch):
+    """The three calls recorded into a graph on exponent planes: every replay, on inputs that change in between (with and without elements
+    outside plane 0, and so wide that they take two bf16 pieces), gives the bits of the eager calls."""
+    monkeypatch.setenv("FMT_GEMM_WINDOW", "3")
     f, g = (6, 9, True), {"pad": (1, 1), "stride": (1, 1)}
     gen = torch.Generator(device="cuda").manual_seed(1)
     draw = lambda *s: torch.randn(s, generator=gen, device="cuda")  # noqa: E731
@@ -542,7 +591,10 @@ def test_exponent_planes_under_capture(fmt):
         with torch.cuda.graph(graph, stream=stream):
             three(Y, dX, dW)
     torch.cuda.synchronize()
-    for turn in range(4):
+    for turn in range(5):
+        if turn == 4:
+            turn = 2
+            W *= torch.exp2(6.0 * draw(*W.shape))
         X.copy_(draw(*X.shape) * 2.0 ** (8 * turn))
         dY.copy_(draw(*dY.shape) * 2.0 ** (-12 * turn))
         if turn % 2:
