@@ -439,8 +439,8 @@ int fmt_linear_pack16(int64_t M, int64_t N, int64_t K,
  * multiple of 32 and stride 1, both with r*s <= 32, gather inside the product kernel: their scratch is of
  * the size of the tensor.  The other cases and fmt_conv2d_wgrad gather in the operand preparation, into a
  * 16-bit operand of the size of the patch matrix (2 bytes per patch element and piece) in scratch.
- * 1/6/8 and 1/6/9 take 6 instead of 4 bytes per element from 1.5e8 products (forward, dgrad) and 7e8 (wgrad,
- * and 4 bytes per element of X) on, unless that does not fit the memory that is left, or the scratch of a stream that is being captured.
+ * 1/6/8 and 1/6/9 take 6 instead of 4 bytes per element from 1.5e8 (forward), 1e9 (dgrad) and 7e8 products (wgrad, and
+ * 4 bytes per element of X) on, unless that does not fit the memory that is left, or the scratch of a stream that is being captured.
  *
  * All pointers are device pointers, 4-byte aligned; the output must not overlap an input.
  * Sizes: n, c, k >= 0; h, w, r, s >= 1; pad >= 0; stride >= 1; h + 2 pad_h >= r, w + 2 pad_w >= s;

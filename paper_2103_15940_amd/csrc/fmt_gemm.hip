@@ -2446,11 +2446,13 @@ static int run_implicit(int M, int N, int K, const OperandSpec &sa, const float 
 }
 
 // Convolutions in 1/6/8 and 1/6/9 on exponent planes with one scale per tensor: one fp16 MFMA product per multiply instead of the four of
-// two bf16 pieces (forward, dgrad and wgrad, 256 -> 256 channels of 14 x 14, 3 x 3 taps, batch 64, us: 79 -> 43, 75 -> 57, 95 -> 73).
-// Below `least` products the scale's sample and the tail cost more than they save.  us, bf16 pieces / planes: forward and dgrad, which
-// gather in the product, 8 to 96 channels, 0.25 - 0.5 x 10^8 products 9.5 / 10.3, 11.2 / 14.5, 2.6 x 10^8 14.8 / 14.0, 3.5 x 10^8 18.8 / 14.1,
-// 8.5 x 10^8 29 / 22; wgrad, whose operands are prepared as patches, 1.2 x 10^8 34 / 36, 3.5 x 10^8 23.8 / 23.7, 8.5 x 10^8 27.1 / 26.2,
-// 1.5 x 10^9 41.2 / 37.3.
+// two bf16 pieces (forward, dgrad and wgrad, 256 -> 256 channels of 14 x 14, 3 x 3 taps, batch 64, us: 80 -> 45, 78 -> 60, 102 -> 76).
+// Below `least` products the scales' samples and the tail cost more than they save.  us, bf16 pieces / planes:
+//   forward   0.25 - 0.5 x 10^8 products 9.5 / 10.3, 11.2 / 14.5; 2 x 10^8 22.5 / 20, 12.2 / 11.8, 18.4 / 16.5; 5 x 10^8 21.5 / 16.3
+//   dgrad     gathers gradients, of which a few lie outside plane 0 (log2|x| ~ N(-20, 5^2), 1e-5): 2 x 10^8 16.7 / 20.4, 17.2 / 19.9;
+//             5 x 10^8 18.4 / 20.2, 15.8 / 18.2, 20.7 / 21; 9.6 x 10^8 22.2 / 24.3, 26 / 24.3; 1.1 x 10^9 38 / 35, 22.6 / 21.7; 2.2 x 10^9 37 / 33
+//   wgrad     whose operands are prepared as patches: 1.2 x 10^8 34 / 36, 3.5 x 10^8 23.8 / 23.7, 9.6 x 10^8 54 / 49, 1.5 x 10^9 44 / 40
+constexpr double kLeastForward = 1.5e8, kLeastDgrad = 1e9, kLeastWgrad = 7e8;
 static bool conv_planes(fmt_format_t f, const QuantParams &p, double mults, double least)
 {
     const int wmode = window_mode();
@@ -2606,7 +2608,7 @@ static int conv_implicit(int which, const fmt_conv2d_t &g, int64_t P, int64_t Q,
     ft.tw = which == 0 ? rs : g.c * rs;
     const OperandSpec sa{filt, 0, true, ft, 0};
     const OutSpec os{out, 0, (int)(gy * gx)};
-    const bool planes = conv_planes(f, p, (double)g.n * gy * gx * g.k * g.c * rs, 1.5e8) && elems > 0 && (elems / 8) * 3 + (int64_t)(g.r * tw + g.s) * (tc / 8) < ((int64_t)1 << 31);
+    const bool planes = conv_planes(f, p, (double)g.n * gy * gx * g.k * g.c * rs, which == 0 ? kLeastForward : kLeastDgrad) && elems > 0 && (elems / 8) * 3 + (int64_t)(g.r * tw + g.s) * (tc / 8) < ((int64_t)1 << 31);
     if (planes) {
         const int rc = run_implicit_window((int)M, (int)N, (int)K, sa, (int64_t)g.k * g.c * rs, tensor, elems, (int)(th * tw), im, os, f, p, stream);
         if (rc <= 0) return rc;
@@ -2703,7 +2705,7 @@ int launch_conv2d(int which, const fmt_conv2d_t &g, const float *a, const float 
     patch.k0 = make_fastdiv(patch.gx); patch.k1 = make_fastdiv(patch.gy);
     const OperandSpec sa{a, 0, true, ch, 0};                       // dY as [K][n*P*Q]
     const OperandSpec sb{b, 0, true, patch, (int64_t)g.n * g.c * g.h * g.w};      // patches of X, k along positions
-    if (conv_planes(f, p, (double)M * N * K, 7e8) && g.r * g.s <= 32 && sb.pre_elems > 0) {
+    if (conv_planes(f, p, (double)M * N * K, kLeastWgrad) && g.r * g.s <= 32 && sb.pre_elems > 0) {
         const int rc = run_wgrad_window((int)M, (int)N, (int)K, sa, M * K, sb, OutSpec{out, N, 0}, f, p, stream);
         if (rc <= 0) return rc;
     }

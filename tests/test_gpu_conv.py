@@ -541,6 +541,20 @@ def test_wide_tensors_by_default(fmt, monkeypatch):
                 assert np.array_equal(got[i], other[i]) == ((mode == "0") == (wide and i > 0)), (wide, mode, i)
 
 
+def test_small_input_gradients_take_pieces(fmt, monkeypatch):
+    """At 2.6e8 products the forward product takes planes and the input gradient, whose gradients have elements outside plane 0, pieces."""
+    f, rng = (6, 9, True), np.random.default_rng(4)
+    monkeypatch.setenv("FMT_GEMM_PLAN", "2,2,1")
+    X, W = spread_over(rng, (16, 96, 14, 14), -3.0, 1.5, f), spread_over(rng, (96, 96, 3, 3), -3.0, 1.5, f)
+    dY = spread_over(rng, (16, 96, 14, 14), -20.0, 5.0, f)
+    monkeypatch.delenv("FMT_GEMM_WINDOW", raising=False)
+    got = run_all(fmt, X, W, dY, f, (1, 1), (1, 1))
+    for mode in "01":
+        monkeypatch.setenv("FMT_GEMM_WINDOW", mode)
+        other = run_all(fmt, X, W, dY, f, (1, 1), (1, 1))
+        assert [np.array_equal(a, b) for a, b in zip(got, other)] == [mode == "1", mode == "0", mode == "0"]
+
+
 def test_infinities_on_exponent_planes(fmt, monkeypatch):
     """An infinite element makes the outputs that meet it non-finite and leaves the others as they are, also where other elements
     lie outside plane 0."""
