@@ -324,3 +324,42 @@ def test_flush_of_random_sums_around_the_smallest_normal(fmt, e, m, M, N):
     ref = oracle.gemm_fmac8(np.ascontiguousarray(A[rows]), np.ascontiguousarray(B[:, cols]), e, m, False)
     assert (ref == 0.0).any() and (ref != 0.0).any()
     assert_bits(np.ascontiguousarray(C.cpu().numpy()[np.ix_(rows, cols)]), ref, "around minN")
+
+
+@pytest.mark.parametrize("M,N", [(16, 48), (70, 133), (700, 800), (2000, 2050)])
+@pytest.mark.parametrize("e,m,d", [(6, 9, True), (6, 9, False), (6, 11, True), (8, 7, True), (7, 14, False)])
+def test_rare_elements_limits_and_strides(fmt, e, m, d, M, N):
+    """What the loads, the roundings and the choice of the form of a stage of 32 k look at, at every tile size, in all layouts and with
+    leading dimensions of their own: rows and columns of which all, or a few at an edge, lie inside a tile (their elements come without
+    tests of their own); elements around the overflow threshold, infinities and NaN in one row, so that one wave of a stage rounds in
+    the general form and the others in the short one; and stages whose largest magnitudes, which are taken before the rounding, have a
+    product at the limit of the wide form, or beyond it before or after the rounding only."""
+    K = 11 * 32 + 5
+    rng = np.random.default_rng(100 * e + m + M)
+    c = oracle.format_constants(e, m)
+    A = rng.standard_normal((M, K)).astype(np.float32)
+    B = (rng.standard_normal((K, N)) * 2.0 ** -3).astype(np.float32)
+    growth = sum((1.0 + 2.0 ** -(m + 1)) ** i for i in range(9))
+    limit = 0.99 * 2.0 ** min(c["Emin"] - m + 52, c["Emax"]) / growth
+    for s, by in enumerate((0.0, 2.0 ** -(m + 2), -2.0 ** -(m + 2), 2.0 ** -(m + 4), -2.0 ** -(m + 4), 2.0 ** -m, -2.0 ** -m)):
+        w = 12.0 * (1.0 + rng.random() / 4)
+        A[rng.integers(0, M), 32 * s + 3], B[32 * s + 3, rng.integers(0, N)] = w, min(limit / w * (1.0 + by), 2.0 ** 60)
+    top, ulp = float(c["maxN"]), 2.0 ** (c["Emax"] - m)
+    over = np.array([top, min(top + ulp / 2, 3.4e38), np.nextafter(np.float32(min(top + ulp / 2, 3.4e38)), np.float32(0)), np.inf, np.nan], np.float32)
+    A[M // 2, 32 * 7 + 1: 32 * 7 + 6], B[32 * 9 + 7, N // 2] = over, over[1]
+    A[M - 1, 32 * 8], B[32 * 10, N - 1] = -top, np.inf
+    rows = np.unique(np.concatenate([[0, M - 1, M // 2, M - 2], rng.integers(0, M, 40)])) if M > 100 else np.arange(M)
+    cols = np.unique(np.concatenate([[0, N - 1, N // 2, N - 2], rng.integers(0, N, 40)])) if M > 100 else np.arange(N)
+    ref = oracle.gemm_fmac8(np.ascontiguousarray(A[rows]), np.ascontiguousarray(B[:, cols]), e, m, d)
+    nan = np.isnan(ref)
+    assert nan.any() and np.isfinite(ref).sum() > ref.size / 2
+    for tA, tB in LAYOUTS:
+        a, b = (dev(x.T if t else x) for x, t in ((A, tA), (B, tB)))
+        wide = [torch.full((x.shape[0], x.shape[1] + 5), float("nan"), device="cuda") for x in (a, b)]
+        for w, x in zip(wide, (a, b)):
+            w[:, :x.shape[1]] = x
+        C = fmt.fmt_gemm_fmac8(wide[0][:, :a.shape[1]], wide[1][:, :b.shape[1]], (e, m, d), transA=tA, transB=tB)
+        torch.cuda.synchronize()
+        got = np.ascontiguousarray(C.cpu().numpy()[np.ix_(rows, cols)])
+        assert np.array_equal(np.isnan(got), nan), "layout %s" % ((tA, tB),)
+        assert_bits(np.where(nan, 0, got).astype(np.float32), np.where(nan, 0, ref).astype(np.float32), "layout %s" % ((tA, tB),))
