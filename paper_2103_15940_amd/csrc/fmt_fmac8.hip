@@ -269,7 +269,7 @@ __global__ __launch_bounds__(256, T > 2 ? 4 : 1) void fmac8_kernel(const uint32_
 
     // The largest tile, whose thread uses a value four times, stores a stage for the form that the stage before it took: as fp64,
     // or (the single form) as fp32 in the low words.  Converting at each use instead made the single form 4 % slower there
-    // (2048 x 2048 x 256 in 1/6/9: 512 us; 496 now); the smaller tiles, which gain nothing, are 2 us faster without the
+    // (2048 x 2048 x 256 in 1/6/9: 512 us against 496 with three workgroups per compute unit, 390 now); the smaller tiles, which gain nothing, are 2 us faster without the
     // code for it (1024 x 1024 x 256, wide form: 66 us against 68).
     constexpr bool kLow = STEP == kStepSingle && T > 2;
     hi_lo pair = {0.0f, 0.0f};
@@ -626,17 +626,18 @@ static int launch(int transA, int transB, int M, int N, int K, const float *A, i
 #define FMT_TILE(T) launch_tile<MODE, FTZ, STEP, T>(transA, transB, M, N, K, A, lda, B, ldb, C, ldc, qp, fp, wc, stream)
     // Which tile, from products of N x N x 256 on 256 compute units.
     if constexpr (STEP == kStepOdd) {
-        // One output per thread at any size.  Measured in 1/8/7 (us, T = 1 / 2 / 4): N = 256: 38 / 105 / 362; 512: 75 / 109 / 363; 640:
-        // 116 / 145 / 360; 768: 145 / 197 / 361; 1024: 239 / 246 / 360; 1500: 489 / 502 / 722; 2048: 880 / 859 / 943; 1/6/15 is alike.
+        // One output per thread at any size.  Measured in 1/8/7 (us, T = 1 / 2 / 4): N = 256: 36 / 103 / 376; 512: 69 / 106 / 378; 640:
+        // 106 / 140 / 382; 768: 131 / 190 / 382; 1024: 221 / 242 / 382; 1500: 464 / 491 / 732; 2048: 837 / 844 / 933; 1/6/15 is alike.
         return FMT_TILE(1);
     } else {
         // `alone` is what one tile on a compute unit takes (the chains' latency with 1, 4 or 16 of them to interleave), `each` the
-        // time per tile of a compute unit with work enough.  Measured in 1/6/9, wide form (us, T = 1 / 2 / 4): N = 64: 13.1 / 21.4 /
-        // 57.7; 384: 23 / 22 / 58; 512: 29 / 23 / 59; 640: 44 / 32 / 59; 768: 53 / 42 / 59; 1024: 88 / 53 / 61; 1500: 185 / 109 / 127;
-        // 2048: 334 / 187 / 165.  The values decide which form a stage takes; at 384 and 512, where four chains per thread would gain
-        // up to 6 us, the single form loses 35, so the line lies above them: the constants are a little above the wide form's times (with
-        // those, 13.4 / 5.4, 21.6 / 12.5 and 58 / 41, N = 448 to 560 would take four chains).  Where all stages take the single
-        // form the rule is off by up to a third (640: 65 / 83 / 228; 1024: 123 / 118 / 228; 1500: 240 / 220 / 448; 2048: 426 / 367 / 497).
+        // time per tile of a compute unit with work enough.  Measured in 1/6/9, wide form (us, T = 1 / 2 / 4): N = 64: 13.2 / 21.6 /
+        // 53; 384: 22 / 23 / 54; 512: 28 / 23 / 55; 600: 38 / 32 / 63; 640: 42 / 31 / 55; 768: 52 / 39 / 56; 1024: 88 / 49 / 56; 1350: 154 / 88 /
+        // 92; 1500: 184 / 98 / 125; 2048: 332 / 165 / 151.  The values decide which form a stage takes; at 448 and 512, where four chains per
+        // thread would gain 5 us, the single form loses 29, so the line lies above them: the constants are a little above the wide form's
+        // times (those are 13.4 / 5.2, 21.6 / 12.3 and 54 / 38).  Elsewhere the rule is within 4 % of the best tile in the wide form.  Where
+        // all stages take the single form it is off by up to a third (640: 61 / 78 / 244; 768: 75 / 94 / 244; 1024: 122 / 115 / 246; 1350: 206 / 199 /
+        // 267; 1500: 247 / 223 / 319; 1900: 386 / 345 / 391; 2048: 441 / 371 / 391).
         int cus = 0;
         const int rc = device_cu_count(&cus);
         if (rc != FMT_OK) return rc;
