@@ -541,6 +541,32 @@ def test_wide_tensors_by_default(fmt, monkeypatch):
                 assert np.array_equal(got[i], other[i]) == ((mode == "0") == (wide and i > 0)), (wide, mode, i)
 
 
+@pytest.mark.parametrize("shape", [(1, 32, 4, 4, 32, 1), (2, 32, 6, 6, 33, 1), (1, 64, 33, 1, 32, 1), (1, 32, 35, 2, 33, 3), (2, 64, 16, 16, 64, 3)])
+def test_samples_of_tensors_that_start_inside_a_line(fmt, shape, monkeypatch):
+    """Tensors at any address, of fewer elements than a sample takes, about as many (1024 + 32, 2048 + 32) and more: the samples lie inside
+    the tensor, whose neighbours would change the answer, and the bits are those of a tensor that starts at a line."""
+    monkeypatch.setenv("FMT_GEMM_WINDOW", "3")
+    n, c, h, w, k, r = shape
+    f, rng = (6, 9, True), np.random.default_rng(sum(shape))
+    g = {"pad": (r // 2, r // 2), "stride": (1, 1)}
+
+    def at(x, offset):
+        buf = torch.full((x.size + 64,), 2.0 ** 30, device="cuda")
+        buf[1::2] = 2.0 ** -39
+        buf[offset: offset + x.size] = dev(x).flatten()
+        return buf[offset: offset + x.size].view(x.shape)
+    for wide in (False, True):
+        X, dY = (spread_over(rng, s, *((-6.0, 12.0) if wide else (-3.0, 1.5)), f) for s in ((n, c, h, w), (n, k, h, w)))
+        W = spread_over(rng, (k, c, r, r), -3.0, 1.5, f)
+        got = []
+        for offset in (0, 1, 17, 31):
+            x, y, v = at(X, offset), at(dY, offset), at(W, offset)
+            got.append((fmt.fmt_conv2d_fwd(x, v, f, **g), fmt.fmt_conv2d_dgrad(y, v, x.shape, f, **g), fmt.fmt_conv2d_wgrad(y, x, v.shape, f, **g)))
+        torch.cuda.synchronize()
+        for other in got[1:]:
+            assert all(torch.equal(a, b) for a, b in zip(got[0], other))
+
+
 def test_small_input_gradients_take_pieces(fmt, monkeypatch):
     """At 2.6e8 products the forward product takes planes and the input gradient, whose gradients have elements outside plane 0, pieces."""
     f, rng = (6, 9, True), np.random.default_rng(4)
