@@ -138,19 +138,20 @@ __device__ __forceinline__ uint32_t wave_max(uint32_t v)
     return (uint32_t)__builtin_amdgcn_readlane((int)v, 63);
 }
 
-// A thread's 4 * LOADS elements of the 1024 * LOADS (of fewer: all, some of them twice).  Runs start at lines, an odd number of lines
-// apart, so that they do not all meet the same pixels of images of a power of two.
+// A thread's 4 * LOADS elements of the 1024 * LOADS (of fewer: all, some of them twice).  Runs start an odd number of lines
+// apart, so that they do not all meet the same pixels of images of a power of two, the first with the tensor: the same elements, and the same results,
+// wherever the tensor lies (of one that starts inside a line a run touches two).
 template <uint32_t LOADS>
 __device__ __forceinline__ void window_sample(const WindowTensor &t, uint32_t wave, uint32_t lane, uint32_t *v)
 {
     constexpr uint32_t kRuns = 32u * LOADS;
+    typedef uint32_t u32x4u __attribute__((ext_vector_type(4), aligned(4)));
     if (t.n >= kRuns * 32u + 32u) {               // the same in the whole launch
-        const uint32_t skip = (32u - (uint32_t)(reinterpret_cast<uintptr_t>(t.x) >> 2)) % 32u;
-        const uint32_t step = (((t.n - 32u - skip) / (kRuns - 1u) / 32u - 1u) | 1u) * 32u;
+        const uint32_t step = (((t.n - 32u) / (kRuns - 1u) / 32u - 1u) | 1u) * 32u;
 #pragma unroll
         for (uint32_t i = 0; i < LOADS; ++i) {
-            const uint32_t *first = t.x + skip + (size_t)((i * 4u + wave) * 8u) * step;
-            const u32x4 w = *reinterpret_cast<const u32x4 *>(first + (lane / 8u * step + lane % 8u * 4u));
+            const uint32_t *first = t.x + (size_t)((i * 4u + wave) * 8u) * step;
+            const u32x4u w = *reinterpret_cast<const u32x4u *>(first + (lane / 8u * step + lane % 8u * 4u));
 #pragma unroll
             for (uint32_t j = 0; j < 4; ++j) v[4 * i + j] = w[j];
         }

@@ -383,7 +383,7 @@ def test_elements_outside_plane_0(fmt, spread, plan, monkeypatch):
 
 
 def sampled(n, runs=64):
-    """The elements that a tensor's scale is chosen from: 32 or 64 runs of 32, an odd number of runs apart (tensors that start at a line)."""
+    """The elements that a tensor's scale is chosen from: 32 or 64 runs of 32, an odd number of runs apart."""
     if n < 32 * runs + 32:
         return np.arange(min(n, 32 * runs))
     step = (((n - 32) // (runs - 1) // 32 - 1) | 1) * 32
@@ -544,7 +544,8 @@ def test_wide_tensors_by_default(fmt, monkeypatch):
 @pytest.mark.parametrize("shape", [(1, 32, 4, 4, 32, 1), (2, 32, 6, 6, 33, 1), (1, 64, 33, 1, 32, 1), (1, 32, 35, 2, 33, 3), (2, 64, 16, 16, 64, 3)])
 def test_samples_of_tensors_that_start_inside_a_line(fmt, shape, monkeypatch):
     """Tensors at any address, of fewer elements than a sample takes, about as many (1024 + 32, 2048 + 32) and more: the samples lie inside
-    the tensor, whose neighbours would change the answer, and the bits are those of a tensor that starts at a line."""
+    the tensor, whose neighbours would change the answer, and the bits are those of a tensor that starts at a line, also where a few of the
+    samples' elements alone decide (the first of every run)."""
     monkeypatch.setenv("FMT_GEMM_WINDOW", "3")
     n, c, h, w, k, r = shape
     f, rng = (6, 9, True), np.random.default_rng(sum(shape))
@@ -555,8 +556,13 @@ def test_samples_of_tensors_that_start_inside_a_line(fmt, shape, monkeypatch):
         buf[1::2] = 2.0 ** -39
         buf[offset: offset + x.size] = dev(x).flatten()
         return buf[offset: offset + x.size].view(x.shape)
-    for wide in (False, True):
-        X, dY = (spread_over(rng, s, *((-6.0, 12.0) if wide else (-3.0, 1.5)), f) for s in ((n, c, h, w), (n, k, h, w)))
+    for values in ("narrow", "wide", "wide in the sample"):
+        X, dY = (spread_over(rng, s, *((-6.0, 12.0) if values == "wide" else (-3.0, 1.5)), f) for s in ((n, c, h, w), (n, k, h, w)))
+        if values == "wide in the sample":
+            for t in (X, dY):
+                for runs in (32, 64):
+                    firsts = sampled(t.size, runs)[::32]
+                    t.ravel()[firsts] = np.where(np.arange(firsts.size) % 2, 2.0 ** 24, 1.5 * 2.0 ** -34)
         W = spread_over(rng, (k, c, r, r), -3.0, 1.5, f)
         got = []
         for offset in (0, 1, 17, 31):
