@@ -1837,7 +1837,8 @@ static Scheme api_scheme(fmt_format_t f, int64_t K);
 // leave to a pass of 4 - 10 us: more than it saves (general / direct and pass, from Python: 192 x 101 x 192 in 1/5/10 with statistics
 // 12.0 / 18.2, 752 x 552 x 192 with codes and statistics 12.7 / 18.0, 276 x 1210 x 194 in 1/8/7 with codes 10.7 / 12.0).  So such layers take
 // the general route (in_product) -- where its sums are the direct one's.  1/6/8 and 1/6/9 have parts of their own, and a layer's outputs
-// depend neither on whether statistics are asked for nor on which of fmt_gemm and fmt_linear makes the sums: there the product alone
+// depend neither on whether statistics are asked for nor on which of fmt_gemm and fmt_linear makes the sums: in one part (k <= 96) the sums are the
+// same, 20 layers 18.0 -> 11.8 with statistics, 12.0 -> 10.4 with codes, 19.2 -> 12.7 with both; in several the product alone
 // decides, and a pass follows (general / direct and pass, 390 x 1142 x 314: 15.3 / 22.1 with statistics, 11.9 / 10.7 without).
 static int direct_parts(int M, int N, int K, const OperandSpec &sa, const OperandSpec &sb, const Plan &plan, fmt_format_t f, Scheme sch,
                         int mode, const LinearOut *lin, int cus)
@@ -1863,7 +1864,7 @@ static int direct_parts(int M, int N, int K, const OperandSpec &sa, const Operan
     if (env != nullptr) return parts;
     const bool layer = lin != nullptr && lin->hist == nullptr && lin->codes == nullptr;     // rounded by the direct kernel
     const bool in_product = lin != nullptr && plan.nsplit == 1 && (lin->hist == nullptr || lin->p.exp_lo >= -126);
-    if (in_product && !layer && !own_parts) return 0;
+    if (in_product && !layer && (!own_parts || parts == 1)) return 0;
     const bool one = pieces_of(sch.ps) == 1;
     const int64_t per_wg = direct_blocks_per_workgroup(parts), wgs = (tiles + per_wg - 1) / per_wg;
     const double n = (double)((wgs + cus - 1) / cus) * (double)(parts * per_wg) / 4.0;

@@ -549,14 +549,23 @@ def kernels_of(call):
     return names
 
 
-@pytest.mark.parametrize("f", [(5, 10, True), (5, 10, False), (8, 7, True), (7, 8, True)])
-@pytest.mark.parametrize("M,N,K", [(192, 101, 192), (752, 552, 192), (8, 380, 197), (40, 49, 156)])
+WITHOUT_A_PASS = [(f, shape) for f in ((5, 10, True), (5, 10, False), (8, 7, True), (7, 8, True))
+                  for shape in ((192, 101, 192), (752, 552, 192), (8, 380, 197), (40, 49, 156))]
+# formats whose products in one launch cut k as they like: where they take it whole
+WITHOUT_A_PASS += [(f, shape) for f in ((6, 9, True), (6, 9, False), (6, 8, True)) for shape in ((192, 101, 96), (752, 552, 95), (8, 380, 31), (1400, 49, 65))]
+
+
+@pytest.mark.parametrize("f,shape", WITHOUT_A_PASS)
 @pytest.mark.parametrize("packed,stats", [(False, True), (True, False), (True, True)])
-def test_codes_and_statistics_without_a_pass(fmt, f, M, N, K, packed, stats):
+def test_codes_and_statistics_without_a_pass(fmt, f, shape, packed, stats):
     """Small layers whose outputs leave as codes or with statistics: wherever a product in one launch would leave these to a pass of
-    their own, the kernel of the general product makes them."""
+    their own, the kernel of the general product makes them, and the outputs are those of the layer without them."""
+    M, N, K = shape
     X, W, b = (torch.randn(shape, device="cuda") for shape in ((M, K), (N, K), (N,)))
     h = fmt.new_hist(X.device) if stats else None
     Y = torch.empty((M, N), dtype=torch.int16 if packed else torch.float32, device="cuda")
     names = kernels_of(lambda: (fmt.fmt_linear_pack16 if packed else fmt.fmt_linear)(X, W, b, f, out=Y, hist=h))
     assert any("product_linear_kernel" in n for n in names) and not any("linear_epilogue" in n or "direct_product" in n for n in names), names
+    want = fmt.fmt_linear(X, W, b, f)
+    torch.cuda.synchronize()
+    assert torch.equal(Y, fmt.fmt_pack16(want, f) if packed else want)
