@@ -1838,8 +1838,11 @@ static Scheme api_scheme(fmt_format_t f, int64_t K);
 // 12.0 / 18.2, 752 x 552 x 192 with codes and statistics 12.7 / 18.0, 276 x 1210 x 194 in 1/8/7 with codes 10.7 / 12.0).  So such layers take
 // the general route (in_product) -- where its sums are the direct one's.  1/6/8 and 1/6/9 have parts of their own, and a layer's outputs
 // depend neither on whether statistics are asked for nor on which of fmt_gemm and fmt_linear makes the sums: in one part (k <= 96) the sums are the
-// same, 20 layers 18.0 -> 11.8 with statistics, 12.0 -> 10.4 with codes, 19.2 -> 12.7 with both; in several the product alone
-// decides, and a pass follows (general / direct and pass, 390 x 1142 x 314: 15.3 / 22.1 with statistics, 11.9 / 10.7 without).
+// same, 20 layers 18.0 -> 11.8 with statistics, 12.0 -> 10.4 with codes, 19.2 -> 12.7 with both; in several the product
+// decides, and a pass follows (general / direct and pass, 165 x 156 x 252: 12.4 / 16.8 with statistics, 10.0 / 7.6 without).  Where there are two waves
+// for a SIMD, and a wave takes more than two blocks, a product whose rows lie along k, as a layer's do, gains so little that the general
+// route takes it for the layers' sake (40 products and layers of 110 x 1400 to 1400 x 1400, k 129 to 480, from Python, general / direct: products 11.4 / 10.9,
+// in graphs 11.4 / 11.3, plain layers 12.4 / 12.1, with codes 13.1 / 14.8, with statistics 15.6 / 19.5, with both 16.3 / 20.5).
 static int direct_parts(int M, int N, int K, const OperandSpec &sa, const OperandSpec &sb, const Plan &plan, fmt_format_t f, Scheme sch,
                         int mode, const LinearOut *lin, int cus)
 {
@@ -1871,6 +1874,7 @@ static int direct_parts(int M, int N, int K, const OperandSpec &sa, const Operan
     const double rounds = std::max(0.0, std::ceil(n / 2.0) - 1.0);
     const double blocks = (double)((kblocks + parts - 1) / parts);
     if (blocks > 11.0) return 0;
+    if (own_parts && plan.nsplit == 1 && parts > 1 && sa.kcontig && sb.kcontig && blocks > 2.0 && tiles * parts >= 4 * (int64_t)cus) return 0;
     const double operands = ((double)M + N) * K * 1e-6, results = (double)M * N * 1e-6;
     const double each = (one ? 0.22 + 0.16 * n : 0.62 + 0.38 * n) + (f.denorm == 0 ? 0.18 : 0.0);
     const double direct = 2.7 + blocks * each + 4.4 * rounds + 1.3 * results + 0.65 * operands;

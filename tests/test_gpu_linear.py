@@ -551,8 +551,9 @@ def kernels_of(call):
 
 WITHOUT_A_PASS = [(f, shape) for f in ((5, 10, True), (5, 10, False), (8, 7, True), (7, 8, True))
                   for shape in ((192, 101, 192), (752, 552, 192), (8, 380, 197), (40, 49, 156))]
-# formats whose products in one launch cut k as they like: where they take it whole
-WITHOUT_A_PASS += [(f, shape) for f in ((6, 9, True), (6, 9, False), (6, 8, True)) for shape in ((192, 101, 96), (752, 552, 95), (8, 380, 31), (1400, 49, 65))]
+# formats whose products in one launch cut k as they like: where they take it whole, and where these have two waves on every SIMD
+WITHOUT_A_PASS += [(f, shape) for f in ((6, 9, True), (6, 9, False), (6, 8, True))
+                   for shape in ((192, 101, 96), (752, 552, 95), (8, 380, 31), (1400, 49, 65), (805, 1147, 129), (613, 564, 288), (512, 512, 257))]
 
 
 @pytest.mark.parametrize("f,shape", WITHOUT_A_PASS)
