@@ -1498,7 +1498,8 @@ __global__ void zero_fill_kernel(float *__restrict__ C, int M, int N, int64_t ld
 // measurements on MI355X: large tiles move fewer LDS and L2 bytes per MFMA, small tiles need
 // several resident workgroups per compute unit to reach their rate, the busiest compute unit sets
 // the time, and cutting k fills the machine at the price of writing and re-reading partial sums.
-static Plan make_plan(int M, int N, int kblocks, int cus, int pieces)
+// most: the largest tile, in 64 x 64 (a forced plan may be larger).
+static Plan make_plan(int M, int N, int kblocks, int cus, int pieces, int most = 16)
 {
     // eff1 / effmax: relative MFMA rate of a compute unit with one / with max_occ resident workgroups
     struct Shape { int tm, tn, max_occ; double eff1, effmax; };
@@ -1522,7 +1523,7 @@ static Plan make_plan(int M, int N, int kblocks, int cus, int pieces)
     Plan best{2, 2, 1, 1, cus};
     double best_t = 1e300;
     for (const auto &sh : shapes) {
-        if (lds_bytes(sh.tm, sh.tn, pieces, pipe_ks(pieces), 2) > 160 * 1024) continue;
+        if (sh.tm * sh.tn > most || lds_bytes(sh.tm, sh.tn, pieces, pipe_ks(pieces), 2) > 160 * 1024) continue;
         const int bm = 64 * sh.tm, bn = 64 * sh.tn;
         const long tiles = (long)((M + bm - 1) / bm) * ((N + bn - 1) / bn);
         for (int ns = 1; ns <= 32; ns = ns < 4 ? ns + 1 : ns * 2) {
@@ -2451,6 +2452,8 @@ static int run_implicit(int M, int N, int K, const OperandSpec &sa, const float 
     return product_gathered<PS>(va, im, M, N, la.kblocks, out, plan, partp, stream);
 }
 
+constexpr int kWindowTile = 4;           // the products of planes: 128 x 128 at most (product_window)
+
 // Convolutions in 1/6/8 and 1/6/9 on exponent planes with one scale per tensor: one fp16 MFMA product per multiply instead of the four of
 // two bf16 pieces (forward, dgrad and wgrad, 256 -> 256 channels of 14 x 14, 3 x 3 taps, batch 64, us: 80 -> 45, 78 -> 60, 102 -> 76).
 // Below `least` products the scales' samples and the tail cost more than they save.  us, bf16 pieces / planes:
@@ -2488,7 +2491,7 @@ static int run_implicit_window(int M, int N, int K, const OperandSpec &sa, int64
     int cus = 0;
     rc = device_cu_count(&cus);
     if (rc != FMT_OK) return rc;
-    const Plan plan = make_plan(M, N, la.kblocks, cus, 1);
+    const Plan plan = make_plan(M, N, la.kblocks, cus, 1, kWindowTile);
     auto up256 = [](size_t b) { return (b + 255) / 256 * 256; };
     const int C = im.c8 * 8;
     const int npix = (int)(tensor_elems / C);
@@ -2537,7 +2540,7 @@ static int run_wgrad_window(int M, int N, int K, const OperandSpec &sa, int64_t 
     int cus = 0;
     rc = device_cu_count(&cus);
     if (rc != FMT_OK) return rc;
-    const Plan plan = make_plan(M, N, la.kblocks, cus, 1);
+    const Plan plan = make_plan(M, N, la.kblocks, cus, 1, kWindowTile);
     const size_t part = part_bytes_of(plan, M, N);
     const int n = (int)sb.pre_elems;
     Scratch s;

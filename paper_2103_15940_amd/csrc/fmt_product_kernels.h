@@ -344,8 +344,10 @@ __device__ __forceinline__ void linear_tile(floatx16 (&acc)[TM][TN], float *C, i
 // dgrad kernel takes 30 us on gradients without such elements, 36 with one and 45 with 43 (the code is met for the first time then, so
 // larger batches or fewer instructions on the common path did not help; reading the masks after the products cost 2 more).
 constexpr int kWindowChunks = 2;
-// Workgroups that a compute unit takes: LDS leaves room for two of 128 x 128 and four of 64 x 64, and the tail's registers must not take it.
-constexpr int window_workgroups(int tiles) { return tiles == 4 ? 2 : tiles == 1 ? 4 : 1; }
+// Tiles of 128 x 128 and 64 x 64: with the tail the larger ones do not fit the registers.  256 x 256 spilled 2.5 KB per lane and took
+// 2 to 5 times as long: 36 x 288 x 27 x 27 -> 480 channels, dgrad, 1 x 1, 170 us against 46, forward of 73 x 64 x 41 x 41 -> 160, 3 x 3, 443 against 90.
+// Workgroups that a compute unit takes: LDS leaves room for two and four, and the tail's registers must not take it.
+constexpr int window_workgroups(int tiles) { return tiles == 4 ? 2 : 4; }
 
 // Bits 1 and 2: operand A has elements of the planes above / below in this wave's rows and block kb; bits 9 and 10: operand B.
 template <int TM, int TN, bool GATHER>
@@ -397,7 +399,7 @@ __device__ __forceinline__ void window_tail(floatx16 (&acc)[TM][TN], const uint3
 {
     // blocks loaded together: an element outside plane 0 of a gathered tensor is met by every tap (as many as leave the
     // 64 x 64 and 128 x 128 tiles their four and two workgroups per compute unit)
-    constexpr int kAhead = TM * TN <= 4 ? 4 : TM * TN == 8 ? 2 : 1;
+    constexpr int kAhead = 4;
     const unsigned long long *pixels = reinterpret_cast<const unsigned long long *>(pb.mask);      // GATHER (see fmt_product.h)
 #pragma unroll 1
     for (int first = kb0; first < kb1; first += 64) {
@@ -1091,13 +1093,8 @@ template <bool GATHER>
 int product_window(const OperandView &va, const OperandView &vb, const Implicit &im, int M, int N, int kblocks, const OutSpec &out,
                    const Plan &plan, float *part, hipStream_t stream)
 {
-#define FMT_PRODUCT(TMV, TNV) launch_window<TMV, TNV, GATHER>(va, vb, im, M, N, kblocks, out, plan, part, stream)
-    if (plan.tm == 4 && plan.tn == 4) return FMT_PRODUCT(4, 4);
-    if (plan.tm == 4 && plan.tn == 2) return FMT_PRODUCT(4, 2);
-    if (plan.tm == 2 && plan.tn == 4) return FMT_PRODUCT(2, 4);
-    if (plan.tm == 2 && plan.tn == 2) return FMT_PRODUCT(2, 2);
-    return FMT_PRODUCT(1, 1);
-#undef FMT_PRODUCT
+    if (plan.tm > 1 && plan.tn > 1) return launch_window<2, 2, GATHER>(va, vb, im, M, N, kblocks, out, plan, part, stream);
+    return launch_window<1, 1, GATHER>(va, vb, im, M, N, kblocks, out, plan, part, stream);
 }
 
 template <int PS, bool SCALED, int T>

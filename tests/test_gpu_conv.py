@@ -6,6 +6,7 @@ import pytest
 
 import oracle
 import workloads
+from graph_kernels import kernels_of
 
 pytestmark = pytest.mark.gpu
 
@@ -571,6 +572,22 @@ def test_samples_of_tensors_that_start_inside_a_line(fmt, shape, monkeypatch):
         torch.cuda.synchronize()
         for other in got[1:]:
             assert all(torch.equal(a, b) for a, b in zip(got[0], other))
+
+
+@pytest.mark.parametrize("shape", [(36, 288, 27, 480, 1), (73, 64, 41, 160, 3), (13, 96, 50, 512, 1), (8, 64, 14, 96, 3)])
+def test_products_of_planes_stay_in_registers(fmt, shape, monkeypatch):
+    """Large products, for which 256 x 256 results per workgroup would be the fastest without the code for the elements outside plane 0, and a
+    small one: none of the kernels keeps sums or fragments in private memory."""
+    monkeypatch.setenv("FMT_GEMM_WINDOW", "1")
+    n, c, h, k, r = shape
+    X, W = torch.randn(n, c, h, h, device="cuda"), torch.randn(k, c, r, r, device="cuda")
+    f, g = (6, 9, True), {"pad": (r // 2, r // 2), "stride": (1, 1)}
+    Y = torch.empty(n, k, h, h, device="cuda")
+    dX, dW = torch.empty_like(X), torch.empty_like(W)
+    for call in (lambda: fmt.fmt_conv2d_fwd(X, W, f, out=Y, **g), lambda: fmt.fmt_conv2d_dgrad(Y, W, X.shape, f, out=dX, **g),
+                 lambda: fmt.fmt_conv2d_dgrad(X, W.transpose(0, 1).contiguous(), Y.shape, f, out=Y, **g), lambda: fmt.fmt_conv2d_wgrad(Y, X, W.shape, f, out=dW, **g)):
+        kernels = kernels_of(call)
+        assert any("window" in name for name, _ in kernels) and all(local == 0 for _, local in kernels), kernels
 
 
 def test_small_input_gradients_take_pieces(fmt, monkeypatch):

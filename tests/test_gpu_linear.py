@@ -13,6 +13,7 @@ import pytest
 
 import oracle
 import workloads
+from graph_kernels import kernels_of
 
 pytestmark = pytest.mark.gpu
 
@@ -518,37 +519,6 @@ def test_layers_repeat(fmt, e, m, d, tile, monkeypatch):
             assert torch.equal(fmt.fmt_linear_prepared(Xp, Wp, b, hist=h), want) and torch.equal(h, hw), (K, i)
 
 
-def kernels_of(call):
-    """The names of the kernels that call(stream) launches."""
-    import ctypes
-
-    class Params(ctypes.Structure):
-        _fields_ = [("block", ctypes.c_uint * 3), ("extra", ctypes.c_void_p), ("func", ctypes.c_void_p), ("grid", ctypes.c_uint * 3),
-                    ("params", ctypes.c_void_p), ("shared", ctypes.c_uint)]
-    with open("/proc/self/maps") as maps:
-        hip = ctypes.CDLL(next(line.split()[-1] for line in maps if "libamdhip64.so" in line))
-    hip.hipKernelNameRefByPtr.restype = ctypes.c_char_p
-    hip.hipKernelNameRefByPtr.argtypes = [ctypes.c_void_p, ctypes.c_void_p]
-    stream = torch.cuda.Stream()
-    with torch.cuda.stream(stream):
-        call()                                            # scratch of the stream
-        stream.synchronize()
-        graph, count = ctypes.c_void_p(), ctypes.c_size_t()
-        assert hip.hipStreamBeginCapture(ctypes.c_void_p(stream.cuda_stream), 2) == 0
-        call()
-        assert hip.hipStreamEndCapture(ctypes.c_void_p(stream.cuda_stream), ctypes.byref(graph)) == 0
-    assert hip.hipGraphGetNodes(graph, None, ctypes.byref(count)) == 0
-    nodes = (ctypes.c_void_p * count.value)()
-    assert hip.hipGraphGetNodes(graph, nodes, ctypes.byref(count)) == 0
-    names = []
-    for node in nodes:
-        at = Params()
-        assert hip.hipGraphKernelNodeGetParams(ctypes.c_void_p(node), ctypes.byref(at)) == 0
-        names.append(hip.hipKernelNameRefByPtr(at.func, None).decode())
-    assert hip.hipGraphDestroy(graph) == 0
-    return names
-
-
 WITHOUT_A_PASS = [(f, shape) for f in ((5, 10, True), (5, 10, False), (8, 7, True), (7, 8, True))
                   for shape in ((192, 101, 192), (752, 552, 192), (8, 380, 197), (40, 49, 156))]
 # formats whose products in one launch cut k as they like: where they take it whole, and where these have two waves on every SIMD
@@ -565,7 +535,7 @@ def test_codes_and_statistics_without_a_pass(fmt, f, shape, packed, stats):
     X, W, b = (torch.randn(shape, device="cuda") for shape in ((M, K), (N, K), (N,)))
     h = fmt.new_hist(X.device) if stats else None
     Y = torch.empty((M, N), dtype=torch.int16 if packed else torch.float32, device="cuda")
-    names = kernels_of(lambda: (fmt.fmt_linear_pack16 if packed else fmt.fmt_linear)(X, W, b, f, out=Y, hist=h))
+    names = [name for name, _ in kernels_of(lambda: (fmt.fmt_linear_pack16 if packed else fmt.fmt_linear)(X, W, b, f, out=Y, hist=h))]
     assert any("product_linear_kernel" in n for n in names) and not any("linear_epilogue" in n or "direct_product" in n for n in names), names
     want = fmt.fmt_linear(X, W, b, f)
     torch.cuda.synchronize()
