@@ -494,7 +494,7 @@ __device__ __forceinline__ void window_tail(floatx16 (&acc)[TM][TN], const uint3
             for (int v = 0; v < 16; ++v) acc[i][j][v] *= unit;
 }
 
-// A stage buffer, by its place in the ring: the two bodies of a kernel that holds planes and pieces (product_kernel) have theirs in common.
+// A stage buffer, by its place in the ring, that the two bodies of a kernel that holds planes and pieces (product_kernel) have in common.
 template <int PLACE, int VECTORS>
 __device__ __forceinline__ auto stage_buffer() -> u32x4 (&)[VECTORS]
 {
@@ -522,7 +522,7 @@ __device__ __forceinline__ auto stage_buffer() -> u32x4 (&)[VECTORS]
 // LINEAR: the results are a fully connected layer's accumulators; they leave as R(R(acc) + R(b)) (lin), HIST: with the
 // statistics of R(acc) + R(b) (sink).
 template <int PS, int TM, int TN, int KS, int NST, bool SPLIT, bool SCHED, bool SCALED, bool GATHER = false, bool LINEAR = false,
-          bool HIST = false, bool WINDOW = false>
+          bool HIST = false, bool WINDOW = false, bool COMMON = WINDOW>
 __device__ __forceinline__ void product_body(const u32x4 *__restrict__ Aw, const u32x4 *__restrict__ Bw,
                                              float *__restrict__ C, int M, int N, int64_t ldc, int img,
                                              int kblocks, int tiles_m, int tiles_n, int kb_per_split,
@@ -545,11 +545,17 @@ __device__ __forceinline__ void product_body(const u32x4 *__restrict__ Aw, const
     // One LDS array per stage buffer, each addressed with a compile-time index: the compiler then knows
     // which loads-to-LDS an LDS read can depend on and leaves the younger stages in flight.
     constexpr int STV = VA + VB;
-    u32x4(&st0)[STV] = stage_buffer<0, STV>();
-    u32x4(&st1)[STV] = stage_buffer<1, STV>();
-    u32x4(&st2)[NST > 2 ? STV : 1] = stage_buffer<2, (NST > 2 ? STV : 1)>();
-    u32x4(&st3)[NST > 3 ? STV : 1] = stage_buffer<3, (NST > 3 ? STV : 1)>();
-    auto stage = [&](int b) -> u32x4 * { return b == 0 ? st0 : b == 1 ? st1 : b == 2 ? st2 : st3; };
+    // (References to these would cost registers: three pieces, 64 x 64, five workgroups per compute unit instead of six, 1 - 4 %.)
+    __shared__ u32x4 st0[STV];
+    __shared__ u32x4 st1[STV];
+    __shared__ u32x4 st2[NST > 2 ? STV : 1];
+    __shared__ u32x4 st3[NST > 3 ? STV : 1];
+    auto stage = [&](int b) -> u32x4 * {
+        if constexpr (COMMON)
+            return b == 0 ? stage_buffer<0, STV>() : b == 1 ? stage_buffer<1, STV>() : b == 2 ? stage_buffer<2, (NST > 2 ? STV : 1)>() : stage_buffer<3, (NST > 3 ? STV : 1)>();
+        else
+            return b == 0 ? st0 : b == 1 ? st1 : b == 2 ? st2 : st3;
+    };
     typedef __attribute__((address_space(3))) void lds_void;
     typedef const __attribute__((address_space(1))) void glb_void;
 
@@ -709,8 +715,8 @@ __device__ __forceinline__ void product_body(const u32x4 *__restrict__ Aw, const
                 barrier();
                 Implicit imp = im;
                 imp.kc = im.kc_pieces;
-                product_body<2, TM, TN, Pieces::ks, Pieces::nst, SPLIT, SCHED, false, GATHER>(Aw, Bw, C, M, N, ldc, img, kblocks, tiles_m, tiles_n,
-                                                                                           kb_per_split, pa, pb, imp, bid);
+                product_body<2, TM, TN, Pieces::ks, Pieces::nst, SPLIT, SCHED, false, GATHER, false, false, false, true>(
+                    Aw, Bw, C, M, N, ldc, img, kblocks, tiles_m, tiles_n, kb_per_split, pa, pb, imp, bid);
                 return;
             }
         }

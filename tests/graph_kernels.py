@@ -15,7 +15,7 @@ class _Attributes(ctypes.Structure):
 
 
 def kernels_of(call):
-    """(name, bytes of private memory per thread) of every kernel that call() launches on the current stream."""
+    """(name, bytes of private memory per thread, workgroups that a compute unit takes) of every kernel that call() launches on the current stream."""
     with open("/proc/self/maps") as maps:
         hip = ctypes.CDLL(next(line.split()[-1] for line in maps if "libamdhip64.so" in line))
     hip.hipKernelNameRefByPtr.restype = ctypes.c_char_p
@@ -36,6 +36,8 @@ def kernels_of(call):
         at, attributes = _Params(), _Attributes()
         assert hip.hipGraphKernelNodeGetParams(ctypes.c_void_p(node), ctypes.byref(at)) == 0
         assert hip.hipFuncGetAttributes(ctypes.byref(attributes), ctypes.c_void_p(at.func)) == 0
-        kernels.append((hip.hipKernelNameRefByPtr(at.func, None).decode(), attributes.local))
+        blocks, threads = ctypes.c_int(), at.block[0] * at.block[1] * at.block[2]
+        assert hip.hipOccupancyMaxActiveBlocksPerMultiprocessor(ctypes.byref(blocks), ctypes.c_void_p(at.func), threads, ctypes.c_size_t(at.shared)) == 0
+        kernels.append((hip.hipKernelNameRefByPtr(at.func, None).decode(), attributes.local, blocks.value))
     assert hip.hipGraphDestroy(graph) == 0
     return kernels

@@ -587,7 +587,7 @@ def test_products_of_planes_stay_in_registers(fmt, shape, monkeypatch):
     for call in (lambda: fmt.fmt_conv2d_fwd(X, W, f, out=Y, **g), lambda: fmt.fmt_conv2d_dgrad(Y, W, X.shape, f, out=dX, **g),
                  lambda: fmt.fmt_conv2d_dgrad(X, W.transpose(0, 1).contiguous(), Y.shape, f, out=Y, **g), lambda: fmt.fmt_conv2d_wgrad(Y, X, W.shape, f, out=dW, **g)):
         kernels = kernels_of(call)
-        assert any("window" in name for name, _ in kernels) and all(local == 0 for _, local in kernels), kernels
+        assert any("window" in name for name, _, _ in kernels) and all(local == 0 for _, local, _ in kernels), kernels
 
 
 def test_small_input_gradients_take_pieces(fmt, monkeypatch):

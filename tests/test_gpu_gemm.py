@@ -7,6 +7,7 @@ import pytest
 
 import oracle
 import workloads
+from graph_kernels import kernels_of
 
 pytestmark = pytest.mark.gpu
 
@@ -514,3 +515,13 @@ def test_three_pieces_on_small_tiles_repeat(fmt, e, m, d, plan, monkeypatch):
     Xd, Wd = dev(X), dev(W)
     for _ in range(12):
         assert torch.equal(fmt.fmt_conv2d_fwd(Xd, Wd, f), wantc)
+
+
+@pytest.mark.parametrize("f", [(8, 18, True), (8, 22, False)])
+def test_three_pieces_fill_a_compute_unit(fmt, f, monkeypatch):
+    """64 x 64 results of three bf16 pieces: LDS has room for six workgroups per compute unit, and so have the registers."""
+    monkeypatch.setenv("FMT_GEMM_PLAN", "1,1,1")
+    A, B = torch.randn(256, 192, device="cuda"), torch.randn(320, 192, device="cuda")
+    C = torch.empty(256, 320, device="cuda")
+    blocks = [n for name, _, n in kernels_of(lambda: fmt.fmt_gemm(A, B, f, transB=True, out=C)) if "product_kernel" in name]
+    assert blocks and min(blocks) >= 6, blocks

@@ -535,7 +535,7 @@ def test_codes_and_statistics_without_a_pass(fmt, f, shape, packed, stats):
     X, W, b = (torch.randn(shape, device="cuda") for shape in ((M, K), (N, K), (N,)))
     h = fmt.new_hist(X.device) if stats else None
     Y = torch.empty((M, N), dtype=torch.int16 if packed else torch.float32, device="cuda")
-    names = [name for name, _ in kernels_of(lambda: (fmt.fmt_linear_pack16 if packed else fmt.fmt_linear)(X, W, b, f, out=Y, hist=h))]
+    names = [name for name, _, _ in kernels_of(lambda: (fmt.fmt_linear_pack16 if packed else fmt.fmt_linear)(X, W, b, f, out=Y, hist=h))]
     assert any("product_linear_kernel" in n for n in names) and not any("linear_epilogue" in n or "direct_product" in n for n in names), names
     want = fmt.fmt_linear(X, W, b, f)
     torch.cuda.synchronize()
