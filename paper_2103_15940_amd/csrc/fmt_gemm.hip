@@ -1837,13 +1837,17 @@ static Scheme api_scheme(fmt_format_t f, int64_t K);
 // Of a layer with nsplit == 1 the general route ends in its product's kernel, statistics and codes included, which the direct one has to
 // leave to a pass of 4 - 10 us: more than it saves (general / direct and pass, from Python: 192 x 101 x 192 in 1/5/10 with statistics
 // 12.0 / 18.2, 752 x 552 x 192 with codes and statistics 12.7 / 18.0, 276 x 1210 x 194 in 1/8/7 with codes 10.7 / 12.0).  So such layers take
-// the general route (in_product) -- where its sums are the direct one's.  1/6/8 and 1/6/9 have parts of their own, and a layer's outputs
-// depend neither on whether statistics are asked for nor on which of fmt_gemm and fmt_linear makes the sums: in one part (k <= 96) the sums are the
-// same, 20 layers 18.0 -> 11.8 with statistics, 12.0 -> 10.4 with codes, 19.2 -> 12.7 with both; in several the product
+// the general route (in_product) -- where its sums are the direct one's.  1/6/8 and 1/6/9 have parts of their own, and where the general
+// route does not cut k a layer's outputs depend neither on whether statistics are asked for nor on which of fmt_gemm and fmt_linear makes the sums: in one part
+// (k <= 96) the sums are the same, 20 layers 18.0 -> 11.8 with statistics, 12.0 -> 10.4 with codes, 19.2 -> 12.7 with both; in several the product
 // decides, and a pass follows (general / direct and pass, 165 x 156 x 252: 12.4 / 16.8 with statistics, 10.0 / 7.6 without).  Where there are two waves
 // for a SIMD, and a wave takes more than two blocks, a product whose rows lie along k, as a layer's do, gains so little that the general
 // route takes it for the layers' sake (40 products and layers of 110 x 1400 to 1400 x 1400, k 129 to 480, from Python, general / direct: products 11.4 / 10.9,
 // in graphs 11.4 / 11.3, plain layers 12.4 / 12.1, with codes 13.1 / 14.8, with statistics 15.6 / 19.5, with both 16.3 / 20.5).
+// Where these formats need a second round of workgroups and the general route cuts k, the direct one comes out slower than the times above say: 40
+// shapes of 32 x 32 to 4000 x 4000, k 256 to 3000, in graphs, general / direct: products with rows along k 20.1 / 21.8, without 19.5 / 20.9, plain
+// layers, whose rounding is a launch of its own in general, 26.5 / 25.0.  So the products leave it there.  The layers keep it, those with codes (25.5 / 27.0) and
+// statistics (34.5 / 36.1) too: their sums are the plain ones'.
 static int direct_parts(int M, int N, int K, const OperandSpec &sa, const OperandSpec &sb, const Plan &plan, fmt_format_t f, Scheme sch,
                         int mode, const LinearOut *lin, int cus)
 {
@@ -1875,6 +1879,7 @@ static int direct_parts(int M, int N, int K, const OperandSpec &sa, const Operan
     const double rounds = std::max(0.0, std::ceil(n / 2.0) - 1.0);
     const double blocks = (double)((kblocks + parts - 1) / parts);
     if (blocks > 11.0) return 0;
+    if (own_parts && plan.nsplit > 1 && n > 2.0 && lin == nullptr) return 0;
     if (own_parts && plan.nsplit == 1 && parts > 1 && sa.kcontig && sb.kcontig && blocks > 2.0 && tiles * parts >= 4 * (int64_t)cus) return 0;
     const double operands = ((double)M + N) * K * 1e-6, results = (double)M * N * 1e-6;
     const double each = (one ? 0.22 + 0.16 * n : 0.62 + 0.38 * n) + (f.denorm == 0 ? 0.18 : 0.0);

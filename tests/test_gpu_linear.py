@@ -540,3 +540,15 @@ def test_codes_and_statistics_without_a_pass(fmt, f, shape, packed, stats):
     want = fmt.fmt_linear(X, W, b, f)
     torch.cuda.synchronize()
     assert torch.equal(Y, fmt.fmt_pack16(want, f) if packed else want)
+
+
+@pytest.mark.parametrize("M,N,K", [(111, 2606, 1270), (1362, 286, 1025)])
+def test_second_round_of_workgroups_beside_a_cut_k(fmt, M, N, K):
+    """1/6/9 where the product in one launch would need a second round of workgroups, and the general one cuts k: products take the general
+    one, layers that in one launch, and their outputs do not depend on the statistics."""
+    f = (6, 9, True)
+    X, W, b = (torch.randn(shape, device="cuda") for shape in ((M, K), (N, K), (N,)))
+    h, Y, Z = fmt.new_hist(X.device), torch.empty((M, N), device="cuda"), torch.empty((M, N), device="cuda")
+    direct = [any("direct_product" in name for name, _, _ in kernels_of(call)) for call in
+              (lambda: fmt.fmt_gemm(X, W, f, transB=True, out=Y), lambda: fmt.fmt_linear(X, W, b, f, out=Y, hist=h), lambda: fmt.fmt_linear(X, W, b, f, out=Z))]
+    assert direct == [False, True, True] and torch.equal(Y, Z)
