@@ -65,6 +65,12 @@ __device__ __forceinline__ void divmod(const FastDiv &f, int a, int &q, int &r)
     r = a - q * f.d;
 }
 
+// Division by twice the divisor (make_fastdiv(2 d): the same m, l one more).
+__device__ __forceinline__ FastDiv fastdiv_twice(const FastDiv &f)
+{
+    return f.d == 1 ? FastDiv{0x80000001u, 0, 2} : FastDiv{f.m, f.sh + 1, 2 * f.d};
+}
+
 // Operand B of a convolution product gathered by the product kernel itself: row = position (n, y, x)
 // on a grid gy x gx, k = (tap, channel) with the channel running fastest, read from the rounded tensor
 // in pixel-major order T[piece][n][iy][ix][channel] (16-bit pieces, 8 channels per 16-byte vector; tc is a
@@ -83,7 +89,6 @@ struct Implicit {
     FastDiv r0, r1;     // row -> (n, y, x): by gx, then by gy
     FastDiv kc;         // stage number -> (tap, channel block): by channels / (k per stage)
     FastDiv ks;         // tap -> (r, s): by S
-    FastDiv kc_pieces;  // planes (product_window): kc of the stages of two bf16 pieces
 };
 
 // A group of independent products in one launch (fmt_gemm_prepared_batch): workgroup ids [first, next first)

@@ -714,7 +714,7 @@ __device__ __forceinline__ void product_body(const u32x4 *__restrict__ Aw, const
                 __builtin_amdgcn_s_waitcnt(0x0F70);
                 barrier();
                 Implicit imp = im;
-                imp.kc = im.kc_pieces;
+                imp.kc = fastdiv_twice(im.kc);
                 product_body<2, TM, TN, Pieces::ks, Pieces::nst, SPLIT, SCHED, false, GATHER, false, false, false, true>(
                     Aw, Bw, C, M, N, ldc, img, kblocks, tiles_m, tiles_n, kb_per_split, pa, pb, imp, bid);
                 return;
@@ -897,7 +897,6 @@ static int launch_product_v2(const u32x4 *Aw, const u32x4 *Bw, float *out, int M
         auto kern = product_kernel<PS, TM, TN, KS, NST, SPLIT, SCHED, SCALED, GATHER, WINDOW>;
         Implicit imk = im;
         if (GATHER) imk.kc = make_fastdiv(im.c8 * 8 / (16 * KS));   // stages of 16*KS k per tap
-        if (GATHER && WINDOW) imk.kc_pieces = make_fastdiv(im.c8 * 8 / (16 * Pipe<2, TM, TN>::ks));
         hipLaunchKernelGGL(kern, dim3((unsigned)(per_xcd * 8 * nsplit)), dim3(256), 0, stream, Aw, Bw, out, M, N, ld, img,
                            kblocks, tiles_m, tiles_n, kb_per, pa, pb, imk);
         FMT_HIP_CHECK(hipGetLastError());
